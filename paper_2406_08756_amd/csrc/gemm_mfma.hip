@@ -528,7 +528,11 @@ __global__ void __launch_bounds__(kThreads, 2) attn_outer_kernel(MfmaGemmArgs g)
         for (int j = 0; j < TM; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[i].operand(), fa[j].operand(), acc[i][j], 0, 0, 0);
     }
-    block_barrier();  // every wavefront has read B(tn): its buffer becomes the staging area
+    // every wavefront has read B(tn), so its buffer can become the staging area.  Read, not merely
+    // requested: without the wait the last fragments may still be on their way when the barrier
+    // opens, and another wavefront's staging writes overtake them.
+    wait_lgkmcnt0();
+    block_barrier();
     // round into this wavefront's staging region, then whole rows back, 16 bytes per lane
     // (acc[i][j][r]: n = wn0 + 32 i + 8 (r / 4) + 4 (lane / 32) + r % 4, m = wm0 + 32 j + lane % 32)
 #pragma unroll
@@ -687,7 +691,11 @@ __global__ void __launch_bounds__(kThreads, 2) attn_dscores_kernel(MfmaGemmArgs 
         for (int j = 0; j < TM; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[i].operand(), fa[j].operand(), acc[i][j], 0, 0, 0);
     }
-    block_barrier();  // every wavefront has read B(tn): its buffer becomes the staging area
+    // every wavefront has read B(tn), so its buffer can become the staging area.  Read, not merely
+    // requested: without the wait the last fragments may still be on their way when the barrier
+    // opens, and another wavefront's staging writes overtake them.
+    wait_lgkmcnt0();
+    block_barrier();
     // round into this wavefront's quarter, read whole rows back, 16 bytes per lane
     // (acc[i][j][r]: n = wn0 + 32 i + 8 (r / 4) + 4 (lane / 32) + r % 4, m = wm0 + 32 j + lane % 32)
 #pragma unroll
