@@ -1,22 +1,107 @@
 // Chooses the kernel for a matrix product.
-#include "kernels.h"
+#include "gemm_plans.h"
 
 namespace lynx {
+namespace {
 
-hipError_t gemm(int dtype, const GemmDesc& d, hipStream_t st) {
-  if (gemm_mfma_supported(dtype, d)) return gemm_mfma(d, st);
-  if (d.epi.kind != kEpiNone) return hipErrorInvalidValue;  // only the matrix-core kernels carry epilogues
-  return gemm_generic(dtype, d, st);
+bool aligned(const void* p, uintptr_t bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
+
+// (The whole-tile pair mixes tile shapes and pads nothing: it wins ties, e.g. 123 against 131 us for the
+// attention projection of the 7B-shaped shard, which the estimates put level.)
+bool uses_whole_pair(const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  const double us = gemm_whole_pair_us(dgrad, wgrad);
+  return us >= 0.0 && us <= 1.05 * ragged_pair(dgrad, wgrad).us;
+}
+double pair_us(const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair_us(dgrad, wgrad) : ragged_pair(dgrad, wgrad).us;
+}
+
+bool unbatched(const GemmDesc& d) { return d.causal == kCausalNone && d.nz1 * d.nz2 == 1; }
+
+}  // namespace
+
+bool gemm_mfma_supported(int dtype, const GemmDesc& d) {
+  if (dtype != 1 || d.M % 8 || d.N % 8 || d.K % 8 || d.M <= 0 || d.N <= 0 || d.K <= 0) return false;
+  if (d.causal == kCausalOutLower && d.M != d.N) return false;
+  if ((d.causal == kCausalKLeM || d.causal == kCausalKGeM) && (d.M != d.K || d.bias != nullptr)) return false;
+  if (d.causal == kCausalNone && d.nz1 * d.nz2 != 1) return false;
+  const bool a_k = d.a_sk == 1, a_mn = d.a_sm == 1;
+  const bool b_k = d.b_sk == 1, b_mn = d.b_sn == 1;
+  if (!(a_k || a_mn) || !(b_k || b_mn) || (!a_k && b_k)) return false;
+  if ((a_k ? d.a_sm : d.a_sk) % 8 || (b_k ? d.b_sn : d.b_sk) % 8 || d.c_sm % 8) return false;
+  if (d.a_sz1 % 8 || d.a_sz2 % 8 || d.b_sz1 % 8 || d.b_sz2 % 8 || d.c_sz1 % 8 || d.c_sz2 % 8) return false;
+  if (!aligned(d.A, 16) || !aligned(d.B, 16) || !aligned(d.C, 16) || !aligned(d.bias, 16)) return false;
+  switch (d.epi.kind) {
+    case kEpiNone:
+      return true;
+    case kEpiSoftmaxBwd:
+      // only the row-block kernel of the score-shaped products carries it
+      return d.causal == kCausalOutLower && d.bias == nullptr && d.K <= 128 && a_k && b_k && d.epi.aux != nullptr &&
+             aligned(d.epi.aux, 16) && d.epi.rowdot != nullptr;
+    case kEpiBiasDropoutAdd:
+      return unbatched(d) && d.bias == nullptr && d.epi.aux != nullptr && aligned(d.epi.aux, 16) &&
+             d.epi.aux_ld % 8 == 0 && d.epi.vec != nullptr && aligned(d.epi.vec, 16) && aligned(d.epi.plain, 16);
+    case kEpiGeluBwd:  // inside a pair only
+      return unbatched(d) && d.bias == nullptr && d.epi.aux != nullptr && aligned(d.epi.aux, 16) &&
+             d.epi.aux_ld % 8 == 0 && d.epi.colsum_partial != nullptr && aligned(d.epi.colsum_partial, 16) &&
+             d.epi.colsum_out != nullptr;
+  }
+  return false;
+}
+
+size_t gemm_scratch_bytes(int dtype, const GemmDesc& d) {
+  if (dtype != 1 || !unbatched(d)) return 0;
+  const RaggedChoice c = ragged_product(d);
+  return gemm_whole_takes(d, c) ? 0 : c.scratch_bytes;
+}
+
+hipError_t gemm(int dtype, const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st) {
+  if (!gemm_mfma_supported(dtype, d)) {
+    if (d.epi.kind != kEpiNone) return hipErrorInvalidValue;  // only the matrix-core kernels carry epilogues
+    return gemm_generic(dtype, d, st);
+  }
+  if (d.epi.kind == kEpiGeluBwd) return hipErrorInvalidValue;
+  if (d.causal != kCausalNone) return gemm_attention(d, st);
+  if (gemm_whole_takes(d, ragged_product(d))) return gemm_whole(d, st);
+  return gemm_ragged(d, scratch, scratch_bytes, st);
+}
+
+bool gemm_mfma_pair_supported(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  if (!gemm_mfma_supported(dtype, dgrad) || !gemm_mfma_supported(dtype, wgrad)) return false;
+  if (!unbatched(dgrad) || !unbatched(wgrad)) return false;
+  if (!(dgrad.a_sk == 1 && dgrad.b_sn == 1 && dgrad.b_sk != 1)) return false;  // A K-major, B MN-major
+  if (!(wgrad.a_sm == 1 && wgrad.a_sk != 1 && wgrad.b_sn == 1 && wgrad.b_sk != 1)) return false;
+  return wgrad.epi.kind == kEpiNone && (dgrad.epi.kind == kEpiNone || dgrad.epi.kind == kEpiGeluBwd);
+}
+
+bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  if (!gemm_mfma_pair_supported(dtype, dgrad, wgrad)) return false;
+  // With few rows the plain product is cut into K ranges, which the epilogue's column sums rule out; a
+  // GeLU kernel of its own (two launches, three passes over [M, N]) costs less than the uncut product.
+  GemmDesc plain = dgrad;
+  plain.epi = GemmEpilogue{};
+  return pair_us(dgrad, wgrad) <= pair_us(plain, wgrad) + 8.0 + 6.0 * dgrad.M * dgrad.N / 4.0e6;
+}
+
+size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  if (dtype != 1) return 0;
+  return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair_scratch_bytes(dgrad, wgrad) : ragged_pair(dgrad, wgrad).scratch_bytes;
+}
+
+size_t gemm_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  const int rows = uses_whole_pair(dgrad, wgrad) ? dgrad.M / 128 : ragged_pair(dgrad, wgrad).colsum_rows;
+  return static_cast<size_t>(rows) * static_cast<size_t>(dgrad.N) * sizeof(float);
 }
 
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,
                      size_t scratch_bytes, hipStream_t st) {
   if (gemm_mfma_pair_supported(dtype, dgrad, wgrad))
-    return gemm_mfma_pair(dgrad, wgrad, scratch, scratch_bytes, st);
+    return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair(dgrad, wgrad, scratch, scratch_bytes, st)
+                                         : gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, st);
   if (dgrad.epi.kind != kEpiNone || wgrad.epi.kind != kEpiNone) return hipErrorInvalidValue;
-  const hipError_t e = gemm(dtype, dgrad, st);
+  const hipError_t e = gemm(dtype, dgrad, nullptr, 0, st);
   if (e != hipSuccess) return e;
-  return gemm(dtype, wgrad, st);
+  return gemm(dtype, wgrad, nullptr, 0, st);
 }
 
 }  // namespace lynx

@@ -1,0 +1,30 @@
+// The bf16 matrix-core products behind gemm() and gemm_pair(): which kernels there are, and what the
+// choice between them needs to know.  Host only.
+#pragma once
+#include "kernels.h"
+
+namespace lynx {
+
+// What the ragged kernels would do with a product (or a pair): estimated time, fp32 scratch for the
+// partial sums of cut contractions, and (pair) rows of column partials of the GeLU epilogue.
+struct RaggedChoice {
+  double us;
+  size_t scratch_bytes;
+  int colsum_rows;
+  bool largest_tile;  // 256 x 256 tiles, uncut: the whole-tile kernels do the same with fewer checks
+};
+RaggedChoice ragged_product(const GemmDesc& d);
+RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad);
+hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st);
+hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
+                            hipStream_t st);
+// Products of whole, large tiles and the products of attention (gemm_mfma.hip).
+bool gemm_whole_takes(const GemmDesc& d, const RaggedChoice& choice);
+hipError_t gemm_whole(const GemmDesc& d, hipStream_t st);
+hipError_t gemm_attention(const GemmDesc& d, hipStream_t st);
+double gemm_whole_pair_us(const GemmDesc& dgrad, const GemmDesc& wgrad);
+size_t gemm_whole_pair_scratch_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad);
+hipError_t gemm_whole_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
+                           hipStream_t st);
+
+}  // namespace lynx

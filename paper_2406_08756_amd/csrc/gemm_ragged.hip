@@ -1,0 +1,360 @@
+// bf16 matrix products whose dimensions are not whole tiles, or which the large tiles of
+// gemm_mfma.hip would leave most of the chip idle: tiles from 256 x 256 down to 64 x 64, each able
+// to overhang the operands, and contractions cut into ranges whose fp32 partial sums a second
+// launch adds in a fixed order.  plan_product / plan_pair_ragged choose by a cost model.
+#include <mutex>
+
+#include "dropout_host.h"
+#include "gemm_launch.h"
+#include "reduce_partials.h"
+
+namespace lynx {
+namespace {
+
+// The tiles.  BK and ring depth per tile: one barrier per 64 contraction indices pays where a slab is
+// so little work that the barrier and the LDS round trip dominate it (64 x 64, K = 4096, one
+// workgroup: 26.8 us with slabs of 32, 19.0 with 64) and where both operands are K-major, whose rows
+// then arrive as whole 128-byte lines (128 x 128 at 4096^3: 182 -> 151 us); with an MN-major operand
+// the deeper ring of slabs of 32 is the faster one for the large tiles (4096^3: 148 against 150, 146
+// against 153).  Eight wavefronts on the 256 x 256 tile: two per SIMD cover each other's waits
+// (8192^3: forward 999 -> 908 us, input gradient 895 -> 892).
+enum RaggedTile { kT256 = 0, kT256x128, kT128, kT128x64, kT64, kNumRaggedTiles };
+template <int TILE, bool BOTH_KMAJOR> struct TileShape;
+template <bool B> struct TileShape<kT256, B> { static constexpr int BM = 256, BN = 256, BK = 32, S = 4, share = 1, waves = 8; };
+template <bool B> struct TileShape<kT256x128, B> { static constexpr int BM = 256, BN = 128, BK = 32, S = 3, share = 2, waves = 4; };
+template <> struct TileShape<kT128, true> { static constexpr int BM = 128, BN = 128, BK = 64, S = 2, share = 2, waves = 4; };
+template <> struct TileShape<kT128, false> { static constexpr int BM = 128, BN = 128, BK = 32, S = 4, share = 2, waves = 4; };
+template <bool B> struct TileShape<kT128x64, B> { static constexpr int BM = 128, BN = 64, BK = 64, S = 3, share = 2, waves = 4; };
+template <bool B> struct TileShape<kT64, B> { static constexpr int BM = 64, BN = 64, BK = 64, S = 4, share = 2, waves = 4; };
+
+template <int TILE> constexpr int tile_threads = TileShape<TILE, false>::waves * kWave;
+template <int TILE> constexpr int tile_waves_per_simd = TileShape<TILE, false>::share * TileShape<TILE, false>::waves / 4;
+
+// Time of 32 contraction indices of a tile, in us: one workgroup on an otherwise idle chip; one on every
+// compute unit; `share` on every unit (then for all of them together).  `fixed`: what a round of
+// workgroups takes beside its contraction.  From loops of single products of 200 ms each, in which the
+// clock is what the power limit leaves, at sizes from one workgroup to eight rounds of them.
+struct TileCost {
+  int bm, bn, share;
+  double alone, one_each, full;
+  double fixed;
+  // us per 32 indices of a round of n workgroups
+  double slab(double n) const {
+    if (n <= kUnits) return alone + (one_each - alone) * n / kUnits;
+    return one_each + (full - one_each) * (n - kUnits) / (kUnits * (share - 1));
+  }
+  static constexpr int kUnits = 256;  // compute units
+};
+constexpr TileCost kTileCost[kNumRaggedTiles] = {
+    {256, 256, 1, 0.50, 0.84, 0.84, 6.0}, {256, 128, 2, 0.36, 0.60, 1.02, 5.0}, {128, 128, 2, 0.235, 0.31, 0.52, 4.0},
+    {128, 64, 2, 0.155, 0.20, 0.34, 3.5}, {64, 64, 2, 0.125, 0.15, 0.22, 3.0}};
+constexpr double kReduceFixed = 3.5, kReduceBytesPerUs = 3.0e6;
+
+constexpr int kMaxBK = 64;   // K ranges of a cut contraction are whole slabs of every tile
+constexpr int kCuts[] = {1, 2, 3, 4, 6, 8, 12, 16};   // K ranges considered
+constexpr int kMinRange = 256;                        // ... of at least this many indices
+
+int ceil_div(int a, int b) { return (a + b - 1) / b; }
+// Indices per range when K is cut into at most `want` ranges of whole slabs (of every tile).
+int range_of(int K, int want) { return ceil_div(K, kMaxBK * want) * kMaxBK; }
+
+// us of a launch of one product: rounds of `share` workgroups on every unit
+double product_cost(const TileCost& t, int M, int N, int K, int k_per) {
+  const int splits = ceil_div(K, k_per);
+  const double slabs = static_cast<double>(ceil_div(k_per < K ? k_per : K, 32));
+  long long wgs = static_cast<long long>(ceil_div(M, t.bm)) * ceil_div(N, t.bn) * splits;
+  const long long round = static_cast<long long>(TileCost::kUnits) * t.share;
+  const long long whole = wgs / round;
+  wgs -= whole * round;
+  double us = static_cast<double>(whole) * (t.fixed + slabs * t.full);
+  if (wgs > 0) us += t.fixed + slabs * t.slab(static_cast<double>(wgs));
+  if (splits > 1) us += kReduceFixed + (static_cast<double>(splits) * 4 * M * N) / kReduceBytesPerUs;
+  return us;
+}
+
+struct ProductPlan {
+  int tile, k_per;
+  double us;
+  int splits(int K) const { return ceil_div(K, k_per); }
+};
+
+ProductPlan search_product(int M, int N, int K) {
+  ProductPlan best{kT64, range_of(K, 1), 1e30};
+  for (int t = 0; t < kNumRaggedTiles; ++t)
+    for (int want : kCuts) {
+      if (want > 1 && K < kMinRange * want) break;
+      const int k_per = range_of(K, want);
+      const double us = product_cost(kTileCost[t], M, N, K, k_per);
+      if (us < best.us) best = {t, k_per, us};
+    }
+  return best;
+}
+
+// A plan is a function of the shape alone; a layer asks for the same few again and again, so every
+// thread keeps the last ones it worked out.
+template <typename Plan, int KEYS>
+struct PlanCache {
+  static constexpr int kSlots = 32;
+  struct Entry { int key[KEYS]; Plan plan; bool used; } entry[kSlots] = {};
+  template <typename F>
+  const Plan& get(const int (&key)[KEYS], F&& search) {
+    unsigned h = 0;
+    for (int k : key) h = (h ^ static_cast<unsigned>(k)) * 0x9E3779B1u;
+    Entry& e = entry[(h >> 16) % kSlots];
+    bool same = e.used;
+    for (int i = 0; i < KEYS; ++i) same = same && e.key[i] == key[i];
+    if (!same) {
+      e.plan = search();
+      for (int i = 0; i < KEYS; ++i) e.key[i] = key[i];
+      e.used = true;
+    }
+    return e.plan;
+  }
+};
+
+ProductPlan plan_product(int M, int N, int K) {
+  static thread_local PlanCache<ProductPlan, 3> cache;
+  return cache.get({M, N, K}, [&] { return search_product(M, N, K); });
+}
+
+// ---- kernels ------------------------------------------------------------------
+template <bool AK, bool BK_, int TILE>
+__global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
+gemm_ragged_kernel(MfmaGemmArgs g) {
+  using T = TileShape<TILE, AK && BK_>;
+  if (g.k_splits > 1) gemm_tile<AK, BK_, T::BM, T::BN, true, T::S, true, T::BK, T::waves>(g, blockIdx.x, blockIdx.y);
+  else gemm_tile<AK, BK_, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(g, blockIdx.x, blockIdx.y);
+}
+
+// Both products of a linear layer's backward in one launch, as gemm_mfma_pair_kernel: the weight
+// gradient's n_w workgroups first (the longer contraction), the input gradient's behind them.
+template <int TILE>
+__global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
+gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_w) {
+  using T = TileShape<TILE, false>;
+  const int x = static_cast<int>(blockIdx.x);
+  const int n_pad = (n_w + 7) & ~7;
+  if (x < n_w) {
+    if (wgrad.k_splits > 1) gemm_tile<false, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves>(wgrad, x, 0);
+    else gemm_tile<false, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(wgrad, x, 0);
+  } else if (x >= n_pad) {
+    if (dgrad.k_splits > 1) gemm_tile<true, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves>(dgrad, x - n_pad, 0);
+    else gemm_tile<true, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(dgrad, x - n_pad, 0);
+  }
+}
+
+template <bool AK, bool BK_, int TILE>
+hipError_t launch_ragged(MfmaGemmArgs a, hipStream_t st) {
+  using T = TileShape<TILE, AK && BK_>;
+  constexpr size_t smem = static_cast<size_t>(T::S) * (T::BM + T::BN) * T::BK * sizeof(bf16_t);
+  auto kern = gemm_ragged_kernel<AK, BK_, TILE>;
+  LYNX_RAISE_LDS_LIMIT(kern, smem);
+  a.tiles_m = ceil_div(a.M, T::BM);
+  a.tiles_n = ceil_div(a.N, T::BN);
+  const int ntiles = a.causal == kCausalOutLower ? a.tiles_m * (a.tiles_m + 1) / 2 : a.tiles_m * a.tiles_n * a.k_splits;
+  const bool flat = a.causal == kCausalKLeM || a.causal == kCausalKGeM;  // (tile, matrix) in x
+  hipLaunchKernelGGL(kern, flat ? dim3(ntiles * a.nz) : dim3(ntiles, a.nz), dim3(T::waves * kWave), smem, st, a);
+  return hipGetLastError();
+}
+
+template <bool AK, bool BK_>
+hipError_t launch_tile(int tile, const MfmaGemmArgs& a, hipStream_t st) {
+  switch (tile) {
+    case kT256: return launch_ragged<AK, BK_, kT256>(a, st);
+    case kT256x128: return launch_ragged<AK, BK_, kT256x128>(a, st);
+    case kT128: return launch_ragged<AK, BK_, kT128>(a, st);
+    case kT128x64: return launch_ragged<AK, BK_, kT128x64>(a, st);
+    default: return launch_ragged<AK, BK_, kT64>(a, st);
+  }
+}
+
+template <int TILE>
+hipError_t launch_ragged_pair(MfmaGemmArgs w, MfmaGemmArgs d, hipStream_t st) {
+  using T = TileShape<TILE, false>;
+  constexpr size_t smem = static_cast<size_t>(T::S) * (T::BM + T::BN) * T::BK * sizeof(bf16_t);
+  auto kern = gemm_ragged_pair_kernel<TILE>;
+  LYNX_RAISE_LDS_LIMIT(kern, smem);
+  for (MfmaGemmArgs* g : {&w, &d}) {
+    g->tiles_m = ceil_div(g->M, T::BM);
+    g->tiles_n = ceil_div(g->N, T::BN);
+  }
+  const int n_w = w.tiles_m * w.tiles_n * w.k_splits;
+  const int n_pad = (n_w + 7) & ~7;
+  hipLaunchKernelGGL(kern, dim3(n_pad + d.tiles_m * d.tiles_n * d.k_splits), dim3(T::waves * kWave), smem, st, w, d, n_w);
+  return hipGetLastError();
+}
+
+// C = round(sum over the K ranges, in range order, of partial[range][m][n] (+ bias)), and what the
+// product's epilogue does with it (GemmEpilogueKind: none, or bias + dropout + residual), for one or
+// two products: the first `n0` workgroups belong to `a`, the rest to `b`.
+__global__ void __launch_bounds__(256) splitk_finish_kernel(MfmaGemmArgs a, MfmaGemmArgs b, int n0) {
+  const bool second = static_cast<int>(blockIdx.x) >= n0;
+  const MfmaGemmArgs& g = second ? b : a;
+  const long long v = static_cast<long long>(blockIdx.x - (second ? n0 : 0)) * 256 + threadIdx.x;  // 8 consecutive n
+  const int per_row = g.N / 8;
+  if (v >= static_cast<long long>(g.M) * per_row) return;
+  const int m = static_cast<int>(v / per_row), n = static_cast<int>(v - static_cast<long long>(m) * per_row) * 8;
+  const float* p = g.partial + static_cast<long long>(m) * g.N + n;
+  float s[8];
+  load8(p, s);
+  for (int sp = 1; sp < g.k_splits; ++sp) {
+    p += static_cast<long long>(g.M) * g.N;
+    float t[8];
+    load8(p, t);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] += t[i];
+  }
+  if (g.bias != nullptr) {
+    float t[8];
+    load8(g.bias + n, t);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] += t[i];
+  }
+  bf16_t* c = g.C + static_cast<long long>(m) * g.ldc + n;
+  if (g.epi == kEpiNone) {
+    store8(c, s);
+    return;
+  }
+  float vec[8], x[8], o[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) s[i] = round_to_storage(s[i], static_cast<bf16_t*>(nullptr));
+  if (g.plain != nullptr) store8(g.plain + static_cast<long long>(m) * g.ldc + n, s);
+  load8(g.vec + n, vec);
+  load8(g.aux + static_cast<long long>(m) * g.aux_ld + n, x);
+  bias_dropout_add8(s, vec, x, g.key, (static_cast<uint64_t>(m) * static_cast<uint64_t>(g.row_len) + n) >> 3, o);
+  store8(c, o);
+}
+
+hipError_t launch_finish(const MfmaGemmArgs* a, const MfmaGemmArgs* b, hipStream_t st) {
+  auto groups = [](const MfmaGemmArgs* g) { return static_cast<int>((static_cast<long long>(g->M) * (g->N / 8) + 255) / 256); };
+  const int n0 = groups(a), n1 = b != nullptr ? groups(b) : 0;
+  hipLaunchKernelGGL(splitk_finish_kernel, dim3(n0 + n1), dim3(256), 0, st, *a, b != nullptr ? *b : *a, n0);
+  return hipGetLastError();
+}
+
+struct RaggedPairPlan {
+  int tile, w_per, d_per;   // indices per K range of the weight gradient, of the input gradient
+  double us;
+};
+
+size_t partial_bytes(int M, int N, int splits) {
+  return splits > 1 ? static_cast<size_t>(splits) * M * N * sizeof(float) : 0;
+}
+
+// us of a pair launch: the units share the work of both products; a unit cannot be done before its
+// longest workgroup is, which has a neighbour for part of its time, and on average half of a short
+// workgroup is left over at the end.
+double pair_cost(const TileCost& t, const GemmDesc& w, int w_per, const GemmDesc& d, int d_per) {
+  const int ws = ceil_div(w.K, w_per), ds = ceil_div(d.K, d_per);
+  const double nw = static_cast<double>(ceil_div(w.M, t.bm)) * ceil_div(w.N, t.bn) * ws;
+  const double nd = static_cast<double>(ceil_div(d.M, t.bm)) * ceil_div(d.N, t.bn) * ds;
+  const double sw = ceil_div(w_per < w.K ? w_per : w.K, 32), sd = ceil_div(d_per < d.K ? d_per : d.K, 32);
+  const double n = nw + nd, round = static_cast<double>(TileCost::kUnits) * t.share;
+  const double rate = t.slab(n < round ? n : round);            // of a round as full as this launch's
+  const double at_once = n < round ? n : round;
+  const double even = (nw * sw + nd * sd) * rate / at_once + (n > round ? 0.5 * (sw < sd ? sw : sd) * rate : 0.0);
+  const double longest = (sw > sd ? sw : sd) * (n <= round ? rate : 0.5 * (t.one_each + t.full));
+  double us = t.fixed * (1.0 + 0.5 * n / round) + (longest > even ? longest : even);
+  const double bytes = static_cast<double>(partial_bytes(w.M, w.N, ws) + partial_bytes(d.M, d.N, ds));
+  if (bytes > 0.0) us += kReduceFixed + bytes / kReduceBytesPerUs;
+  return us;
+}
+
+RaggedPairPlan search_pair(const GemmDesc& w, const GemmDesc& d) {
+  // (the GeLU epilogue's column sums are formed tile by tile, so such an input gradient is not cut)
+  const bool cut_d = d.epi.kind == kEpiNone;
+  RaggedPairPlan best{kT64, range_of(w.K, 1), range_of(d.K, 1), 1e30};
+  for (int t = 0; t < kNumRaggedTiles; ++t) {
+    if (t == kT128x64) continue;   // (no pair kernel of this tile)
+    for (int cw : kCuts) {
+      if (cw > 1 && w.K < kMinRange * cw) break;
+      for (int cd : kCuts) {
+        if (cd > 1 && (!cut_d || d.K < kMinRange * cd)) break;
+        const double us = pair_cost(kTileCost[t], w, range_of(w.K, cw), d, range_of(d.K, cd));
+        if (us < best.us) best = {t, range_of(w.K, cw), range_of(d.K, cd), us};
+      }
+    }
+  }
+  return best;
+}
+
+RaggedPairPlan plan_pair_ragged(const GemmDesc& w, const GemmDesc& d) {
+  static thread_local PlanCache<RaggedPairPlan, 7> cache;
+  return cache.get({w.M, w.N, w.K, d.M, d.N, d.K, d.epi.kind}, [&] { return search_pair(w, d); });
+}
+
+}  // namespace
+
+RaggedChoice ragged_product(const GemmDesc& d) {
+  const ProductPlan p = plan_product(d.M, d.N, d.K);
+  return {p.us, partial_bytes(d.M, d.N, p.splits(d.K)), 0, p.tile == kT256 && p.splits(d.K) == 1};
+}
+
+hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st) {
+  MfmaGemmArgs a = make_args(d);
+  const bool a_k = d.a_sk == 1, b_k = d.b_sk == 1;
+  int tile;
+  if (d.causal == kCausalNone && a.nz == 1) {
+    const ProductPlan p = plan_product(d.M, d.N, d.K);
+    tile = p.tile;
+    if (p.splits(d.K) > 1) {
+      // the cut is part of the shape's summation order: no silent change where scratch is short
+      if (scratch == nullptr || scratch_bytes < partial_bytes(d.M, d.N, p.splits(d.K))) return hipErrorInvalidValue;
+      a.k_splits = p.splits(d.K);
+      a.k_per = p.k_per;
+      a.partial = scratch;
+    }
+  } else {
+    // attention products: 128 rows (the zero padding of the seq x seq operands reaches the next
+    // multiple of 128), and a head dimension of up to 64 is half a tile wide
+    tile = d.causal == kCausalOutLower || d.N > 64 ? kT128 : kT128x64;
+  }
+  hipError_t e;
+  if (a_k && b_k) e = launch_tile<true, true>(tile, a, st);
+  else if (a_k) e = launch_tile<true, false>(tile, a, st);
+  else if (!b_k) e = launch_tile<false, false>(tile, a, st);
+  else return hipErrorInvalidValue;
+  if (e != hipSuccess || a.k_splits == 1) return e;
+  return launch_finish(&a, nullptr, st);
+}
+
+RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  const RaggedPairPlan p = plan_pair_ragged(wgrad, dgrad);
+  const int ws = ceil_div(wgrad.K, p.w_per), ds = ceil_div(dgrad.K, p.d_per);
+  return {p.us, partial_bytes(wgrad.M, wgrad.N, ws) + partial_bytes(dgrad.M, dgrad.N, ds),
+          ceil_div(dgrad.M, kTileCost[p.tile].bm / 2), p.tile == kT256 && ds == 1};
+}
+
+hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
+                            hipStream_t st) {
+  const RaggedPairPlan p = plan_pair_ragged(wgrad, dgrad);
+  MfmaGemmArgs d = make_args(dgrad), w = make_args(wgrad);
+  w.k_splits = ceil_div(w.K, p.w_per);
+  w.k_per = p.w_per;
+  d.k_splits = ceil_div(d.K, p.d_per);
+  d.k_per = p.d_per;
+  const size_t w_bytes = partial_bytes(w.M, w.N, w.k_splits), d_bytes = partial_bytes(d.M, d.N, d.k_splits);
+  if (w_bytes + d_bytes > 0 && (scratch == nullptr || scratch_bytes < w_bytes + d_bytes)) return hipErrorInvalidValue;
+  w.partial = scratch;
+  d.partial = scratch + w_bytes / sizeof(float);
+  hipError_t e;
+  switch (p.tile) {
+    case kT256: e = launch_ragged_pair<kT256>(w, d, st); break;
+    case kT256x128: e = launch_ragged_pair<kT256x128>(w, d, st); break;
+    case kT128: e = launch_ragged_pair<kT128>(w, d, st); break;
+    default: e = launch_ragged_pair<kT64>(w, d, st); break;
+  }
+  if (e != hipSuccess) return e;
+  if (w.k_splits > 1 && d.k_splits > 1) e = launch_finish(&w, &d, st);
+  else if (w.k_splits > 1) e = launch_finish(&w, nullptr, st);
+  else if (d.k_splits > 1) e = launch_finish(&d, nullptr, st);
+  if (e != hipSuccess) return e;
+  if (dgrad.epi.kind == kEpiGeluBwd) {
+    launch_reduce_partials<bf16_t>(dgrad.epi.colsum_partial, static_cast<bf16_t*>(dgrad.epi.colsum_out), nullptr,
+                                   nullptr, ceil_div(dgrad.M, kTileCost[p.tile].bm / 2), dgrad.N, st);
+    return hipGetLastError();
+  }
+  return hipSuccess;
+}
+
+}  // namespace lynx

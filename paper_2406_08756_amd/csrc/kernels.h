@@ -119,7 +119,7 @@ enum GemmEpilogueKind : int {
   kEpiBiasDropoutAdd = 1,
   // GeLU backward (input gradient of FC2 only, inside gemm_pair): C = P gelu'(aux) and
   // colsum_out[n] = sum_m C[m, n] (the FC1 bias gradient), reduced in two fixed-order stages
-  // through `colsum_partial` (gemm_colsum_partial_bytes).
+  // through `colsum_partial` (gemm_pair_colsum_bytes).
   kEpiGeluBwd = 2,
   // dropout + softmax backward (B5 + B4) on the score-shaped product dPd = dC V^T (causal,
   // batched): C = dS = scale aux (keep c P - rowdot), aux = the softmax output P in the layout
@@ -155,20 +155,19 @@ struct GemmDesc {
   int causal;                              // CausalMode
   GemmEpilogue epi;                        // kind 0 (none) unless the matrix-core path is used
 };
-hipError_t gemm(int dtype, const GemmDesc& d, hipStream_t st);          // picks a kernel
+// Picks a kernel.  `scratch` (fp32, 16-byte aligned, gemm_scratch_bytes or more; null when that is 0)
+// takes the partial sums of a contraction that is cut into ranges; they are added in a fixed order.
+hipError_t gemm(int dtype, const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st);
+size_t gemm_scratch_bytes(int dtype, const GemmDesc& d);                 // shapes only
 hipError_t gemm_generic(int dtype, const GemmDesc& d, hipStream_t st);  // any shape, vector ALUs
-bool gemm_mfma_supported(int dtype, const GemmDesc& d);                  // bf16, tile-aligned, unbatched
-hipError_t gemm_mfma(const GemmDesc& d, hipStream_t st);                // matrix cores
-// Input gradient and weight gradient of one linear layer, in one launch when the
-// matrix-core kernel can pair them, else one after the other.
-// `scratch` (fp32, 16-byte aligned, gemm_pair_scratch_bytes or more; may be null) lets the
-// weight gradient be cut into K ranges whose partial sums are added in a fixed order.
+bool gemm_mfma_supported(int dtype, const GemmDesc& d);                  // the bf16 matrix-core kernels take it
+// Input gradient and weight gradient of one linear layer, in one launch when the matrix-core
+// kernels can pair them, else one after the other.  `scratch` as above (gemm_pair_scratch_bytes).
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,
                      size_t scratch_bytes, hipStream_t st);
-size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // shapes only
+size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // shapes and epilogue only
 bool gemm_mfma_pair_supported(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);
-size_t gemm_colsum_partial_bytes(int M, int N);  // kEpiGeluBwd
-hipError_t gemm_mfma_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
-                          hipStream_t st);
+bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // supported, and it pays
+size_t gemm_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad);  // kEpiGeluBwd: its column partials
 
 }  // namespace lynx

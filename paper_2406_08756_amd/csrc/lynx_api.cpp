@@ -308,6 +308,17 @@ GemmDesc attn_cols(const void* sq, const void* y, long long ldy, void* out, long
   return g;
 }
 
+// One linear product, with scratch of its own for the partial sums of a cut contraction.
+lynx_status run_linear(Ctx& cx, int slot, const GemmDesc& g) {
+  const int dt = cx.L->D.dtype;
+  const size_t bytes = lynx::gemm_scratch_bytes(dt, g);
+  Temp scratch;
+  if (bytes > 0) LYNX_TRY(alloc_temp(cx, bytes, &scratch));
+  LYNX_LAUNCH(cx, slot, lynx::gemm(dt, g, bytes > 0 ? reinterpret_cast<float*>(temp_ptr(cx, scratch)) : nullptr, bytes, cx.st));
+  free_temp(cx, &scratch);
+  return LYNX_OK;
+}
+
 // ---- forward operators ------------------------------------------------------
 // Runs OP_i; its inputs are resident.  `fuse_dropout`: OP4 also emits Pd
 // (then OP5 is skipped by the caller); `write_p`: whether OP4 stores P.
@@ -332,13 +343,11 @@ lynx_status run_op(Ctx& cx, int i, bool fuse_dropout = false, bool write_p = tru
                                           L->cfg.ln_eps, cx.st));
       break;
     case 2:
-      LYNX_LAUNCH(cx, i, lynx::gemm(dt, linear_fwd(act_ptr(cx, 1), w.wqkv, w.bqkv, act_ptr(cx, 2), D.T,
-                                                3 * D.p, D.h), cx.st));
-      break;
+      return run_linear(cx, i, linear_fwd(act_ptr(cx, 1), w.wqkv, w.bqkv, act_ptr(cx, 2), D.T, 3 * D.p, D.h));
     case 3:
       LYNX_LAUNCH(cx, i, lynx::gemm(dt, attn_outer(col_block(act_ptr(cx, 2), D, 0), 3 * D.p,
                                                 col_block(act_ptr(cx, 2), D, 1), 3 * D.p,
-                                                act_ptr(cx, 3), D), cx.st));
+                                                act_ptr(cx, 3), D), nullptr, 0, cx.st));
       break;
     case 4: {
       void* pd = nullptr;
@@ -357,12 +366,10 @@ lynx_status run_op(Ctx& cx, int i, bool fuse_dropout = false, bool write_p = tru
       break;
     case 6:
       LYNX_LAUNCH(cx, i, lynx::gemm(dt, attn_rows(act_ptr(cx, 5), col_block(act_ptr(cx, 2), D, 2),
-                                               3 * D.p, act_ptr(cx, 6), D.p, D), cx.st));
+                                               3 * D.p, act_ptr(cx, 6), D.p, D), nullptr, 0, cx.st));
       break;
     case 7:
-      LYNX_LAUNCH(cx, i, lynx::gemm(dt, linear_fwd(act_ptr(cx, 6), w.wo, nullptr, act_ptr(cx, 7), D.T,
-                                                D.h, D.p), cx.st));
-      break;
+      return run_linear(cx, i, linear_fwd(act_ptr(cx, 6), w.wo, nullptr, act_ptr(cx, 7), D.T, D.h, D.p));
     case 8:
       LYNX_LAUNCH(cx, i, lynx::bias_dropout_add_fwd(dt, act_ptr(cx, 7), w.bo, act_ptr(cx, 0),
                                                  act_ptr(cx, 8), D.T, D.h, 1, dropout_params(L),
@@ -374,17 +381,13 @@ lynx_status run_op(Ctx& cx, int i, bool fuse_dropout = false, bool write_p = tru
                                           L->cfg.ln_eps, cx.st));
       break;
     case 10:
-      LYNX_LAUNCH(cx, i, lynx::gemm(dt, linear_fwd(act_ptr(cx, 9), w.w1, w.b1, act_ptr(cx, 10), D.T,
-                                                D.f, D.h), cx.st));
-      break;
+      return run_linear(cx, i, linear_fwd(act_ptr(cx, 9), w.w1, w.b1, act_ptr(cx, 10), D.T, D.f, D.h));
     case 11:
       LYNX_LAUNCH(cx, i, lynx::gelu_fwd(dt, act_ptr(cx, 10), act_ptr(cx, 11),
                                      static_cast<size_t>(D.T) * D.f, cx.st));
       break;
     case 12:
-      LYNX_LAUNCH(cx, i, lynx::gemm(dt, linear_fwd(act_ptr(cx, 11), w.w2, nullptr, act_ptr(cx, 12),
-                                                D.T, D.h, D.f), cx.st));
-      break;
+      return run_linear(cx, i, linear_fwd(act_ptr(cx, 11), w.w2, nullptr, act_ptr(cx, 12), D.T, D.h, D.f));
     case 13:
       LYNX_LAUNCH(cx, i, lynx::bias_dropout_add_fwd(dt, act_ptr(cx, 12), w.b2, act_ptr(cx, 8),
                                                  act_ptr(cx, 13), D.T, D.h, 2, dropout_params(L),
@@ -433,8 +436,7 @@ lynx_status run_fused_linear(Ctx& cx, int lin) {
   const bool keep_product = (cx.bk->retain >> lin) & 1u;
   if (keep_product) LYNX_TRY(alloc_act(cx, lin));
   LYNX_TRY(alloc_act(cx, lin + 1));
-  LYNX_LAUNCH(cx, lin, lynx::gemm(cx.L->D.dtype, fused_linear_desc(cx, lin, keep_product), cx.st));
-  return LYNX_OK;
+  return run_linear(cx, lin, fused_linear_desc(cx, lin, keep_product));
 }
 
 // Operators 3-6 as one launch (attn_fused.hip): C and its row statistics from QKV.
@@ -570,11 +572,14 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   if (ln_bytes > scratch_bytes) scratch_bytes = ln_bytes;
   {  // fp32 partial sums of weight gradients that are cut into K ranges
     const int lin[4][2] = {{D.h, D.f}, {D.f, D.h}, {D.h, D.p}, {3 * D.p, D.h}};  // {outputs, inputs}
-    for (const auto& nk : lin) {
-      const size_t b = lynx::gemm_pair_scratch_bytes(dt, linear_dgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]),
-                                                     linear_wgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]));
-      if (b > scratch_bytes) scratch_bytes = b;
-    }
+    for (const auto& nk : lin)
+      for (int gelu = 0; gelu <= (&nk == &lin[0] ? 1 : 0); ++gelu) {
+        // (FC2's input gradient carries the GeLU backward where it can; its plan is another then)
+        GemmDesc d = linear_dgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
+        d.epi.kind = gelu ? lynx::kEpiGeluBwd : lynx::kEpiNone;
+        const size_t b = lynx::gemm_pair_scratch_bytes(dt, d, linear_wgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]));
+        if (b > scratch_bytes) scratch_bytes = b;
+      }
   }
   Temp scratch, t_dv2, t_dg, t_du, t_dy2, t_dx2, t_do, t_dc, t_dpd, t_dqkv, t_dy1;
   LYNX_TRY(alloc_temp(cx, scratch_bytes, &scratch));
@@ -594,14 +599,14 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
     GemmDesc dg = linear_dgrad(temp_ptr(cx, t_dv2), w.w2, temp_ptr(cx, t_du), D.T, D.h, D.f);
     const GemmDesc wg = linear_wgrad(temp_ptr(cx, t_dv2), act_ptr(cx, 11), gr->w2, D.T, D.h, D.f);
     Temp t_colsum;
-    LYNX_TRY(alloc_temp(cx, lynx::gemm_colsum_partial_bytes(D.T, D.f), &t_colsum));
     dg.epi.kind = lynx::kEpiGeluBwd;
+    LYNX_TRY(alloc_temp(cx, lynx::gemm_pair_colsum_bytes(dg, wg), &t_colsum));
     dg.epi.aux = act_ptr(cx, 10);
     dg.epi.aux_ld = D.f;
     dg.epi.colsum_partial = reinterpret_cast<float*>(temp_ptr(cx, t_colsum));
     dg.epi.colsum_out = gr->b1;
-    if (lynx::gemm_mfma_pair_supported(dt, dg, wg)) {
-      LYNX_LAUNCH(cx, kB12Grads, lynx::gemm_mfma_pair(dg, wg, scr, scratch_bytes, cx.st));
+    if (lynx::gemm_pair_absorbs_gelu(dt, dg, wg)) {
+      LYNX_LAUNCH(cx, kB12Grads, lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, cx.st));
       free_temp(cx, &t_colsum);
       free_temp(cx, &t_dv2);
       free_act(cx, 11);
@@ -673,7 +678,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   auto launch_dv = [&]() -> lynx_status {
     LYNX_LAUNCH(cx, kB6DV, lynx::gemm(dt, attn_cols(act_ptr(cx, 5), temp_ptr(cx, t_dc), D.p,
                                              const_cast<char*>(col_block(dqkv, D, 2)), 3 * D.p, D),
-                               cx.st));
+                               nullptr, 0, cx.st));
     return LYNX_OK;
   };
   if (dv_first) {
@@ -692,10 +697,10 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
     LYNX_LAUNCH(cx, kB6RowDot, lynx::attn_rowdot(dt, temp_ptr(cx, t_dc), act_ptr(cx, 6),
                                                  reinterpret_cast<float*>(temp_ptr(cx, t_rowdot)), D.b, D.a, D.s,
                                                  D.d, D.p, cx.st));
-    LYNX_LAUNCH(cx, kB654DScores, lynx::gemm_mfma(dpd, cx.st));
+    LYNX_LAUNCH(cx, kB654DScores, lynx::gemm(dt, dpd, nullptr, 0, cx.st));
   } else {
     dpd.epi = lynx::GemmEpilogue{};
-    LYNX_LAUNCH(cx, kB6DPd, lynx::gemm(dt, dpd, cx.st));
+    LYNX_LAUNCH(cx, kB6DPd, lynx::gemm(dt, dpd, nullptr, 0, cx.st));
   }
   free_temp(cx, &t_rowdot);
   if (cx.bk->fused_attn) {
@@ -719,10 +724,10 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   // B3: S = Q K^T
   LYNX_LAUNCH(cx, kB3DQ, lynx::gemm(dt, attn_rows(temp_ptr(cx, t_dpd), col_block(qkv, D, 1), 3 * D.p,
                                            const_cast<char*>(col_block(dqkv, D, 0)), 3 * D.p, D),
-                             cx.st));
+                             nullptr, 0, cx.st));
   LYNX_LAUNCH(cx, kB3DK, lynx::gemm(dt, attn_cols(temp_ptr(cx, t_dpd), col_block(qkv, D, 0), 3 * D.p,
                                            const_cast<char*>(col_block(dqkv, D, 1)), 3 * D.p, D),
-                             cx.st));
+                             nullptr, 0, cx.st));
   free_temp(cx, &t_dpd);
   free_act(cx, 3);
   LYNX_TRY(tap(cx, 2, dqkv));
@@ -932,13 +937,13 @@ size_t lynx_workspace_bytes_for_schedule(const lynx_layer_config* cfg, uint32_t 
   lynx_layer_s L;
   L.cfg = *cfg;
   L.D = D;
-  L.base = nullptr;
   L.book.arena = Arena(static_cast<size_t>(1) << 60);
   Ctx cx{&L, &L.book, false, nullptr};
   // Nothing is launched; the placeholders only have to look like what a real call passes
   // (non-null, aligned), so that the rehearsal takes the kernel path a real call takes.
   void* const fake = reinterpret_cast<void*>(static_cast<uintptr_t>(Arena::kAlign));
   const lynx_grads g{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
+  L.base = static_cast<char*>(fake);
   L.params = lynx_params{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
   L.x = fake;
   L.out = fake;

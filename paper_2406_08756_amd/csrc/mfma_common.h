@@ -26,17 +26,22 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
+__device__ __forceinline__ void wait_lgkmcnt0() {
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8));
+}
 // Workgroup barrier that neither the optimiser nor the scheduler moves memory
 // accesses across (and that, unlike __syncthreads, does not drain the loads
-// still in flight).
+// still in flight).  This wavefront's LDS accesses are complete before it: a
+// fragment that is merely requested when the barrier opens can be overtaken by
+// another wavefront's writes to the buffer the barrier releases.  (WAITED: the
+// caller has just waited for them.)
+template <bool WAITED = false>
 __device__ __forceinline__ void block_barrier() {
   asm volatile("" ::: "memory");
+  if (!WAITED) wait_lgkmcnt0();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
-}
-__device__ __forceinline__ void wait_lgkmcnt0() {
-  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8));
 }
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
@@ -64,48 +69,58 @@ template <> struct Frag<false> {
   __device__ __forceinline__ void settle() { asm volatile("" : "+v"(lo), "+v"(hi)); }
 };
 
-// One slab (ROWS x 32 elements) of an operand.
-template <int ROWS, bool KMAJOR>
+// One slab (ROWS x BK elements) of an operand, BK = 32 or 64, loaded by WAVES wavefronts.
+template <int ROWS, bool KMAJOR, int BK = kBK, int WAVES = kWaves>
 struct Slab {
-  static constexpr int kElems = ROWS * kBK;
-  static constexpr int kLoadsPerWave = ROWS / 16 / kWaves;  // 1 KB direct loads per wavefront
-  static_assert(ROWS % (16 * kWaves) == 0, "slab must split over the wavefronts");
-  // 16-byte chunk permutation of row `row` of a K-major slab (see the file comment of gemm_mfma.hip)
-  __device__ static __forceinline__ int kswz(int row) { return (row >> 2) & 3; }
+  static constexpr int kElems = ROWS * BK;
+  static constexpr int kLoadsPerWave = kElems / 512 / WAVES;  // 1 KB direct loads per wavefront
+  static constexpr int kLanesPerRow = BK / 8;               // K-major: 16-byte chunks per row
+  static constexpr int kRowChunks = ROWS / 8;               // MN-major: 16-byte chunks per k-row
+  static constexpr int kRowsPerLoad = 64 / kRowChunks;      // MN-major: k-rows per 1 KB
+  static_assert(kElems % (512 * WAVES) == 0 && (BK == 32 || BK == 64), "slab must split over the wavefronts");
+  // 16-byte chunk permutation of row `row` of a K-major slab: 16 lanes of a fragment read are 16
+  // consecutive rows, and their chunks have to fall into 16 different 16-byte columns of the 64
+  // banks, of which a row covers a quarter (BK = 32) or half
+  __device__ static __forceinline__ int kswz(int row) { return BK == 32 ? (row >> 2) & 3 : (row >> 1) & 7; }
+  // ... and of k-row `k` of an MN-major slab: four consecutive k-rows in four different 64-byte
+  // windows of the 64 banks (a row of 64 elements is half the banks wide, so its parity does half of it)
+  __device__ static __forceinline__ int mnswz(int k) { return ROWS >= 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; }
 
-  // Global element offset, relative to the slab origin (row0, k0), that lane
-  // `lane` fetches in this wavefront's j-th load; and that load's LDS offset.
-  __device__ static __forceinline__ long long global_offset(int wave, int j, int lane, long long ld) {
-    const int q = wave + kWaves * j;  // which 1 KB piece of the slab
-    if (KMAJOR) {
-      const int row = 16 * q + (lane >> 2);
-      const int chunk = (lane & 3) ^ kswz(row);
-      return static_cast<long long>(row) * ld + chunk * 8;
-    } else {
-      constexpr int kRowChunks = ROWS / 8;          // 16-byte chunks per k-row
-      constexpr int kRowsPerLoad = 64 / kRowChunks; // k-rows per 1 KB
-      const int k = kRowsPerLoad * q + lane / kRowChunks;
-      const int chunk = (lane % kRowChunks) ^ ((k & 3) << 2);
-      return static_cast<long long>(k) * ld + chunk * 8;
-    }
+  // Which elements lane `lane` fetches in this wavefront's j-th load: 8 consecutive ones along
+  // the contiguous index, starting at row mn and contraction index k of the slab.
+  __device__ static __forceinline__ int lane_mn(int wave, int j, int lane) {
+    const int q = wave + WAVES * j;  // which 1 KB piece of the slab
+    if (KMAJOR) return (64 / kLanesPerRow) * q + lane / kLanesPerRow;
+    return ((lane % kRowChunks) ^ mnswz(lane_k(wave, j, lane))) * 8;
   }
-  __device__ static __forceinline__ int lds_offset(int wave, int j) { return (wave + kWaves * j) * 512; }
+  __device__ static __forceinline__ int lane_k(int wave, int j, int lane) {
+    const int q = wave + WAVES * j;
+    if (KMAJOR) return ((lane % kLanesPerRow) ^ kswz(lane_mn(wave, j, lane))) * 8;
+    return kRowsPerLoad * q + lane / kRowChunks;
+  }
+  // Global element offset of that fetch relative to the slab origin (row0, k0), and the
+  // load's LDS offset.
+  __device__ static __forceinline__ long long global_offset(int wave, int j, int lane, long long ld) {
+    const long long mn = lane_mn(wave, j, lane), k = lane_k(wave, j, lane);
+    return KMAJOR ? mn * ld + k : k * ld + mn;
+  }
+  __device__ static __forceinline__ int lds_offset(int wave, int j) { return (wave + WAVES * j) * 512; }
 
-  // MFMA operand fragment: 8 consecutive k (at 16 ks + 8 (lane / 32)) of slab
+  // MFMA operand fragment of step ks: 8 consecutive k (at 16 ks + 8 (lane / 32)) of slab
   // row tile_row0 + lane % 32.
   __device__ static __forceinline__ Frag<KMAJOR> fragment(const bf16_t* slab, int tile_row0, int ks, int lane) {
     Frag<KMAJOR> f;
     if constexpr (KMAJOR) {
       const int r = tile_row0 + (lane & 31);
       const int chunk = (2 * ks + (lane >> 5)) ^ kswz(r);
-      f.v = *reinterpret_cast<const bf16x8_t*>(slab + r * kBK + chunk * 8);
+      f.v = *reinterpret_cast<const bf16x8_t*>(slab + r * BK + chunk * 8);
     } else {
       // four blocks of 16 lanes: block b holds rows (b & 1) * 16.. of k-group b >> 1; in a
       // block, lane i points at k-row i / 4, columns 4 (i % 4)..+3 and receives column i.
       const int b = lane >> 4, i = lane & 15;
       const int k = ks * 16 + (b >> 1) * 8 + (i >> 2);
       const int col = tile_row0 + (b & 1) * 16 + ((i & 3) << 2);
-      const int sw = (k & 3) << 2;  // same for k and k + 4
+      const int sw = mnswz(k);  // same for k and k + 4
       const bf16_t* p = slab + k * ROWS + (((col >> 3) ^ sw) << 3) + (col & 7);
       typedef const __attribute__((address_space(3))) bf16_t* lds_ptr_t;
       const uint32_t addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)(p)));

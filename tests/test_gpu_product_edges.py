@@ -1,0 +1,62 @@
+"""Matrix products at the sizes where a tile, a contraction slab or a K range can go wrong: one octet
+more or less than a tile, a contraction of a single octet, head dimensions around the two the score
+kernels are built for, few rows against a long contraction (cut into ranges).  Whole layers against the
+fp64 oracle at the suite's tolerance (one rounding of 2^-9 per named activation, at most twelve in a row
+that add in quadrature: 2e-2 of the largest entry in bf16, 1e-4 in fp32), twice under store-all and once
+under full recomputation with the same bits."""
+import numpy as np
+import pytest
+import torch
+
+import lynx_synth as synth
+from oracle import lynx_oracle as orc
+from oracle import policy_model as pm
+from harness import GpuLayer, rel_err
+
+pytestmark = pytest.mark.gpu
+
+TOL = {synth.F32: 1e-4, synth.BF16: 2e-2}
+
+# name: (dtype, hidden, heads, head_dim, ffn, seq, micro_batch)
+SHAPES = {
+    "octets_bf16": (synth.BF16, 8, 1, 8, 8, 8, 1),
+    "one_over_64": (synth.BF16, 72, 1, 72, 136, 72, 1),
+    "one_under_128": (synth.BF16, 120, 1, 120, 248, 120, 2),
+    "one_over_128": (synth.BF16, 136, 1, 136, 264, 136, 1),
+    "head64_tiles": (synth.BF16, 256, 3, 64, 512, 384, 1),
+    "head56_ragged": (synth.BF16, 200, 2, 56, 328, 264, 2),
+    "head128_ragged": (synth.BF16, 264, 2, 128, 520, 392, 1),
+    "cut_contractions": (synth.BF16, 2056, 1, 64, 4104, 24, 1),
+    "long_tokens_narrow": (synth.BF16, 72, 1, 40, 72, 520, 6),
+    "wide_ragged": (synth.BF16, 2312, 2, 104, 2568, 520, 2),
+}
+
+
+def run(layer, X, dOUT, mask):
+    layer.forward(X, mask, step=2)
+    layer.backward(dOUT)
+    torch.cuda.synchronize()
+    return [layer.out.clone(), layer.dx.clone()] + [layer.grads[k].clone() for k in synth.PARAM_NAMES]
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_layer_at_tile_edges(name):
+    dtype, h, a, d, f, s, b = SHAPES[name]
+    cfg = synth.LayerConfig(dtype, h, a, d, f, s, b, tp_size=2, tp_rank=1, seed=7, layer_id=3)
+    params = synth.make_params(cfg, random_ln=True)
+    X, dOUT = synth.make_x(cfg), synth.make_dout(cfg)
+    acts, grads = orc.layer_forward_backward(cfg, params, X, dOUT, step=2)
+    from paper_2406_08756_amd import binding as B
+    layer = GpuLayer(cfg, params, workspace_bytes=max(B.lynx_workspace_bytes(cfg, m)
+                                                      for m in (pm.STORE_ALL, pm.FULL_RECOMPUTE)))
+    layer.workspace.fill_(0xFF)              # NaNs: nothing may be read that was not written
+    first = run(layer, X, dOUT, pm.STORE_ALL)
+    got = layer.results()
+    out = layer.out.float().cpu().numpy().astype(np.float64)
+    assert rel_err(out, acts["OUT"]) <= TOL[dtype]
+    for k, ref in grads.items():
+        assert rel_err(got[k], ref) <= TOL[dtype], (k, rel_err(got[k], ref))
+    for mask in (pm.STORE_ALL, pm.FULL_RECOMPUTE):
+        again = run(layer, X, dOUT, mask)
+        assert all(torch.equal(p, q) for p, q in zip(first, again)), hex(mask)
+    layer.close()
