@@ -18,8 +18,6 @@ double pair_us(const GemmDesc& dgrad, const GemmDesc& wgrad) {
 
 bool unbatched(const GemmDesc& d) { return d.causal == kCausalNone && d.nz1 * d.nz2 == 1; }
 
-}  // namespace
-
 bool gemm_mfma_supported(int dtype, const GemmDesc& d) {
   if (dtype != 1 || d.M % 8 || d.N % 8 || d.K % 8 || d.M <= 0 || d.N <= 0 || d.K <= 0) return false;
   if (d.causal == kCausalOutLower && d.M != d.N) return false;
@@ -49,6 +47,12 @@ bool gemm_mfma_supported(int dtype, const GemmDesc& d) {
   return false;
 }
 
+}  // namespace
+
+bool gemm_supported(int dtype, const GemmDesc& d) {
+  return dtype == 1 ? gemm_mfma_supported(dtype, d) : gemm_f32_supported(d);
+}
+
 size_t gemm_scratch_bytes(int dtype, const GemmDesc& d) {
   if (dtype != 1 || !unbatched(d)) return 0;
   const RaggedChoice c = ragged_product(d);
@@ -56,18 +60,15 @@ size_t gemm_scratch_bytes(int dtype, const GemmDesc& d) {
 }
 
 hipError_t gemm(int dtype, const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st) {
-  if (!gemm_mfma_supported(dtype, d)) {
-    if (d.epi.kind != kEpiNone) return hipErrorInvalidValue;  // only the matrix-core kernels carry epilogues
-    return gemm_generic(dtype, d, st);
-  }
-  if (d.epi.kind == kEpiGeluBwd) return hipErrorInvalidValue;
+  if (!gemm_supported(dtype, d) || d.epi.kind == kEpiGeluBwd) return hipErrorInvalidValue;
+  if (dtype != 1) return gemm_f32(d, st);
   if (d.causal != kCausalNone) return gemm_attention(d, st);
   if (gemm_whole_takes(d, ragged_product(d))) return gemm_whole(d, st);
   return gemm_ragged(d, scratch, scratch_bytes, st);
 }
 
-bool gemm_mfma_pair_supported(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
-  if (!gemm_mfma_supported(dtype, dgrad) || !gemm_mfma_supported(dtype, wgrad)) return false;
+bool gemm_pair_supported(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  if (!gemm_supported(dtype, dgrad) || !gemm_supported(dtype, wgrad)) return false;
   if (!unbatched(dgrad) || !unbatched(wgrad)) return false;
   if (!(dgrad.a_sk == 1 && dgrad.b_sn == 1 && dgrad.b_sk != 1)) return false;  // A K-major, B MN-major
   if (!(wgrad.a_sm == 1 && wgrad.a_sk != 1 && wgrad.b_sn == 1 && wgrad.b_sk != 1)) return false;
@@ -75,7 +76,8 @@ bool gemm_mfma_pair_supported(int dtype, const GemmDesc& dgrad, const GemmDesc& 
 }
 
 bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
-  if (!gemm_mfma_pair_supported(dtype, dgrad, wgrad)) return false;
+  if (!gemm_pair_supported(dtype, dgrad, wgrad)) return false;
+  if (dtype != 1) return true;
   // With few rows the plain product is cut into K ranges, which the epilogue's column sums rule out; a
   // GeLU kernel of its own (two launches, three passes over [M, N]) costs less than the uncut product.
   GemmDesc plain = dgrad;
@@ -88,20 +90,18 @@ size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc&
   return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair_scratch_bytes(dgrad, wgrad) : ragged_pair(dgrad, wgrad).scratch_bytes;
 }
 
-size_t gemm_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad) {
+size_t gemm_pair_colsum_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  if (dtype != 1) return gemm_f32_pair_colsum_bytes(dgrad, wgrad);
   const int rows = uses_whole_pair(dgrad, wgrad) ? dgrad.M / 128 : ragged_pair(dgrad, wgrad).colsum_rows;
   return static_cast<size_t>(rows) * static_cast<size_t>(dgrad.N) * sizeof(float);
 }
 
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,
                      size_t scratch_bytes, hipStream_t st) {
-  if (gemm_mfma_pair_supported(dtype, dgrad, wgrad))
-    return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair(dgrad, wgrad, scratch, scratch_bytes, st)
-                                         : gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, st);
-  if (dgrad.epi.kind != kEpiNone || wgrad.epi.kind != kEpiNone) return hipErrorInvalidValue;
-  const hipError_t e = gemm(dtype, dgrad, nullptr, 0, st);
-  if (e != hipSuccess) return e;
-  return gemm(dtype, wgrad, nullptr, 0, st);
+  if (!gemm_pair_supported(dtype, dgrad, wgrad)) return hipErrorInvalidValue;
+  if (dtype != 1) return gemm_f32_pair(dgrad, wgrad, st);
+  return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair(dgrad, wgrad, scratch, scratch_bytes, st)
+                                       : gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, st);
 }
 
 }  // namespace lynx

@@ -1,0 +1,383 @@
+// fp32 matrix products on the matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands, fp32 sums).
+//
+// A 32 x 32 x 2 instruction occupies its SIMD's matrix pipe for 64 cycles and reads one register of
+// each operand per lane, so the contraction index can run in octets: lane half hb of a fragment holds
+// indices 8 c + 4 hb + 0..3 of its row, and instruction j of the octet multiplies element j of both halves.
+//
+// Contraction slabs travel through a four-stage LDS ring filled by direct global -> LDS loads; LDS and
+// the loads have time to spare, so no large tile is needed.  Two forms of 16 KB a stage.  64 x 64 per
+// workgroup and slabs of 32: a 32 x 32 quarter per wavefront.  32 x 32 per workgroup and slabs of 64, where
+// the larger tiles would be fewer than the compute units: each wavefront takes every fourth octet of the
+// contraction, and the four sums are added in order at the end.
+//
+// Sizes are multiples of 8, so chunks of four elements never straddle an edge.  Rows and columns beyond
+// the operands repeat the last ones and are not stored, contraction indices beyond K read zeros.
+#include "device_common.h"
+#include "dropout_host.h"
+#include "kernels.h"
+#include "mfma_common.h"
+#include "pointwise_math.h"
+#include "reduce_partials.h"
+
+#include <type_traits>
+
+namespace lynx {
+namespace {
+
+__device__ const uint4 kZeros = {0u, 0u, 0u, 0u};
+
+// One slab (ROWS x 2048 / ROWS elements, 8 KB) of an operand.
+template <int ROWS, bool KMAJOR>
+struct SlabF {
+  static constexpr int kElems = 2048, kDepth = kElems / ROWS;  // kDepth: contraction indices
+  static constexpr int kLoadsPerWave = kElems / 256 / kWaves;  // 1 KB direct loads per wavefront
+  static constexpr int kRowChunks = (KMAJOR ? kDepth : ROWS) / 4;  // 16-byte chunks per row of LDS
+  // K-major: the chunk permutation spreads 16 consecutive rows, each half the banks wide (kDepth 32) or
+  // all of them (64), over all 16-byte columns of the banks.
+  __device__ static __forceinline__ int kswz(int row) { return kDepth == 32 ? (row >> 1) & 7 : row & 15; }
+  // MN-major: the two lane halves read k-rows four apart, which have to lie in different halves of the
+  // banks.  64-wide rows: the columns of every second group of four k-rows are exchanged by halves.
+  // 32-wide rows are half the banks themselves: bits 0 and 2 of the k-row trade places.
+  __device__ static __forceinline__ int place(int k) { return ROWS == 32 ? (k & ~5) | ((k >> 2) & 1) | ((k & 1) << 2) : k; }
+  __device__ static __forceinline__ int mnswz(int k) { return ROWS == 32 ? 0 : ((k >> 2) & 1) << 5; }
+
+  // first element (row mn, contraction index k) of the four that lane `lane` fetches in load j
+  __device__ static __forceinline__ int lane_row(int wave, int j, int lane) {  // row of LDS
+    return 64 / kRowChunks * (wave + kWaves * j) + lane / kRowChunks;
+  }
+  __device__ static __forceinline__ int lane_k(int wave, int j, int lane) {
+    const int row = lane_row(wave, j, lane);
+    return KMAJOR ? ((lane % kRowChunks) ^ kswz(row)) * 4 : place(row);  // (place is its own inverse)
+  }
+  __device__ static __forceinline__ int lane_mn(int wave, int j, int lane) {
+    const int row = lane_row(wave, j, lane);
+    return KMAJOR ? row : ((lane % kRowChunks) * 4) ^ mnswz(place(row));
+  }
+  __device__ static __forceinline__ int lds_offset(int wave, int j) { return (wave + kWaves * j) * 256; }
+
+  // elements 8 c + 4 (lane / 32) + 0..3 of slab row row0 + lane % 32
+  __device__ static __forceinline__ void fragment(const float* slab, int row0, int c, int lane, float (&v)[4]) {
+    const int r = row0 + (lane & 31), hb = lane >> 5;
+    if (KMAJOR) {
+      const float32x4_t x = *reinterpret_cast<const float32x4_t*>(slab + r * kDepth + (((2 * c + hb) ^ kswz(r)) << 2));
+      v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = 8 * c + 4 * hb + j;
+        v[j] = slab[place(k) * ROWS + (r ^ mnswz(k))];
+      }
+    }
+  }
+};
+
+constexpr int kLarge = 64, kSmall = 32;   // tile sides
+constexpr int kStages = 4;
+constexpr int kPitchPad = 4;              // floats: keeps the 16-byte accesses of the staged tile off each other's banks
+constexpr size_t kLdsBytes = kStages * 2 * 2048 * sizeof(float);
+static_assert(kLdsBytes >= kWaves * 32 * (kSmall + kPitchPad) * sizeof(float) && kLdsBytes >= kLarge * (kLarge + kPitchPad) * sizeof(float),
+              "the staged tile fits the ring");
+
+// Where a tile lies and what it contracts over.
+struct F32Tile {
+  int tm, m0, n0, k_begin, k_end;
+  const float *A, *B;
+  float* C;
+};
+template <int BM>
+__device__ __forceinline__ F32Tile locate(const GemmDesc& d, int block_x, int block_z) {
+  F32Tile t;
+  const int tiles_n = (d.N + BM - 1) / BM;
+  int tn;
+  if (d.causal == kCausalOutLower) {          // square output, tiles on or below the diagonal only
+    t.tm = static_cast<int>((sqrtf(8.0f * static_cast<float>(block_x) + 1.0f) - 1.0f) * 0.5f);
+    while (t.tm * (t.tm + 1) / 2 > block_x) --t.tm;
+    while ((t.tm + 1) * (t.tm + 2) / 2 <= block_x) ++t.tm;
+    tn = block_x - t.tm * (t.tm + 1) / 2;
+  } else {
+    t.tm = block_x / tiles_n;
+    tn = block_x - t.tm * tiles_n;
+    if (d.causal == kCausalKLeM) t.tm = (d.M + BM - 1) / BM - 1 - t.tm;   // longest contraction first
+  }
+  t.m0 = t.tm * BM;
+  t.n0 = tn * BM;
+  // (the seq x seq operands are zero beyond the diagonal up to the next multiple of 128)
+  t.k_begin = d.causal == kCausalKGeM ? t.m0 : 0;
+  t.k_end = d.causal == kCausalKLeM ? min(d.K, t.m0 + BM) : d.K;
+  const int z1 = block_z / d.nz2, z2 = block_z - z1 * d.nz2;
+  t.A = static_cast<const float*>(d.A) + z1 * d.a_sz1 + z2 * d.a_sz2;
+  t.B = static_cast<const float*>(d.B) + z1 * d.b_sz1 + z2 * d.b_sz2;
+  t.C = static_cast<float*>(d.C) + z1 * d.c_sz1 + z2 * d.c_sz2;
+  return t;
+}
+
+// The store pass.  acc[r] is the element n = 8 (r / 4) + 4 (lane / 32) + r % 4, m = lane % 32 of the
+// wavefront's 32 x 32: through LDS into octets of a row, which take bias and epilogue.
+template <int BM>
+__device__ __forceinline__ void store_tile(const GemmDesc& d, const DropoutKey& key, const F32Tile& t, float* smem,
+                                           const floatx16_t& acc, int wave, int lane) {
+  constexpr bool kSum = BM == kSmall;        // the four wavefronts hold parts of the same 32 x 32
+  constexpr int kPitch = BM + kPitchPad, kPart = 32 * kPitch;
+  const int tid = threadIdx.x;
+  float* stage = smem + (kSum ? wave * kPart : (wave >> 1) * 32 * kPitch + (wave & 1) * 32);
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    *reinterpret_cast<float4*>(stage + (lane & 31) * kPitch + 8 * q + 4 * (lane >> 5)) =
+        make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+  __syncthreads();
+  constexpr int kRowOctets = BM / 8, kRowsAtOnce = kThreads / kRowOctets;
+  const int lr = tid / kRowOctets, lc = tid % kRowOctets;
+  const int n = t.n0 + lc * 8;
+  const bool col_in = n < d.N;
+  float bias[8] = {}, colacc[8] = {};
+  if (d.bias != nullptr && col_in) load8(static_cast<const float*>(d.bias) + n, bias);
+  if (d.epi.kind == kEpiBiasDropoutAdd && col_in) load8(static_cast<const float*>(d.epi.vec) + n, bias);
+#pragma unroll
+  for (int r0 = 0; r0 < BM; r0 += kRowsAtOnce) {
+    const int r = r0 + lr, m = t.m0 + r;
+    if (r >= BM || m >= d.M || !col_in) continue;
+    float v[8];
+    load8(smem + r * kPitch + lc * 8, v);
+    if (kSum) {
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) {
+        float p[8];
+        load8(smem + w * kPart + r * kPitch + lc * 8, p);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] += p[i];
+      }
+    }
+    float* c = t.C + m * d.c_sm + n;
+    if (d.epi.kind == kEpiNone) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] += bias[i];
+      store8(c, v);
+    } else {
+      float x[8], o[8];
+      load8(static_cast<const float*>(d.epi.aux) + m * d.epi.aux_ld + n, x);
+      if (d.epi.kind == kEpiBiasDropoutAdd) {
+        if (d.epi.plain != nullptr) store8(static_cast<float*>(d.epi.plain) + m * d.c_sm + n, v);
+        bias_dropout_add8(v, bias, x, key, (static_cast<uint64_t>(m) * static_cast<uint64_t>(d.N) + n) >> 3, o);
+      } else {
+        gelu_bwd8<float>(v, x, o);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) colacc[i] += o[i];
+      }
+      store8(c, o);
+    }
+  }
+  if (d.epi.kind == kEpiGeluBwd) {
+    // column sums of the tile: over the rows of a wavefront, then over the wavefronts in order
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int o = kRowOctets; o < kWave; o <<= 1) colacc[i] += __shfl_xor(colacc[i], o, kWave);
+    __syncthreads();
+    if (lane < kRowOctets)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) smem[wave * BM + lane * 8 + i] = colacc[i];
+    __syncthreads();
+    if (tid < BM && t.n0 + tid < d.N)
+      d.epi.colsum_partial[static_cast<long long>(t.tm) * d.N + t.n0 + tid] =
+          (smem[tid] + smem[BM + tid]) + (smem[2 * BM + tid] + smem[3 * BM + tid]);
+  }
+}
+
+template <bool AK, bool BK, int BM>
+__device__ __forceinline__ void f32_tile(const GemmDesc& d, const DropoutKey& key, int block_x, int block_z) {
+  constexpr int S = kStages, kAhead = S - 1;
+  using SA = SlabF<BM, AK>;
+  using SB = SlabF<BM, BK>;
+  constexpr bool kShareTile = BM == kSmall;  // the wavefronts divide the contraction, not the tile
+  constexpr int kSlab = SA::kDepth;
+  constexpr int kOctets = kSlab / 8 / (kShareTile ? kWaves : 1);  // per wavefront and slab
+  constexpr int kStage = SA::kElems + SB::kElems;
+  constexpr int kLoads = SA::kLoadsPerWave + SB::kLoadsPerWave;
+  extern __shared__ __align__(1024) unsigned char smem_raw[];
+  float* smem = reinterpret_cast<float*>(smem_raw);
+  const F32Tile t = locate<BM>(d, block_x, block_z);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = kShareTile ? 0 : (wave >> 1) * 32, wn0 = kShareTile ? 0 : (wave & 1) * 32;
+
+  const long long lda = AK ? d.a_sm : d.a_sk, ldb = BK ? d.b_sn : d.b_sk;
+  const float* ga[SA::kLoadsPerWave];
+  const float* gb[SB::kLoadsPerWave];
+#pragma unroll
+  for (int j = 0; j < SA::kLoadsPerWave; ++j) {
+    const long long mn = min(t.m0 + SA::lane_mn(wave, j, lane), d.M - (AK ? 1 : 4)), k = t.k_begin + SA::lane_k(wave, j, lane);
+    ga[j] = t.A + (AK ? mn * lda + k : k * lda + mn);
+  }
+#pragma unroll
+  for (int j = 0; j < SB::kLoadsPerWave; ++j) {
+    const long long mn = min(t.n0 + SB::lane_mn(wave, j, lane), d.N - (BK ? 1 : 4)), k = t.k_begin + SB::lane_k(wave, j, lane);
+    gb[j] = t.B + (BK ? mn * ldb + k : k * ldb + mn);
+  }
+  const long long a_step = AK ? kSlab : kSlab * lda, b_step = BK ? kSlab : kSlab * ldb;
+  const int nk = (t.k_end - t.k_begin + kSlab - 1) / kSlab;
+  const int k_rem = (t.k_end - t.k_begin) % kSlab;
+  const int tail = k_rem != 0 ? nk - 1 : -1;  // the slab that reaches beyond the contraction range
+  auto issue_load = [&](int kt, int j) {
+    float* s = smem + (kt % S) * kStage;
+    if (j < SA::kLoadsPerWave) {
+      const float* from = ga[j] + kt * a_step;
+      if (kt == tail && SA::lane_k(wave, j, lane) >= k_rem) from = reinterpret_cast<const float*>(&kZeros);
+      __builtin_amdgcn_global_load_lds((global_void_ptr)(from), (lds_void_ptr)(s + SA::lds_offset(wave, j)), 16, 0, 0);
+    } else {
+      const int jb = j - SA::kLoadsPerWave;
+      const float* from = gb[jb] + kt * b_step;
+      if (kt == tail && SB::lane_k(wave, jb, lane) >= k_rem) from = reinterpret_cast<const float*>(&kZeros);
+      __builtin_amdgcn_global_load_lds((global_void_ptr)(from), (lds_void_ptr)(s + SA::kElems + SB::lds_offset(wave, jb)), 16, 0, 0);
+    }
+  };
+
+  floatx16_t acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i)
+    if (i < nk)
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) issue_load(i, j);
+  wait_slabs<kLoads, kAhead - 1>(nk - 1);
+  block_barrier();
+  // A slab is kOctets octets of four instructions.  Over the first half of them the octets of the second
+  // half are read and the ring stage that was finished before the last barrier is refilled; then [next
+  // slab landed?] [barrier]; over the second half the next slab's first octets are read.
+  float fa[kOctets][4], fb[kOctets][4];
+  auto read = [&](const float* stage, int f, int i0) {   // f: A and B of octets i0, i0 + 1, ... in turn
+    const int i = i0 + (f >> 1), c = kShareTile ? wave + kWaves * i : i;
+    if ((f & 1) == 0) SA::fragment(stage, wm0, c, lane, fa[i]);
+    else SB::fragment(stage + SA::kElems, wn0, c, lane, fb[i]);
+  };
+#pragma unroll
+  for (int f = 0; f < kOctets; ++f) read(smem, f, 0);
+  constexpr int kHalf = 2 * kOctets;                         // instructions of half a slab
+  constexpr int kPer = (kOctets + kLoads + kHalf - 1) / kHalf;  // side operations per instruction
+  auto slab_step = [&](int kt, auto steady_tag) {
+    constexpr bool steady = decltype(steady_tag)::value;
+    const float* cur = smem + (kt % S) * kStage;
+    const float* next = smem + ((kt + 1) % S) * kStage;
+    const bool refill = steady || kt + kAhead < nk, more = steady || kt + 1 < nk;
+#pragma unroll
+    for (int m = 0; m < 2 * kHalf; ++m) {
+      if (m == kHalf) {
+        if (steady) wait_vmcnt<(kAhead - 1) * kLoads>();
+        else wait_slabs<kLoads, kAhead - 1>(nk - 2 - kt);
+        block_barrier();
+      }
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[m >> 2][m & 3], fa[m >> 2][m & 3], acc, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int op = (m % kHalf) * kPer + u;
+        if (m >= kHalf) {
+          if (op < kOctets && more) read(next, op, 0);
+        } else if (op < kOctets) {
+          read(cur, op, kOctets / 2);
+        } else if (op < kOctets + kLoads && refill) {
+          issue_load(kt + kAhead, op - kOctets);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  int kt = 0;
+  for (; kt + kAhead < (tail < 0 ? nk : tail); ++kt) slab_step(kt, std::true_type{});
+  for (; kt < nk; ++kt) slab_step(kt, std::false_type{});
+  block_barrier();
+  store_tile<BM>(d, key, t, smem, acc, wave, lane);
+}
+
+template <bool AK, bool BK, int BM>
+__global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmDesc d, DropoutKey key) {
+  f32_tile<AK, BK, BM>(d, key, blockIdx.x, blockIdx.y);
+}
+
+// Input and weight gradient of a linear layer in one launch, so that together they fill the chip.
+template <int BM>
+__global__ void __launch_bounds__(kThreads) gemm_f32_pair_kernel(GemmDesc wgrad, GemmDesc dgrad, DropoutKey key, int n_w) {
+  const int x = static_cast<int>(blockIdx.x);
+  if (x < n_w) f32_tile<false, false, BM>(wgrad, key, x, 0);
+  else f32_tile<true, false, BM>(dgrad, key, x - n_w, 0);
+}
+
+long long tiles(const GemmDesc& d, int bm) {
+  const long long tm = (d.M + bm - 1) / bm, tn = (d.N + bm - 1) / bm;
+  return d.causal == kCausalOutLower ? tm * (tm + 1) / 2 : tm * tn;
+}
+
+// 64 x 64 tiles take 1.15 times less per multiplication where they fill the chip (4096^3: 1207 against 1354 us,
+// 114 and 101 TFLOP/s; the vector-ALU kernel before these ran at 20); 32 x 32 where whole rounds of the
+// larger ones over the 256 compute units would cost more than that (256 x 256 x 1024: 24.1 against 8.5 us,
+// 85 before; 1024^3, one 64 x 64 tile per unit: 25.3 against 24.7).
+bool small_tiles(long long tiles64) { return (tiles64 + 255) / 256 * 256 > 1.15 * tiles64; }
+
+DropoutKey epilogue_key(const GemmDesc& d) {
+  return d.epi.kind == kEpiBiasDropoutAdd ? make_dropout_key(d.epi.dp, d.epi.site) : DropoutKey{};
+}
+
+template <bool AK, bool BK, int BM>
+hipError_t launch(const GemmDesc& d, hipStream_t st) {
+  hipLaunchKernelGGL((gemm_f32_kernel<AK, BK, BM>), dim3(static_cast<unsigned>(tiles(d, BM)), d.nz1 * d.nz2), dim3(kThreads),
+                     kLdsBytes, st, d, epilogue_key(d));
+  return hipGetLastError();
+}
+template <bool AK, bool BK>
+hipError_t launch(const GemmDesc& d, hipStream_t st) {
+  return small_tiles(tiles(d, 64) * d.nz1 * d.nz2) ? launch<AK, BK, 32>(d, st) : launch<AK, BK, 64>(d, st);
+}
+
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
+}  // namespace
+
+bool gemm_f32_supported(const GemmDesc& d) {
+  if (d.M % 8 || d.N % 8 || d.K % 8 || d.M <= 0 || d.N <= 0 || d.K <= 0) return false;
+  if (d.causal == kCausalOutLower && d.M != d.N) return false;
+  const bool a_k = d.a_sk == 1, b_k = d.b_sk == 1;
+  if ((!a_k && d.a_sm != 1) || (!b_k && d.b_sn != 1) || (!a_k && b_k)) return false;
+  if ((a_k ? d.a_sm : d.a_sk) % 4 || (b_k ? d.b_sn : d.b_sk) % 4 || d.c_sm % 4) return false;
+  if (d.a_sz1 % 4 || d.a_sz2 % 4 || d.b_sz1 % 4 || d.b_sz2 % 4 || d.c_sz1 % 4 || d.c_sz2 % 4) return false;
+  if (!aligned16(d.A) || !aligned16(d.B) || !aligned16(d.C) || !aligned16(d.bias)) return false;
+  switch (d.epi.kind) {
+    case kEpiNone: return true;
+    case kEpiBiasDropoutAdd:
+      return d.causal == kCausalNone && d.nz1 * d.nz2 == 1 && d.bias == nullptr && d.epi.aux != nullptr &&
+             aligned16(d.epi.aux) && d.epi.aux_ld % 4 == 0 && d.epi.vec != nullptr && aligned16(d.epi.vec) &&
+             aligned16(d.epi.plain);
+    case kEpiGeluBwd:
+      return d.causal == kCausalNone && d.nz1 * d.nz2 == 1 && d.bias == nullptr && d.epi.aux != nullptr &&
+             aligned16(d.epi.aux) && d.epi.aux_ld % 4 == 0 && d.epi.colsum_partial != nullptr && d.epi.colsum_out != nullptr;
+  }
+  return false;
+}
+
+hipError_t gemm_f32(const GemmDesc& d, hipStream_t st) {
+  if (d.epi.kind == kEpiGeluBwd) return hipErrorInvalidValue;  // in a pair only
+  if (d.a_sk != 1) return launch<false, false>(d, st);
+  return d.b_sk == 1 ? launch<true, true>(d, st) : launch<true, false>(d, st);
+}
+
+size_t gemm_f32_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  const int bm = small_tiles(tiles(dgrad, 64) + tiles(wgrad, 64)) ? 32 : 64;
+  return static_cast<size_t>((dgrad.M + bm - 1) / bm) * dgrad.N * sizeof(float);
+}
+
+hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, hipStream_t st) {
+  const bool small = small_tiles(tiles(dgrad, 64) + tiles(wgrad, 64));
+  const int bm = small ? 32 : 64;
+  const int n_w = static_cast<int>(tiles(wgrad, bm)), n_d = static_cast<int>(tiles(dgrad, bm));
+  if (small)
+    hipLaunchKernelGGL((gemm_f32_pair_kernel<32>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes, st, wgrad, dgrad,
+                       DropoutKey{}, n_w);
+  else
+    hipLaunchKernelGGL((gemm_f32_pair_kernel<64>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes, st, wgrad, dgrad,
+                       DropoutKey{}, n_w);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || dgrad.epi.kind != kEpiGeluBwd) return e;
+  launch_reduce_partials<float>(dgrad.epi.colsum_partial, static_cast<float*>(dgrad.epi.colsum_out), nullptr, nullptr,
+                                (dgrad.M + bm - 1) / bm, dgrad.N, st);
+  return hipGetLastError();
+}
+
+}  // namespace lynx

@@ -1,4 +1,4 @@
-// The bf16 matrix-core products behind gemm() and gemm_pair(): which kernels there are, and what the
+// The matrix-core products behind gemm() and gemm_pair(): which kernels there are, and what the
 // choice between them needs to know.  Host only.
 #pragma once
 #include "kernels.h"
@@ -26,5 +26,11 @@ double gemm_whole_pair_us(const GemmDesc& dgrad, const GemmDesc& wgrad);
 size_t gemm_whole_pair_scratch_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad);
 hipError_t gemm_whole_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
                            hipStream_t st);
+
+// fp32 storage (gemm_f32.hip).
+bool gemm_f32_supported(const GemmDesc& d);
+hipError_t gemm_f32(const GemmDesc& d, hipStream_t st);
+size_t gemm_f32_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad);
+hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, hipStream_t st);
 
 }  // namespace lynx

@@ -69,14 +69,6 @@ struct MfmaGemmArgs {
 // 16 bytes of zeros: what a ragged tile multiplies in place of contraction indices beyond K.
 __device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
 
-// Waits until at most n newer slabs of LOADS loads each are still in flight (n is uniform).
-template <int LOADS, int MOST>
-__device__ __forceinline__ void wait_slabs(int n) {
-  if constexpr (MOST == 0) wait_vmcnt<0>();
-  else if (n >= MOST) wait_vmcnt<MOST * LOADS>();
-  else wait_slabs<LOADS, MOST - 1>(n);
-}
-
 // One output tile: `block_x` selects the tile, `block_z` the matrix of a batch.
 //
 // RAGGED: M, N and K need not be whole tiles, only multiples of 8 (every dimension of this library

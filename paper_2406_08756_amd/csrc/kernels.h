@@ -158,16 +158,17 @@ struct GemmDesc {
 // Picks a kernel.  `scratch` (fp32, 16-byte aligned, gemm_scratch_bytes or more; null when that is 0)
 // takes the partial sums of a contraction that is cut into ranges; they are added in a fixed order.
 hipError_t gemm(int dtype, const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st);
-size_t gemm_scratch_bytes(int dtype, const GemmDesc& d);                 // shapes only
-hipError_t gemm_generic(int dtype, const GemmDesc& d, hipStream_t st);  // any shape, vector ALUs
-bool gemm_mfma_supported(int dtype, const GemmDesc& d);                  // the bf16 matrix-core kernels take it
-// Input gradient and weight gradient of one linear layer, in one launch when the matrix-core
-// kernels can pair them, else one after the other.  `scratch` as above (gemm_pair_scratch_bytes).
+size_t gemm_scratch_bytes(int dtype, const GemmDesc& d);  // shapes only
+// Sizes multiples of 8, operands 16-byte aligned and contiguous along one index, an epilogue this
+// product can carry: everything the layer asks for except fp32 with kEpiSoftmaxBwd.
+bool gemm_supported(int dtype, const GemmDesc& d);
+// Input gradient and weight gradient of one linear layer in one launch.  `scratch` as above
+// (gemm_pair_scratch_bytes).
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,
                      size_t scratch_bytes, hipStream_t st);
 size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // shapes and epilogue only
-bool gemm_mfma_pair_supported(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);
-bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // supported, and it pays
-size_t gemm_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad);  // kEpiGeluBwd: its column partials
+// Whether the input gradient should carry the GeLU backward (kEpiGeluBwd): supported, and it pays.
+bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);
+size_t gemm_pair_colsum_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // its column partials
 
 }  // namespace lynx

@@ -430,7 +430,7 @@ bool can_fuse_linear(const lynx_layer_s* L, int lin) {
   g.epi.aux = reinterpret_cast<const void*>(256);
   g.epi.aux_ld = D.h;
   g.epi.vec = reinterpret_cast<const void*>(256);
-  return lynx::gemm_mfma_supported(D.dtype, g);
+  return lynx::gemm_supported(D.dtype, g);
 }
 lynx_status run_fused_linear(Ctx& cx, int lin) {
   const bool keep_product = (cx.bk->retain >> lin) & 1u;
@@ -600,7 +600,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
     const GemmDesc wg = linear_wgrad(temp_ptr(cx, t_dv2), act_ptr(cx, 11), gr->w2, D.T, D.h, D.f);
     Temp t_colsum;
     dg.epi.kind = lynx::kEpiGeluBwd;
-    LYNX_TRY(alloc_temp(cx, lynx::gemm_pair_colsum_bytes(dg, wg), &t_colsum));
+    LYNX_TRY(alloc_temp(cx, lynx::gemm_pair_colsum_bytes(dt, dg, wg), &t_colsum));
     dg.epi.aux = act_ptr(cx, 10);
     dg.epi.aux_ld = D.f;
     dg.epi.colsum_partial = reinterpret_cast<float*>(temp_ptr(cx, t_colsum));
@@ -671,7 +671,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   dpd.epi.dp = dropout_params(L);
   dpd.epi.global_heads = D.a * L->cfg.tp_size;
   dpd.epi.head0 = L->cfg.tp_rank * D.a;
-  const bool fused_ds = lynx::gemm_mfma_supported(dt, dpd);
+  const bool fused_ds = lynx::gemm_supported(dt, dpd);
   // dV = Pd^T dC.  With the one-pass dS kernel it goes first, so that dQ and dK read dS right
   // after it is written, while much of it is still in the caches (measured: dQ 0.070 -> 0.05x ms).
   const bool dv_first = fused_ds && !cx.bk->fused_attn;

@@ -29,6 +29,14 @@ __device__ __forceinline__ void wait_vmcnt() {
 __device__ __forceinline__ void wait_lgkmcnt0() {
   __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8));
 }
+// Waits until at most n newer slabs of LOADS loads each are still in flight (n is uniform).
+template <int LOADS, int MOST>
+__device__ __forceinline__ void wait_slabs(int n) {
+  if constexpr (MOST == 0) wait_vmcnt<0>();
+  else if (n >= MOST) wait_vmcnt<MOST * LOADS>();
+  else wait_slabs<LOADS, MOST - 1>(n);
+}
+
 // Workgroup barrier that neither the optimiser nor the scheduler moves memory
 // accesses across (and that, unlike __syncthreads, does not drain the loads
 // still in flight).  This wavefront's LDS accesses are complete before it: a

@@ -19,6 +19,11 @@ TOL = {synth.F32: 1e-4, synth.BF16: 2e-2}
 
 # name: (dtype, hidden, heads, head_dim, ffn, seq, micro_batch)
 SHAPES = {
+    "octets_f32": (synth.F32, 8, 1, 8, 8, 8, 1),
+    "one_over_32_f32": (synth.F32, 40, 1, 40, 72, 40, 1),
+    "one_under_64_f32": (synth.F32, 56, 1, 56, 120, 56, 2),
+    "one_over_64_f32": (synth.F32, 72, 2, 72, 136, 136, 1),
+    "large_tiles_f32": (synth.F32, 520, 2, 72, 1096, 328, 2),   # 64 x 64 tiles, tails everywhere
     "octets_bf16": (synth.BF16, 8, 1, 8, 8, 8, 1),
     "one_over_64": (synth.BF16, 72, 1, 72, 136, 72, 1),
     "one_under_128": (synth.BF16, 120, 1, 120, 248, 120, 2),
