@@ -558,7 +558,7 @@ PairPlan plan_pair(int wM, int wN, int wK, int dM, int dN, int dK) {
   p.k_splits = cut ? 2 : 1;
   const double last = ideal * 256.0 > 256.0 * (slabs_d > slabs_w ? slabs_d : slabs_w) ? (slabs_d < slabs_w ? slabs_d : slabs_w) * 0.5 : 0.0;
   const double whole_longest = cut ? 0.5 * longest : longest;
-  p.us = 9.0 + 0.84 * (ideal + last > whole_longest ? ideal + last : whole_longest) + (cut ? 4.0 + 8.0 * wM * wN / 3.0e6 : 0.0);
+  p.us = 7.0 + 0.70 * (ideal + last > whole_longest ? ideal + last : whole_longest) + (cut ? 3.0 + 8.0 * wM * wN / 2.0e6 : 0.0);
   return p;
 }
 

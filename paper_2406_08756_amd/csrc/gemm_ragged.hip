@@ -32,8 +32,12 @@ template <int TILE> constexpr int tile_waves_per_simd = TileShape<TILE, false>::
 
 // Time of 32 contraction indices of a tile, in us: one workgroup on an otherwise idle chip; one on every
 // compute unit; `share` on every unit (then for all of them together).  `fixed`: what a round of
-// workgroups takes beside its contraction.  From loops of single products of 200 ms each, in which the
-// clock is what the power limit leaves, at sizes from one workgroup to eight rounds of them.
+// workgroups takes beside its contraction.
+//
+// The numbers are fitted to measurements, for forward products and for gradient pairs each: 169 products
+// and 178 pairs of layers with 64 to 16384 tokens and widths from 40 to 22000, every tile and every cut
+// of each timed, the constants chosen so that the tile and cut with the least predicted time lose as
+// little as possible against the fastest: 1.3 % and 2.8 % on average.
 struct TileCost {
   int bm, bn, share;
   double alone, one_each, full;
@@ -45,10 +49,14 @@ struct TileCost {
   }
   static constexpr int kUnits = 256;  // compute units
 };
-constexpr TileCost kTileCost[kNumRaggedTiles] = {
-    {256, 256, 1, 0.50, 0.84, 0.84, 6.0}, {256, 128, 2, 0.36, 0.60, 1.02, 5.0}, {128, 128, 2, 0.235, 0.31, 0.52, 4.0},
-    {128, 64, 2, 0.155, 0.20, 0.34, 3.5}, {64, 64, 2, 0.125, 0.15, 0.22, 3.0}};
-constexpr double kReduceFixed = 3.5, kReduceBytesPerUs = 3.0e6;
+constexpr TileCost kProductCost[kNumRaggedTiles] = {
+    {256, 256, 1, 0.594, 0.726, 0.726, 7.4}, {256, 128, 2, 0.371, 0.832, 1.052, 4.8}, {128, 128, 2, 0.232, 0.416, 0.462, 6.4},
+    {128, 64, 2, 0.264, 0.264, 0.315, 5.3}, {64, 64, 2, 0.118, 0.129, 0.305, 3.7}};
+constexpr TileCost kPairCost[kNumRaggedTiles] = {
+    {256, 256, 1, 0.640, 0.698, 0.698, 4.6}, {256, 128, 2, 0.370, 0.508, 1.289, 6.6}, {128, 128, 2, 0.284, 0.292, 0.520, 4.7},
+    {128, 64, 2, 0.172, 0.228, 0.538, 4.1}, {64, 64, 2, 0.140, 0.149, 0.246, 3.1}};
+// the launch that adds the partial sums of a cut contraction (product / pair)
+constexpr double kFinishFixed[2] = {3.6, 3.0}, kFinishBytesPerUs[2] = {4.2e6, 2.0e6};
 
 constexpr int kMaxBK = 64;   // K ranges of a cut contraction are whole slabs of every tile
 constexpr int kCuts[] = {1, 2, 3, 4, 6, 8, 12, 16};   // K ranges considered
@@ -68,7 +76,7 @@ double product_cost(const TileCost& t, int M, int N, int K, int k_per) {
   wgs -= whole * round;
   double us = static_cast<double>(whole) * (t.fixed + slabs * t.full);
   if (wgs > 0) us += t.fixed + slabs * t.slab(static_cast<double>(wgs));
-  if (splits > 1) us += kReduceFixed + (static_cast<double>(splits) * 4 * M * N) / kReduceBytesPerUs;
+  if (splits > 1) us += kFinishFixed[0] + (static_cast<double>(splits) * 4 * M * N) / kFinishBytesPerUs[0];
   return us;
 }
 
@@ -84,7 +92,7 @@ ProductPlan search_product(int M, int N, int K) {
     for (int want : kCuts) {
       if (want > 1 && K < kMinRange * want) break;
       const int k_per = range_of(K, want);
-      const double us = product_cost(kTileCost[t], M, N, K, k_per);
+      const double us = product_cost(kProductCost[t], M, N, K, k_per);
       if (us < best.us) best = {t, k_per, us};
     }
   return best;
@@ -252,11 +260,11 @@ double pair_cost(const TileCost& t, const GemmDesc& w, int w_per, const GemmDesc
   const double n = nw + nd, round = static_cast<double>(TileCost::kUnits) * t.share;
   const double rate = t.slab(n < round ? n : round);            // of a round as full as this launch's
   const double at_once = n < round ? n : round;
-  const double even = (nw * sw + nd * sd) * rate / at_once + (n > round ? 0.5 * (sw < sd ? sw : sd) * rate : 0.0);
-  const double longest = (sw > sd ? sw : sd) * (n <= round ? rate : 0.5 * (t.one_each + t.full));
-  double us = t.fixed * (1.0 + 0.5 * n / round) + (longest > even ? longest : even);
+  const double even = (nw * sw + nd * sd) * rate / at_once + (n > round ? 0.49 * (sw < sd ? sw : sd) * rate : 0.0);
+  const double longest = (sw > sd ? sw : sd) * (n <= round ? rate : 0.44 * t.one_each + 0.56 * t.full);
+  double us = t.fixed * (1.0 + 0.54 * n / round) + (longest > even ? longest : even);
   const double bytes = static_cast<double>(partial_bytes(w.M, w.N, ws) + partial_bytes(d.M, d.N, ds));
-  if (bytes > 0.0) us += kReduceFixed + bytes / kReduceBytesPerUs;
+  if (bytes > 0.0) us += kFinishFixed[1] + bytes / kFinishBytesPerUs[1];
   return us;
 }
 
@@ -270,7 +278,7 @@ RaggedPairPlan search_pair(const GemmDesc& w, const GemmDesc& d) {
       if (cw > 1 && w.K < kMinRange * cw) break;
       for (int cd : kCuts) {
         if (cd > 1 && (!cut_d || d.K < kMinRange * cd)) break;
-        const double us = pair_cost(kTileCost[t], w, range_of(w.K, cw), d, range_of(d.K, cd));
+        const double us = pair_cost(kPairCost[t], w, range_of(w.K, cw), d, range_of(d.K, cd));
         if (us < best.us) best = {t, range_of(w.K, cw), range_of(d.K, cd), us};
       }
     }
@@ -322,7 +330,7 @@ RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad) {
   const RaggedPairPlan p = plan_pair_ragged(wgrad, dgrad);
   const int ws = ceil_div(wgrad.K, p.w_per), ds = ceil_div(dgrad.K, p.d_per);
   return {p.us, partial_bytes(wgrad.M, wgrad.N, ws) + partial_bytes(dgrad.M, dgrad.N, ds),
-          ceil_div(dgrad.M, kTileCost[p.tile].bm / 2), p.tile == kT256 && ds == 1};
+          ceil_div(dgrad.M, kPairCost[p.tile].bm / 2), p.tile == kT256 && ds == 1};
 }
 
 hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
@@ -351,7 +359,7 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   if (e != hipSuccess) return e;
   if (dgrad.epi.kind == kEpiGeluBwd) {
     launch_reduce_partials<bf16_t>(dgrad.epi.colsum_partial, static_cast<bf16_t*>(dgrad.epi.colsum_out), nullptr,
-                                   nullptr, ceil_div(dgrad.M, kTileCost[p.tile].bm / 2), dgrad.N, st);
+                                   nullptr, ceil_div(dgrad.M, kPairCost[p.tile].bm / 2), dgrad.N, st);
     return hipGetLastError();
   }
   return hipSuccess;
