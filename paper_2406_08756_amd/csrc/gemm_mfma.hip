@@ -43,26 +43,35 @@ __global__ void __launch_bounds__(kThreads, 2) gemm_mfma_duo_kernel(MfmaGemmArgs
 }
 
 // Work items of the score-shaped row-block kernels: row block tm (128 rows) owns tiles
-// tn = 0..tm; it is cut into runs of at most kAttnRun tiles, one workgroup each, so that no
-// workgroup walks more than kAttnRun tiles (a workgroup per whole row block leaves the launch
+// tn = 0..tm; it is cut into runs of at most `run` tiles, one workgroup each, so that no
+// workgroup walks more than `run` tiles (a workgroup per whole row block leaves the launch
 // waiting for the 16-tile blocks while most compute units have run out of work).  Items are
 // numbered longest row block first; item * nz + z is the workgroup of matrix z.
+//
+// Runs of four tiles share the A tile and hide the loads of the next B tile; where they would
+// not give every compute unit its two workgroups, a short launch is what counts: runs of two or one
+// (8 slices of s = 384, dS: 24 workgroups of up to three tiles 17.3 us, 48 of one 10.5).
 constexpr int kAttnRun = 4;
-__host__ __device__ inline int attn_runs_of(int tm) { return (tm + kAttnRun) / kAttnRun; }
-inline int attn_items(int tiles_m) {
+__host__ __device__ inline int attn_runs_of(int tm, int run) { return (tm + run) / run; }
+inline int attn_items(int tiles_m, int run) {
   int n = 0;
-  for (int tm = 0; tm < tiles_m; ++tm) n += attn_runs_of(tm);
+  for (int tm = 0; tm < tiles_m; ++tm) n += attn_runs_of(tm, run);
   return n;
 }
+inline int attn_run(int tiles_m, int nz) {
+  int run = kAttnRun;
+  while (run > 1 && static_cast<long long>(attn_items(tiles_m, run)) * nz < 512) run /= 2;
+  return run;
+}
 // item -> (tm, first tile, one past the last tile)
-__device__ __forceinline__ void attn_item(int item, int tiles_m, int& tm, int& tn0, int& tn1) {
+__device__ __forceinline__ void attn_item(int item, int tiles_m, int run, int& tm, int& tn0, int& tn1) {
   tm = tiles_m - 1;
-  while (tm > 0 && item >= attn_runs_of(tm)) {
-    item -= attn_runs_of(tm);
+  while (tm > 0 && item >= attn_runs_of(tm, run)) {
+    item -= attn_runs_of(tm, run);
     --tm;
   }
-  tn0 = item * kAttnRun;
-  tn1 = min(tn0 + kAttnRun, tm + 1);
+  tn0 = item * run;
+  tn1 = min(tn0 + run, tm + 1);
 }
 
 // Score-shaped batched products with a short contraction (S = Q K^T, dPd = dC V^T: K = head
@@ -113,7 +122,7 @@ __global__ void __launch_bounds__(kThreads, 2) attn_outer_kernel(MfmaGemmArgs g)
   const int item = blockIdx.x / g.nz;
   const int bz = blockIdx.x - item * g.nz;
   int tm, tn0, tn1;
-  attn_item(item, g.tiles_m, tm, tn0, tn1);
+  attn_item(item, g.tiles_m, g.run, tm, tn0, tn1);
   const int z1 = bz / g.nz2, z2 = bz - z1 * g.nz2;
   const bf16_t* Abase = g.A + z1 * g.a_z1 + z2 * g.a_z2;
   const bf16_t* Bbase = g.B + z1 * g.b_z1 + z2 * g.b_z2;
@@ -238,7 +247,7 @@ __global__ void __launch_bounds__(kThreads, 2) attn_dscores_kernel(MfmaGemmArgs 
   const int item = blockIdx.x / g.nz;
   const int bz = blockIdx.x - item * g.nz;
   int tm, tn0, tn1;
-  attn_item(item, g.tiles_m, tm, tn0, tn1);
+  attn_item(item, g.tiles_m, g.run, tm, tn0, tn1);
   const int z1 = bz / g.nz2, z2 = bz - z1 * g.nz2;
   const bf16_t* Abase = g.A + z1 * g.a_z1 + z2 * g.a_z2;
   const bf16_t* Bbase = g.B + z1 * g.b_z1 + z2 * g.b_z2;
@@ -507,7 +516,8 @@ hipError_t launch_scores(MfmaGemmArgs a, hipStream_t st) {
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   a.tiles_m = (a.M + 127) / 128;
   a.tiles_n = a.tiles_m;
-  hipLaunchKernelGGL(kern, dim3(attn_items(a.tiles_m) * a.nz), dim3(kThreads), smem, st, a);
+  a.run = attn_run(a.tiles_m, a.nz);
+  hipLaunchKernelGGL(kern, dim3(attn_items(a.tiles_m, a.run) * a.nz), dim3(kThreads), smem, st, a);
   return hipGetLastError();
 }
 template <bool DSCORES>
@@ -638,7 +648,8 @@ hipError_t gemm_attention(const GemmDesc& d, hipStream_t st) {
     if (d.K <= 128) return scores<false>(a, st);
     return gemm_ragged(d, nullptr, 0, st);
   }
-  if (d.M % 128 || d.N % 128) return gemm_ragged(d, nullptr, 0, st);
+  // (few tiles: the ragged kernels' 64 x 64 ones)
+  if (d.M % 128 || d.N % 128 || static_cast<long long>(d.M / 128) * (d.N / 128) * a.nz < 256) return gemm_ragged(d, nullptr, 0, st);
   return d.a_sk == 1 ? launch_attn_product<true>(a, st) : launch_attn_product<false>(a, st);
 }
 

@@ -313,9 +313,12 @@ hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, 
       a.partial = scratch;
     }
   } else {
-    // attention products: 128 rows (the zero padding of the seq x seq operands reaches the next
-    // multiple of 128), and a head dimension of up to 64 is half a tile wide
+    // attention products: up to 128 rows (the zero padding of the seq x seq operands reaches the next
+    // multiple of 128), a head dimension of up to 64 is half a tile wide, and where that leaves compute
+    // units without a workgroup, 64 x 64 (21 slices of s = 328, d = 104: 10.2 us with 128 x 128 tiles)
     tile = d.causal == kCausalOutLower || d.N > 64 ? kT128 : kT128x64;
+    const TileCost& t = kProductCost[tile];
+    if (static_cast<long long>(ceil_div(d.M, t.bm)) * ceil_div(d.N, t.bn) * a.nz < TileCost::kUnits) tile = kT64;
   }
   hipError_t e;
   if (a_k && b_k) e = launch_tile<true, true>(tile, a, st);

@@ -45,6 +45,7 @@ struct MfmaGemmArgs {
   long long a_z1, a_z2, b_z1, b_z2, c_z1, c_z2;
   int nz, nz2;
   int causal;  // CausalMode
+  int run;     // score-shaped row-block kernels: tiles per workgroup
   // split contraction: workgroup x computes K range x / (tiles_m tiles_n) of k_splits ranges of
   // k_per indices (whole slabs; the last range may be shorter, none is empty) and leaves its fp32
   // sums in partial[split][M][N] instead of rounding into C
