@@ -134,20 +134,25 @@ gemm_ragged_kernel(MfmaGemmArgs g) {
   else gemm_tile<AK, BK_, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(g, blockIdx.x, blockIdx.y);
 }
 
-// Both products of a linear layer's backward in one launch, as gemm_mfma_pair_kernel: the weight
-// gradient's n_w workgroups first (the longer contraction), the input gradient's behind them.
+// Both products of a linear layer's backward in one launch: the first n_first workgroups belong to the one
+// whose tiles take longer, the others behind them fill what they leave idle.  (Weight gradient first
+// throughout: 237 us for 4000 tokens, 1600 inputs and 6400 outputs, whose input gradient has the longer
+// contraction; 198 this way.)
 template <int TILE>
 __global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
-gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_w) {
+gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int dgrad_first) {
   using T = TileShape<TILE, false>;
-  const int x = static_cast<int>(blockIdx.x);
-  const int n_pad = (n_w + 7) & ~7;
-  if (x < n_w) {
-    if (wgrad.k_splits > 1) gemm_tile<false, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves>(wgrad, x, 0);
-    else gemm_tile<false, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(wgrad, x, 0);
-  } else if (x >= n_pad) {
-    if (dgrad.k_splits > 1) gemm_tile<true, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves>(dgrad, x - n_pad, 0);
-    else gemm_tile<true, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(dgrad, x - n_pad, 0);
+  // the second product starts at a multiple of 8 workgroups, as its tile order, which takes the workgroup
+  // id mod 8 for the XCD, needs it; the few workgroups in between idle
+  const int x = static_cast<int>(blockIdx.x), n_pad = (n_first + 7) & ~7;
+  if (x >= n_first && x < n_pad) return;
+  const int tile = x < n_first ? x : x - n_pad;
+  if ((x < n_first) != (dgrad_first != 0)) {
+    if (wgrad.k_splits > 1) gemm_tile<false, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves>(wgrad, tile, 0);
+    else gemm_tile<false, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(wgrad, tile, 0);
+  } else {
+    if (dgrad.k_splits > 1) gemm_tile<true, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves>(dgrad, tile, 0);
+    else gemm_tile<true, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(dgrad, tile, 0);
   }
 }
 
@@ -186,9 +191,10 @@ hipError_t launch_ragged_pair(MfmaGemmArgs w, MfmaGemmArgs d, hipStream_t st) {
     g->tiles_m = ceil_div(g->M, T::BM);
     g->tiles_n = ceil_div(g->N, T::BN);
   }
-  const int n_w = w.tiles_m * w.tiles_n * w.k_splits;
-  const int n_pad = (n_w + 7) & ~7;
-  hipLaunchKernelGGL(kern, dim3(n_pad + d.tiles_m * d.tiles_n * d.k_splits), dim3(T::waves * kWave), smem, st, w, d, n_w);
+  const int n_w = w.tiles_m * w.tiles_n * w.k_splits, n_d = d.tiles_m * d.tiles_n * d.k_splits;
+  const bool dgrad_first = d.k_per > w.k_per;
+  const int n_first = dgrad_first ? n_d : n_w, n_pad = (n_first + 7) & ~7;
+  hipLaunchKernelGGL(kern, dim3(n_pad + n_w + n_d - n_first), dim3(T::waves * kWave), smem, st, w, d, n_first, dgrad_first);
   return hipGetLastError();
 }
 
