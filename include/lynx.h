@@ -130,7 +130,12 @@ size_t lynx_activation_bytes(const lynx_layer_config* cfg, int act_id);
  * anything, so it is exact for that sequence.  Explicit segments issued in
  * another order place buffers differently and can need more; a planner can
  * rehearse any sequence with lynx_layer_set_dry_run and read
- * lynx_layer_peak_bytes.  0 on a bad config. */
+ * lynx_layer_peak_bytes.  0 on a bad config.
+ *
+ * Where few tokens leave the chip idle, the size includes fp32 partial sums of
+ * contractions that are cut into ranges.  A smaller workspace that the sequence
+ * fits without them is accepted too: the run then keeps its contractions whole
+ * (slower; the results differ from the cut ones' by the order of fp32 sums). */
 size_t lynx_workspace_bytes(const lynx_layer_config* cfg, uint32_t retain_mask);
 
 /* The same for a schedule with explicit regeneration phases (Sec. 4.2: the
@@ -161,7 +166,7 @@ lynx_status lynx_layer_destroy(lynx_layer_t layer);
  * may live in it per GPU: two would overwrite each other, so a second create on
  * the same device before the first is destroyed fails with STATE.  Errors:
  * INVALID_ARG, SHAPE, OOM when even the leanest schedule of this shape
- * (lynx_workspace_bytes(cfg, LYNX_RETAIN_FULL_RECOMPUTE)) exceeds the block -
+ * (input retained only, contractions whole) exceeds the block -
  * later calls return OOM as usual when a richer retain mask does not fit -,
  * HIP when the block's address cannot be obtained. */
 #define LYNX_STATIC_WORKSPACE_BYTES ((size_t)64 << 20)

@@ -77,7 +77,7 @@ bool gemm_pair_supported(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad
 
 bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
   if (!gemm_pair_supported(dtype, dgrad, wgrad)) return false;
-  if (dtype != 1) return true;
+  if (dtype != 1 || dgrad.uncut) return true;   // (uncut: the smaller workspace)
   // With few rows the plain product is cut into K ranges, which the epilogue's column sums rule out; a
   // GeLU kernel of its own (two launches, three passes over [M, N]) costs less than the uncut product.
   GemmDesc plain = dgrad;

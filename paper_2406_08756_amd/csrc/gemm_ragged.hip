@@ -86,11 +86,11 @@ struct ProductPlan {
   int splits(int K) const { return ceil_div(K, k_per); }
 };
 
-ProductPlan search_product(int M, int N, int K) {
+ProductPlan search_product(int M, int N, int K, bool uncut) {
   ProductPlan best{kT64, range_of(K, 1), 1e30};
   for (int t = 0; t < kNumRaggedTiles; ++t)
     for (int want : kCuts) {
-      if (want > 1 && K < kMinRange * want) break;
+      if (want > 1 && (uncut || K < kMinRange * want)) break;
       const int k_per = range_of(K, want);
       const double us = product_cost(kProductCost[t], M, N, K, k_per);
       if (us < best.us) best = {t, k_per, us};
@@ -120,9 +120,9 @@ struct PlanCache {
   }
 };
 
-ProductPlan plan_product(int M, int N, int K) {
-  static thread_local PlanCache<ProductPlan, 3> cache;
-  return cache.get({M, N, K}, [&] { return search_product(M, N, K); });
+ProductPlan plan_product(const GemmDesc& d) {
+  static thread_local PlanCache<ProductPlan, 4> cache;
+  return cache.get({d.M, d.N, d.K, d.uncut}, [&] { return search_product(d.M, d.N, d.K, d.uncut); });
 }
 
 // ---- kernels ------------------------------------------------------------------
@@ -280,10 +280,11 @@ RaggedPairPlan search_pair(const GemmDesc& w, const GemmDesc& d) {
   RaggedPairPlan best{kT64, range_of(w.K, 1), range_of(d.K, 1), 1e30};
   for (int t = 0; t < kNumRaggedTiles; ++t) {
     if (t == kT128x64) continue;   // (no pair kernel of this tile)
+    if (d.uncut && !cut_d && kPairCost[t].bm < 256) continue;   // (fewest column partials)
     for (int cw : kCuts) {
-      if (cw > 1 && w.K < kMinRange * cw) break;
+      if (cw > 1 && (w.uncut || w.K < kMinRange * cw)) break;
       for (int cd : kCuts) {
-        if (cd > 1 && (!cut_d || d.K < kMinRange * cd)) break;
+        if (cd > 1 && (!cut_d || d.uncut || d.K < kMinRange * cd)) break;
         const double us = pair_cost(kPairCost[t], w, range_of(w.K, cw), d, range_of(d.K, cd));
         if (us < best.us) best = {t, range_of(w.K, cw), range_of(d.K, cd), us};
       }
@@ -293,14 +294,14 @@ RaggedPairPlan search_pair(const GemmDesc& w, const GemmDesc& d) {
 }
 
 RaggedPairPlan plan_pair_ragged(const GemmDesc& w, const GemmDesc& d) {
-  static thread_local PlanCache<RaggedPairPlan, 7> cache;
-  return cache.get({w.M, w.N, w.K, d.M, d.N, d.K, d.epi.kind}, [&] { return search_pair(w, d); });
+  static thread_local PlanCache<RaggedPairPlan, 8> cache;
+  return cache.get({w.M, w.N, w.K, d.M, d.N, d.K, d.epi.kind, w.uncut + 2 * d.uncut}, [&] { return search_pair(w, d); });
 }
 
 }  // namespace
 
 RaggedChoice ragged_product(const GemmDesc& d) {
-  const ProductPlan p = plan_product(d.M, d.N, d.K);
+  const ProductPlan p = plan_product(d);
   return {p.us, partial_bytes(d.M, d.N, p.splits(d.K)), 0, p.tile == kT256 && p.splits(d.K) == 1};
 }
 
@@ -309,7 +310,7 @@ hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, 
   const bool a_k = d.a_sk == 1, b_k = d.b_sk == 1;
   int tile;
   if (d.causal == kCausalNone && a.nz == 1) {
-    const ProductPlan p = plan_product(d.M, d.N, d.K);
+    const ProductPlan p = plan_product(d);
     tile = p.tile;
     if (p.splits(d.K) > 1) {
       // the cut is part of the shape's summation order: no silent change where scratch is short

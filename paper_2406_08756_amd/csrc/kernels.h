@@ -154,6 +154,7 @@ struct GemmDesc {
   int nz1, nz2;
   int causal;                              // CausalMode
   GemmEpilogue epi;                        // kind 0 (none) unless the matrix-core path is used
+  bool uncut;                              // leave contractions whole that would be cut for speed (less scratch)
 };
 // Picks a kernel.  `scratch` (fp32, 16-byte aligned, gemm_scratch_bytes or more; null when that is 0)
 // takes the partial sums of a contraction that is cut into ranges; they are added in a fixed order.

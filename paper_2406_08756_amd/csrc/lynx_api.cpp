@@ -92,7 +92,12 @@ struct Book {
   // the policy keeps none of S, P, Pd and the shape is one the fused attention kernels take:
   // operators 3-5 never run, operator 6 reads QKV alone
   bool fused_attn = false;
+  // what the run goes without because the workspace has no room for it: 1, scratch that only buys
+  // time (contractions stay whole); 2, also the fusion of operators 7 + 8 and 12 + 13, which places the
+  // activations after them elsewhere
+  int thrift = 0;
 };
+constexpr int kMaxThrift = 2;
 
 }  // namespace
 
@@ -116,6 +121,9 @@ struct lynx_layer_s {
   // parity aid: where backward copies the gradient with respect to activation A_i (null: nowhere)
   void* grad_tap[LYNX_NUM_ACTIVATIONS] = {};
   int static_device = -1;  // >= 0: the workspace is that device's built-in block
+  // the least Book::thrift at which forward(thrift_mask) -> backward fits the workspace
+  uint32_t thrift_mask = ~0u;
+  int thrift = 0;
 };
 
 namespace {
@@ -309,8 +317,9 @@ GemmDesc attn_cols(const void* sq, const void* y, long long ldy, void* out, long
 }
 
 // One linear product, with scratch of its own for the partial sums of a cut contraction.
-lynx_status run_linear(Ctx& cx, int slot, const GemmDesc& g) {
+lynx_status run_linear(Ctx& cx, int slot, GemmDesc g) {
   const int dt = cx.L->D.dtype;
+  g.uncut = cx.bk->thrift > 0;
   const size_t bytes = lynx::gemm_scratch_bytes(dt, g);
   Temp scratch;
   if (bytes > 0) LYNX_TRY(alloc_temp(cx, bytes, &scratch));
@@ -421,8 +430,9 @@ GemmDesc fused_linear_desc(Ctx& cx, int lin, bool keep_product) {
   g.epi.dp = dropout_params(L);
   return g;
 }
-bool can_fuse_linear(const lynx_layer_s* L, int lin) {
-  const Dims& D = L->D;
+bool can_fuse_linear(const Ctx& cx, int lin) {
+  const Dims& D = cx.L->D;
+  if (cx.bk->thrift > 1) return false;
   // shapes only (pointers are 256-byte aligned arena blocks or checked caller buffers)
   GemmDesc g = linear_fwd(reinterpret_cast<const void*>(256), reinterpret_cast<const void*>(256), nullptr,
                           reinterpret_cast<void*>(256), D.T, D.h, lin == 7 ? D.p : D.f);
@@ -465,7 +475,7 @@ lynx_status forward_pass(Ctx& cx, uint32_t retain) {
     } else if (i == 4) {
       LYNX_TRY(run_op(cx, 4, /*fuse_dropout=*/true, /*write_p=*/(bk.retain >> 4) & 1u));
       done = 5;  // OP4's launch covers OP5
-    } else if ((i == 7 || i == 12) && can_fuse_linear(cx.L, i)) {
+    } else if ((i == 7 || i == 12) && can_fuse_linear(cx, i)) {
       LYNX_TRY(run_fused_linear(cx, i));
       done = ++i;  // the launch covers the bias + dropout + residual operator too
     } else {
@@ -546,7 +556,7 @@ lynx_status recompute_pass(Ctx& cx, uint32_t segment) {
     } else if (i == 4 && ((segment >> 5) & 1u) && !bk.live[5]) {
       LYNX_TRY(run_op(cx, 4, /*fuse_dropout=*/true));
     } else if ((i == 7 || i == 12) && ((segment >> (i + 1)) & 1u) && !bk.live[i + 1] &&
-               can_fuse_linear(cx.L, i)) {
+               can_fuse_linear(cx, i)) {
       LYNX_TRY(run_fused_linear(cx, i));
       ++i;
     } else {
@@ -576,14 +586,22 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
       for (int gelu = 0; gelu <= (&nk == &lin[0] ? 1 : 0); ++gelu) {
         // (FC2's input gradient carries the GeLU backward where it can; its plan is another then)
         GemmDesc d = linear_dgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
+        GemmDesc g = linear_wgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
         d.epi.kind = gelu ? lynx::kEpiGeluBwd : lynx::kEpiNone;
-        const size_t b = lynx::gemm_pair_scratch_bytes(dt, d, linear_wgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]));
+        d.uncut = g.uncut = cx.bk->thrift > 0;
+        const size_t b = lynx::gemm_pair_scratch_bytes(dt, d, g);
         if (b > scratch_bytes) scratch_bytes = b;
       }
   }
   Temp scratch, t_dv2, t_dg, t_du, t_dy2, t_dx2, t_do, t_dc, t_dpd, t_dqkv, t_dy1;
   LYNX_TRY(alloc_temp(cx, scratch_bytes, &scratch));
   float* scr = reinterpret_cast<float*>(temp_ptr(cx, scratch));
+  // both gradients of a linear layer
+  auto launch_pair = [&](int slot, GemmDesc dg, GemmDesc wg) -> lynx_status {
+    dg.uncut = wg.uncut = cx.bk->thrift > 0;
+    LYNX_LAUNCH(cx, slot, lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, cx.st));
+    return LYNX_OK;
+  };
   const size_t th = static_cast<size_t>(D.T) * D.h * e, tf = static_cast<size_t>(D.T) * D.f * e;
 
   // B13: OUT = X2 + keep2 (V2 + b2) c
@@ -597,25 +615,26 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   LYNX_TRY(alloc_temp(cx, tf, &t_du));
   {
     GemmDesc dg = linear_dgrad(temp_ptr(cx, t_dv2), w.w2, temp_ptr(cx, t_du), D.T, D.h, D.f);
-    const GemmDesc wg = linear_wgrad(temp_ptr(cx, t_dv2), act_ptr(cx, 11), gr->w2, D.T, D.h, D.f);
+    GemmDesc wg = linear_wgrad(temp_ptr(cx, t_dv2), act_ptr(cx, 11), gr->w2, D.T, D.h, D.f);
     Temp t_colsum;
     dg.epi.kind = lynx::kEpiGeluBwd;
-    LYNX_TRY(alloc_temp(cx, lynx::gemm_pair_colsum_bytes(dt, dg, wg), &t_colsum));
+    dg.uncut = wg.uncut = cx.bk->thrift > 0;
     dg.epi.aux = act_ptr(cx, 10);
     dg.epi.aux_ld = D.f;
-    dg.epi.colsum_partial = reinterpret_cast<float*>(temp_ptr(cx, t_colsum));
+    dg.epi.colsum_partial = scr;
     dg.epi.colsum_out = gr->b1;
     if (lynx::gemm_pair_absorbs_gelu(dt, dg, wg)) {
-      LYNX_LAUNCH(cx, kB12Grads, lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, cx.st));
+      LYNX_TRY(alloc_temp(cx, lynx::gemm_pair_colsum_bytes(dt, dg, wg), &t_colsum));
+      dg.epi.colsum_partial = reinterpret_cast<float*>(temp_ptr(cx, t_colsum));
+      LYNX_TRY(launch_pair(kB12Grads, dg, wg));
       free_temp(cx, &t_colsum);
       free_temp(cx, &t_dv2);
       free_act(cx, 11);
     } else {
-      free_temp(cx, &t_colsum);
       dg.epi = lynx::GemmEpilogue{};
       LYNX_TRY(alloc_temp(cx, tf, &t_dg));
       dg.C = temp_ptr(cx, t_dg);
-      LYNX_LAUNCH(cx, kB12Grads, lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, cx.st));
+      LYNX_TRY(launch_pair(kB12Grads, dg, wg));
       free_temp(cx, &t_dv2);
       free_act(cx, 11);
       LYNX_LAUNCH(cx, kB11Gelu, lynx::gelu_bwd(dt, temp_ptr(cx, t_dg), act_ptr(cx, 10), temp_ptr(cx, t_du),
@@ -627,8 +646,8 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   LYNX_TRY(tap(cx, 10, temp_ptr(cx, t_du)));
   // B10: U = Y2 W1^T + b1
   LYNX_TRY(alloc_temp(cx, th, &t_dy2));
-  LYNX_LAUNCH(cx, kB10Grads, lynx::gemm_pair(dt, linear_dgrad(temp_ptr(cx, t_du), w.w1, temp_ptr(cx, t_dy2), D.T, D.f, D.h),
-                                                  linear_wgrad(temp_ptr(cx, t_du), act_ptr(cx, 9), gr->w1, D.T, D.f, D.h), scr, scratch_bytes, cx.st));
+  LYNX_TRY(launch_pair(kB10Grads, linear_dgrad(temp_ptr(cx, t_du), w.w1, temp_ptr(cx, t_dy2), D.T, D.f, D.h),
+                       linear_wgrad(temp_ptr(cx, t_du), act_ptr(cx, 9), gr->w1, D.T, D.f, D.h)));
   free_temp(cx, &t_du);
   LYNX_TRY(tap(cx, 9, temp_ptr(cx, t_dy2)));
   // B9: Y2 = LN2(X2); dX2 = dOUT + dLN.  B8 in the same pass: X2 = X + keep1 (O + bo) c,
@@ -647,8 +666,8 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   free_act(cx, 8);
   // B7: O = C Wo^T
   LYNX_TRY(alloc_temp(cx, static_cast<size_t>(D.T) * D.p * e, &t_dc));
-  LYNX_LAUNCH(cx, kB7Grads, lynx::gemm_pair(dt, linear_dgrad(temp_ptr(cx, t_do), w.wo, temp_ptr(cx, t_dc), D.T, D.h, D.p),
-                                                  linear_wgrad(temp_ptr(cx, t_do), act_ptr(cx, 6), gr->wo, D.T, D.h, D.p), scr, scratch_bytes, cx.st));
+  LYNX_TRY(launch_pair(kB7Grads, linear_dgrad(temp_ptr(cx, t_do), w.wo, temp_ptr(cx, t_dc), D.T, D.h, D.p),
+                       linear_wgrad(temp_ptr(cx, t_do), act_ptr(cx, 6), gr->wo, D.T, D.h, D.p)));
   free_temp(cx, &t_do);
   LYNX_TRY(tap(cx, 6, temp_ptr(cx, t_dc)));
   // B6: C = Pd V (C itself is read once more below, for the row dot products)
@@ -733,8 +752,8 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   LYNX_TRY(tap(cx, 2, dqkv));
   // B2: QKV = Y1 Wqkv^T + bqkv
   LYNX_TRY(alloc_temp(cx, th, &t_dy1));
-  LYNX_LAUNCH(cx, kB2Grads, lynx::gemm_pair(dt, linear_dgrad(dqkv, w.wqkv, temp_ptr(cx, t_dy1), D.T, 3 * D.p, D.h),
-                                                  linear_wgrad(dqkv, act_ptr(cx, 1), gr->wqkv, D.T, 3 * D.p, D.h), scr, scratch_bytes, cx.st));
+  LYNX_TRY(launch_pair(kB2Grads, linear_dgrad(dqkv, w.wqkv, temp_ptr(cx, t_dy1), D.T, 3 * D.p, D.h),
+                       linear_wgrad(dqkv, act_ptr(cx, 1), gr->wqkv, D.T, 3 * D.p, D.h)));
   LYNX_LAUNCH(cx, kB2BiasGrad, lynx::column_sum(dt, dqkv, gr->bqkv, scr, D.T, 3 * D.p, cx.st));
   free_temp(cx, &t_dqkv);
   free_act(cx, 2);
@@ -762,14 +781,67 @@ bool grads_ok(const lynx_grads* g) {
   return true;
 }
 
-// Rehearse on a copy, then run for real.
+// The least thrift at which forward(retain) -> backward fits the workspace (none: 1, for the forward's sake).
+int thrift_for(lynx_layer_s* L, uint32_t retain) {
+  if (L->thrift_mask != retain) {
+    // (placeholders, non-null and aligned: the rehearsal takes the kernel path a real call takes)
+    void* const fake = reinterpret_cast<void*>(static_cast<uintptr_t>(Arena::kAlign));
+    const lynx_grads g{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
+    L->thrift = 1;
+    for (int level = 0; level <= kMaxThrift; ++level) {
+      Book book;
+      book.arena = Arena(L->book.arena.capacity());
+      book.thrift = level;
+      Ctx cx{L, &book, false, nullptr};
+      if (forward_pass(cx, retain) != LYNX_OK || backward_pass(cx, fake, fake, &g) != LYNX_OK) continue;
+      L->thrift = level;
+      break;
+    }
+    L->thrift_mask = retain;
+  }
+  return L->thrift;
+}
+
+// Rehearse on a copy, then run for real.  A call that does not fit, though the sequence the run's
+// thrift was chosen for does (segments can hold more than backward alone), goes on with more of it.
 template <typename F>
 lynx_status two_pass(lynx_layer_s* L, hipStream_t st, F&& body) {
-  Book copy = L->book;
-  Ctx rehearsal{L, &copy, false, st};
-  LYNX_TRY(body(rehearsal));
+  lynx_status s = LYNX_ERR_OOM;
+  for (int level = L->book.thrift; s == LYNX_ERR_OOM && level <= kMaxThrift; ++level) {
+    Book copy = L->book;
+    copy.thrift = level;
+    Ctx rehearsal{L, &copy, false, st};
+    s = body(rehearsal);
+    if (s == LYNX_OK) L->book.thrift = level;
+  }
+  LYNX_TRY(s);
   Ctx real{L, &L->book, !L->dry, st};
   return body(real);
+}
+
+// The workspace a call sequence reaches into: forward, the phases, backward.
+size_t workspace_need(const lynx_layer_config* cfg, uint32_t retain_mask, const uint32_t* phase_masks, int thrift) {
+  Dims D;
+  if (!make_dims(cfg, &D) || (retain_mask & ~0x3FFFu)) return 0;
+  lynx_layer_s L;
+  L.cfg = *cfg;
+  L.D = D;
+  L.book.arena = Arena(static_cast<size_t>(1) << 60);
+  L.book.thrift = thrift;
+  Ctx cx{&L, &L.book, false, nullptr};
+  // Nothing is launched; the placeholders only have to look like what a real call passes
+  // (non-null, aligned), so that the rehearsal takes the kernel path a real call takes.
+  void* const fake = reinterpret_cast<void*>(static_cast<uintptr_t>(Arena::kAlign));
+  const lynx_grads g{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
+  L.base = static_cast<char*>(fake);
+  L.params = lynx_params{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
+  L.x = fake;
+  L.out = fake;
+  if (forward_pass(cx, retain_mask) != LYNX_OK) return 0;
+  for (int t = 0; phase_masks != nullptr && t < 4; ++t)
+    if (phase_masks[t] != 0 && recompute_pass(cx, phase_masks[t]) != LYNX_OK) return 0;
+  if (backward_pass(cx, fake, fake, &g) != LYNX_OK) return 0;
+  return L.book.arena.extent_peak();
 }
 
 }  // namespace
@@ -804,7 +876,11 @@ lynx_status lynx_layer_create_static(const lynx_layer_config* cfg, lynx_layer_t*
   Dims D;
   if (!make_dims(cfg, &D)) return LYNX_ERR_SHAPE;
   // the leanest schedule of this shape (keep the input only) must fit the block
-  const size_t least = lynx_workspace_bytes(cfg, LYNX_RETAIN_FULL_RECOMPUTE);
+  size_t least = 0;
+  for (int thrift = 0; thrift <= kMaxThrift; ++thrift) {
+    const size_t need = workspace_need(cfg, LYNX_RETAIN_FULL_RECOMPUTE, nullptr, thrift);
+    if (thrift == 0 || need < least) least = need;
+  }
   if (least == 0 || least > lynx::kStaticWorkspaceBytes) return LYNX_ERR_OOM;
   lynx_layer_s* L = new (std::nothrow) lynx_layer_s;
   if (L == nullptr) return LYNX_ERR_OOM;
@@ -858,6 +934,7 @@ lynx_status lynx_layer_forward(lynx_layer_t L, const void* x, void* out, uint32_
   void* old_out = L->out;
   const uint64_t old_step = L->step;
   L->x = x; L->out = out; L->step = step;
+  L->book.thrift = thrift_for(L, retain_mask);
   const lynx_status s = two_pass(L, static_cast<hipStream_t>(hip_stream),
                                  [&](Ctx& cx) { return forward_pass(cx, retain_mask); });
   if (s != LYNX_OK && s != LYNX_ERR_HIP) { L->x = old_x; L->out = old_out; L->step = old_step; }
@@ -932,26 +1009,7 @@ lynx_status lynx_layer_activation(lynx_layer_t L, int act_id, const void** devic
 
 size_t lynx_workspace_bytes_for_schedule(const lynx_layer_config* cfg, uint32_t retain_mask,
                                          const uint32_t* phase_masks) {
-  Dims D;
-  if (!make_dims(cfg, &D) || (retain_mask & ~0x3FFFu)) return 0;
-  lynx_layer_s L;
-  L.cfg = *cfg;
-  L.D = D;
-  L.book.arena = Arena(static_cast<size_t>(1) << 60);
-  Ctx cx{&L, &L.book, false, nullptr};
-  // Nothing is launched; the placeholders only have to look like what a real call passes
-  // (non-null, aligned), so that the rehearsal takes the kernel path a real call takes.
-  void* const fake = reinterpret_cast<void*>(static_cast<uintptr_t>(Arena::kAlign));
-  const lynx_grads g{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
-  L.base = static_cast<char*>(fake);
-  L.params = lynx_params{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
-  L.x = fake;
-  L.out = fake;
-  if (forward_pass(cx, retain_mask) != LYNX_OK) return 0;
-  for (int t = 0; phase_masks != nullptr && t < 4; ++t)
-    if (phase_masks[t] != 0 && recompute_pass(cx, phase_masks[t]) != LYNX_OK) return 0;
-  if (backward_pass(cx, fake, fake, &g) != LYNX_OK) return 0;
-  return L.book.arena.extent_peak();
+  return workspace_need(cfg, retain_mask, phase_masks, 0);
 }
 
 size_t lynx_workspace_bytes(const lynx_layer_config* cfg, uint32_t retain_mask) {

@@ -1,0 +1,86 @@
+"""Workspaces without room for the partial sums of cut contractions: the sizes below are what the call
+sequence takes with every contraction whole, which is less than lynx_workspace_bytes names where cutting
+pays.  They have to be accepted and kept, and runs that leave contractions whole have to agree bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import lynx_synth as synth
+from oracle import lynx_oracle as orc
+from oracle import policy_model as pm
+from harness import GpuLayer, rel_err
+from test_host_runtime import FAKE, FDOUT, FDX, FOUT, FX, dry_layer
+
+B = pytest.importorskip("paper_2406_08756_amd.binding")
+
+MASKS = (pm.FULL_RECOMPUTE, pm.ATTENTION_ONLY, pm.STORE_ALL)
+# name: (dtype, hidden, heads, head_dim, ffn, seq, micro_batch), bytes under each mask
+SHAPES = {
+    "few_rows": ((synth.BF16, 2056, 1, 64, 4104, 24, 1), (1496832, 1694464, 1694464)),
+    "prompt": ((synth.BF16, 5120, 5, 128, 2560, 128, 1), (12950528, 15571968, 15571968)),
+    "heads104": ((synth.BF16, 256, 2, 104, 1024, 768, 1), (14333952, 15065088, 16662528)),
+    "narrow": ((synth.BF16, 432, 1, 40, 216, 640, 2), (13416448, 15751168, 16857088)),
+    "f32": ((synth.F32, 208, 1, 128, 104, 336, 2), (7945728, 9047808, 9886464)),
+    "built_in_block": ((synth.BF16, 5840, 23, 128, 11648, 128, 2), (B.LYNX_STATIC_WORKSPACE_BYTES,) * 3),
+}
+
+
+def config(name):
+    dtype, h, a, d, f, s, b = SHAPES[name][0]
+    return synth.LayerConfig(dtype, h, a, d, f, s, b, tp_size=2, tp_rank=1, seed=7, layer_id=3)
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_small_workspace_is_accepted(name):
+    cfg = config(name)
+    for mask, size in zip(MASKS, SHAPES[name][1]):
+        for segments in ((), (B.LYNX_SEG_ALL_MISSING,)):
+            h = dry_layer(cfg, ws_bytes=size)
+            B.lynx_layer_forward(h, FX, FOUT, mask, 0)
+            for seg in segments:
+                B.lynx_recompute(h, seg)
+            B.lynx_layer_backward(h, FDOUT, FDX, FAKE)
+            assert B.lynx_layer_peak_bytes(h) <= size
+            B.lynx_layer_destroy(h)
+
+
+def test_a_workspace_of_the_named_size_is_used_as_named():
+    cfg = config("prompt")
+    for mask, size in zip(MASKS, SHAPES["prompt"][1]):
+        need = B.lynx_workspace_bytes(cfg, mask)
+        assert need > size
+        h = dry_layer(cfg, ws_bytes=need)
+        for _ in range(2):
+            B.lynx_layer_forward(h, FX, FOUT, mask, 0)
+            B.lynx_layer_backward(h, FDOUT, FDX, FAKE)
+        assert B.lynx_layer_peak_bytes(h) == need
+        B.lynx_layer_destroy(h)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["few_rows", "heads104", "narrow", "f32"])
+def test_layer_in_a_small_workspace(name):
+    cfg = config(name)
+    params = synth.make_params(cfg, random_ln=True)
+    X, dOUT = synth.make_x(cfg), synth.make_dout(cfg)
+    acts, grads = orc.layer_forward_backward(cfg, params, X, dOUT, step=2)
+    tol = {synth.F32: 1e-4, synth.BF16: 2e-2}[cfg.dtype]
+    first = None
+    for mask, size in zip(MASKS, SHAPES[name][1]):
+        layer = GpuLayer(cfg, params, workspace_bytes=size)
+        layer.workspace.fill_(0xFF)              # NaNs: nothing may be read that was not written
+        layer.forward(X, mask, step=2)
+        layer.backward(dOUT)
+        torch.cuda.synchronize()
+        end = layer.ws_base + size - layer.workspace.data_ptr()
+        assert bool((layer.workspace[end:] == 0xFF).all())
+        got = layer.results()
+        out = layer.out.float().cpu().numpy().astype(np.float64)
+        assert rel_err(out, acts["OUT"]) <= tol
+        for k, ref in grads.items():
+            assert rel_err(got[k], ref) <= tol, (k, rel_err(got[k], ref))
+        if name == "few_rows":                   # (contractions whole under each of the masks)
+            bits = [layer.out.clone(), layer.dx.clone()] + [layer.grads[k].clone() for k in synth.PARAM_NAMES]
+            first = first or bits
+            assert all(torch.equal(p, q) for p, q in zip(first, bits)), hex(mask)
+        layer.close()
