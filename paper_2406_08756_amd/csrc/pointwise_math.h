@@ -12,27 +12,36 @@ namespace lynx {
 constexpr float kGeluKappa = 0.7978845608028654f;  // sqrt(2/pi)
 constexpr float kGeluC = 0.044715f;
 
-__device__ __forceinline__ float tanh_fast(float x) {
+// 1 / (1 + 2^x) from the hardware exponential and reciprocal, the latter with one Newton step: a third of the
+// instructions of an IEEE division, which were half of the GeLU kernels' work.  Forward, 16384 x 2560:
+// 32.6 -> 27.8 us (6.0 TB/s), 8192 x 4096: 28.5 -> 23.2; the gradient, in the store pass of the FC2 gradient
+// pair, 8192 tokens, h 1024, f 4096: 178 -> 171 us for the launch.
+__device__ __forceinline__ float inv_1p_exp2(float x) {
 #pragma clang fp contract(off)
-  // 1 - 2/(1+e^{2x}); saturates correctly at both ends
-  return 1.0f - __fdividef(2.0f, 1.0f + __expf(2.0f * x));
+  const float d = fminf(1.0f + __builtin_amdgcn_exp2f(x), 3.0e38f);  // (of infinity the Newton step makes NaN)
+  const float r = __builtin_amdgcn_rcpf(d);
+  return __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
 }
-// kappa (u + c u^3) = u (kappa + kappa c u^2)
+constexpr float kLog2e = 1.4426950408889634f;
+// y = kappa (u + c u^3) = u (kappa + kappa c u^2)
 __device__ __forceinline__ float gelu_inner(float u) {
 #pragma clang fp contract(off)
   return u * __builtin_fmaf(kGeluKappa * kGeluC, u * u, kGeluKappa);
 }
+// u (1 + tanh y) / 2, tanh y = 1 - 2 / (1 + e^(2y)).  Error against 64 bits as with the division (4 M
+// normal deviates of deviation 0.05 to 20: 2-norm 3.4e-9 to 5.8e-8).
 __device__ __forceinline__ float gelu_f(float u) {
 #pragma clang fp contract(off)
-  const float th = tanh_fast(gelu_inner(u));
+  const float th = __builtin_fmaf(-2.0f, inv_1p_exp2(gelu_inner(u) * (2.0f * kLog2e)), 1.0f);
   return 0.5f * u * (1.0f + th);
 }
+// With sigma = (1 + tanh y) / 2 = 1 / (1 + e^(-2y)): gelu' = sigma + 2 u y' sigma (1 - sigma), in which
+// nothing cancels for u < 0: error in the 2-norm 0.86 to 0.97 of the tanh form's, largest no larger.
 __device__ __forceinline__ float gelu_grad_f(float u) {
 #pragma clang fp contract(off)
-  const float th = tanh_fast(gelu_inner(u));
-  const float dinner = __builtin_fmaf(3.0f * kGeluKappa * kGeluC, u * u, kGeluKappa);
-  const float sech2 = __builtin_fmaf(-th, th, 1.0f);
-  return __builtin_fmaf(0.5f * u * sech2, dinner, 0.5f * (1.0f + th));
+  const float sg = inv_1p_exp2(gelu_inner(u) * (-2.0f * kLog2e));
+  const float two_dinner = __builtin_fmaf(6.0f * kGeluKappa * kGeluC, u * u, 2.0f * kGeluKappa);
+  return __builtin_fmaf(u * two_dinner, sg * (1.0f - sg), sg);
 }
 
 // du = round(dg gelu'(u)) for 8 elements.
