@@ -72,6 +72,9 @@ def slot_work(cfg):
         # times; only the algorithmic two count).  Backward: dPd and dV likewise.
         "op3456_attention_fused": ("mfma", 2 * att), "b654_dscores_fused": ("mfma", att),
         "b6_dv_fused": ("mfma", att),
+        # fp32 partial rows: 32 tokens each for the two plain column sums, 128 for the FC1 bias, 512 at most
+        # for the LayerNorm gradients and the projection bias
+        "b_column_sums": ("hbm", 4 * (T // 32 * (h + 3 * p) + T // 128 * f + 5 * min(512, T // 2) * h)),
     }
 
 

@@ -97,11 +97,11 @@ size_t gemm_pair_colsum_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& 
 }
 
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,
-                     size_t scratch_bytes, hipStream_t st) {
+                     size_t scratch_bytes, ColumnSums* sums, hipStream_t st) {
   if (!gemm_pair_supported(dtype, dgrad, wgrad)) return hipErrorInvalidValue;
-  if (dtype != 1) return gemm_f32_pair(dgrad, wgrad, st);
-  return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair(dgrad, wgrad, scratch, scratch_bytes, st)
-                                       : gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, st);
+  if (dtype != 1) return gemm_f32_pair(dgrad, wgrad, sums, st);
+  return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair(dgrad, wgrad, scratch, scratch_bytes, sums, st)
+                                       : gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, sums, st);
 }
 
 }  // namespace lynx

@@ -17,7 +17,6 @@
 #include "kernels.h"
 #include "mfma_common.h"
 #include "pointwise_math.h"
-#include "reduce_partials.h"
 
 #include <type_traits>
 
@@ -363,7 +362,7 @@ size_t gemm_f32_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad) 
   return static_cast<size_t>((dgrad.M + bm - 1) / bm) * dgrad.N * sizeof(float);
 }
 
-hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, hipStream_t st) {
+hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, ColumnSums* sums, hipStream_t st) {
   const bool small = small_tiles(tiles(dgrad, 64) + tiles(wgrad, 64));
   const int bm = small ? 32 : 64;
   const int n_w = static_cast<int>(tiles(wgrad, bm)), n_d = static_cast<int>(tiles(dgrad, bm));
@@ -375,9 +374,7 @@ hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, hipStream
                        DropoutKey{}, n_w);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || dgrad.epi.kind != kEpiGeluBwd) return e;
-  launch_reduce_partials<float>(dgrad.epi.colsum_partial, static_cast<float*>(dgrad.epi.colsum_out), nullptr, nullptr,
-                                (dgrad.M + bm - 1) / bm, dgrad.N, st);
-  return hipGetLastError();
+  return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, (dgrad.M + bm - 1) / bm, dgrad.N);
 }
 
 }  // namespace lynx

@@ -3,7 +3,6 @@
 #include <mutex>
 
 #include "gemm_launch.h"
-#include "reduce_partials.h"
 
 namespace lynx {
 namespace {
@@ -667,7 +666,7 @@ size_t gemm_whole_pair_scratch_bytes(const GemmDesc& dgrad, const GemmDesc& wgra
 }
 
 hipError_t gemm_whole_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
-                          hipStream_t st) {
+                          ColumnSums* sums, hipStream_t st) {
   const MfmaGemmArgs d = make_args(dgrad);
   MfmaGemmArgs w = make_args(wgrad);
   const PairPlan p = plan_pair(w.M, w.N, w.K, d.M, d.N, d.K);
@@ -697,13 +696,8 @@ hipError_t gemm_whole_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* 
   };
   const hipError_t e = run();
   if (e != hipSuccess) return e;
-  if (dgrad.epi.kind == kEpiGeluBwd) {
-    // second, fixed-order stage of the bias gradient: one partial row per 128 output rows
-    launch_reduce_partials<bf16_t>(dgrad.epi.colsum_partial, static_cast<bf16_t*>(dgrad.epi.colsum_out), nullptr,
-                                   nullptr, dgrad.M / 128, dgrad.N, st);
-    return hipGetLastError();
-  }
-  return hipSuccess;
+  if (dgrad.epi.kind != kEpiGeluBwd) return hipSuccess;
+  return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, dgrad.M / 128, dgrad.N);  // a partial row per 128 rows
 }
 
 }  // namespace lynx

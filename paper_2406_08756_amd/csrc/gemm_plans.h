@@ -17,7 +17,7 @@ RaggedChoice ragged_product(const GemmDesc& d);
 RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad);
 hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st);
 hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
-                            hipStream_t st);
+                            ColumnSums* sums, hipStream_t st);
 // Products of whole, large tiles and the products of attention (gemm_mfma.hip).
 bool gemm_whole_takes(const GemmDesc& d, const RaggedChoice& choice);
 hipError_t gemm_whole(const GemmDesc& d, hipStream_t st);
@@ -25,12 +25,12 @@ hipError_t gemm_attention(const GemmDesc& d, hipStream_t st);
 double gemm_whole_pair_us(const GemmDesc& dgrad, const GemmDesc& wgrad);
 size_t gemm_whole_pair_scratch_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad);
 hipError_t gemm_whole_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
-                           hipStream_t st);
+                           ColumnSums* sums, hipStream_t st);
 
 // fp32 storage (gemm_f32.hip).
 bool gemm_f32_supported(const GemmDesc& d);
 hipError_t gemm_f32(const GemmDesc& d, hipStream_t st);
 size_t gemm_f32_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad);
-hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, hipStream_t st);
+hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, ColumnSums* sums, hipStream_t st);
 
 }  // namespace lynx

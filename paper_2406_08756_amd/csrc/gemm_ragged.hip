@@ -6,7 +6,6 @@
 
 #include "dropout_host.h"
 #include "gemm_launch.h"
-#include "reduce_partials.h"
 
 namespace lynx {
 namespace {
@@ -344,7 +343,7 @@ RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad) {
 }
 
 hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
-                            hipStream_t st) {
+                            ColumnSums* sums, hipStream_t st) {
   const RaggedPairPlan p = plan_pair_ragged(wgrad, dgrad);
   MfmaGemmArgs d = make_args(dgrad), w = make_args(wgrad);
   w.k_splits = ceil_div(w.K, p.w_per);
@@ -366,13 +365,8 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   if (w.k_splits > 1 && d.k_splits > 1) e = launch_finish(&w, &d, st);
   else if (w.k_splits > 1) e = launch_finish(&w, nullptr, st);
   else if (d.k_splits > 1) e = launch_finish(&d, nullptr, st);
-  if (e != hipSuccess) return e;
-  if (dgrad.epi.kind == kEpiGeluBwd) {
-    launch_reduce_partials<bf16_t>(dgrad.epi.colsum_partial, static_cast<bf16_t*>(dgrad.epi.colsum_out), nullptr,
-                                   nullptr, ceil_div(dgrad.M, kPairCost[p.tile].bm / 2), dgrad.N, st);
-    return hipGetLastError();
-  }
-  return hipSuccess;
+  if (e != hipSuccess || dgrad.epi.kind != kEpiGeluBwd) return e;
+  return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, ceil_div(dgrad.M, kPairCost[p.tile].bm / 2), dgrad.N);
 }
 
 }  // namespace lynx

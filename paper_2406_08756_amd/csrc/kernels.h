@@ -22,22 +22,39 @@ struct AttnShape {
   int global_heads, head0;
 };
 
+// ---- column sums over the rows of a tensor ---------------------------------
+// Their first stage runs inside the kernels that form the rows and leaves partial sums, one row of `cols`
+// floats per workgroup; the second stage, out[c] = the sum of the partial rows in a fixed order, is asked for
+// here and done for every job at once by finish_column_sums (which empties the list).
+struct ColumnSums {
+  struct Job { const float* part; void* out; int rows, cols; };
+  static constexpr int kMaxJobs = 8;
+  Job job[kMaxJobs];
+  int n = 0;
+  hipError_t add(const float* part, void* out, int rows, int cols) {
+    if (n == kMaxJobs) return hipErrorInvalidValue;
+    job[n++] = {part, out, rows, cols};
+    return hipSuccess;
+  }
+};
+hipError_t finish_column_sums(int dtype, ColumnSums* sums, hipStream_t st);
+
 // ---- LayerNorm ------------------------------------------------------------
 hipError_t layernorm_fwd(int dtype, const void* x, const void* gamma, const void* beta, void* y,
                          float* mean, float* rstd, int rows, int cols, float eps, hipStream_t st);
 // dx_out = dres + dLN/dx (dres may alias nothing; dx_out may alias dres);
-// dgamma/dbeta are reduced over rows in two fixed-order stages through scratch.
-size_t layernorm_bwd_scratch_bytes(int rows, int cols);
+// the partial sums of dgamma / dbeta (and dbias) go to `scratch`, their second stage to `sums`.
+size_t layernorm_bwd_scratch_bytes(int rows, int cols, bool dropout);
 hipError_t layernorm_bwd(int dtype, const void* dy, const void* x, const float* mean,
                          const float* rstd, const void* gamma, const void* dres, void* dx_out,
                          void* dgamma, void* dbeta, float* scratch, int rows, int cols,
-                         hipStream_t st);
+                         ColumnSums* sums, hipStream_t st);
 // The same, and in the same pass the backward of the bias + dropout + residual operator
 // whose output the LayerNorm read: dropped = keep c round(dx_out), dbias = its column sums.
 hipError_t layernorm_bwd_dropout_bwd(int dtype, const void* dy, const void* x, const float* mean,
                                      const float* rstd, const void* gamma, const void* dres, void* dx_out,
                                      void* dgamma, void* dbeta, void* dropped, void* dbias, float* scratch,
-                                     int rows, int cols, int site, DropoutParams dp, hipStream_t st);
+                                     int rows, int cols, int site, DropoutParams dp, ColumnSums* sums, hipStream_t st);
 
 // ---- attention softmax / dropout -----------------------------------------
 // P = softmax_{j<=i}(S * scale) (written if P != null), Pd = keep * P * c
@@ -57,17 +74,17 @@ hipError_t gelu_fwd(int dtype, const void* u, void* g, size_t n, hipStream_t st)
 size_t colsum_scratch_bytes(int rows, int cols);
 // du = dg * gelu'(u); dbias[c] = sum_r du[r, c]
 hipError_t gelu_bwd(int dtype, const void* dg, const void* u, void* du, void* dbias,
-                    float* scratch, int rows, int cols, hipStream_t st);
+                    float* scratch, int rows, int cols, ColumnSums* sums, hipStream_t st);
 // out = res + keep * (in + bias) * c, dropout site `site`, element index r*cols + c
 hipError_t bias_dropout_add_fwd(int dtype, const void* in, const void* bias, const void* res,
                                 void* out, int rows, int cols, int site, DropoutParams dp,
                                 hipStream_t st);
 // din = keep * dout * c; dbias[c] = sum_r din[r, c]
 hipError_t dropout_bwd(int dtype, const void* dout, void* din, void* dbias, float* scratch,
-                       int rows, int cols, int site, DropoutParams dp, hipStream_t st);
+                       int rows, int cols, int site, DropoutParams dp, ColumnSums* sums, hipStream_t st);
 // dbias[c] = sum_r x[r, c]
 hipError_t column_sum(int dtype, const void* x, void* dbias, float* scratch, int rows, int cols,
-                      hipStream_t st);
+                      ColumnSums* sums, hipStream_t st);
 // out[(bi * a + hd) * s + i] = sum_dd x[t, hd * d + dd] * y[t, hd * d + dd], t = bi * s + i (fp32);
 // x and y are [T, a * d] with row stride ld.  With x = dC and y = C this is the row dot
 // product sum_j dP_ij P_ij of the softmax backward.
@@ -118,8 +135,8 @@ enum GemmEpilogueKind : int {
   // stride = c_sm).  Bit-identical to bias_dropout_add_fwd run on a stored P.
   kEpiBiasDropoutAdd = 1,
   // GeLU backward (input gradient of FC2 only, inside gemm_pair): C = P gelu'(aux) and
-  // colsum_out[n] = sum_m C[m, n] (the FC1 bias gradient), reduced in two fixed-order stages
-  // through `colsum_partial` (gemm_pair_colsum_bytes).
+  // colsum_out[n] = sum_m C[m, n] (the FC1 bias gradient): partial sums to `colsum_partial`
+  // (gemm_pair_colsum_bytes), second stage to the pair's `sums`.
   kEpiGeluBwd = 2,
   // dropout + softmax backward (B5 + B4) on the score-shaped product dPd = dC V^T (causal,
   // batched): C = dS = scale aux (keep c P - rowdot), aux = the softmax output P in the layout
@@ -166,7 +183,7 @@ bool gemm_supported(int dtype, const GemmDesc& d);
 // Input gradient and weight gradient of one linear layer in one launch.  `scratch` as above
 // (gemm_pair_scratch_bytes).
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,
-                     size_t scratch_bytes, hipStream_t st);
+                     size_t scratch_bytes, ColumnSums* sums, hipStream_t st);
 size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // shapes and epilogue only
 // Whether the input gradient should carry the GeLU backward (kEpiGeluBwd): supported, and it pays.
 bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);

@@ -5,7 +5,7 @@
 // sums for dgamma / dbeta accumulate in registers over the rows the workgroup
 // visits, and are then reduced over workgroups in a second fixed-order stage.
 #include "dropout_host.h"
-#include "reduce_partials.h"
+#include "device_common.h"
 
 namespace lynx {
 namespace {
@@ -373,8 +373,8 @@ hipError_t layernorm_fwd(int dtype, const void* x, const void* gamma, const void
   return hipGetLastError();
 }
 
-size_t layernorm_bwd_scratch_bytes(int rows, int cols) {
-  return 3 * static_cast<size_t>(bwd_blocks(rows)) * cols * sizeof(float);
+size_t layernorm_bwd_scratch_bytes(int rows, int cols, bool dropout) {
+  return (dropout ? 3 : 2) * static_cast<size_t>(bwd_blocks(rows)) * cols * sizeof(float);
 }
 
 namespace {
@@ -382,7 +382,7 @@ namespace {
 template <typename T, bool DROP>
 hipError_t launch_bwd(const T* dy, const T* x, const float* mean, const float* rstd, const T* gamma,
                       const T* dres, T* dx_out, T* dgamma, T* dbeta, float* scratch, int rows, int cols,
-                      T* dropped, T* dbias, DropoutKey key, hipStream_t st) {
+                      T* dropped, T* dbias, DropoutKey key, ColumnSums* sums, hipStream_t st) {
   const int nb = bwd_blocks(rows);
   float* part_dg = scratch;
   float* part_db = scratch + static_cast<size_t>(nb) * cols;
@@ -397,9 +397,11 @@ hipError_t launch_bwd(const T* dy, const T* x, const float* mean, const float* r
   else if (nc <= 3) { CALL(3); }
   else { CALL(4); }
 #undef CALL
-  launch_reduce_partials<T>(part_dg, dgamma, part_db, dbeta, nb, cols, st);
-  if (DROP) launch_reduce_partials<T>(part_dbias, dbias, nullptr, nullptr, nb, cols, st);
-  return hipGetLastError();
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = sums->add(part_dg, dgamma, nb, cols);
+  if (e == hipSuccess) e = sums->add(part_db, dbeta, nb, cols);
+  if (DROP && e == hipSuccess) e = sums->add(part_dbias, dbias, nb, cols);
+  return e;
 }
 
 }  // namespace
@@ -407,24 +409,24 @@ hipError_t launch_bwd(const T* dy, const T* x, const float* mean, const float* r
 hipError_t layernorm_bwd(int dtype, const void* dy, const void* x, const float* mean,
                          const float* rstd, const void* gamma, const void* dres, void* dx_out,
                          void* dgamma, void* dbeta, float* scratch, int rows, int cols,
-                         hipStream_t st) {
+                         ColumnSums* sums, hipStream_t st) {
   if (cols > 8192 || cols % 8) return hipErrorInvalidValue;
   const DropoutKey none{};
   if (dtype == 1)
     return launch_bwd<bf16_t, false>(static_cast<const bf16_t*>(dy), static_cast<const bf16_t*>(x), mean, rstd,
                                      static_cast<const bf16_t*>(gamma), static_cast<const bf16_t*>(dres),
                                      static_cast<bf16_t*>(dx_out), static_cast<bf16_t*>(dgamma),
-                                     static_cast<bf16_t*>(dbeta), scratch, rows, cols, nullptr, nullptr, none, st);
+                                     static_cast<bf16_t*>(dbeta), scratch, rows, cols, nullptr, nullptr, none, sums, st);
   return launch_bwd<float, false>(static_cast<const float*>(dy), static_cast<const float*>(x), mean, rstd,
                                   static_cast<const float*>(gamma), static_cast<const float*>(dres),
                                   static_cast<float*>(dx_out), static_cast<float*>(dgamma),
-                                  static_cast<float*>(dbeta), scratch, rows, cols, nullptr, nullptr, none, st);
+                                  static_cast<float*>(dbeta), scratch, rows, cols, nullptr, nullptr, none, sums, st);
 }
 
 hipError_t layernorm_bwd_dropout_bwd(int dtype, const void* dy, const void* x, const float* mean,
                                      const float* rstd, const void* gamma, const void* dres, void* dx_out,
                                      void* dgamma, void* dbeta, void* dropped, void* dbias, float* scratch,
-                                     int rows, int cols, int site, DropoutParams dp, hipStream_t st) {
+                                     int rows, int cols, int site, DropoutParams dp, ColumnSums* sums, hipStream_t st) {
   if (cols > 8192 || cols % 8) return hipErrorInvalidValue;
   const DropoutKey key = make_dropout_key(dp, site);
   if (dtype == 1)
@@ -432,12 +434,12 @@ hipError_t layernorm_bwd_dropout_bwd(int dtype, const void* dy, const void* x, c
                                     static_cast<const bf16_t*>(gamma), static_cast<const bf16_t*>(dres),
                                     static_cast<bf16_t*>(dx_out), static_cast<bf16_t*>(dgamma),
                                     static_cast<bf16_t*>(dbeta), scratch, rows, cols,
-                                    static_cast<bf16_t*>(dropped), static_cast<bf16_t*>(dbias), key, st);
+                                    static_cast<bf16_t*>(dropped), static_cast<bf16_t*>(dbias), key, sums, st);
   return launch_bwd<float, true>(static_cast<const float*>(dy), static_cast<const float*>(x), mean, rstd,
                                  static_cast<const float*>(gamma), static_cast<const float*>(dres),
                                  static_cast<float*>(dx_out), static_cast<float*>(dgamma),
                                  static_cast<float*>(dbeta), scratch, rows, cols,
-                                 static_cast<float*>(dropped), static_cast<float*>(dbias), key, st);
+                                 static_cast<float*>(dropped), static_cast<float*>(dbias), key, sums, st);
 }
 
 }  // namespace lynx

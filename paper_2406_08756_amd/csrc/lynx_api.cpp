@@ -92,12 +92,13 @@ struct Book {
   // the policy keeps none of S, P, Pd and the shape is one the fused attention kernels take:
   // operators 3-5 never run, operator 6 reads QKV alone
   bool fused_attn = false;
-  // what the run goes without because the workspace has no room for it: 1, scratch that only buys
-  // time (contractions stay whole); 2, also the fusion of operators 7 + 8 and 12 + 13, which places the
+  // what the run goes without because the workspace has no room for it: 1, partial sums of every column
+  // sum of backward at once (each is finished before the next); 2, also scratch that only buys
+  // time (contractions stay whole); 3, also the fusion of operators 7 + 8 and 12 + 13, which places the
   // activations after them elsewhere
   int thrift = 0;
 };
-constexpr int kMaxThrift = 2;
+constexpr int kNoDeferredSums = 1, kUncut = 2, kMaxThrift = 3;
 
 }  // namespace
 
@@ -160,7 +161,7 @@ struct Ctx {  // one pass (rehearsal or real) of a call
 enum BackwardSlot {
   kB13Dropout = 14, kB12Grads, kB11Gelu, kB10Grads, kB98LayerNormDropout, kB7Grads, kB6DPd,
   kB6DV, kB54Softmax, kB3DQ, kB3DK, kB2Grads, kB2BiasGrad, kB1LayerNorm, kB6RowDot, kB654DScores,
-  kOp36Fused, kB654DScoresFused, kB6DVFused, kNumSlots
+  kOp36Fused, kB654DScoresFused, kB6DVFused, kColumnSums, kNumSlots
 };
 static_assert(kNumSlots <= LYNX_PROFILE_SLOTS, "profile slots");
 static_assert(LYNX_STATIC_WORKSPACE_BYTES == lynx::kStaticWorkspaceBytes, "header and library agree on the block size");
@@ -171,7 +172,7 @@ const char* const kSlotNames[kNumSlots] = {
     "b12_fc2_dgrad_wgrad", "b11_gelu_bwd", "b10_fc1_dgrad_wgrad",
     "b98_layernorm2_dropout_bwd", "b7_proj_dgrad_wgrad", "b6_dpd", "b6_dv", "b54_softmax_dropout_bwd", "b3_dq",
     "b3_dk", "b2_qkv_dgrad_wgrad", "b2_bias_grad", "b1_layernorm1_bwd", "b6_rowdot", "b654_dscores",
-    "op3456_attention_fused", "b654_dscores_fused", "b6_dv_fused"};
+    "op3456_attention_fused", "b654_dscores_fused", "b6_dv_fused", "b_column_sums"};
 
 char* act_ptr(const Ctx& cx, int i) {
   if (i == 0) return const_cast<char*>(static_cast<const char*>(cx.L->x));
@@ -319,7 +320,7 @@ GemmDesc attn_cols(const void* sq, const void* y, long long ldy, void* out, long
 // One linear product, with scratch of its own for the partial sums of a cut contraction.
 lynx_status run_linear(Ctx& cx, int slot, GemmDesc g) {
   const int dt = cx.L->D.dtype;
-  g.uncut = cx.bk->thrift > 0;
+  g.uncut = cx.bk->thrift >= kUncut;
   const size_t bytes = lynx::gemm_scratch_bytes(dt, g);
   Temp scratch;
   if (bytes > 0) LYNX_TRY(alloc_temp(cx, bytes, &scratch));
@@ -432,7 +433,7 @@ GemmDesc fused_linear_desc(Ctx& cx, int lin, bool keep_product) {
 }
 bool can_fuse_linear(const Ctx& cx, int lin) {
   const Dims& D = cx.L->D;
-  if (cx.bk->thrift > 1) return false;
+  if (cx.bk->thrift >= kMaxThrift) return false;
   // shapes only (pointers are 256-byte aligned arena blocks or checked caller buffers)
   GemmDesc g = linear_fwd(reinterpret_cast<const void*>(256), reinterpret_cast<const void*>(256), nullptr,
                           reinterpret_cast<void*>(256), D.T, D.h, lin == 7 ? D.p : D.f);
@@ -577,9 +578,16 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   LYNX_TRY(recompute_pass(cx, LYNX_SEG_ALL_MISSING));
 
   const int widest = D.h > 3 * D.p ? (D.h > D.f ? D.h : D.f) : (3 * D.p > D.f ? 3 * D.p : D.f);
-  size_t scratch_bytes = lynx::colsum_scratch_bytes(D.T, widest);
-  const size_t ln_bytes = lynx::layernorm_bwd_scratch_bytes(D.T, D.h);
-  if (ln_bytes > scratch_bytes) scratch_bytes = ln_bytes;
+  // The second stage of the eight column sums (bias and LayerNorm gradients) is one launch at the end;
+  // without the room for all their partial sums, each producer reuses `scr` and is finished at once.
+  const bool defer = cx.bk->thrift < kNoDeferredSums;
+  lynx::ColumnSums sums;
+  size_t scratch_bytes = 0;
+  if (!defer) {
+    scratch_bytes = lynx::colsum_scratch_bytes(D.T, widest);
+    const size_t ln_bytes = lynx::layernorm_bwd_scratch_bytes(D.T, D.h, true);
+    if (ln_bytes > scratch_bytes) scratch_bytes = ln_bytes;
+  }
   {  // fp32 partial sums of weight gradients that are cut into K ranges
     const int lin[4][2] = {{D.h, D.f}, {D.f, D.h}, {D.h, D.p}, {3 * D.p, D.h}};  // {outputs, inputs}
     for (const auto& nk : lin)
@@ -588,7 +596,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
         GemmDesc d = linear_dgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
         GemmDesc g = linear_wgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
         d.epi.kind = gelu ? lynx::kEpiGeluBwd : lynx::kEpiNone;
-        d.uncut = g.uncut = cx.bk->thrift > 0;
+        d.uncut = g.uncut = cx.bk->thrift >= kUncut;
         const size_t b = lynx::gemm_pair_scratch_bytes(dt, d, g);
         if (b > scratch_bytes) scratch_bytes = b;
       }
@@ -596,18 +604,33 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   Temp scratch, t_dv2, t_dg, t_du, t_dy2, t_dx2, t_do, t_dc, t_dpd, t_dqkv, t_dy1;
   LYNX_TRY(alloc_temp(cx, scratch_bytes, &scratch));
   float* scr = reinterpret_cast<float*>(temp_ptr(cx, scratch));
+  Temp t_part[4];  // partial sums of: b2, b1 (two producers), LayerNorm 2 with bo, bqkv and LayerNorm 1
+  float* part = scr;
+  auto alloc_partials = [&](int i, size_t bytes) -> lynx_status {
+    if (!defer) return LYNX_OK;
+    LYNX_TRY(alloc_temp(cx, bytes, &t_part[i]));
+    part = reinterpret_cast<float*>(temp_ptr(cx, t_part[i]));
+    return LYNX_OK;
+  };
+  auto finish_sums = [&](bool last) -> lynx_status {
+    if (defer != last) return LYNX_OK;
+    LYNX_LAUNCH(cx, kColumnSums, lynx::finish_column_sums(dt, &sums, cx.st));
+    return LYNX_OK;
+  };
   // both gradients of a linear layer
   auto launch_pair = [&](int slot, GemmDesc dg, GemmDesc wg) -> lynx_status {
-    dg.uncut = wg.uncut = cx.bk->thrift > 0;
-    LYNX_LAUNCH(cx, slot, lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, cx.st));
+    dg.uncut = wg.uncut = cx.bk->thrift >= kUncut;
+    LYNX_LAUNCH(cx, slot, lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, &sums, cx.st));
     return LYNX_OK;
   };
   const size_t th = static_cast<size_t>(D.T) * D.h * e, tf = static_cast<size_t>(D.T) * D.f * e;
 
   // B13: OUT = X2 + keep2 (V2 + b2) c
   LYNX_TRY(alloc_temp(cx, th, &t_dv2));
-  LYNX_LAUNCH(cx, kB13Dropout, lynx::dropout_bwd(dt, d_out, temp_ptr(cx, t_dv2), gr->b2, scr, D.T, D.h, 2,
-                                    dropout_params(L), cx.st));
+  LYNX_TRY(alloc_partials(0, lynx::colsum_scratch_bytes(D.T, D.h)));
+  LYNX_LAUNCH(cx, kB13Dropout, lynx::dropout_bwd(dt, d_out, temp_ptr(cx, t_dv2), gr->b2, part, D.T, D.h, 2,
+                                    dropout_params(L), &sums, cx.st));
+  LYNX_TRY(finish_sums(false));
   LYNX_TRY(tap(cx, 12, temp_ptr(cx, t_dv2)));
   // B12: V2 = G W2^T, and B11: G = gelu(U).  When the matrix-core pair launch applies, the
   // store pass of the input gradient multiplies by gelu'(U) and sums the columns (the FC1
@@ -616,18 +639,19 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   {
     GemmDesc dg = linear_dgrad(temp_ptr(cx, t_dv2), w.w2, temp_ptr(cx, t_du), D.T, D.h, D.f);
     GemmDesc wg = linear_wgrad(temp_ptr(cx, t_dv2), act_ptr(cx, 11), gr->w2, D.T, D.h, D.f);
-    Temp t_colsum;
     dg.epi.kind = lynx::kEpiGeluBwd;
-    dg.uncut = wg.uncut = cx.bk->thrift > 0;
+    dg.uncut = wg.uncut = cx.bk->thrift >= kUncut;
     dg.epi.aux = act_ptr(cx, 10);
     dg.epi.aux_ld = D.f;
     dg.epi.colsum_partial = scr;
     dg.epi.colsum_out = gr->b1;
     if (lynx::gemm_pair_absorbs_gelu(dt, dg, wg)) {
-      LYNX_TRY(alloc_temp(cx, lynx::gemm_pair_colsum_bytes(dt, dg, wg), &t_colsum));
-      dg.epi.colsum_partial = reinterpret_cast<float*>(temp_ptr(cx, t_colsum));
+      // (not in `scr`, where the same launch leaves the partial sums of a cut weight gradient)
+      LYNX_TRY(alloc_temp(cx, lynx::gemm_pair_colsum_bytes(dt, dg, wg), &t_part[1]));
+      dg.epi.colsum_partial = reinterpret_cast<float*>(temp_ptr(cx, t_part[1]));
       LYNX_TRY(launch_pair(kB12Grads, dg, wg));
-      free_temp(cx, &t_colsum);
+      LYNX_TRY(finish_sums(false));
+      if (!defer) free_temp(cx, &t_part[1]);
       free_temp(cx, &t_dv2);
       free_act(cx, 11);
     } else {
@@ -637,8 +661,10 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
       LYNX_TRY(launch_pair(kB12Grads, dg, wg));
       free_temp(cx, &t_dv2);
       free_act(cx, 11);
+      LYNX_TRY(alloc_partials(1, lynx::colsum_scratch_bytes(D.T, D.f)));
       LYNX_LAUNCH(cx, kB11Gelu, lynx::gelu_bwd(dt, temp_ptr(cx, t_dg), act_ptr(cx, 10), temp_ptr(cx, t_du),
-                                               gr->b1, scr, D.T, D.f, cx.st));
+                                               gr->b1, part, D.T, D.f, &sums, cx.st));
+      LYNX_TRY(finish_sums(false));
       free_temp(cx, &t_dg);
     }
   }
@@ -654,11 +680,13 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   // so dO = keep1 c dX2 and dbo = its column sums
   LYNX_TRY(alloc_temp(cx, th, &t_dx2));
   LYNX_TRY(alloc_temp(cx, th, &t_do));
+  LYNX_TRY(alloc_partials(2, lynx::layernorm_bwd_scratch_bytes(D.T, D.h, true)));
   LYNX_LAUNCH(cx, kB98LayerNormDropout,
               lynx::layernorm_bwd_dropout_bwd(dt, temp_ptr(cx, t_dy2), act_ptr(cx, 8), stats_ptr(cx, 9),
                                               stats_ptr(cx, 9) + D.T, w.g2, d_out, temp_ptr(cx, t_dx2), gr->g2,
-                                              gr->be2, temp_ptr(cx, t_do), gr->bo, scr, D.T, D.h, 1,
-                                              dropout_params(L), cx.st));
+                                              gr->be2, temp_ptr(cx, t_do), gr->bo, part, D.T, D.h, 1,
+                                              dropout_params(L), &sums, cx.st));
+  LYNX_TRY(finish_sums(false));
   LYNX_TRY(tap(cx, 8, temp_ptr(cx, t_dx2)));
   LYNX_TRY(tap(cx, 7, temp_ptr(cx, t_do)));
   free_temp(cx, &t_dy2);
@@ -754,14 +782,21 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   LYNX_TRY(alloc_temp(cx, th, &t_dy1));
   LYNX_TRY(launch_pair(kB2Grads, linear_dgrad(dqkv, w.wqkv, temp_ptr(cx, t_dy1), D.T, 3 * D.p, D.h),
                        linear_wgrad(dqkv, act_ptr(cx, 1), gr->wqkv, D.T, 3 * D.p, D.h)));
-  LYNX_LAUNCH(cx, kB2BiasGrad, lynx::column_sum(dt, dqkv, gr->bqkv, scr, D.T, 3 * D.p, cx.st));
+  const size_t bqkv_bytes = Arena::round_up(lynx::colsum_scratch_bytes(D.T, 3 * D.p));
+  LYNX_TRY(alloc_partials(3, bqkv_bytes + lynx::layernorm_bwd_scratch_bytes(D.T, D.h, false)));
+  LYNX_LAUNCH(cx, kB2BiasGrad, lynx::column_sum(dt, dqkv, gr->bqkv, part, D.T, 3 * D.p, &sums, cx.st));
+  LYNX_TRY(finish_sums(false));
+  if (defer) part += bqkv_bytes / sizeof(float);
   free_temp(cx, &t_dqkv);
   free_act(cx, 2);
   LYNX_TRY(tap(cx, 1, temp_ptr(cx, t_dy1)));
   // B1: Y1 = LN1(X); dX = dX2 + dLN
   LYNX_LAUNCH(cx, kB1LayerNorm, lynx::layernorm_bwd(dt, temp_ptr(cx, t_dy1), act_ptr(cx, 0), stats_ptr(cx, 1),
                                       stats_ptr(cx, 1) + D.T, w.g1, temp_ptr(cx, t_dx2), d_x, gr->g1,
-                                      gr->be1, scr, D.T, D.h, cx.st));
+                                      gr->be1, part, D.T, D.h, &sums, cx.st));
+  LYNX_TRY(finish_sums(false));
+  LYNX_TRY(finish_sums(true));
+  for (Temp& t : t_part) free_temp(cx, &t);
   free_temp(cx, &t_dy1);
   free_temp(cx, &t_dx2);
   free_temp(cx, &scratch);
@@ -781,13 +816,13 @@ bool grads_ok(const lynx_grads* g) {
   return true;
 }
 
-// The least thrift at which forward(retain) -> backward fits the workspace (none: 1, for the forward's sake).
+// The least thrift at which forward(retain) -> backward fits the workspace (none: kUncut, for the forward's sake).
 int thrift_for(lynx_layer_s* L, uint32_t retain) {
   if (L->thrift_mask != retain) {
     // (placeholders, non-null and aligned: the rehearsal takes the kernel path a real call takes)
     void* const fake = reinterpret_cast<void*>(static_cast<uintptr_t>(Arena::kAlign));
     const lynx_grads g{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
-    L->thrift = 1;
+    L->thrift = kUncut;
     for (int level = 0; level <= kMaxThrift; ++level) {
       Book book;
       book.arena = Arena(L->book.arena.capacity());

@@ -84,3 +84,43 @@ def test_layer_in_a_small_workspace(name):
             first = first or bits
             assert all(torch.equal(p, q) for p, q in zip(first, bits)), hex(mask)
         layer.close()
+
+
+def least_workspace(cfg, mask):
+    """The smallest workspace, in steps of 256 bytes, that takes forward and backward."""
+    lo, hi = 0, B.lynx_workspace_bytes(cfg, mask) // 256
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        h = dry_layer(cfg, ws_bytes=256 * mid)
+        try:
+            B.lynx_layer_forward(h, FX, FOUT, mask, 0)
+            B.lynx_layer_backward(h, FDOUT, FDX, FAKE)
+            hi = mid
+        except B.LynxError:
+            lo = mid
+        B.lynx_layer_destroy(h)
+    return 256 * hi
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,tokens", [(synth.BF16, 8), (synth.BF16, 200), (synth.F32, 16)])
+def test_column_sums_together_or_one_after_the_other(dtype, tokens):
+    # (every contraction under 512: none is cut, so the bits depend on the column sums alone.  200 tokens and
+    # widths of 264, 120 and 72 leave partly filled groups of 32 and 128 rows and of 64 columns)
+    cfg = synth.LayerConfig(dtype, 264, 1, 40, 72, tokens, 1, tp_size=2, seed=5)
+    params, X, dOUT = synth.make_params(cfg, random_ln=True), synth.make_x(cfg), synth.make_dout(cfg)
+    _, grads = orc.layer_forward_backward(cfg, params, X, dOUT)
+    need, least = B.lynx_workspace_bytes(cfg, pm.FULL_RECOMPUTE), least_workspace(cfg, pm.FULL_RECOMPUTE)
+    assert least < need
+    runs = []
+    for size in (need, least):
+        layer = GpuLayer(cfg, params, workspace_bytes=size)
+        layer.workspace.fill_(0xFF)
+        layer.forward(X, pm.FULL_RECOMPUTE)
+        layer.backward(dOUT)
+        runs.append([layer.dx.clone()] + [layer.grads[k].clone() for k in synth.PARAM_NAMES])
+        got = layer.results()
+        for k, ref in grads.items():
+            assert rel_err(got[k], ref) <= {synth.F32: 1e-4, synth.BF16: 2e-2}[dtype], (k, rel_err(got[k], ref))
+        layer.close()
+    assert all(torch.equal(p, q) for p, q in zip(*runs))
