@@ -166,11 +166,13 @@ layernorm_fwd_stream_kernel(const T* __restrict__ x, const T* __restrict__ gamma
   }
 }
 
-// Block-wide sums of four values; every thread gets all totals.  The combination
-// order is fixed.
-__device__ __forceinline__ void block_sum4(float (&v)[4], float* smem) {
+// Sums of four values over each of the G groups of wavefronts of a workgroup; every thread gets its
+// group's totals.  The combination order is fixed.
+template <int G>
+__device__ __forceinline__ void group_sum4(float (&v)[4], float* smem) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) v[i] = wave_sum(v[i]);
+  if (G == kBwdThreads / kWave) return;
   const int w = threadIdx.x >> 6;
   __syncthreads();  // previous use of smem is over
   if ((threadIdx.x & (kWave - 1)) == 0) {
@@ -180,7 +182,28 @@ __device__ __forceinline__ void block_sum4(float (&v)[4], float* smem) {
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-    v[i] = (smem[4 * i] + smem[4 * i + 1]) + (smem[4 * i + 2] + smem[4 * i + 3]);
+    v[i] = G == 1 ? (smem[4 * i] + smem[4 * i + 1]) + (smem[4 * i + 2] + smem[4 * i + 3])
+                  : smem[4 * i + (w & ~1)] + smem[4 * i + (w | 1)];
+}
+
+// One row of column partials of the workgroup: the groups' sums, added in order, to `part` + the thread's column.
+template <int G>
+__device__ __forceinline__ void store_partial(float (&acc)[8], float* part, bool on, float* lds) {
+  constexpr int kGroup = kBwdThreads / G;
+  if (G > 1) {
+    __syncthreads();  // previous use of lds is over
+    if (threadIdx.x >= kGroup) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) lds[k * kBwdThreads + threadIdx.x] = acc[k];
+    }
+    __syncthreads();
+    if (threadIdx.x >= kGroup) return;
+#pragma unroll
+    for (int g = 1; g < G; ++g)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc[k] += lds[k * kBwdThreads + g * kGroup + threadIdx.x];
+  }
+  if (on) store8(part, acc);
 }
 
 // RPI rows per iteration: all loads of those rows (dy, x, residual gradient) are issued
@@ -192,14 +215,23 @@ __device__ __forceinline__ void block_sum4(float (&v)[4], float* smem) {
 // residual operator (dx_out = d(X + keep (O + b) c)): the same pass writes
 // dO = keep c round(dx_out) to `dropped` and accumulates its column sums (the bias
 // gradient), which saves the separate pass that would read dx_out again.
-template <typename T, int NC, int RPI, bool DROP>
+//
+// G: rows of at most 1024 or 512 columns leave half or three quarters of the workgroup without a vector, so
+// there it is G = 2 or 4 groups of wavefronts, each on RPI rows of its own; the groups' column sums meet in LDS
+// at the end.  8192 rows of bf16, with dropout: h 256 21.2 -> 12.0 us, h 512 22.2 -> 12.9, h 1024 29.2 -> 23.0 (3.7 TB/s;
+// loads, reduction and stores of a row pair take turns; 1024 workgroups instead of 512 measure the same).
+template <typename T, int NC, int RPI, int G, bool DROP>
 __global__ void __launch_bounds__(kBwdThreads)
 layernorm_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x,
                      const float* __restrict__ mean, const float* __restrict__ rstd,
                      const T* __restrict__ gamma, const T* dres, T* dx_out,
                      float* __restrict__ part_dg, float* __restrict__ part_db, int rows, int cols,
                      T* __restrict__ dropped, float* __restrict__ part_dbias, DropoutKey key) {
+  static_assert(G == 1 || NC == 1, "a group's row is one vector per thread");
+  constexpr int kGroup = kBwdThreads / G;
   __shared__ float smem[16];
+  __shared__ float combine[G > 1 ? 8 * kBwdThreads : 1];
+  const int grp = G == 1 ? 0 : threadIdx.x / kGroup, lane = G == 1 ? threadIdx.x : threadIdx.x % kGroup;
   Raw8<T> graw[NC];
   float adg[NC][8], adb[NC][8], adbias[DROP ? NC : 1][8];
 #pragma unroll
@@ -208,25 +240,26 @@ layernorm_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x,
     for (int k = 0; k < 8; ++k) adbias[c][k] = 0.f;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    const int j0 = (threadIdx.x + c * kBwdThreads) * 8;
+    const int j0 = (lane + c * kGroup) * 8;
     if (j0 < cols) load_raw(gamma + j0, graw[c]);
 #pragma unroll
     for (int k = 0; k < 8; ++k) { adg[c][k] = 0.f; adb[c][k] = 0.f; }
   }
   const float inv_n = 1.0f / static_cast<float>(cols);
-  for (int r0 = RPI * blockIdx.x; r0 < rows; r0 += RPI * gridDim.x) {
+  for (int b0 = G * RPI * blockIdx.x; b0 < rows; b0 += G * RPI * gridDim.x) {
+    const int r0 = b0 + RPI * grp;
     int rr[RPI];
     float mu[RPI], rs[RPI];
     Raw8<T> rdy[RPI][NC], rx[RPI][NC], rdr[RPI][NC];
 #pragma unroll
     for (int q = 0; q < RPI; ++q) {
-      rr[q] = r0 + q < rows ? r0 + q : r0;  // a missing row re-reads the first, uncounted
+      rr[q] = r0 + q < rows ? r0 + q : b0;  // a missing row re-reads the first, uncounted
       mu[q] = mean[rr[q]];
       rs[q] = rstd[rr[q]];
       const size_t base = static_cast<size_t>(rr[q]) * cols;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        const int j0 = (threadIdx.x + c * kBwdThreads) * 8;
+        const int j0 = (lane + c * kGroup) * 8;
         if (j0 < cols) {
           if (DROP) {
             load_raw(dy + base + j0, rdy[q][c]);
@@ -246,7 +279,7 @@ layernorm_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x,
       const float live = r0 + q < rows ? 1.0f : 0.0f;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        const int j0 = (threadIdx.x + c * kBwdThreads) * 8;
+        const int j0 = (lane + c * kGroup) * 8;
         if (j0 < cols) {
           float gd[8], xh[8], g[8];
           unpack(rdy[q][c], gd);
@@ -264,7 +297,7 @@ layernorm_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x,
         }
       }
     }
-    block_sum4(sums, smem);
+    group_sum4<G>(sums, smem);
 #pragma unroll
     for (int q = 0; q < RPI; ++q)
 #pragma unroll
@@ -279,7 +312,7 @@ layernorm_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x,
       const float m1 = sums[2 * q] * inv_n, m2 = sums[2 * q + 1] * inv_n;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        const int j0 = (threadIdx.x + c * kBwdThreads) * 8;
+        const int j0 = (lane + c * kGroup) * 8;
         if (j0 < cols) {
           float gd[8], xh[8], g[8], dr[8], o[8];
           unpack(rdy[q][c], gd);
@@ -310,20 +343,29 @@ layernorm_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x,
   }
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    const int j0 = (threadIdx.x + c * kBwdThreads) * 8;
-    if (j0 < cols) {
-      store8(part_dg + static_cast<size_t>(blockIdx.x) * cols + j0, adg[c]);
-      store8(part_db + static_cast<size_t>(blockIdx.x) * cols + j0, adb[c]);
-      if (DROP) store8(part_dbias + static_cast<size_t>(blockIdx.x) * cols + j0, adbias[DROP ? c : 0]);
-    }
+    const int j0 = (lane + c * kGroup) * 8;
+    const size_t at = static_cast<size_t>(blockIdx.x) * cols + j0;
+    store_partial<G>(adg[c], part_dg + at, j0 < cols, combine);
+    store_partial<G>(adb[c], part_db + at, j0 < cols, combine);
+    if (DROP) store_partial<G>(adbias[DROP ? c : 0], part_dbias + at, j0 < cols, combine);
   }
 }
 
 constexpr int kBwdRowsPerIter = 2;
+// One pass with dropout, one without, bf16, a workgroup per row -> groups: 1024 rows of 256 5.4 + 4.5 -> 5.8 + 5.0 us,
+// of 1024 7.2 + 6.2 -> 6.6 + 6.0; 2048 rows of 256 7.9 + 6.8 -> 6.2 + 5.4, of 1024 10.5 + 8.2 -> 9.3 + 7.5.  Below 2048
+// rows the groups only make fewer workgroups of the same latency (a pass of h 512, 768 tokens: 137.2 -> 139.4 us).
+constexpr int kBwdGroupedRows = 2048;
 
-int bwd_blocks(int rows) {
-  const int groups = (rows + kBwdRowsPerIter - 1) / kBwdRowsPerIter;
-  return groups < kBwdMaxBlocks ? groups : kBwdMaxBlocks;
+int bwd_groups(int rows, int cols) {
+  if (rows < kBwdGroupedRows) return 1;
+  return cols <= kBwdThreads * 2 ? 4 : cols <= kBwdThreads * 4 ? 2 : 1;
+}
+
+int bwd_blocks(int rows, int cols) {
+  const int per_block = bwd_groups(rows, cols) * kBwdRowsPerIter;
+  const int blocks = (rows + per_block - 1) / per_block;
+  return blocks < kBwdMaxBlocks ? blocks : kBwdMaxBlocks;
 }
 
 }  // namespace
@@ -374,7 +416,7 @@ hipError_t layernorm_fwd(int dtype, const void* x, const void* gamma, const void
 }
 
 size_t layernorm_bwd_scratch_bytes(int rows, int cols, bool dropout) {
-  return (dropout ? 3 : 2) * static_cast<size_t>(bwd_blocks(rows)) * cols * sizeof(float);
+  return (dropout ? 3 : 2) * static_cast<size_t>(bwd_blocks(rows, cols)) * cols * sizeof(float);
 }
 
 namespace {
@@ -383,19 +425,24 @@ template <typename T, bool DROP>
 hipError_t launch_bwd(const T* dy, const T* x, const float* mean, const float* rstd, const T* gamma,
                       const T* dres, T* dx_out, T* dgamma, T* dbeta, float* scratch, int rows, int cols,
                       T* dropped, T* dbias, DropoutKey key, ColumnSums* sums, hipStream_t st) {
-  const int nb = bwd_blocks(rows);
+  const int nb = bwd_blocks(rows, cols);
   float* part_dg = scratch;
   float* part_db = scratch + static_cast<size_t>(nb) * cols;
   float* part_dbias = scratch + 2 * static_cast<size_t>(nb) * cols;
   const int nc = (cols / 8 + kBwdThreads - 1) / kBwdThreads;
-#define CALL(NC)                                                                                     \
-  hipLaunchKernelGGL((layernorm_bwd_kernel<T, NC, kBwdRowsPerIter, DROP>), dim3(nb), dim3(kBwdThreads), 0, st, \
+#define CALL(NC, G)                                                                                  \
+  hipLaunchKernelGGL((layernorm_bwd_kernel<T, NC, kBwdRowsPerIter, G, DROP>), dim3(nb), dim3(kBwdThreads), 0, st, \
                      dy, x, mean, rstd, gamma, dres, dx_out, part_dg, part_db, rows, cols, dropped,   \
                      part_dbias, key)
-  if (nc <= 1) { CALL(1); }
-  else if (nc <= 2) { CALL(2); }
-  else if (nc <= 3) { CALL(3); }
-  else { CALL(4); }
+  switch (bwd_groups(rows, cols)) {
+    case 4: CALL(1, 4); break;
+    case 2: CALL(1, 2); break;
+    default:
+      if (nc <= 1) { CALL(1, 1); }
+      else if (nc <= 2) { CALL(2, 1); }
+      else if (nc <= 3) { CALL(3, 1); }
+      else { CALL(4, 1); }
+  }
 #undef CALL
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = sums->add(part_dg, dgamma, nb, cols);

@@ -34,6 +34,12 @@ SHAPES = {
     "cut_contractions": (synth.BF16, 2056, 1, 64, 4104, 24, 1),
     "long_tokens_narrow": (synth.BF16, 72, 1, 40, 72, 520, 6),
     "wide_ragged": (synth.BF16, 2312, 2, 104, 2568, 520, 2),
+    # LayerNorm backward: rows of a wavefront, half a workgroup and a whole one, more rows than one round of workgroups
+    "norm_512": (synth.BF16, 512, 1, 64, 64, 152, 27),
+    "norm_504_f32": (synth.F32, 504, 1, 56, 64, 152, 27),
+    "norm_520": (synth.BF16, 520, 1, 64, 64, 152, 27),
+    "norm_1024_f32": (synth.F32, 1024, 1, 64, 64, 152, 27),
+    "norm_1032": (synth.BF16, 1032, 1, 64, 64, 152, 27),
 }
 
 
