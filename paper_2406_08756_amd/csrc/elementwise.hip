@@ -70,14 +70,18 @@ struct IdentityOp {
 // thread's loads are issued before its first store; the four wavefronts' column sums
 // are added in a fixed order through LDS.  Many small workgroups keep enough
 // wavefronts resident to overlap the Philox / GeLU arithmetic with the memory traffic.
-constexpr int kRowsPerThread = kRowsPerBlock / (kThreads / kWave);
-template <typename T, typename Op>
+// V: vectors of the tile's width, 64 as above, or 16 where that gives the chip too few workgroups: then 16 lanes
+// share a row, a thread has two rows instead of eight and four times the workgroups share the latency.
+// The partial rows, and with them the scratch, are the same.  Dropout backward, 64 -> 16 vectors: 256 x 256 fp32
+// 6.6 -> 3.7 us, 768 x 512 bf16 6.8 -> 5.4, 984 x 3016 7.6 -> 6.0, 4000 x 1600 (500 workgroups of 64) 11.1 -> 8.4.
+template <typename T, typename Op, int V>
 __global__ void __launch_bounds__(kThreads)
 rows_colsum_kernel(Op op, const T* __restrict__ in0, const T* __restrict__ in1, T* __restrict__ outp,
                    int rows, int cols, float* __restrict__ partial) {
-  __shared__ float sm[kThreads / kWave][kWave][8];
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6;
-  const int vec = blockIdx.x * kWave + lane;
+  constexpr int kGroups = kThreads / V, kRowsPerThread = kRowsPerBlock / kGroups;
+  __shared__ float sm[kGroups][V][8];
+  const int lane = threadIdx.x % V, w = threadIdx.x / V;
+  const int vec = blockIdx.x * V + lane;
   const bool active = vec < (cols >> 3);
   const int r0 = blockIdx.y * kRowsPerBlock + w;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -85,7 +89,7 @@ rows_colsum_kernel(Op op, const T* __restrict__ in0, const T* __restrict__ in1, 
     Raw8<T> ra[kRowsPerThread], rb[Op::kInputs == 2 ? kRowsPerThread : 1];
 #pragma unroll
     for (int k = 0; k < kRowsPerThread; ++k) {
-      const int r = r0 + k * (kThreads / kWave);
+      const int r = r0 + k * kGroups;
       if (r < rows) {
         const size_t off = static_cast<size_t>(r) * cols + static_cast<size_t>(vec) * 8;
         load_raw_streaming(in0 + off, ra[k]);
@@ -94,7 +98,7 @@ rows_colsum_kernel(Op op, const T* __restrict__ in0, const T* __restrict__ in1, 
     }
 #pragma unroll
     for (int k = 0; k < kRowsPerThread; ++k) {
-      const int r = r0 + k * (kThreads / kWave);
+      const int r = r0 + k * kGroups;
       if (r < rows) {
         const size_t off = static_cast<size_t>(r) * cols + static_cast<size_t>(vec) * 8;
         float a[8], b[8] = {}, v[8];
@@ -110,21 +114,36 @@ rows_colsum_kernel(Op op, const T* __restrict__ in0, const T* __restrict__ in1, 
 #pragma unroll
   for (int i = 0; i < 8; ++i) sm[w][lane][i] = acc[i];
   __syncthreads();
-  if (w == 0 && active) {
+  if (V < kWave) {  // one column per thread, the row groups in order
+    const int c = blockIdx.x * V * 8 + threadIdx.x;
+    if (threadIdx.x < V * 8 && c < cols) {
+      float t = 0.f;
+#pragma unroll
+      for (int g = 0; g < kGroups; ++g) t += sm[g][threadIdx.x >> 3][threadIdx.x & 7];
+      partial[static_cast<size_t>(blockIdx.y) * cols + c] = t;
+    }
+  } else if (w == 0 && active) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = (sm[0][lane][i] + sm[1][lane][i]) + (sm[2][lane][i] + sm[3][lane][i]);
     store8(partial + static_cast<size_t>(blockIdx.y) * cols + static_cast<size_t>(vec) * 8, acc);
   }
 }
 
+// Workgroups of 64 vectors, two per compute unit: narrower tiles gain up to there (500: 11.1 -> 8.4 us; the plain
+// sum, which is shorter, is level from 150 on: 4.6 us).  Larger grids keep whole-KB rows per wavefront access.
+constexpr int kNarrowBelow = 512;
+
 template <typename T, typename Op>
 hipError_t launch_rows_colsum(Op op, const T* in0, const T* in1, T* outp, T* dbias, float* scratch,
                               int rows, int cols, ColumnSums* sums, hipStream_t st) {
   const int nvec = cols / 8;
   const int nrb = (rows + kRowsPerBlock - 1) / kRowsPerBlock;
-  const dim3 grid((nvec + kWave - 1) / kWave, nrb);
-  hipLaunchKernelGGL((rows_colsum_kernel<T, Op>), grid, dim3(kThreads), 0, st, op, in0, in1, outp,
-                     rows, cols, scratch);
+  if ((nvec + kWave - 1) / kWave * nrb < kNarrowBelow)
+    hipLaunchKernelGGL((rows_colsum_kernel<T, Op, 16>), dim3((nvec + 15) / 16, nrb), dim3(kThreads), 0, st, op, in0,
+                       in1, outp, rows, cols, scratch);
+  else
+    hipLaunchKernelGGL((rows_colsum_kernel<T, Op, kWave>), dim3((nvec + kWave - 1) / kWave, nrb), dim3(kThreads), 0,
+                       st, op, in0, in1, outp, rows, cols, scratch);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? sums->add(scratch, dbias, nrb, cols) : e;
 }
