@@ -134,8 +134,9 @@ size_t lynx_activation_bytes(const lynx_layer_config* cfg, int act_id);
  *
  * Where few tokens leave the chip idle, the size includes fp32 partial sums of
  * contractions that are cut into ranges.  A smaller workspace that the sequence
- * fits without them is accepted too: the run then keeps its contractions whole
- * (slower; the results differ from the cut ones' by the order of fp32 sums). */
+ * fits without them is accepted too: the products then sum their ranges one
+ * after the other (slower, the same bits; the gradients' contractions are left
+ * whole, which is another order of fp32 sums). */
 size_t lynx_workspace_bytes(const lynx_layer_config* cfg, uint32_t retain_mask);
 
 /* The same for a schedule with explicit regeneration phases (Sec. 4.2: the

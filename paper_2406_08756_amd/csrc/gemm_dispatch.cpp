@@ -54,7 +54,7 @@ bool gemm_supported(int dtype, const GemmDesc& d) {
 }
 
 size_t gemm_scratch_bytes(int dtype, const GemmDesc& d) {
-  if (dtype != 1 || !unbatched(d)) return 0;
+  if (dtype != 1 || !unbatched(d) || d.serial) return 0;
   const RaggedChoice c = ragged_product(d);
   return gemm_whole_takes(d, c) ? 0 : c.scratch_bytes;
 }

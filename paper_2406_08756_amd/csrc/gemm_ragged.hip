@@ -85,11 +85,11 @@ struct ProductPlan {
   int splits(int K) const { return ceil_div(K, k_per); }
 };
 
-ProductPlan search_product(int M, int N, int K, bool uncut) {
+ProductPlan search_product(int M, int N, int K) {
   ProductPlan best{kT64, range_of(K, 1), 1e30};
   for (int t = 0; t < kNumRaggedTiles; ++t)
     for (int want : kCuts) {
-      if (want > 1 && (uncut || K < kMinRange * want)) break;
+      if (want > 1 && K < kMinRange * want) break;
       const int k_per = range_of(K, want);
       const double us = product_cost(kProductCost[t], M, N, K, k_per);
       if (us < best.us) best = {t, k_per, us};
@@ -120,8 +120,8 @@ struct PlanCache {
 };
 
 ProductPlan plan_product(const GemmDesc& d) {
-  static thread_local PlanCache<ProductPlan, 4> cache;
-  return cache.get({d.M, d.N, d.K, d.uncut}, [&] { return search_product(d.M, d.N, d.K, d.uncut); });
+  static thread_local PlanCache<ProductPlan, 3> cache;
+  return cache.get({d.M, d.N, d.K}, [&] { return search_product(d.M, d.N, d.K); });
 }
 
 // ---- kernels ------------------------------------------------------------------
@@ -178,6 +178,27 @@ hipError_t launch_tile(int tile, const MfmaGemmArgs& a, hipStream_t st) {
     case kT128x64: return launch_ragged<AK, BK_, kT128x64>(a, st);
     default: return launch_ragged<AK, BK_, kT64>(a, st);
   }
+}
+
+// The ranges of a cut contraction in one workgroup, one after the other (GemmDesc::serial).  The smallest tile,
+// whichever the plan has: a product is cut because its tiles are few, and the tile does not enter the sums.
+template <bool AK, bool BK_>
+__global__ void __launch_bounds__((tile_threads<kT64>), (tile_waves_per_simd<kT64>)) gemm_serial_kernel(MfmaGemmArgs g) {
+  using T = TileShape<kT64, AK && BK_>;
+  gemm_tile<AK, BK_, T::BM, T::BN, false, T::S, true, T::BK, T::waves, true>(g, blockIdx.x, 0);
+}
+
+template <bool AK, bool BK_>
+hipError_t launch_serial(MfmaGemmArgs a, hipStream_t st) {
+  using T = TileShape<kT64, AK && BK_>;
+  static_assert(kMaxBK % T::BK == 0, "ranges are whole slabs");
+  constexpr size_t smem = static_cast<size_t>(T::S) * (T::BM + T::BN) * T::BK * sizeof(bf16_t);
+  auto kern = gemm_serial_kernel<AK, BK_>;
+  LYNX_RAISE_LDS_LIMIT(kern, smem);
+  a.tiles_m = ceil_div(a.M, T::BM);
+  a.tiles_n = ceil_div(a.N, T::BN);
+  hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n), dim3(T::waves * kWave), smem, st, a);
+  return hipGetLastError();
 }
 
 template <int TILE>
@@ -311,6 +332,11 @@ hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, 
   if (d.causal == kCausalNone && a.nz == 1) {
     const ProductPlan p = plan_product(d);
     tile = p.tile;
+    if (p.splits(d.K) > 1 && d.serial) {
+      a.k_per = p.k_per;
+      if (!a_k) return hipErrorInvalidValue;  // (weight gradients come in pairs)
+      return b_k ? launch_serial<true, true>(a, st) : launch_serial<true, false>(a, st);
+    }
     if (p.splits(d.K) > 1) {
       // the cut is part of the shape's summation order: no silent change where scratch is short
       if (scratch == nullptr || scratch_bytes < partial_bytes(d.M, d.N, p.splits(d.K))) return hipErrorInvalidValue;

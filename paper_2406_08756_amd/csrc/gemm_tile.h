@@ -76,8 +76,12 @@ __device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
 // is).  Rows and 8-column chunks beyond the operand repeat its last ones, so every address is inside
 // it, and their outputs are not stored; contraction indices beyond K, which only the last slab can
 // have, read zeros.  Nothing else differs, so a tile that is whole has the bits of the plain form.
+//
+// SERIAL: the K ranges (k_per indices, whole slabs) of a cut contraction one after the other: each is summed
+// from zero and added to the sum of those before it, which is what SPLITK and the launch that adds its partial
+// sums do, bit for bit, with registers in the place of the partial sums.
 template <bool A_KMAJOR, bool B_KMAJOR, int BM, int BN, bool SPLITK = false, int STAGES = kStages, bool RAGGED = false,
-          int BK = kBK, int WAVES = kWaves>
+          int BK = kBK, int WAVES = kWaves, bool SERIAL = false>
 __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block_x, const int block_z) {
   constexpr int kWavesN = WAVES / 2;
   constexpr int WM = BM / 2, WN = BN / kWavesN;  // wavefronts in a grid of 2 x kWavesN
@@ -289,11 +293,42 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
     wait_lgkmcnt0();  // the next slab's first fragments have arrived
     if (more) settle(last ^ 1);
   };
+  static_assert(!(SERIAL && SPLITK), "ranges one after the other, or one each");
+  floatx16_t total[SERIAL ? TN : 1][SERIAL ? TM : 1];  // SERIAL: sum of the ranges that are complete
+  if constexpr (SERIAL) {
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) total[i][j][r] = -0.f;  // (-0 + x has the bits of x)
+  }
+  const int range_slabs = SERIAL ? g.k_per / BK : 0;
+  auto end_range = [&](int kt) {
+    if constexpr (SERIAL) {
+      if (kt + 1 < nk && (kt + 1) % range_slabs != 0) return;
+#pragma unroll
+      for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            total[i][j][r] += acc[i][j][r];
+            acc[i][j][r] = kt + 1 < nk ? 0.f : total[i][j][r];
+          }
+    }
+  };
   wait_lgkmcnt0();
   settle(0);
   int kt = 0;
-  for (; kt + kAhead < (tail < 0 ? nk : tail); ++kt) slab_step(kt, std::true_type{});
-  for (; kt < nk; ++kt) slab_step(kt, std::false_type{});
+  for (; kt + kAhead < (tail < 0 ? nk : tail); ++kt) {
+    slab_step(kt, std::true_type{});
+    end_range(kt);
+  }
+  for (; kt < nk; ++kt) {
+    slab_step(kt, std::false_type{});
+    end_range(kt);
+  }
 
   // Epilogue.  acc[i][j][r] is the element n = wn0 + 32 i + 8 (r/4) + 4 (lane/32) + r%4,
   // m = wm0 + 32 j + lane%32.  Each wavefront rounds its quarter tile (+ bias) to bf16 into

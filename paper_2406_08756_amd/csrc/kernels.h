@@ -171,12 +171,15 @@ struct GemmDesc {
   int nz1, nz2;
   int causal;                              // CausalMode
   GemmEpilogue epi;                        // kind 0 (none) unless the matrix-core path is used
-  bool uncut;                              // leave contractions whole that would be cut for speed (less scratch)
+  // No room for the partial sums of a contraction that is cut for speed: one workgroup sums its ranges one after
+  // the other (slower, same bits).
+  bool serial;
+  bool uncut;                              // (pairs) leave contractions whole that would be cut for speed (less scratch)
 };
 // Picks a kernel.  `scratch` (fp32, 16-byte aligned, gemm_scratch_bytes or more; null when that is 0)
 // takes the partial sums of a contraction that is cut into ranges; they are added in a fixed order.
 hipError_t gemm(int dtype, const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st);
-size_t gemm_scratch_bytes(int dtype, const GemmDesc& d);  // shapes only
+size_t gemm_scratch_bytes(int dtype, const GemmDesc& d);  // shapes and `serial` only
 // Sizes multiples of 8, operands 16-byte aligned and contiguous along one index, an epilogue this
 // product can carry: everything the layer asks for except fp32 with kEpiSoftmaxBwd.
 bool gemm_supported(int dtype, const GemmDesc& d);

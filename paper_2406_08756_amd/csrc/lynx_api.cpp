@@ -93,12 +93,13 @@ struct Book {
   // operators 3-5 never run, operator 6 reads QKV alone
   bool fused_attn = false;
   // what the run goes without because the workspace has no room for it: 1, partial sums of every column
-  // sum of backward at once (each is finished before the next); 2, also scratch that only buys
-  // time (contractions stay whole); 3, also the fusion of operators 7 + 8 and 12 + 13, which places the
-  // activations after them elsewhere
+  // sum of backward at once (each is finished before the next); 2, also the partial sums of contractions that
+  // are cut for speed (their ranges are summed one after the other); 3, also the fusion of operators 7 + 8 and
+  // 12 + 13, which places the activations after them elsewhere.  It can rise within a run (two_pass) and differ
+  // from one policy to the next, so no value may depend on it: every level sums in the same order.
   int thrift = 0;
 };
-constexpr int kNoDeferredSums = 1, kUncut = 2, kMaxThrift = 3;
+constexpr int kNoDeferredSums = 1, kSerial = 2, kMaxThrift = 3;
 
 }  // namespace
 
@@ -320,7 +321,7 @@ GemmDesc attn_cols(const void* sq, const void* y, long long ldy, void* out, long
 // One linear product, with scratch of its own for the partial sums of a cut contraction.
 lynx_status run_linear(Ctx& cx, int slot, GemmDesc g) {
   const int dt = cx.L->D.dtype;
-  g.uncut = cx.bk->thrift >= kUncut;
+  g.serial = cx.bk->thrift >= kSerial;
   const size_t bytes = lynx::gemm_scratch_bytes(dt, g);
   Temp scratch;
   if (bytes > 0) LYNX_TRY(alloc_temp(cx, bytes, &scratch));
@@ -596,7 +597,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
         GemmDesc d = linear_dgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
         GemmDesc g = linear_wgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
         d.epi.kind = gelu ? lynx::kEpiGeluBwd : lynx::kEpiNone;
-        d.uncut = g.uncut = cx.bk->thrift >= kUncut;
+        d.uncut = g.uncut = cx.bk->thrift >= kSerial;
         const size_t b = lynx::gemm_pair_scratch_bytes(dt, d, g);
         if (b > scratch_bytes) scratch_bytes = b;
       }
@@ -619,7 +620,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   };
   // both gradients of a linear layer
   auto launch_pair = [&](int slot, GemmDesc dg, GemmDesc wg) -> lynx_status {
-    dg.uncut = wg.uncut = cx.bk->thrift >= kUncut;
+    dg.uncut = wg.uncut = cx.bk->thrift >= kSerial;
     LYNX_LAUNCH(cx, slot, lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, &sums, cx.st));
     return LYNX_OK;
   };
@@ -640,7 +641,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
     GemmDesc dg = linear_dgrad(temp_ptr(cx, t_dv2), w.w2, temp_ptr(cx, t_du), D.T, D.h, D.f);
     GemmDesc wg = linear_wgrad(temp_ptr(cx, t_dv2), act_ptr(cx, 11), gr->w2, D.T, D.h, D.f);
     dg.epi.kind = lynx::kEpiGeluBwd;
-    dg.uncut = wg.uncut = cx.bk->thrift >= kUncut;
+    dg.uncut = wg.uncut = cx.bk->thrift >= kSerial;
     dg.epi.aux = act_ptr(cx, 10);
     dg.epi.aux_ld = D.f;
     dg.epi.colsum_partial = scr;
@@ -816,13 +817,13 @@ bool grads_ok(const lynx_grads* g) {
   return true;
 }
 
-// The least thrift at which forward(retain) -> backward fits the workspace (none: kUncut, for the forward's sake).
+// The least thrift at which forward(retain) -> backward fits the workspace (none: kSerial, for the forward's sake).
 int thrift_for(lynx_layer_s* L, uint32_t retain) {
   if (L->thrift_mask != retain) {
     // (placeholders, non-null and aligned: the rehearsal takes the kernel path a real call takes)
     void* const fake = reinterpret_cast<void*>(static_cast<uintptr_t>(Arena::kAlign));
     const lynx_grads g{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
-    L->thrift = kUncut;
+    L->thrift = kSerial;
     for (int level = 0; level <= kMaxThrift; ++level) {
       Book book;
       book.arena = Arena(L->book.arena.capacity());

@@ -124,3 +124,40 @@ def test_column_sums_together_or_one_after_the_other(dtype, tokens):
             assert rel_err(got[k], ref) <= {synth.F32: 1e-4, synth.BF16: 2e-2}[dtype], (k, rel_err(got[k], ref))
         layer.close()
     assert all(torch.equal(p, q) for p, q in zip(*runs))
+
+
+# A segment can hold more than forward and backward alone need, so that it does not fit with the partial sums of
+# the cut products beside it, though the forward did.  (hidden, heads, head_dim, ffn, seq, micro_batch), retain
+# mask, segment, workspace (None: what the library names for the mask).
+TIGHT_SEGMENTS = {
+    "named_size": ((3072, 2, 64, 4096, 256, 2), 0x2001, 0x1FFE, None),
+    "uncut_size": ((5120, 5, 104, 8192, 256, 2), 0x2693, 0x196C, 76578816),
+    "uncut_size_heads8": ((5120, 8, 64, 8192, 256, 2), 0x026B, 0x3D94, 73441280),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(TIGHT_SEGMENTS))
+def test_regeneration_in_a_tight_workspace_keeps_the_bits(name):
+    shape, mask, segment, size = TIGHT_SEGMENTS[name]
+    cfg = synth.LayerConfig(synth.BF16, *shape, tp_size=2, tp_rank=1, seed=7, layer_id=3)
+    params = synth.make_params(cfg, random_ln=True)
+    X = synth.make_x(cfg)
+    linear = (1, 2, 6, 7, 8, 9, 10, 11, 12)      # (S, P and Pd are defined on and below the diagonal only)
+
+    roomy = GpuLayer(cfg, params, workspace_bytes=2 * B.lynx_workspace_bytes(cfg, pm.STORE_ALL))
+    roomy.forward(X, pm.STORE_ALL, step=2)
+    forward = {i: roomy.activation_raw(i) for i in linear}
+    roomy.close()
+    tight = GpuLayer(cfg, params, workspace_bytes=size or B.lynx_workspace_bytes(cfg, mask))
+    tight.workspace.fill_(0xFF)
+    tight.forward(X, mask, step=2)
+    tight.recompute(segment)
+    compared = 0
+    for i in linear:
+        got = tight.activation_raw(i)
+        if got is not None:
+            assert torch.equal(got, forward[i]), i
+            compared += 1
+    assert compared >= 4
+    tight.close()
