@@ -134,9 +134,8 @@ size_t lynx_activation_bytes(const lynx_layer_config* cfg, int act_id);
  *
  * Where few tokens leave the chip idle, the size includes fp32 partial sums of
  * contractions that are cut into ranges.  A smaller workspace that the sequence
- * fits without them is accepted too: the products then sum their ranges one
- * after the other (slower, the same bits; the gradients' contractions are left
- * whole, which is another order of fp32 sums). */
+ * fits without them is accepted too: the ranges are then summed one after the
+ * other (slower, the same bits). */
 size_t lynx_workspace_bytes(const lynx_layer_config* cfg, uint32_t retain_mask);
 
 /* The same for a schedule with explicit regeneration phases (Sec. 4.2: the
@@ -167,7 +166,7 @@ lynx_status lynx_layer_destroy(lynx_layer_t layer);
  * may live in it per GPU: two would overwrite each other, so a second create on
  * the same device before the first is destroyed fails with STATE.  Errors:
  * INVALID_ARG, SHAPE, OOM when even the leanest schedule of this shape
- * (input retained only, contractions whole) exceeds the block -
+ * (input retained only, none of those partial sums) exceeds the block -
  * later calls return OOM as usual when a richer retain mask does not fit -,
  * HIP when the block's address cannot be obtained. */
 #define LYNX_STATIC_WORKSPACE_BYTES ((size_t)64 << 20)

@@ -76,7 +76,7 @@ struct IdentityOp {
 // 6.6 -> 3.7 us, 768 x 512 bf16 6.8 -> 5.4, 984 x 3016 7.6 -> 6.0, 4000 x 1600 (500 workgroups of 64) 11.1 -> 8.4.
 template <typename T, typename Op, int V>
 __global__ void __launch_bounds__(kThreads)
-rows_colsum_kernel(Op op, const T* __restrict__ in0, const T* __restrict__ in1, T* __restrict__ outp,
+rows_colsum_kernel(Op op, const T* in0, const T* __restrict__ in1, T* outp,  // outp may be in0
                    int rows, int cols, float* __restrict__ partial) {
   constexpr int kGroups = kThreads / V, kRowsPerThread = kRowsPerBlock / kGroups;
   __shared__ float sm[kGroups][V][8];

@@ -77,7 +77,7 @@ bool gemm_pair_supported(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad
 
 bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
   if (!gemm_pair_supported(dtype, dgrad, wgrad)) return false;
-  if (dtype != 1 || dgrad.uncut) return true;   // (uncut: the smaller workspace)
+  if (dtype != 1) return true;
   // With few rows the plain product is cut into K ranges, which the epilogue's column sums rule out; a
   // GeLU kernel of its own (two launches, three passes over [M, N]) costs less than the uncut product.
   GemmDesc plain = dgrad;
@@ -87,7 +87,8 @@ bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wg
 
 size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
   if (dtype != 1) return 0;
-  return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair_scratch_bytes(dgrad, wgrad) : ragged_pair(dgrad, wgrad).scratch_bytes;
+  if (uses_whole_pair(dgrad, wgrad)) return gemm_whole_pair_scratch_bytes(dgrad, wgrad);
+  return dgrad.serial ? 0 : ragged_pair(dgrad, wgrad).scratch_bytes;
 }
 
 size_t gemm_pair_colsum_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {

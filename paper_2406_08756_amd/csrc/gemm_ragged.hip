@@ -300,11 +300,10 @@ RaggedPairPlan search_pair(const GemmDesc& w, const GemmDesc& d) {
   RaggedPairPlan best{kT64, range_of(w.K, 1), range_of(d.K, 1), 1e30};
   for (int t = 0; t < kNumRaggedTiles; ++t) {
     if (t == kT128x64) continue;   // (no pair kernel of this tile)
-    if (d.uncut && !cut_d && kPairCost[t].bm < 256) continue;   // (fewest column partials)
     for (int cw : kCuts) {
-      if (cw > 1 && (w.uncut || w.K < kMinRange * cw)) break;
+      if (cw > 1 && w.K < kMinRange * cw) break;
       for (int cd : kCuts) {
-        if (cd > 1 && (!cut_d || d.uncut || d.K < kMinRange * cd)) break;
+        if (cd > 1 && (!cut_d || d.K < kMinRange * cd)) break;
         const double us = pair_cost(kPairCost[t], w, range_of(w.K, cw), d, range_of(d.K, cd));
         if (us < best.us) best = {t, range_of(w.K, cw), range_of(d.K, cd), us};
       }
@@ -314,8 +313,8 @@ RaggedPairPlan search_pair(const GemmDesc& w, const GemmDesc& d) {
 }
 
 RaggedPairPlan plan_pair_ragged(const GemmDesc& w, const GemmDesc& d) {
-  static thread_local PlanCache<RaggedPairPlan, 8> cache;
-  return cache.get({w.M, w.N, w.K, d.M, d.N, d.K, d.epi.kind, w.uncut + 2 * d.uncut}, [&] { return search_pair(w, d); });
+  static thread_local PlanCache<RaggedPairPlan, 7> cache;
+  return cache.get({w.M, w.N, w.K, d.M, d.N, d.K, d.epi.kind}, [&] { return search_pair(w, d); });
 }
 
 }  // namespace
@@ -334,8 +333,8 @@ hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, 
     tile = p.tile;
     if (p.splits(d.K) > 1 && d.serial) {
       a.k_per = p.k_per;
-      if (!a_k) return hipErrorInvalidValue;  // (weight gradients come in pairs)
-      return b_k ? launch_serial<true, true>(a, st) : launch_serial<true, false>(a, st);
+      if (!a_k || !b_k) return hipErrorInvalidValue;  // (gradients come in pairs)
+      return launch_serial<true, true>(a, st);
     }
     if (p.splits(d.K) > 1) {
       // the cut is part of the shape's summation order: no silent change where scratch is short
@@ -377,15 +376,23 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   d.k_splits = ceil_div(d.K, p.d_per);
   d.k_per = p.d_per;
   const size_t w_bytes = partial_bytes(w.M, w.N, w.k_splits), d_bytes = partial_bytes(d.M, d.N, d.k_splits);
-  if (w_bytes + d_bytes > 0 && (scratch == nullptr || scratch_bytes < w_bytes + d_bytes)) return hipErrorInvalidValue;
-  w.partial = scratch;
-  d.partial = scratch + w_bytes / sizeof(float);
+  const bool serial = dgrad.serial && w_bytes + d_bytes > 0;
+  if (w_bytes + d_bytes > 0 && !serial && (scratch == nullptr || scratch_bytes < w_bytes + d_bytes)) return hipErrorInvalidValue;
   hipError_t e;
-  switch (p.tile) {
-    case kT256: e = launch_ragged_pair<kT256>(w, d, st); break;
-    case kT256x128: e = launch_ragged_pair<kT256x128>(w, d, st); break;
-    case kT128: e = launch_ragged_pair<kT128>(w, d, st); break;
-    default: e = launch_ragged_pair<kT64>(w, d, st); break;
+  if (serial) {
+    // (the GeLU epilogue's column partials are a row per half tile: the plan's tile, whose contraction is whole)
+    w.k_splits = d.k_splits = 1;
+    e = launch_serial<false, false>(w, st);
+    if (e == hipSuccess) e = dgrad.epi.kind == kEpiGeluBwd ? launch_tile<true, false>(p.tile, d, st) : launch_serial<true, false>(d, st);
+  } else {
+    w.partial = scratch;
+    d.partial = scratch + w_bytes / sizeof(float);
+    switch (p.tile) {
+      case kT256: e = launch_ragged_pair<kT256>(w, d, st); break;
+      case kT256x128: e = launch_ragged_pair<kT256x128>(w, d, st); break;
+      case kT128: e = launch_ragged_pair<kT128>(w, d, st); break;
+      default: e = launch_ragged_pair<kT64>(w, d, st); break;
+    }
   }
   if (e != hipSuccess) return e;
   if (w.k_splits > 1 && d.k_splits > 1) e = launch_finish(&w, &d, st);

@@ -72,7 +72,7 @@ hipError_t softmax_dropout_bwd(int dtype, const void* dPd, const void* P, void* 
 // ---- elementwise over [rows, cols] -----------------------------------------
 hipError_t gelu_fwd(int dtype, const void* u, void* g, size_t n, hipStream_t st);
 size_t colsum_scratch_bytes(int rows, int cols);
-// du = dg * gelu'(u); dbias[c] = sum_r du[r, c]
+// du = dg * gelu'(u) (du may be dg); dbias[c] = sum_r du[r, c]
 hipError_t gelu_bwd(int dtype, const void* dg, const void* u, void* du, void* dbias,
                     float* scratch, int rows, int cols, ColumnSums* sums, hipStream_t st);
 // out = res + keep * (in + bias) * c, dropout site `site`, element index r*cols + c
@@ -172,9 +172,8 @@ struct GemmDesc {
   int causal;                              // CausalMode
   GemmEpilogue epi;                        // kind 0 (none) unless the matrix-core path is used
   // No room for the partial sums of a contraction that is cut for speed: one workgroup sums its ranges one after
-  // the other (slower, same bits).
+  // the other (slower, same bits).  In a pair, of both products; a pair of whole tiles keeps its cut and scratch.
   bool serial;
-  bool uncut;                              // (pairs) leave contractions whole that would be cut for speed (less scratch)
 };
 // Picks a kernel.  `scratch` (fp32, 16-byte aligned, gemm_scratch_bytes or more; null when that is 0)
 // takes the partial sums of a contraction that is cut into ranges; they are added in a fixed order.
@@ -187,7 +186,7 @@ bool gemm_supported(int dtype, const GemmDesc& d);
 // (gemm_pair_scratch_bytes).
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,
                      size_t scratch_bytes, ColumnSums* sums, hipStream_t st);
-size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // shapes and epilogue only
+size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // shapes, epilogue and `serial` only
 // Whether the input gradient should carry the GeLU backward (kEpiGeluBwd): supported, and it pays.
 bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);
 size_t gemm_pair_colsum_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // its column partials

@@ -597,12 +597,12 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
         GemmDesc d = linear_dgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
         GemmDesc g = linear_wgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
         d.epi.kind = gelu ? lynx::kEpiGeluBwd : lynx::kEpiNone;
-        d.uncut = g.uncut = cx.bk->thrift >= kSerial;
+        d.serial = g.serial = cx.bk->thrift >= kSerial;
         const size_t b = lynx::gemm_pair_scratch_bytes(dt, d, g);
         if (b > scratch_bytes) scratch_bytes = b;
       }
   }
-  Temp scratch, t_dv2, t_dg, t_du, t_dy2, t_dx2, t_do, t_dc, t_dpd, t_dqkv, t_dy1;
+  Temp scratch, t_dv2, t_du, t_dy2, t_dx2, t_do, t_dc, t_dpd, t_dqkv, t_dy1;
   LYNX_TRY(alloc_temp(cx, scratch_bytes, &scratch));
   float* scr = reinterpret_cast<float*>(temp_ptr(cx, scratch));
   Temp t_part[4];  // partial sums of: b2, b1 (two producers), LayerNorm 2 with bo, bqkv and LayerNorm 1
@@ -620,7 +620,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   };
   // both gradients of a linear layer
   auto launch_pair = [&](int slot, GemmDesc dg, GemmDesc wg) -> lynx_status {
-    dg.uncut = wg.uncut = cx.bk->thrift >= kSerial;
+    dg.serial = wg.serial = cx.bk->thrift >= kSerial;
     LYNX_LAUNCH(cx, slot, lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, &sums, cx.st));
     return LYNX_OK;
   };
@@ -633,23 +633,26 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
                                     dropout_params(L), &sums, cx.st));
   LYNX_TRY(finish_sums(false));
   LYNX_TRY(tap(cx, 12, temp_ptr(cx, t_dv2)));
-  // B12: V2 = G W2^T, and B11: G = gelu(U).  When the matrix-core pair launch applies, the
-  // store pass of the input gradient multiplies by gelu'(U) and sums the columns (the FC1
-  // bias gradient), so dG is never written and the GeLU backward never runs as a kernel.
+  // B12: V2 = G W2^T, and B11: G = gelu(U).  Where it pays, the store pass of the input gradient
+  // multiplies by gelu'(U) and sums the columns (the FC1 bias gradient), so dG is never written and
+  // the GeLU backward never runs as a kernel; elsewhere that kernel replaces dG by dU in place.
   LYNX_TRY(alloc_temp(cx, tf, &t_du));
   {
     GemmDesc dg = linear_dgrad(temp_ptr(cx, t_dv2), w.w2, temp_ptr(cx, t_du), D.T, D.h, D.f);
     GemmDesc wg = linear_wgrad(temp_ptr(cx, t_dv2), act_ptr(cx, 11), gr->w2, D.T, D.h, D.f);
     dg.epi.kind = lynx::kEpiGeluBwd;
-    dg.uncut = wg.uncut = cx.bk->thrift >= kSerial;
+    dg.serial = wg.serial = cx.bk->thrift >= kSerial;
     dg.epi.aux = act_ptr(cx, 10);
     dg.epi.aux_ld = D.f;
     dg.epi.colsum_partial = scr;
     dg.epi.colsum_out = gr->b1;
     if (lynx::gemm_pair_absorbs_gelu(dt, dg, wg)) {
-      // (not in `scr`, where the same launch leaves the partial sums of a cut weight gradient)
-      LYNX_TRY(alloc_temp(cx, lynx::gemm_pair_colsum_bytes(dt, dg, wg), &t_part[1]));
-      dg.epi.colsum_partial = reinterpret_cast<float*>(temp_ptr(cx, t_part[1]));
+      // (not in `scr` where the same launch leaves the partial sums of a cut weight gradient there)
+      const size_t colsum_bytes = lynx::gemm_pair_colsum_bytes(dt, dg, wg);
+      if (defer || colsum_bytes > scratch_bytes || lynx::gemm_pair_scratch_bytes(dt, dg, wg) > 0) {
+        LYNX_TRY(alloc_temp(cx, colsum_bytes, &t_part[1]));
+        dg.epi.colsum_partial = reinterpret_cast<float*>(temp_ptr(cx, t_part[1]));
+      }
       LYNX_TRY(launch_pair(kB12Grads, dg, wg));
       LYNX_TRY(finish_sums(false));
       if (!defer) free_temp(cx, &t_part[1]);
@@ -657,16 +660,13 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
       free_act(cx, 11);
     } else {
       dg.epi = lynx::GemmEpilogue{};
-      LYNX_TRY(alloc_temp(cx, tf, &t_dg));
-      dg.C = temp_ptr(cx, t_dg);
       LYNX_TRY(launch_pair(kB12Grads, dg, wg));
       free_temp(cx, &t_dv2);
       free_act(cx, 11);
       LYNX_TRY(alloc_partials(1, lynx::colsum_scratch_bytes(D.T, D.f)));
-      LYNX_LAUNCH(cx, kB11Gelu, lynx::gelu_bwd(dt, temp_ptr(cx, t_dg), act_ptr(cx, 10), temp_ptr(cx, t_du),
+      LYNX_LAUNCH(cx, kB11Gelu, lynx::gelu_bwd(dt, temp_ptr(cx, t_du), act_ptr(cx, 10), temp_ptr(cx, t_du),
                                                gr->b1, part, D.T, D.f, &sums, cx.st));
       LYNX_TRY(finish_sums(false));
-      free_temp(cx, &t_dg);
     }
   }
   free_act(cx, 10);
