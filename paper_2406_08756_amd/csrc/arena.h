@@ -36,6 +36,25 @@ class Arena {
     return false;
   }
 
+  // The upper end of the highest block that fits.
+  bool alloc_high(size_t bytes, size_t* offset) {
+    const size_t need = round_up(bytes == 0 ? 1 : bytes);
+    for (auto it = free_.rbegin(); it != free_.rend(); ++it) {
+      const size_t first = it->first, end = it->first + it->second;
+      if (it->second < need || (end - need) / kAlign * kAlign < first) continue;
+      const size_t off = (end - need) / kAlign * kAlign;
+      free_.erase(first);
+      if (off > first) free_[first] = off - first;
+      if (end > off + need) free_[off + need] = end - (off + need);
+      used_[off] = need;
+      in_use_ += need;
+      if (off + need > extent_peak_) extent_peak_ = off + need;
+      *offset = off;
+      return true;
+    }
+    return false;
+  }
+
   void release(size_t offset) {
     auto u = used_.find(offset);
     if (u == used_.end()) return;

@@ -95,11 +95,12 @@ struct Book {
   // what the run goes without because the workspace has no room for it: 1, partial sums of every column
   // sum of backward at once (each is finished before the next); 2, also the partial sums of contractions that
   // are cut for speed (their ranges are summed one after the other); 3, also the fusion of operators 7 + 8 and
-  // 12 + 13, which places the activations after them elsewhere.  It can rise within a run (two_pass) and differ
-  // from one policy to the next, so no value may depend on it: every level sums in the same order.
+  // 12 + 13, which places the activations after them elsewhere; 4, also backward's scratch lies at the upper end,
+  // where it leaves the holes to the blocks after it.  It can change within a run (two_pass) and differ from one
+  // policy to the next, so no value may depend on it: every level sums in the same order.
   int thrift = 0;
 };
-constexpr int kNoDeferredSums = 1, kSerial = 2, kMaxThrift = 3;
+constexpr int kNoDeferredSums = 1, kSerial = 2, kUnfused = 3, kScratchHigh = 4, kMaxThrift = kScratchHigh;
 
 }  // namespace
 
@@ -205,8 +206,8 @@ struct Temp {  // transient workspace block
   size_t off = 0;
   bool held = false;
 };
-lynx_status alloc_temp(Ctx& cx, size_t bytes, Temp* t) {
-  if (!cx.bk->arena.alloc(bytes, &t->off)) return LYNX_ERR_OOM;
+lynx_status alloc_temp(Ctx& cx, size_t bytes, Temp* t, bool high = false) {
+  if (!(high ? cx.bk->arena.alloc_high(bytes, &t->off) : cx.bk->arena.alloc(bytes, &t->off))) return LYNX_ERR_OOM;
   t->held = true;
   return LYNX_OK;
 }
@@ -434,7 +435,7 @@ GemmDesc fused_linear_desc(Ctx& cx, int lin, bool keep_product) {
 }
 bool can_fuse_linear(const Ctx& cx, int lin) {
   const Dims& D = cx.L->D;
-  if (cx.bk->thrift >= kMaxThrift) return false;
+  if (cx.bk->thrift >= kUnfused) return false;
   // shapes only (pointers are 256-byte aligned arena blocks or checked caller buffers)
   GemmDesc g = linear_fwd(reinterpret_cast<const void*>(256), reinterpret_cast<const void*>(256), nullptr,
                           reinterpret_cast<void*>(256), D.T, D.h, lin == 7 ? D.p : D.f);
@@ -603,7 +604,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
       }
   }
   Temp scratch, t_dv2, t_du, t_dy2, t_dx2, t_do, t_dc, t_dpd, t_dqkv, t_dy1;
-  LYNX_TRY(alloc_temp(cx, scratch_bytes, &scratch));
+  LYNX_TRY(alloc_temp(cx, scratch_bytes, &scratch, cx.bk->thrift >= kScratchHigh));
   float* scr = reinterpret_cast<float*>(temp_ptr(cx, scratch));
   Temp t_part[4];  // partial sums of: b2, b1 (two producers), LayerNorm 2 with bo, bqkv and LayerNorm 1
   float* part = scr;
@@ -838,21 +839,27 @@ int thrift_for(lynx_layer_s* L, uint32_t retain) {
   return L->thrift;
 }
 
-// Rehearse on a copy, then run for real.  A call that does not fit, though the sequence the run's
-// thrift was chosen for does (segments can hold more than backward alone), goes on with more of it.
+// Rehearse on a copy, then run for real.  The run's thrift was chosen for forward -> backward, and segments in
+// between move the blocks: a call that does not fit at that level is tried at those above it and then at those
+// below it (more thrift is another placement, not always a smaller one).  No value depends on the level.
 template <typename F>
 lynx_status two_pass(lynx_layer_s* L, hipStream_t st, F&& body) {
+  const int base = L->book.thrift;
   lynx_status s = LYNX_ERR_OOM;
-  for (int level = L->book.thrift; s == LYNX_ERR_OOM && level <= kMaxThrift; ++level) {
+  int level = base;
+  for (int k = 0; s == LYNX_ERR_OOM && k <= kMaxThrift; ++k) {
+    level = base + k <= kMaxThrift ? base + k : kMaxThrift - k;
     Book copy = L->book;
     copy.thrift = level;
     Ctx rehearsal{L, &copy, false, st};
     s = body(rehearsal);
-    if (s == LYNX_OK) L->book.thrift = level;
   }
   LYNX_TRY(s);
+  L->book.thrift = level;
   Ctx real{L, &L->book, !L->dry, st};
-  return body(real);
+  s = body(real);
+  L->book.thrift = base;
+  return s;
 }
 
 // The workspace a call sequence reaches into: forward, the phases, backward.
@@ -913,7 +920,7 @@ lynx_status lynx_layer_create_static(const lynx_layer_config* cfg, lynx_layer_t*
   if (!make_dims(cfg, &D)) return LYNX_ERR_SHAPE;
   // the leanest schedule of this shape (keep the input only) must fit the block
   size_t least = 0;
-  for (int thrift = 0; thrift <= kMaxThrift; ++thrift) {
+  for (int thrift = 0; thrift <= kUnfused; ++thrift) {
     const size_t need = workspace_need(cfg, LYNX_RETAIN_FULL_RECOMPUTE, nullptr, thrift);
     if (thrift == 0 || need < least) least = need;
   }

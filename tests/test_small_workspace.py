@@ -126,6 +126,35 @@ def test_column_sums_together_or_one_after_the_other(dtype, tokens):
     assert all(torch.equal(p, q) for p, q in zip(*runs))
 
 
+# Schedules at sizes that a plan which only ever takes less scratch than forward -> backward left it refuses:
+# (dtype, hidden, heads, head_dim, ffn, seq, micro_batch), flags, retain mask, phases, workspace (None: what
+# lynx_workspace_bytes_for_schedule names).
+SCHEDULES = {
+    "phases_f32": ((synth.F32, 256, 7, 256, 7296, 416, 3), 0, 0x3FC7, (0x2BDE, 0, 0, 0), None),
+    "phases": ((synth.BF16, 1480, 2, 64, 3328, 96, 5), 0, 0x3545, (0x3900, 0, 0, 0), None),
+    "phases_heads256": ((synth.BF16, 4096, 7, 256, 5248, 512, 8), 0, 0x37CF, (0x0EDE, 0, 0, 0), None),
+    "phases_heads136": ((synth.BF16, 5136, 2, 136, 5504, 1152, 3), 1, 0x2949, (0, 0x1386, 0, 0), None),
+    "scratch_in_a_hole": ((synth.BF16, 2528, 4, 72, 896, 1152, 2), 0, 0x2BA5, (0, 0, 0, 0), 165337088),
+    "scratch_in_a_hole_heads96": ((synth.BF16, 1696, 4, 96, 232, 1536, 3), 0, 0x3001, (0, 0, 0, 0), 286175232),
+}
+
+
+@pytest.mark.parametrize("name", list(SCHEDULES))
+def test_schedule_fits_the_size_named_for_it(name):
+    (dtype, h, a, d, f, s, b), flags, mask, phases, size = SCHEDULES[name]
+    cfg = synth.LayerConfig(dtype, h, a, d, f, s, b, tp_size=2, flags=flags)
+    size = size or B.lynx_workspace_bytes_for_schedule(cfg, mask, phases)
+    handle = dry_layer(cfg, ws_bytes=size)
+    for _ in range(2):
+        B.lynx_layer_forward(handle, FX, FOUT, mask, 0)
+        for segment in phases:
+            if segment:
+                B.lynx_recompute(handle, segment)
+        B.lynx_layer_backward(handle, FDOUT, FDX, FAKE)
+        assert B.lynx_layer_peak_bytes(handle) <= size
+    B.lynx_layer_destroy(handle)
+
+
 # A segment can hold more than forward and backward alone need, so that it does not fit with the partial sums of
 # the cut products beside it, though the forward did.  (hidden, heads, head_dim, ffn, seq, micro_batch), retain
 # mask, segment, workspace (None: what the library names for the mask).
@@ -194,3 +223,20 @@ def test_bits_depend_neither_on_the_workspace_nor_on_the_mask(name):
             differing = [n for n, p, q in zip(("OUT", "dX") + synth.PARAM_NAMES, first, bits) if not torch.equal(p, q)]
             assert not differing, (size, hex(mask), differing)
         layer.close()
+
+
+@pytest.mark.gpu
+def test_scratch_at_the_upper_end_keeps_the_bits():
+    (dtype, *shape), flags, mask, _, size = SCHEDULES["scratch_in_a_hole"]
+    cfg = synth.LayerConfig(dtype, *shape, tp_size=2, flags=flags, seed=7)
+    params, X, dOUT = synth.make_params(cfg, random_ln=True), synth.make_x(cfg), synth.make_dout(cfg)
+    runs = []
+    for nbytes in (B.lynx_workspace_bytes(cfg, mask), size):
+        layer = GpuLayer(cfg, params, workspace_bytes=nbytes)
+        layer.workspace.fill_(0xFF)
+        layer.forward(X, mask, step=2)
+        layer.backward(dOUT)
+        runs.append([layer.out.clone(), layer.dx.clone()] + [layer.grads[k].clone() for k in synth.PARAM_NAMES])
+        assert bool((layer.workspace[layer.ws_base + nbytes - layer.workspace.data_ptr():] == 0xFF).all())
+        layer.close()
+    assert all(torch.equal(p, q) for p, q in zip(*runs))
