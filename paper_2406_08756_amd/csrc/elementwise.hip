@@ -72,14 +72,19 @@ struct IdentityOp {
 // wavefronts resident to overlap the Philox / GeLU arithmetic with the memory traffic.
 // V: vectors of the tile's width, 64 as above, or 16 where that gives the chip too few workgroups: then 16 lanes
 // share a row, a thread has two rows instead of eight and four times the workgroups share the latency.
-// The partial rows, and with them the scratch, are the same.  Dropout backward, 64 -> 16 vectors: 256 x 256 fp32
-// 6.6 -> 3.7 us, 768 x 512 bf16 6.8 -> 5.4, 984 x 3016 7.6 -> 6.0, 4000 x 1600 (500 workgroups of 64) 11.1 -> 8.4.
+// The partial rows, their order of sums and with it their bits are the same: the narrow tile brings its 32 rows
+// together in LDS, one column per thread (sums of the thread's two rows and then of the 16 row groups in series are
+// another order, with 1.1 to 1.2 times the error against 64 bits in fp32).  Dropout backward, 64 -> 16 vectors:
+// 256 x 256 fp32 6.6 -> 3.7 us, 768 x 512 bf16 6.8 -> 5.4, 984 x 3016 7.6 -> 6.0, 4000 x 1600 (500 workgroups of 64)
+// 11.1 -> 8.4.
 template <typename T, typename Op, int V>
 __global__ void __launch_bounds__(kThreads)
 rows_colsum_kernel(Op op, const T* in0, const T* __restrict__ in1, T* outp,  // outp may be in0
                    int rows, int cols, float* __restrict__ partial) {
   constexpr int kGroups = kThreads / V, kRowsPerThread = kRowsPerBlock / kGroups;
-  __shared__ float sm[kGroups][V][8];
+  constexpr bool kNarrow = V < kWave;
+  constexpr int kSumRows = kThreads / kWave;  // rows r, r + 4, ... of the tile form one sum, of four
+  __shared__ __align__(16) float sm[kNarrow ? kRowsPerBlock : kGroups][V][8];
   const int lane = threadIdx.x % V, w = threadIdx.x / V;
   const int vec = blockIdx.x * V + lane;
   const bool active = vec < (cols >> 3);
@@ -99,9 +104,10 @@ rows_colsum_kernel(Op op, const T* in0, const T* __restrict__ in1, T* outp,  // 
 #pragma unroll
     for (int k = 0; k < kRowsPerThread; ++k) {
       const int r = r0 + k * kGroups;
+      float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       if (r < rows) {
         const size_t off = static_cast<size_t>(r) * cols + static_cast<size_t>(vec) * 8;
-        float a[8], b[8] = {}, v[8];
+        float a[8], b[8] = {};
         unpack(ra[k], a);
         if (Op::kInputs == 2) unpack(rb[Op::kInputs == 2 ? k : 0], b);
         op.apply(a, b, off >> 3, v);
@@ -109,18 +115,18 @@ rows_colsum_kernel(Op op, const T* in0, const T* __restrict__ in1, T* outp,  // 
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] += v[i];
       }
+      if (kNarrow) store8(&sm[kNarrow ? w + k * kGroups : 0][lane][0], v);
     }
   }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) sm[w][lane][i] = acc[i];
+  if (!kNarrow) store8(&sm[kNarrow ? 0 : w][lane][0], acc);
   __syncthreads();
-  if (V < kWave) {  // one column per thread, the row groups in order
+  if (kNarrow) {  // one column per thread
     const int c = blockIdx.x * V * 8 + threadIdx.x;
     if (threadIdx.x < V * 8 && c < cols) {
-      float t = 0.f;
+      float t[kSumRows] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int g = 0; g < kGroups; ++g) t += sm[g][threadIdx.x >> 3][threadIdx.x & 7];
-      partial[static_cast<size_t>(blockIdx.y) * cols + c] = t;
+      for (int r = 0; r < kRowsPerBlock; ++r) t[r % kSumRows] += sm[kNarrow ? r : 0][threadIdx.x >> 3][threadIdx.x & 7];
+      partial[static_cast<size_t>(blockIdx.y) * cols + c] = (t[0] + t[1]) + (t[2] + t[3]);
     }
   } else if (w == 0 && active) {
 #pragma unroll

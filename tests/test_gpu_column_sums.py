@@ -1,0 +1,46 @@
+"""Bias gradients are sums over the tokens in one order, whatever the tile of the kernel that forms them: 32 rows as
+four sums of every fourth row, ((0 + 1) + (2 + 3)); of those partial rows every sixteenth in turn, and the sixteen
+sums in order.  Exactly that in numpy's fp32 is the expected result, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import lynx_synth as synth
+from harness import GpuLayer
+
+B = pytest.importorskip("paper_2406_08756_amd.binding")
+
+pytestmark = pytest.mark.gpu
+
+
+def serial(rows):
+    total = np.zeros(rows.shape[1:], dtype=np.float32)
+    for r in rows:
+        total = total + r
+    return total
+
+
+def column_sum(x, dtype):
+    x = np.concatenate([x, np.zeros((-len(x) % 32, x.shape[1]), np.float32)]).reshape(-1, 32, x.shape[1])
+    four = [serial(np.moveaxis(x[:, q::4], 1, 0)) for q in range(4)]
+    partial = (four[0] + four[1]) + (four[2] + four[3])
+    return synth._store(serial(np.stack([serial(partial[g::16]) for g in range(16)])), dtype)
+
+
+# (hidden, seq, micro_batch): tiles of 16 vectors where tiles of 64 would be fewer than 512, of 64 elsewhere
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("h,s,b", [(256, 128, 2), (264, 40, 5), (136, 1000, 1), (4088, 72, 28), (4104, 72, 28),
+                                   (1024, 64, 128), (1032, 88, 93)])
+def test_bias_gradients_are_summed_in_one_order(dtype, h, s, b):
+    cfg = synth.LayerConfig(dtype, h, 1, 40, 8, s, b, dropout_p=0.0)
+    layer = GpuLayer(cfg, synth.make_params(cfg))
+    dQKV = layer.tap_gradients(["dQKV"])["dQKV"]
+    dOUT = synth.make_dout(cfg)
+    layer.forward(synth.make_x(cfg), B.LYNX_RETAIN_STORE_ALL)
+    layer.backward(dOUT)
+    torch.cuda.synchronize()
+    got = {k: layer.grads[k].float().cpu().numpy() for k in ("b2", "bqkv")}
+    layer.close()
+    np.testing.assert_array_equal(got["b2"], column_sum(dOUT, dtype))
+    dQKV = dQKV.float().cpu().numpy().reshape(cfg.tokens, 3 * cfg.proj)
+    np.testing.assert_array_equal(got["bqkv"], column_sum(dQKV, dtype))
