@@ -233,8 +233,8 @@ __global__ void __launch_bounds__(kThreads, 2) attn_outer_kernel(MfmaGemmArgs g)
 // and the 64 KB of LDS let two workgroups share a compute unit.  The loads of P are inline
 // assembly with waits counted by hand: loads the compiler tracks would be waited for at
 // the loop's back edge together with everything issued after them.
-template <int KD, bool RAGGED>
 __global__ void __launch_bounds__(kThreads, 2) attn_dscores_kernel(MfmaGemmArgs g) {
+  constexpr int KD = 128;
   constexpr int WM = 64, WN = 64, TM = 2, TN = 2;
   constexpr int kSlabs = KD / kBK;
   using SL = Slab<128, true>;
@@ -257,8 +257,8 @@ __global__ void __launch_bounds__(kThreads, 2) attn_dscores_kernel(MfmaGemmArgs 
   const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;
 
   constexpr int kTileLoads = kSlabs * SL::kLoadsPerWave;  // direct loads per wavefront per tile
-  load_score_tile<KD, RAGGED, false>(Abase, g.lda, tm * 128, g.M, g.K, sA, wave, lane);
-  load_score_tile<KD, RAGGED, true>(Bbase, g.ldb, tn0 * 128, g.M, g.K, sB, wave, lane);
+  load_score_tile<KD, false, false>(Abase, g.lda, tm * 128, g.M, g.K, sA, wave, lane);
+  load_score_tile<KD, false, true>(Bbase, g.ldb, tn0 * 128, g.M, g.K, sB, wave, lane);
 
   constexpr int kRowChunks = WN / 8;                 // 8
   constexpr int kRowsPerStore = kWave / kRowChunks;  // 8
@@ -268,14 +268,8 @@ __global__ void __launch_bounds__(kThreads, 2) attn_dscores_kernel(MfmaGemmArgs 
 
   // this lane's eight rows: dot products, dropout indices, vectors of P (two sets)
   const bf16_t* Pbase = g.aux + z1 * g.c_z1 + z2 * g.c_z2;
-  auto row_of = [&](int u) {
-    const int i = tm * 128 + wm0 + u * kRowsPerStore + lr;
-    return RAGGED ? repeat_row(i, g.M) : i;
-  };
-  auto col_of = [&](int tn) {
-    const int j = tn * 128 + wn0 + lc * 8;
-    return RAGGED ? repeat_octet(j, g.M) : j;
-  };
+  auto row_of = [&](int u) { return tm * 128 + wm0 + u * kRowsPerStore + lr; };
+  auto col_of = [&](int tn) { return tn * 128 + wn0 + lc * 8; };
   const uint64_t rows_before = (static_cast<uint64_t>(z1) * g.global_heads + g.head0 + z2) * g.M;
   float dot[kStores];
   uint64_t gidx[kStores];
@@ -360,7 +354,7 @@ __global__ void __launch_bounds__(kThreads, 2) attn_dscores_kernel(MfmaGemmArgs 
     for (int u = 0; u < kStores; ++u) asm volatile("" : "+v"(rows[u]));
     block_barrier();  // every wavefront has its rows: the buffer can take the next B tile
     if (tn + 1 < tn1) {
-      load_score_tile<KD, RAGGED, true>(Bbase, g.ldb, (tn + 1) * 128, g.M, g.K, sB, wave, lane);
+      load_score_tile<KD, false, true>(Bbase, g.ldb, (tn + 1) * 128, g.M, g.K, sB, wave, lane);
       request_p(tn + 1, pn);
     }
     // this tile's P: requested a step ago; issued since: the previous step's stores and, if
@@ -507,23 +501,22 @@ hipError_t launch_edge(const MfmaGemmArgs& a, hipStream_t st) {
 
 // The score-shaped kernels: LDS for the A tile and the B tile / staging area (4 x 64 x 64, the
 // larger of the two for short head dimensions).
-template <int KD, bool RAGGED, bool DSCORES>
+template <int KD, void (*KERN)(MfmaGemmArgs)>
 hipError_t launch_scores(MfmaGemmArgs a, hipStream_t st) {
   constexpr size_t op = static_cast<size_t>(KD / kBK) * 128 * kBK;
   constexpr size_t smem = (op + (op > 4 * 64 * 64 ? op : 4 * 64 * 64)) * sizeof(bf16_t);
-  void (*kern)(MfmaGemmArgs) = DSCORES ? attn_dscores_kernel<KD, RAGGED> : attn_outer_kernel<KD, RAGGED>;
-  LYNX_RAISE_LDS_LIMIT(kern, smem);
+  LYNX_RAISE_LDS_LIMIT(KERN, smem);
   a.tiles_m = (a.M + 127) / 128;
   a.tiles_n = a.tiles_m;
   a.run = attn_run(a.tiles_m, a.nz);
-  hipLaunchKernelGGL(kern, dim3(attn_items(a.tiles_m, a.run) * a.nz), dim3(kThreads), smem, st, a);
+  hipLaunchKernelGGL(KERN, dim3(attn_items(a.tiles_m, a.run) * a.nz), dim3(kThreads), smem, st, a);
   return hipGetLastError();
 }
-template <bool DSCORES>
 hipError_t scores(const MfmaGemmArgs& a, hipStream_t st) {
   const bool whole = a.M % 128 == 0 && (a.K == 64 || a.K == 128);
-  if (a.K <= 64) return whole ? launch_scores<64, false, DSCORES>(a, st) : launch_scores<64, true, DSCORES>(a, st);
-  return whole ? launch_scores<128, false, DSCORES>(a, st) : launch_scores<128, true, DSCORES>(a, st);
+  if (a.K <= 64)
+    return whole ? launch_scores<64, attn_outer_kernel<64, false>>(a, st) : launch_scores<64, attn_outer_kernel<64, true>>(a, st);
+  return whole ? launch_scores<128, attn_outer_kernel<128, false>>(a, st) : launch_scores<128, attn_outer_kernel<128, true>>(a, st);
 }
 
 // How a pair is launched.  Tiles: the largest that divides the output (pair launches
@@ -643,8 +636,8 @@ hipError_t gemm_whole(const GemmDesc& d, hipStream_t st) {
 hipError_t gemm_attention(const GemmDesc& d, hipStream_t st) {
   const MfmaGemmArgs a = make_args(d);
   if (d.causal == kCausalOutLower) {
-    if (d.epi.kind == kEpiSoftmaxBwd) return scores<true>(a, st);
-    if (d.K <= 128) return scores<false>(a, st);
+    if (d.epi.kind == kEpiSoftmaxBwd) return launch_scores<128, attn_dscores_kernel>(a, st);
+    if (d.K <= 128) return scores(a, st);
     return gemm_ragged(d, nullptr, 0, st);
   }
   // (few tiles: the ragged kernels' 64 x 64 ones)
