@@ -124,9 +124,10 @@ struct lynx_layer_s {
   // parity aid: where backward copies the gradient with respect to activation A_i (null: nowhere)
   void* grad_tap[LYNX_NUM_ACTIVATIONS] = {};
   int static_device = -1;  // >= 0: the workspace is that device's built-in block
-  // the least Book::thrift at which forward(thrift_mask) -> backward fits the workspace
-  uint32_t thrift_mask = ~0u;
-  int thrift = 0;
+  // per retain mask (bits 1..12) the least Book::thrift at which forward -> backward fits the workspace, -1: not
+  // rehearsed yet.  A byte for each of the 4096 masks: a caller may change policy from one micro-batch to the next.
+  signed char thrift[1 << 12];
+  lynx_layer_s() { memset(thrift, -1, sizeof(thrift)); }
 };
 
 namespace {
@@ -820,23 +821,23 @@ bool grads_ok(const lynx_grads* g) {
 
 // The least thrift at which forward(retain) -> backward fits the workspace (none: kSerial, for the forward's sake).
 int thrift_for(lynx_layer_s* L, uint32_t retain) {
-  if (L->thrift_mask != retain) {
+  signed char& thrift = L->thrift[(retain >> 1) & 0xFFFu];
+  if (thrift < 0) {
     // (placeholders, non-null and aligned: the rehearsal takes the kernel path a real call takes)
     void* const fake = reinterpret_cast<void*>(static_cast<uintptr_t>(Arena::kAlign));
     const lynx_grads g{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
-    L->thrift = kSerial;
+    thrift = kSerial;
     for (int level = 0; level <= kMaxThrift; ++level) {
       Book book;
       book.arena = Arena(L->book.arena.capacity());
       book.thrift = level;
       Ctx cx{L, &book, false, nullptr};
       if (forward_pass(cx, retain) != LYNX_OK || backward_pass(cx, fake, fake, &g) != LYNX_OK) continue;
-      L->thrift = level;
+      thrift = static_cast<signed char>(level);
       break;
     }
-    L->thrift_mask = retain;
   }
-  return L->thrift;
+  return thrift;
 }
 
 // Rehearse on a copy, then run for real.  The run's thrift was chosen for forward -> backward, and segments in
