@@ -260,8 +260,11 @@ lynx_status lynx_layer_set_dry_run(lynx_layer_t layer, int on);
  * no time of its own (-1) and is covered by that slot: OP5 by slot 4, and,
  * where the matrix-core kernels apply, OP8 by slot 7 and OP13 by slot 12.  The
  * rest are the backward kernels (likewise the GeLU backward may run inside
- * the FC2 gradient launch, and dPd with the softmax backward as one launch);
- * lynx_profile_slot_name names them ("" when unused). */
+ * the FC2 gradient launch, and dPd with the softmax backward as one launch).
+ * The second stage of the column sums (bias and LayerNorm gradients) is one launch
+ * at the end, with a slot of its own; a run whose workspace has no room for all their
+ * partial sums finishes each in the slot of the kernel that forms them.
+ * lynx_profile_slot_name names the slots ("" when unused). */
 #define LYNX_PROFILE_SLOTS 40
 lynx_status lynx_layer_set_profiling(lynx_layer_t layer, int on);
 lynx_status lynx_layer_profile_ms(lynx_layer_t layer, float* ms_out /* [LYNX_PROFILE_SLOTS], host */);

@@ -615,15 +615,12 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
     part = reinterpret_cast<float*>(temp_ptr(cx, t_part[i]));
     return LYNX_OK;
   };
-  auto finish_sums = [&](bool last) -> lynx_status {
-    if (defer != last) return LYNX_OK;
-    LYNX_LAUNCH(cx, kColumnSums, lynx::finish_column_sums(dt, &sums, cx.st));
-    return LYNX_OK;
-  };
+  // after a producer's launch, and timed with it: its sums, where they cannot wait
+  auto summed = [&](hipError_t e) { return e != hipSuccess || defer ? e : lynx::finish_column_sums(dt, &sums, cx.st); };
   // both gradients of a linear layer
   auto launch_pair = [&](int slot, GemmDesc dg, GemmDesc wg) -> lynx_status {
     dg.serial = wg.serial = cx.bk->thrift >= kSerial;
-    LYNX_LAUNCH(cx, slot, lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, &sums, cx.st));
+    LYNX_LAUNCH(cx, slot, summed(lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, &sums, cx.st)));
     return LYNX_OK;
   };
   const size_t th = static_cast<size_t>(D.T) * D.h * e, tf = static_cast<size_t>(D.T) * D.f * e;
@@ -631,9 +628,8 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   // B13: OUT = X2 + keep2 (V2 + b2) c
   LYNX_TRY(alloc_temp(cx, th, &t_dv2));
   LYNX_TRY(alloc_partials(0, lynx::colsum_scratch_bytes(D.T, D.h)));
-  LYNX_LAUNCH(cx, kB13Dropout, lynx::dropout_bwd(dt, d_out, temp_ptr(cx, t_dv2), gr->b2, part, D.T, D.h, 2,
-                                    dropout_params(L), &sums, cx.st));
-  LYNX_TRY(finish_sums(false));
+  LYNX_LAUNCH(cx, kB13Dropout, summed(lynx::dropout_bwd(dt, d_out, temp_ptr(cx, t_dv2), gr->b2, part, D.T, D.h, 2,
+                                    dropout_params(L), &sums, cx.st)));
   LYNX_TRY(tap(cx, 12, temp_ptr(cx, t_dv2)));
   // B12: V2 = G W2^T, and B11: G = gelu(U).  Where it pays, the store pass of the input gradient
   // multiplies by gelu'(U) and sums the columns (the FC1 bias gradient), so dG is never written and
@@ -656,7 +652,6 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
         dg.epi.colsum_partial = reinterpret_cast<float*>(temp_ptr(cx, t_part[1]));
       }
       LYNX_TRY(launch_pair(kB12Grads, dg, wg));
-      LYNX_TRY(finish_sums(false));
       if (!defer) free_temp(cx, &t_part[1]);
       free_temp(cx, &t_dv2);
       free_act(cx, 11);
@@ -666,9 +661,8 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
       free_temp(cx, &t_dv2);
       free_act(cx, 11);
       LYNX_TRY(alloc_partials(1, lynx::colsum_scratch_bytes(D.T, D.f)));
-      LYNX_LAUNCH(cx, kB11Gelu, lynx::gelu_bwd(dt, temp_ptr(cx, t_du), act_ptr(cx, 10), temp_ptr(cx, t_du),
-                                               gr->b1, part, D.T, D.f, &sums, cx.st));
-      LYNX_TRY(finish_sums(false));
+      LYNX_LAUNCH(cx, kB11Gelu, summed(lynx::gelu_bwd(dt, temp_ptr(cx, t_du), act_ptr(cx, 10), temp_ptr(cx, t_du),
+                                               gr->b1, part, D.T, D.f, &sums, cx.st)));
     }
   }
   free_act(cx, 10);
@@ -685,11 +679,10 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   LYNX_TRY(alloc_temp(cx, th, &t_do));
   LYNX_TRY(alloc_partials(2, lynx::layernorm_bwd_scratch_bytes(D.T, D.h, true)));
   LYNX_LAUNCH(cx, kB98LayerNormDropout,
-              lynx::layernorm_bwd_dropout_bwd(dt, temp_ptr(cx, t_dy2), act_ptr(cx, 8), stats_ptr(cx, 9),
+              summed(lynx::layernorm_bwd_dropout_bwd(dt, temp_ptr(cx, t_dy2), act_ptr(cx, 8), stats_ptr(cx, 9),
                                               stats_ptr(cx, 9) + D.T, w.g2, d_out, temp_ptr(cx, t_dx2), gr->g2,
                                               gr->be2, temp_ptr(cx, t_do), gr->bo, part, D.T, D.h, 1,
-                                              dropout_params(L), &sums, cx.st));
-  LYNX_TRY(finish_sums(false));
+                                              dropout_params(L), &sums, cx.st)));
   LYNX_TRY(tap(cx, 8, temp_ptr(cx, t_dx2)));
   LYNX_TRY(tap(cx, 7, temp_ptr(cx, t_do)));
   free_temp(cx, &t_dy2);
@@ -787,18 +780,16 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
                        linear_wgrad(dqkv, act_ptr(cx, 1), gr->wqkv, D.T, 3 * D.p, D.h)));
   const size_t bqkv_bytes = Arena::round_up(lynx::colsum_scratch_bytes(D.T, 3 * D.p));
   LYNX_TRY(alloc_partials(3, bqkv_bytes + lynx::layernorm_bwd_scratch_bytes(D.T, D.h, false)));
-  LYNX_LAUNCH(cx, kB2BiasGrad, lynx::column_sum(dt, dqkv, gr->bqkv, part, D.T, 3 * D.p, &sums, cx.st));
-  LYNX_TRY(finish_sums(false));
+  LYNX_LAUNCH(cx, kB2BiasGrad, summed(lynx::column_sum(dt, dqkv, gr->bqkv, part, D.T, 3 * D.p, &sums, cx.st)));
   if (defer) part += bqkv_bytes / sizeof(float);
   free_temp(cx, &t_dqkv);
   free_act(cx, 2);
   LYNX_TRY(tap(cx, 1, temp_ptr(cx, t_dy1)));
   // B1: Y1 = LN1(X); dX = dX2 + dLN
-  LYNX_LAUNCH(cx, kB1LayerNorm, lynx::layernorm_bwd(dt, temp_ptr(cx, t_dy1), act_ptr(cx, 0), stats_ptr(cx, 1),
+  LYNX_LAUNCH(cx, kB1LayerNorm, summed(lynx::layernorm_bwd(dt, temp_ptr(cx, t_dy1), act_ptr(cx, 0), stats_ptr(cx, 1),
                                       stats_ptr(cx, 1) + D.T, w.g1, temp_ptr(cx, t_dx2), d_x, gr->g1,
-                                      gr->be1, part, D.T, D.h, &sums, cx.st));
-  LYNX_TRY(finish_sums(false));
-  LYNX_TRY(finish_sums(true));
+                                      gr->be1, part, D.T, D.h, &sums, cx.st)));
+  if (defer) LYNX_LAUNCH(cx, kColumnSums, lynx::finish_column_sums(dt, &sums, cx.st));
   for (Temp& t : t_part) free_temp(cx, &t);
   free_temp(cx, &t_dy1);
   free_temp(cx, &t_dx2);

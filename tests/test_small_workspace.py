@@ -262,3 +262,19 @@ def test_scratch_at_the_upper_end_keeps_the_bits():
         assert bool((layer.workspace[layer.ws_base + nbytes - layer.workspace.data_ptr():] == 0xFF).all())
         layer.close()
     assert all(torch.equal(p, q) for p, q in zip(*runs))
+
+
+@pytest.mark.gpu
+def test_column_sums_are_timed_with_their_producers_where_they_cannot_wait():
+    cfg = synth.LayerConfig(synth.BF16, 264, 1, 40, 72, 200, 1, tp_size=2, seed=5)
+    params, X, dOUT = synth.make_params(cfg), synth.make_x(cfg), synth.make_dout(cfg)
+    for size, together in ((B.lynx_workspace_bytes(cfg, pm.FULL_RECOMPUTE), True),
+                           (least_workspace(cfg, pm.FULL_RECOMPUTE), False)):
+        layer = GpuLayer(cfg, params, workspace_bytes=size)
+        B.lynx_layer_set_profiling(layer.handle, True)
+        layer.forward(X, pm.FULL_RECOMPUTE)
+        layer.backward(dOUT)
+        slots = B.lynx_layer_profile_ms(layer.handle)
+        assert ("b_column_sums" in slots) == together
+        assert "b13_dropout_bwd" in slots and "b1_layernorm1_bwd" in slots
+        layer.close()
