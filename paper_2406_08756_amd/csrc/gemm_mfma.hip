@@ -13,9 +13,8 @@ constexpr double kPairCutFraction = 0.9;  // see plan_pair
 // covered by the other's matrix instructions.  Against four wavefronts of 128 x 128 (one per SIMD, 1.5
 // times less LDS traffic): 8192^3 forward 999 -> 908 us, 16384 x 2560 x 5120 402 -> 391 us.
 constexpr int kWholeWaves = 8;
-template <bool A_KMAJOR, bool B_KMAJOR>
 __global__ void __launch_bounds__(kWholeWaves * kWave, 2) gemm_mfma_kernel(MfmaGemmArgs g) {
-  gemm_tile<A_KMAJOR, B_KMAJOR, 256, 256, false, kStages, false, kBK, kWholeWaves>(g, blockIdx.x, 0);
+  gemm_tile<true, true, 256, 256, false, kStages, false, kBK, kWholeWaves>(g, blockIdx.x, 0);
 }
 
 // The products of attention with the seq x seq operand: memory-bound.  128 x 128 tiles: the zero
@@ -36,9 +35,8 @@ constexpr int kDuoStages = 3;
 // attention projection, K = 640, 0.198 -> 0.178 ms; FC2, K = 2560, 0.442 -> 0.461 ms: there the
 // larger tile's lower LDS and L2 traffic wins over the overlapped store pass)
 constexpr int kDuoMaxK = 1024;
-template <bool A_KMAJOR, bool B_KMAJOR>
 __global__ void __launch_bounds__(kThreads, 2) gemm_mfma_duo_kernel(MfmaGemmArgs g) {
-  gemm_tile<A_KMAJOR, B_KMAJOR, 256, 128, false, kDuoStages>(g, blockIdx.x, blockIdx.y);
+  gemm_tile<true, true, 256, 128, false, kDuoStages>(g, blockIdx.x, blockIdx.y);
 }
 
 // Work items of the score-shaped row-block kernels: row block tm (128 rows) owns tiles
@@ -392,11 +390,10 @@ __global__ void __launch_bounds__(kThreads, 2) attn_dscores_kernel(MfmaGemmArgs 
 // An output whose width is an odd multiple of 128: 256 x 256 tiles over the columns that
 // whole tiles cover, and one column of 256 x 128 tiles (`edge`: the same product on the last
 // 128 columns) behind them in the same launch, where they fill the last round of workgroups.
-template <bool A_KMAJOR, bool B_KMAJOR>
 __global__ void __launch_bounds__(kThreads)
 gemm_mfma_edge_kernel(MfmaGemmArgs body, MfmaGemmArgs edge, int n_body) {
-  if (static_cast<int>(blockIdx.x) < n_body) gemm_tile<A_KMAJOR, B_KMAJOR, 256, 256>(body, blockIdx.x, 0);
-  else gemm_tile<A_KMAJOR, B_KMAJOR, 256, 128>(edge, blockIdx.x - n_body, 0);
+  if (static_cast<int>(blockIdx.x) < n_body) gemm_tile<true, true, 256, 256>(body, blockIdx.x, 0);
+  else gemm_tile<true, true, 256, 128>(edge, blockIdx.x - n_body, 0);
 }
 
 // The two products of a linear layer's backward in one launch: the weight gradient
@@ -445,10 +442,9 @@ splitk_reduce_kernel(const float* __restrict__ partial, bf16_t* __restrict__ C, 
   *reinterpret_cast<uint4*>(C + static_cast<long long>(m) * ldc + n) = o;
 }
 
-template <bool AK, bool BK_>
 hipError_t launch_whole(MfmaGemmArgs a, hipStream_t st) {
   constexpr size_t smem = static_cast<size_t>(kStages) * (256 + 256) * kBK * sizeof(bf16_t);
-  auto kern = gemm_mfma_kernel<AK, BK_>;
+  auto kern = gemm_mfma_kernel;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   a.tiles_m = a.M / 256;
   a.tiles_n = a.N / 256;
@@ -468,10 +464,9 @@ hipError_t launch_attn_product(MfmaGemmArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <bool AK, bool BK_>
 hipError_t launch_duo(MfmaGemmArgs a, hipStream_t st) {
   constexpr size_t smem = static_cast<size_t>(kDuoStages) * (256 + 128) * kBK * sizeof(bf16_t);
-  auto kern = gemm_mfma_duo_kernel<AK, BK_>;
+  auto kern = gemm_mfma_duo_kernel;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   a.tiles_m = a.M / 256;
   a.tiles_n = a.N / 128;
@@ -479,10 +474,9 @@ hipError_t launch_duo(MfmaGemmArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <bool AK, bool BK_>
 hipError_t launch_edge(const MfmaGemmArgs& a, hipStream_t st) {
   constexpr size_t smem = static_cast<size_t>(kStages) * (256 + 256) * kBK * sizeof(bf16_t);
-  auto kern = gemm_mfma_edge_kernel<AK, BK_>;
+  auto kern = gemm_mfma_edge_kernel;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   MfmaGemmArgs body = a, edge = a;
   const int n_body_cols = a.N - 128;
@@ -490,7 +484,7 @@ hipError_t launch_edge(const MfmaGemmArgs& a, hipStream_t st) {
   body.tiles_m = a.M / 256; body.tiles_n = n_body_cols / 256;
   edge.N = 128;
   edge.tiles_m = a.M / 256; edge.tiles_n = 1;
-  edge.B = a.B + (BK_ ? static_cast<long long>(n_body_cols) * a.ldb : static_cast<long long>(n_body_cols));
+  edge.B = a.B + static_cast<long long>(n_body_cols) * a.ldb;
   edge.C = a.C + n_body_cols;
   if (a.bias != nullptr) edge.bias = a.bias + n_body_cols;
   edge.col0 = a.col0 + n_body_cols;
@@ -613,7 +607,7 @@ hipError_t launch_pair(MfmaGemmArgs w, MfmaGemmArgs d, const PairPlan& plan, hip
 // Whole tiles, and large enough that the 256 x 256 tile is the right one (`choice`: the ragged plan).
 bool gemm_whole_takes(const GemmDesc& d, const RaggedChoice& choice) {
   if (d.nz1 * d.nz2 != 1 || d.causal != kCausalNone || d.M % 256 || d.N % 128 || d.K % kBK) return false;
-  if (!(d.a_sk == 1)) return false;
+  if (d.a_sk != 1 || d.b_sk != 1) return false;  // (forward products: gradients come in pairs)
   // (a cut contraction is summed in another order: with and without the epilogue a shape is cut alike)
   if (choice.scratch_bytes != 0) return false;
   if (d.epi.kind == kEpiBiasDropoutAdd && d.K <= kDuoMaxK)
@@ -623,13 +617,8 @@ bool gemm_whole_takes(const GemmDesc& d, const RaggedChoice& choice) {
 
 hipError_t gemm_whole(const GemmDesc& d, hipStream_t st) {
   const MfmaGemmArgs a = make_args(d);
-  auto run = [&](auto bk) -> hipError_t {
-    constexpr bool kB = decltype(bk)::value;
-    if (d.epi.kind == kEpiBiasDropoutAdd && d.K <= kDuoMaxK) return launch_duo<true, kB>(a, st);
-    if (d.N % 256) return launch_edge<true, kB>(a, st);
-    return launch_whole<true, kB>(a, st);
-  };
-  return d.b_sk == 1 ? run(std::true_type{}) : run(std::false_type{});
+  if (d.epi.kind == kEpiBiasDropoutAdd && d.K <= kDuoMaxK) return launch_duo(a, st);
+  return d.N % 256 ? launch_edge(a, st) : launch_whole(a, st);
 }
 
 // Attention: score-shaped (S = Q K^T, dPd = dC V^T and dS in its place) and contraction-restricted.

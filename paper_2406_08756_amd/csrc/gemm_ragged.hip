@@ -171,9 +171,11 @@ hipError_t launch_ragged(MfmaGemmArgs a, hipStream_t st) {
 
 template <bool AK, bool BK_>
 hipError_t launch_tile(int tile, const MfmaGemmArgs& a, hipStream_t st) {
+  if constexpr (AK) {  // (both MN-major: attention, in tiles of at most 128 x 128)
+    if (tile == kT256) return launch_ragged<AK, BK_, kT256>(a, st);
+    if (tile == kT256x128) return launch_ragged<AK, BK_, kT256x128>(a, st);
+  }
   switch (tile) {
-    case kT256: return launch_ragged<AK, BK_, kT256>(a, st);
-    case kT256x128: return launch_ragged<AK, BK_, kT256x128>(a, st);
     case kT128: return launch_ragged<AK, BK_, kT128>(a, st);
     case kT128x64: return launch_ragged<AK, BK_, kT128x64>(a, st);
     default: return launch_ragged<AK, BK_, kT64>(a, st);
