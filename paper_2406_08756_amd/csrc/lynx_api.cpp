@@ -854,29 +854,50 @@ lynx_status two_pass(lynx_layer_s* L, hipStream_t st, F&& body) {
   return s;
 }
 
+// A layer without device memory.  Nothing is launched; the placeholders only have to look like what a real call
+// passes (non-null, aligned), so that a rehearsal takes the kernel path a real call takes.
+struct Rehearsal {
+  void* const fake = reinterpret_cast<void*>(static_cast<uintptr_t>(Arena::kAlign));
+  const lynx_grads g{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
+  lynx_layer_s L;
+  Rehearsal(const lynx_layer_config& cfg, const Dims& D, size_t capacity) {
+    L.cfg = cfg;
+    L.D = D;
+    L.book.arena = Arena(capacity);
+    L.dry = true;
+    L.base = static_cast<char*>(fake);
+    L.params = lynx_params{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
+    L.x = fake;
+    L.out = fake;
+  }
+};
+
 // The workspace a call sequence reaches into: forward, the phases, backward.
 size_t workspace_need(const lynx_layer_config* cfg, uint32_t retain_mask, const uint32_t* phase_masks, int thrift) {
   Dims D;
   if (!make_dims(cfg, &D) || (retain_mask & ~0x3FFFu)) return 0;
-  lynx_layer_s L;
-  L.cfg = *cfg;
-  L.D = D;
-  L.book.arena = Arena(static_cast<size_t>(1) << 60);
-  L.book.thrift = thrift;
-  Ctx cx{&L, &L.book, false, nullptr};
-  // Nothing is launched; the placeholders only have to look like what a real call passes
-  // (non-null, aligned), so that the rehearsal takes the kernel path a real call takes.
-  void* const fake = reinterpret_cast<void*>(static_cast<uintptr_t>(Arena::kAlign));
-  const lynx_grads g{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
-  L.base = static_cast<char*>(fake);
-  L.params = lynx_params{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
-  L.x = fake;
-  L.out = fake;
+  Rehearsal r(*cfg, D, static_cast<size_t>(1) << 60);
+  r.L.book.thrift = thrift;
+  Ctx cx{&r.L, &r.L.book, false, nullptr};
   if (forward_pass(cx, retain_mask) != LYNX_OK) return 0;
   for (int t = 0; phase_masks != nullptr && t < 4; ++t)
     if (phase_masks[t] != 0 && recompute_pass(cx, phase_masks[t]) != LYNX_OK) return 0;
-  if (backward_pass(cx, fake, fake, &g) != LYNX_OK) return 0;
-  return L.book.arena.extent_peak();
+  if (backward_pass(cx, r.fake, r.fake, &r.g) != LYNX_OK) return 0;
+  return r.L.book.arena.extent_peak();
+}
+
+// Whether a layer over `bytes` takes that sequence, call by call.
+bool sequence_fits(const lynx_layer_config* cfg, uint32_t retain_mask, const uint32_t* phase_masks, size_t bytes) {
+  Dims D;
+  if (!make_dims(cfg, &D)) return false;
+  Rehearsal r(*cfg, D, bytes);
+  r.L.book.thrift = thrift_for(&r.L, retain_mask);
+  if (two_pass(&r.L, nullptr, [&](Ctx& cx) { return forward_pass(cx, retain_mask); }) != LYNX_OK) return false;
+  for (int t = 0; t < 4; ++t)
+    if (phase_masks[t] != 0 &&
+        two_pass(&r.L, nullptr, [&](Ctx& cx) { return recompute_pass(cx, phase_masks[t]); }) != LYNX_OK)
+      return false;
+  return two_pass(&r.L, nullptr, [&](Ctx& cx) { return backward_pass(cx, r.fake, r.fake, &r.g); }) == LYNX_OK;
 }
 
 }  // namespace
@@ -1044,7 +1065,12 @@ lynx_status lynx_layer_activation(lynx_layer_t L, int act_id, const void** devic
 
 size_t lynx_workspace_bytes_for_schedule(const lynx_layer_config* cfg, uint32_t retain_mask,
                                          const uint32_t* phase_masks) {
-  return workspace_need(cfg, retain_mask, phase_masks, 0);
+  const size_t need = workspace_need(cfg, retain_mask, phase_masks, 0);
+  // A run starts at the thrift that forward -> backward alone needs.  Where phases leave less room than that takes,
+  // this can be another placement than the one just rehearsed; with the room of both it is the same.
+  if (need == 0 || phase_masks == nullptr || sequence_fits(cfg, retain_mask, phase_masks, need)) return need;
+  const size_t alone = workspace_need(cfg, retain_mask, nullptr, 0);
+  return alone > need ? alone : need;
 }
 
 size_t lynx_workspace_bytes(const lynx_layer_config* cfg, uint32_t retain_mask) {

@@ -136,6 +136,7 @@ SCHEDULES = {
     "phases": ((synth.BF16, 1480, 2, 64, 3328, 96, 5), 0, 0x3545, (0x3900, 0, 0, 0), None),
     "phases_heads256": ((synth.BF16, 4096, 7, 256, 5248, 512, 8), 0, 0x37CF, (0x0EDE, 0, 0, 0), None),
     "phases_heads136": ((synth.BF16, 5136, 2, 136, 5504, 1152, 3), 1, 0x2949, (0, 0x1386, 0, 0), None),
+    "phase_needs_less_than_none": ((synth.BF16, 7448, 8, 128, 528, 768, 5), 0, 0x2E71, (0, 0x2DF0, 0, 0), None),
     "scratch_in_a_hole": ((synth.BF16, 2528, 4, 72, 896, 1152, 2), 0, 0x2BA5, (0, 0, 0, 0), 165337088),
     "scratch_in_a_hole_heads96": ((synth.BF16, 1696, 4, 96, 232, 1536, 3), 0, 0x3001, (0, 0, 0, 0), 286175232),
 }
