@@ -75,7 +75,7 @@ struct IdentityOp {
 // The partial rows, their order of sums and with it their bits are the same: the narrow tile brings its 32 rows
 // together in LDS, one column per thread (sums of the thread's two rows and then of the 16 row groups in series are
 // another order, with 1.1 to 1.2 times the error against 64 bits in fp32).  Dropout backward, 64 -> 16 vectors:
-// 256 x 256 fp32 6.6 -> 3.7 us, 768 x 512 bf16 6.8 -> 5.4, 984 x 3016 7.6 -> 6.0, 4000 x 1600 (500 workgroups of 64)
+// 256 x 256 fp32 6.6 -> 3.6 us, 768 x 512 bf16 6.8 -> 4.2, 984 x 3016 7.6 -> 6.0, 4000 x 1600 (500 workgroups of 64)
 // 11.1 -> 8.4.
 template <typename T, typename Op, int V>
 __global__ void __launch_bounds__(kThreads)

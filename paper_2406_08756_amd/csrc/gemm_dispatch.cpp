@@ -83,7 +83,7 @@ bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wg
   if (!gemm_pair_supported(dtype, dgrad, wgrad)) return false;
   if (dtype != 1) return true;
   // With few rows the plain product is cut into K ranges, which the epilogue's column sums rule out; a
-  // GeLU kernel of its own (two launches, three passes over [M, N]) costs less than the uncut product.
+  // GeLU kernel of its own (two launches, three passes over [M, N]) costs less than the product left whole.
   GemmDesc plain = dgrad;
   plain.epi = GemmEpilogue{};
   return pair_us(dgrad, wgrad) <= pair_us(plain, wgrad) + 8.0 + 6.0 * dgrad.M * dgrad.N / 4.0e6;

@@ -11,7 +11,7 @@ struct RaggedChoice {
   double us;
   size_t scratch_bytes;
   int colsum_rows;
-  bool largest_tile;  // 256 x 256 tiles, uncut: the whole-tile kernels do the same with fewer checks
+  bool largest_tile;  // 256 x 256 tiles, contraction whole: the whole-tile kernels do the same with fewer checks
 };
 RaggedChoice ragged_product(const GemmDesc& d);
 RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad);

@@ -36,7 +36,9 @@ template <int TILE> constexpr int tile_waves_per_simd = TileShape<TILE, false>::
 // The numbers are fitted to measurements, for forward products and for gradient pairs each: 169 products
 // and 178 pairs of layers with 64 to 16384 tokens and widths from 40 to 22000, every tile and every cut
 // of each timed, the constants chosen so that the tile and cut with the least predicted time lose as
-// little as possible against the fastest: 1.3 % and 2.8 % on average.
+// little as possible against the fastest: 1.3 % and 2.8 % on average.  None of the products had an epilogue: the
+// store pass with bias, dropout and residual is not in the model (984 tokens of h 3016, 128 x 64 tiles, two projections and
+// one FC2: 12, 12 and 19.5 us predicted, 20.5 measured on average); for those the choice is that of the plain product.
 struct TileCost {
   int bm, bn, share;
   double alone, one_each, full;
@@ -184,6 +186,9 @@ hipError_t launch_tile(int tile, const MfmaGemmArgs& a, hipStream_t st) {
 
 // The ranges of a cut contraction in one workgroup, one after the other (GemmDesc::serial).  The smallest tile,
 // whichever the plan has: a product is cut because its tiles are few, and the tile does not enter the sums.
+// Latency of the whole contraction on a part of the chip bounds it; it is for workspaces that have no room for the
+// cut form.  128 tokens of h 5120 (QKV of width 1920, FC1 of 2560): 29 us each, cut 14 and 16; a step of that layer
+// 419 us against 268, of 512 tokens of h 3072 437 against 411, with both gradients of a layer as launches of their own.
 template <bool AK, bool BK_>
 __global__ void __launch_bounds__((tile_threads<kT64>), (tile_waves_per_simd<kT64>)) gemm_serial_kernel(MfmaGemmArgs g) {
   using T = TileShape<kT64, AK && BK_>;

@@ -36,7 +36,8 @@ __device__ __forceinline__ float gelu_f(float u) {
   return 0.5f * u * (1.0f + th);
 }
 // With sigma = (1 + tanh y) / 2 = 1 / (1 + e^(-2y)): gelu' = sigma + 2 u y' sigma (1 - sigma), in which
-// nothing cancels for u < 0: error in the 2-norm 0.86 to 0.97 of the tanh form's, largest no larger.
+// nothing cancels for u < 0: error in the 2-norm 0.86 to 0.97 of the tanh form's (deviates of deviation 0.05 to 20);
+// largest 0.7 of it at 0.05, 1.3 and 1.1 times at 0.5 and 1 (3.7e-7 and 1.4e-6), the same beyond.
 // sigma (1 - sigma) comes first: it is 0 from |u| of about 10 on, where u y' grows with u^3 and overflows at 1e13
 // (for u < 0 too: the hardware reciprocal of anything beyond 2^126, whose reciprocal is subnormal, is 0).
 __device__ __forceinline__ float gelu_grad_f(float u) {
