@@ -135,7 +135,8 @@ size_t lynx_activation_bytes(const lynx_layer_config* cfg, int act_id);
  * Where few tokens leave the chip idle, the size includes fp32 partial sums of
  * contractions that are cut into ranges.  A smaller workspace that the sequence
  * fits without them is accepted too: the ranges are then summed one after the
- * other (slower, the same bits). */
+ * other (slower, the same bits).  (A weight gradient over 2048 tokens or more
+ * that is cut into two keeps its partial sums in every workspace.) */
 size_t lynx_workspace_bytes(const lynx_layer_config* cfg, uint32_t retain_mask);
 
 /* The same for a schedule with explicit regeneration phases (Sec. 4.2: the
@@ -184,9 +185,10 @@ lynx_status lynx_layer_forward(lynx_layer_t layer, const void* x_device, void* o
                                uint32_t retain_mask, uint64_t step, void* hip_stream);
 
 /* Regenerate a segment: the operators named in segment_mask run in index
- * order with the forward's kernels and launch geometry, so their outputs are
- * bit-identical to the forward's.  An operator whose output is resident is
- * skipped.  An operator with an absent input that no earlier operator of the
+ * order with the forward's order of every sum, so their outputs are
+ * bit-identical to the forward's (also where the segment leaves the workspace
+ * without room for scratch that the forward had).  An operator whose output is
+ * resident is skipped.  An operator with an absent input that no earlier operator of the
  * segment produces fails the whole call with DEPENDENCY (Eq. 4: a parent must
  * be stored or already regenerated).  Regenerated S, O or V2 (which backward
  * never reads) are released again as soon as their consumers are resident.
