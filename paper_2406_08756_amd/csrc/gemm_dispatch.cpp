@@ -6,16 +6,6 @@ namespace {
 
 bool aligned(const void* p, uintptr_t bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
 
-// (The whole-tile pair mixes tile shapes and pads nothing: it wins ties, e.g. 123 against 131 us for the
-// attention projection of the 7B-shaped shard, which the estimates put level.)
-bool uses_whole_pair(const GemmDesc& dgrad, const GemmDesc& wgrad) {
-  const double us = gemm_whole_pair_us(dgrad, wgrad);
-  return us >= 0.0 && us <= 1.05 * ragged_pair(dgrad, wgrad).us;
-}
-double pair_us(const GemmDesc& dgrad, const GemmDesc& wgrad) {
-  return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair_us(dgrad, wgrad) : ragged_pair(dgrad, wgrad).us;
-}
-
 bool unbatched(const GemmDesc& d) { return d.causal == kCausalNone && d.nz1 * d.nz2 == 1; }
 
 bool gemm_mfma_supported(int dtype, const GemmDesc& d) {
@@ -59,15 +49,13 @@ bool gemm_supported(int dtype, const GemmDesc& d) {
 
 size_t gemm_scratch_bytes(int dtype, const GemmDesc& d) {
   if (dtype != 1 || !unbatched(d) || d.serial) return 0;
-  const RaggedChoice c = ragged_product(d);
-  return gemm_whole_takes(d, c) ? 0 : c.scratch_bytes;
+  return ragged_product(d).scratch_bytes;
 }
 
 hipError_t gemm(int dtype, const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st) {
   if (!gemm_supported(dtype, d) || d.epi.kind == kEpiGeluBwd) return hipErrorInvalidValue;
   if (dtype != 1) return gemm_f32(d, st);
   if (d.causal != kCausalNone) return gemm_attention(d, st);
-  if (gemm_whole_takes(d, ragged_product(d))) return gemm_whole(d, st);
   return gemm_ragged(d, scratch, scratch_bytes, st);
 }
 
@@ -86,18 +74,17 @@ bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wg
   // GeLU kernel of its own (two launches, three passes over [M, N]) costs less than the product left whole.
   GemmDesc plain = dgrad;
   plain.epi = GemmEpilogue{};
-  return pair_us(dgrad, wgrad) <= pair_us(plain, wgrad) + 8.0 + 6.0 * dgrad.M * dgrad.N / 4.0e6;
+  return ragged_pair(dgrad, wgrad).us <= ragged_pair(plain, wgrad).us + 8.0 + 6.0 * dgrad.M * dgrad.N / 4.0e6;
 }
 
 size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
   if (dtype != 1) return 0;
-  if (uses_whole_pair(dgrad, wgrad)) return gemm_whole_pair_scratch_bytes(dgrad, wgrad);
   return dgrad.serial ? 0 : ragged_pair(dgrad, wgrad).scratch_bytes;
 }
 
 size_t gemm_pair_colsum_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
   if (dtype != 1) return gemm_f32_pair_colsum_bytes(dgrad, wgrad);
-  const int rows = uses_whole_pair(dgrad, wgrad) ? dgrad.M / 128 : ragged_pair(dgrad, wgrad).colsum_rows;
+  const int rows = ragged_pair(dgrad, wgrad).colsum_rows;
   return static_cast<size_t>(rows) * static_cast<size_t>(dgrad.N) * sizeof(float);
 }
 
@@ -105,8 +92,7 @@ hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, fl
                      size_t scratch_bytes, ColumnSums* sums, hipStream_t st) {
   if (!gemm_pair_supported(dtype, dgrad, wgrad)) return hipErrorInvalidValue;
   if (dtype != 1) return gemm_f32_pair(dgrad, wgrad, sums, st);
-  return uses_whole_pair(dgrad, wgrad) ? gemm_whole_pair(dgrad, wgrad, scratch, scratch_bytes, sums, st)
-                                       : gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, sums, st);
+  return gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, sums, st);
 }
 
 }  // namespace lynx

@@ -23,6 +23,11 @@ namespace {
     if (err_ != hipSuccess) return err_;                                                        \
   } while (0)
 
+// Strides that only the tiles with 64-bit load offsets take (kFarStride).
+bool is_far(const GemmDesc& d) {
+  return (d.a_sk == 1 ? d.a_sm : d.a_sk) >= kFarStride || (d.b_sk == 1 ? d.b_sn : d.b_sk) >= kFarStride;
+}
+
 MfmaGemmArgs make_args(const GemmDesc& d) {
   MfmaGemmArgs a{};
   const bool a_k = d.a_sk == 1, b_k = d.b_sk == 1;

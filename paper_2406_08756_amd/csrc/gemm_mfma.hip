@@ -1,5 +1,5 @@
-// bf16 matrix products of whole tiles on the matrix cores: launches and their choice (the tile
-// itself is gemm_tile.h).
+// bf16 matrix products of attention: kernels and launches (the tile of those that contract over tokens is
+// gemm_tile.h; linear products: gemm_ragged.hip).
 #include <mutex>
 
 #include "gemm_launch.h"
@@ -7,36 +7,12 @@
 namespace lynx {
 namespace {
 
-constexpr double kPairCutFraction = 0.9;  // see plan_pair
-
-// Eight wavefronts on a 256 x 256 tile: two per SIMD, so one's waits for LDS and for the barrier are
-// covered by the other's matrix instructions.  Against four wavefronts of 128 x 128 (one per SIMD, 1.5
-// times less LDS traffic): 8192^3 forward 999 -> 908 us, 16384 x 2560 x 5120 402 -> 391 us.
-constexpr int kWholeWaves = 8;
-__global__ void __launch_bounds__(kWholeWaves * kWave, 2) gemm_mfma_kernel(MfmaGemmArgs g) {
-  gemm_tile<true, true, 256, 256, false, kStages, false, kBK, kWholeWaves>(g, blockIdx.x, 0);
-}
-
 // The products of attention with the seq x seq operand: memory-bound.  128 x 128 tiles: the zero
 // padding of that operand reaches the next multiple of 128 only, and two workgroups fit a compute
 // unit (one loads while the other stores).
 template <bool A_KMAJOR>
 __global__ void __launch_bounds__(kThreads, 2) attn_product_kernel(MfmaGemmArgs g) {
   gemm_tile<A_KMAJOR, false, 128, 128>(g, blockIdx.x, 0);
-}
-
-// 256 x 128 tiles with a three-stage ring (72 KB) and at most 256 registers, so that two
-// workgroups share a compute unit: for launches whose store pass is long (bias + dropout +
-// residual: one Philox call per 8 outputs, about as long as a 20-slab contraction), one
-// workgroup's store pass then runs on the vector ALUs while the other's contraction keeps
-// the matrix cores busy.
-constexpr int kDuoStages = 3;
-// contractions up to this length take the two-workgroup form (measured at the 13B shard: the
-// attention projection, K = 640, 0.198 -> 0.178 ms; FC2, K = 2560, 0.442 -> 0.461 ms: there the
-// larger tile's lower LDS and L2 traffic wins over the overlapped store pass)
-constexpr int kDuoMaxK = 1024;
-__global__ void __launch_bounds__(kThreads, 2) gemm_mfma_duo_kernel(MfmaGemmArgs g) {
-  gemm_tile<true, true, 256, 128, false, kDuoStages>(g, blockIdx.x, blockIdx.y);
 }
 
 // Work items of the score-shaped row-block kernels: row block tm (128 rows) owns tiles
@@ -387,71 +363,6 @@ __global__ void __launch_bounds__(kThreads, 2) attn_dscores_kernel(MfmaGemmArgs 
   }
 }
 
-// An output whose width is an odd multiple of 128: 256 x 256 tiles over the columns that
-// whole tiles cover, and one column of 256 x 128 tiles (`edge`: the same product on the last
-// 128 columns) behind them in the same launch, where they fill the last round of workgroups.
-__global__ void __launch_bounds__(kThreads)
-gemm_mfma_edge_kernel(MfmaGemmArgs body, MfmaGemmArgs edge, int n_body) {
-  if (static_cast<int>(blockIdx.x) < n_body) gemm_tile<true, true, 256, 256>(body, blockIdx.x, 0);
-  else gemm_tile<true, true, 256, 128>(edge, blockIdx.x - n_body, 0);
-}
-
-// The two products of a linear layer's backward in one launch: the weight gradient
-// (both operands MN-major, long contraction over the tokens) takes the first n_w
-// workgroups, the input gradient (weight MN-major) the rest.  Sharing a launch lets
-// the second product's tiles fill the compute units the first leaves idle in its
-// last, partial round.  When one side of the weight gradient is an odd multiple of 128,
-// its 256 x 256 tiles cover all but the last 128 rows (or columns) and `wedge`, the same
-// product on that strip with EBM x EBN tiles, takes the n_e workgroups after them.
-template <int DBM, int DBN, int WBM, int WBN, int EBM, int EBN>
-__global__ void __launch_bounds__(kThreads)
-gemm_mfma_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs wedge, MfmaGemmArgs dgrad, int n_w, int n_e) {
-  const int x = static_cast<int>(blockIdx.x);
-  // the input gradient starts at a multiple of 8 workgroups, so that its tile order, which
-  // takes workgroup id mod 8 for the XCD, still holds; the few workgroups in between idle
-  const int n_pad = (n_w + n_e + 7) & ~7;
-  if (x < n_w) {
-    if (wgrad.k_splits > 1) gemm_tile<false, false, WBM, WBN, true>(wgrad, x, 0);
-    else gemm_tile<false, false, WBM, WBN>(wgrad, x, 0);
-  } else if (EBM != 0 && x < n_w + n_e) {
-    if constexpr (EBM != 0) gemm_tile<false, false, EBM, EBN>(wedge, x - n_w, 0);
-  } else if (x >= n_pad) {
-    gemm_tile<true, false, DBM, DBN>(dgrad, x - n_pad, 0);
-  }
-}
-
-// C[m][n] = round(sum over the K ranges, in range order, of partial[split][m][n]).
-__global__ void __launch_bounds__(256)
-splitk_reduce_kernel(const float* __restrict__ partial, bf16_t* __restrict__ C, int M, int N, long long ldc,
-                     int k_splits) {
-  const long long v = static_cast<long long>(blockIdx.x) * 256 + threadIdx.x;  // 8 consecutive n
-  const int per_row = N / 8;
-  if (v >= static_cast<long long>(M) * per_row) return;
-  const int m = static_cast<int>(v / per_row), n = static_cast<int>(v - static_cast<long long>(m) * per_row) * 8;
-  const float* p = partial + static_cast<long long>(m) * N + n;
-  float4 lo = *reinterpret_cast<const float4*>(p), hi = *reinterpret_cast<const float4*>(p + 4);
-  for (int sp = 1; sp < k_splits; ++sp) {
-    p += static_cast<long long>(M) * N;
-    const float4 l2 = *reinterpret_cast<const float4*>(p), h2 = *reinterpret_cast<const float4*>(p + 4);
-    lo.x += l2.x; lo.y += l2.y; lo.z += l2.z; lo.w += l2.w;
-    hi.x += h2.x; hi.y += h2.y; hi.z += h2.z; hi.w += h2.w;
-  }
-  uint4 o;
-  o.x = pack_bf16(lo.x, lo.y); o.y = pack_bf16(lo.z, lo.w);
-  o.z = pack_bf16(hi.x, hi.y); o.w = pack_bf16(hi.z, hi.w);
-  *reinterpret_cast<uint4*>(C + static_cast<long long>(m) * ldc + n) = o;
-}
-
-hipError_t launch_whole(MfmaGemmArgs a, hipStream_t st) {
-  constexpr size_t smem = static_cast<size_t>(kStages) * (256 + 256) * kBK * sizeof(bf16_t);
-  auto kern = gemm_mfma_kernel;
-  LYNX_RAISE_LDS_LIMIT(kern, smem);
-  a.tiles_m = a.M / 256;
-  a.tiles_n = a.N / 256;
-  hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n), dim3(kWholeWaves * kWave), smem, st, a);
-  return hipGetLastError();
-}
-
 // attention products over whole tiles (grid: tile x matrix in one dimension)
 template <bool AK>
 hipError_t launch_attn_product(MfmaGemmArgs a, hipStream_t st) {
@@ -461,35 +372,6 @@ hipError_t launch_attn_product(MfmaGemmArgs a, hipStream_t st) {
   a.tiles_m = a.M / 128;
   a.tiles_n = a.N / 128;
   hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n * a.nz), dim3(kThreads), smem, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_duo(MfmaGemmArgs a, hipStream_t st) {
-  constexpr size_t smem = static_cast<size_t>(kDuoStages) * (256 + 128) * kBK * sizeof(bf16_t);
-  auto kern = gemm_mfma_duo_kernel;
-  LYNX_RAISE_LDS_LIMIT(kern, smem);
-  a.tiles_m = a.M / 256;
-  a.tiles_n = a.N / 128;
-  hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n), dim3(kThreads), smem, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_edge(const MfmaGemmArgs& a, hipStream_t st) {
-  constexpr size_t smem = static_cast<size_t>(kStages) * (256 + 256) * kBK * sizeof(bf16_t);
-  auto kern = gemm_mfma_edge_kernel;
-  LYNX_RAISE_LDS_LIMIT(kern, smem);
-  MfmaGemmArgs body = a, edge = a;
-  const int n_body_cols = a.N - 128;
-  body.N = n_body_cols;
-  body.tiles_m = a.M / 256; body.tiles_n = n_body_cols / 256;
-  edge.N = 128;
-  edge.tiles_m = a.M / 256; edge.tiles_n = 1;
-  edge.B = a.B + static_cast<long long>(n_body_cols) * a.ldb;
-  edge.C = a.C + n_body_cols;
-  if (a.bias != nullptr) edge.bias = a.bias + n_body_cols;
-  edge.col0 = a.col0 + n_body_cols;
-  const int n_body = body.tiles_m * body.tiles_n;
-  hipLaunchKernelGGL(kern, dim3(n_body + edge.tiles_m), dim3(kThreads), smem, st, body, edge, n_body);
   return hipGetLastError();
 }
 
@@ -513,113 +395,7 @@ hipError_t scores(const MfmaGemmArgs& a, hipStream_t st) {
   return whole ? launch_scores<128, attn_outer_kernel<128, false>>(a, st) : launch_scores<128, attn_outer_kernel<128, true>>(a, st);
 }
 
-// How a pair is launched.  Tiles: the largest that divides the output (pair launches
-// share their tail, so there is no reason to shrink tiles for occupancy); a weight gradient
-// with one side an odd multiple of 128 and at least half a round of whole tiles gets
-// 256 x 256 tiles plus an edge strip.  K ranges (1 or 2) of the weight gradient: its tiles
-// contract over all tokens and are few; when one of them lasts longer than nine tenths
-// of the launch's ideal duration, the compute units that have finished the input gradient
-// wait for it, and halving it pays for the extra pass over the fp32 partial sums (measured:
-// 10-30 % on the attention-projection shapes; finer cuts and cuts of the wide layers lose
-// to that pass).  Durations in slab units: 1 per slab for a 256 x 256 tile, about 0.55 for
-// the narrower ones.
-struct PairPlan {
-  int dbm, dbn;      // input-gradient tile
-  int wbm, wbn;      // weight-gradient tile
-  int edge;          // 0 none, 1 last 128 rows (128 x 256 tiles), 2 last 128 columns (256 x 128)
-  int k_splits;
-  double us;         // estimate, in the terms of the ragged kernels' cost model
-};
-
-PairPlan plan_pair(int wM, int wN, int wK, int dM, int dN, int dK) {
-  PairPlan p{};
-  p.dbm = dM % 256 == 0 ? 256 : 128;
-  p.dbn = dN % 256 == 0 ? 256 : 128;
-  p.wbm = wM % 256 == 0 ? 256 : 128;
-  p.wbn = wN % 256 == 0 ? 256 : 128;
-  if (wM % 256 == 128 && wN % 256 == 0 && (wM / 256) * (wN / 256) >= 128) { p.edge = 1; p.wbm = 256; }
-  else if (wN % 256 == 128 && wM % 256 == 0 && (wM / 256) * (wN / 256) >= 128) { p.edge = 2; p.wbn = 256; }
-  auto cost = [](int bm, int bn) { return (bm == 256 && bn == 256) ? 1.0 : 0.55; };
-  const double slabs_w = wK / kBK, slabs_d = dK / kBK;
-  double work_w, longest;
-  if (p.edge == 0) {
-    work_w = static_cast<double>(wM / p.wbm) * (wN / p.wbn) * slabs_w * cost(p.wbm, p.wbn);
-    longest = slabs_w * cost(p.wbm, p.wbn);
-  } else {
-    const double body = static_cast<double>(wM / 256) * (wN / 256);
-    const double strip = p.edge == 1 ? wN / 256 : wM / 256;
-    work_w = (body + strip * 0.55) * slabs_w;
-    longest = slabs_w;
-  }
-  const double work_d = static_cast<double>(dM / p.dbm) * (dN / p.dbn) * slabs_d * cost(p.dbm, p.dbn);
-  const double ideal = (work_w + work_d) / 256.0;
-  // (a weight gradient with an edge strip is never cut: with half a round of whole tiles or
-  // more its tiles are not the ones the launch waits for)
-  const bool cut = p.edge == 0 && wK % (2 * kBK) == 0 && wK >= 2048 && longest > kPairCutFraction * ideal;
-  p.k_splits = cut ? 2 : 1;
-  const double last = ideal * 256.0 > 256.0 * (slabs_d > slabs_w ? slabs_d : slabs_w) ? (slabs_d < slabs_w ? slabs_d : slabs_w) * 0.5 : 0.0;
-  const double whole_longest = cut ? 0.5 * longest : longest;
-  p.us = 7.0 + 0.70 * (ideal + last > whole_longest ? ideal + last : whole_longest) + (cut ? 3.0 + 8.0 * wM * wN / 2.0e6 : 0.0);
-  return p;
-}
-
-template <int DBM, int DBN, int WBM, int WBN, int EBM, int EBN>
-hipError_t launch_pair(MfmaGemmArgs w, MfmaGemmArgs d, const PairPlan& plan, hipStream_t st) {
-  constexpr int dsum = DBM + DBN, wsum = WBM + WBN;
-  constexpr size_t smem = static_cast<size_t>(kStages) * (dsum > wsum ? dsum : wsum) * kBK * sizeof(bf16_t);
-  auto kern = gemm_mfma_pair_kernel<DBM, DBN, WBM, WBN, EBM, EBN>;
-  LYNX_RAISE_LDS_LIMIT(kern, smem);
-  // the edge strip: the same product restricted to the last 128 rows or columns of dW
-  MfmaGemmArgs e = w;
-  int n_e = 0;
-  if (EBM != 0) {
-    if (plan.edge == 1) {
-      const int body_rows = w.M - 128;
-      e.A = w.A + body_rows;  // A is MN-major: column m of the stored [K, M] array
-      e.C = w.C + static_cast<long long>(body_rows) * w.ldc;
-      e.M = 128;
-      w.M = body_rows;
-    } else {
-      const int body_cols = w.N - 128;
-      e.B = w.B + body_cols;
-      e.C = w.C + body_cols;
-      e.N = 128;
-      w.N = body_cols;
-    }
-    e.tiles_m = e.M / EBM; e.tiles_n = e.N / EBN;
-    n_e = e.tiles_m * e.tiles_n;
-  }
-  w.tiles_m = w.M / WBM; w.tiles_n = w.N / WBN;
-  d.tiles_m = d.M / DBM; d.tiles_n = d.N / DBN;
-  const int n_w = w.tiles_m * w.tiles_n * w.k_splits;
-  const int n_pad = (n_w + n_e + 7) & ~7;
-  hipLaunchKernelGGL(kern, dim3(n_pad + d.tiles_m * d.tiles_n), dim3(kThreads), smem, st, w, e, d, n_w, n_e);
-  if (w.k_splits > 1) {
-    const long long vecs = static_cast<long long>(w.M) * (w.N / 8);
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(static_cast<unsigned>((vecs + 255) / 256)), dim3(256), 0, st,
-                       w.partial, w.C, w.M, w.N, w.ldc, w.k_splits);
-  }
-  return hipGetLastError();
-}
-
 }  // namespace
-
-// Whole tiles, and large enough that the 256 x 256 tile is the right one (`choice`: the ragged plan).
-bool gemm_whole_takes(const GemmDesc& d, const RaggedChoice& choice) {
-  if (d.nz1 * d.nz2 != 1 || d.causal != kCausalNone || d.M % 256 || d.N % 128 || d.K % kBK) return false;
-  if (d.a_sk != 1 || d.b_sk != 1) return false;  // (forward products: gradients come in pairs)
-  // (a cut contraction is summed in another order: with and without the epilogue a shape is cut alike)
-  if (choice.scratch_bytes != 0) return false;
-  if (d.epi.kind == kEpiBiasDropoutAdd && d.K <= kDuoMaxK)
-    return choice.largest_tile || static_cast<long long>(d.M / 256) * (d.N / 128) >= 512;
-  return choice.largest_tile;
-}
-
-hipError_t gemm_whole(const GemmDesc& d, hipStream_t st) {
-  const MfmaGemmArgs a = make_args(d);
-  if (d.epi.kind == kEpiBiasDropoutAdd && d.K <= kDuoMaxK) return launch_duo(a, st);
-  return d.N % 256 ? launch_edge(a, st) : launch_whole(a, st);
-}
 
 // Attention: score-shaped (S = Q K^T, dPd = dC V^T and dS in its place) and contraction-restricted.
 hipError_t gemm_attention(const GemmDesc& d, hipStream_t st) {
@@ -630,56 +406,8 @@ hipError_t gemm_attention(const GemmDesc& d, hipStream_t st) {
     return gemm_ragged(d, nullptr, 0, st);
   }
   // (few tiles: the ragged kernels' 64 x 64 ones)
-  if (d.M % 128 || d.N % 128 || static_cast<long long>(d.M / 128) * (d.N / 128) * a.nz < 256) return gemm_ragged(d, nullptr, 0, st);
+  if (d.M % 128 || d.N % 128 || is_far(d) || static_cast<long long>(d.M / 128) * (d.N / 128) * a.nz < 256) return gemm_ragged(d, nullptr, 0, st);
   return d.a_sk == 1 ? launch_attn_product<true>(a, st) : launch_attn_product<false>(a, st);
-}
-
-// Estimated time of the whole-tile pair launch, < 0 where it does not apply.
-double gemm_whole_pair_us(const GemmDesc& dgrad, const GemmDesc& wgrad) {
-  for (const GemmDesc* g : {&dgrad, &wgrad})
-    if (g->M % 128 || g->N % 128 || g->K % kBK) return -1.0;
-  const PairPlan p = plan_pair(wgrad.M, wgrad.N, wgrad.K, dgrad.M, dgrad.N, dgrad.K);
-  return p.dbm != 256 || (p.wbm == 128 && p.wbn == 128) ? -1.0 : p.us;
-}
-
-size_t gemm_whole_pair_scratch_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad) {
-  const PairPlan p = plan_pair(wgrad.M, wgrad.N, wgrad.K, dgrad.M, dgrad.N, dgrad.K);
-  return p.k_splits > 1 ? static_cast<size_t>(p.k_splits) * wgrad.M * wgrad.N * sizeof(float) : 0;
-}
-
-hipError_t gemm_whole_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
-                          ColumnSums* sums, hipStream_t st) {
-  const MfmaGemmArgs d = make_args(dgrad);
-  MfmaGemmArgs w = make_args(wgrad);
-  const PairPlan p = plan_pair(w.M, w.N, w.K, d.M, d.N, d.K);
-  if (p.k_splits > 1) {
-    // The cut is part of the shape's fixed summation order: a scratch block that cannot hold
-    // the partial sums is an error, never a silent change of the gradient's bits.
-    if (scratch == nullptr || (reinterpret_cast<uintptr_t>(scratch) & 15) != 0 ||
-        scratch_bytes < static_cast<size_t>(p.k_splits) * w.M * w.N * sizeof(float))
-      return hipErrorInvalidValue;
-    w.k_splits = p.k_splits;
-    w.k_per = w.K / p.k_splits;
-    w.partial = scratch;
-  }
-  auto run = [&]() -> hipError_t {
-    if (p.dbn == 256) {
-      if (p.edge == 1) return launch_pair<256, 256, 256, 256, 128, 256>(w, d, p, st);
-      if (p.edge == 2) return launch_pair<256, 256, 256, 256, 256, 128>(w, d, p, st);
-      if (p.wbm == 256 && p.wbn == 256) return launch_pair<256, 256, 256, 256, 0, 0>(w, d, p, st);
-      if (p.wbm == 256) return launch_pair<256, 256, 256, 128, 0, 0>(w, d, p, st);
-      return launch_pair<256, 256, 128, 256, 0, 0>(w, d, p, st);
-    }
-    if (p.edge == 1) return launch_pair<256, 128, 256, 256, 128, 256>(w, d, p, st);
-    if (p.edge == 2) return launch_pair<256, 128, 256, 256, 256, 128>(w, d, p, st);
-    if (p.wbm == 256 && p.wbn == 256) return launch_pair<256, 128, 256, 256, 0, 0>(w, d, p, st);
-    if (p.wbm == 256) return launch_pair<256, 128, 256, 128, 0, 0>(w, d, p, st);
-    return launch_pair<256, 128, 128, 256, 0, 0>(w, d, p, st);
-  };
-  const hipError_t e = run();
-  if (e != hipSuccess) return e;
-  if (dgrad.epi.kind != kEpiGeluBwd) return hipSuccess;
-  return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, dgrad.M / 128, dgrad.N);  // a partial row per 128 rows
 }
 
 }  // namespace lynx

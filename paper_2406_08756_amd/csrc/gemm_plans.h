@@ -11,21 +11,14 @@ struct RaggedChoice {
   double us;
   size_t scratch_bytes;
   int colsum_rows;
-  bool largest_tile;  // 256 x 256 tiles, contraction whole: the whole-tile kernels do the same with fewer checks
 };
 RaggedChoice ragged_product(const GemmDesc& d);
 RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad);
 hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st);
 hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
                             ColumnSums* sums, hipStream_t st);
-// Products of whole, large tiles and the products of attention (gemm_mfma.hip).
-bool gemm_whole_takes(const GemmDesc& d, const RaggedChoice& choice);
-hipError_t gemm_whole(const GemmDesc& d, hipStream_t st);
+// Products of attention (gemm_mfma.hip).
 hipError_t gemm_attention(const GemmDesc& d, hipStream_t st);
-double gemm_whole_pair_us(const GemmDesc& dgrad, const GemmDesc& wgrad);
-size_t gemm_whole_pair_scratch_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad);
-hipError_t gemm_whole_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
-                           ColumnSums* sums, hipStream_t st);
 
 // fp32 storage (gemm_f32.hip).
 bool gemm_f32_supported(const GemmDesc& d);

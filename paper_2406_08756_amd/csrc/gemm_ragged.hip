@@ -1,7 +1,6 @@
-// bf16 matrix products whose dimensions are not whole tiles, or which the large tiles of
-// gemm_mfma.hip would leave most of the chip idle: tiles from 256 x 256 down to 64 x 64, each able
-// to overhang the operands, and contractions cut into ranges whose fp32 partial sums a second
-// launch adds in a fixed order.  plan_product / plan_pair_ragged choose by a cost model.
+// bf16 products of linear layers, any size: tiles from 256 x 256 down to 64 x 64, each able to overhang the
+// operands, and contractions cut into ranges whose fp32 partial sums a second launch adds in a fixed order.
+// plan_product / plan_pair_ragged choose by a cost model.
 #include <mutex>
 
 #include "dropout_host.h"
@@ -10,22 +9,28 @@
 namespace lynx {
 namespace {
 
-// The tiles.  BK and ring depth per tile: one barrier per 64 contraction indices pays where a slab is
-// so little work that the barrier and the LDS round trip dominate it (64 x 64, K = 4096, one
-// workgroup: 26.8 us with slabs of 32, 19.0 with 64) and where both operands are K-major, whose rows
+// The tiles.  The two largest: eight wavefronts in two groups that take turns (gemm_tile.h).  256 x 128 reads 1.5 times
+// as much per operation but gives twice the workgroups: 8192 x 1024 x 4096 1086 TFLOP/s against 876 with
+// 256 x 256 (128 workgroups) and 980 with 128 x 128; before these had this form 641, 796 and 980.
+// The others: four wavefronts, two workgroups per compute unit.  BK and ring depth: one barrier per 64 contraction
+// indices pays where a slab is so little work that the barrier and the LDS round trip dominate it (64 x 64, K = 4096,
+// one workgroup: 26.8 us with slabs of 32, 19.0 with 64) and where both operands are K-major, whose rows
 // then arrive as whole 128-byte lines (128 x 128 at 4096^3: 182 -> 151 us); with an MN-major operand
-// the deeper ring of slabs of 32 is the faster one for the large tiles (4096^3: 148 against 150, 146
-// against 153).  Eight wavefronts on the 256 x 256 tile: two per SIMD cover each other's waits
-// (8192^3: forward 999 -> 908 us, input gradient 895 -> 892).
+// the deeper ring of slabs of 32 is the faster one (128 x 128 at 4096^3: 148 against 150, 146 against 153).
 enum RaggedTile { kT256 = 0, kT256x128, kT128, kT128x64, kT64, kNumRaggedTiles };
 template <int TILE, bool BOTH_KMAJOR> struct TileShape;
-template <bool B> struct TileShape<kT256, B> { static constexpr int BM = 256, BN = 256, BK = 32, S = 4, share = 1, waves = 8; };
-template <bool B> struct TileShape<kT256x128, B> { static constexpr int BM = 256, BN = 128, BK = 32, S = 3, share = 2, waves = 4; };
+template <bool B> struct TileShape<kT256, B> { static constexpr int BM = 256, BN = 256, BK = 64, S = kSlots, share = 1, waves = 8; };
+template <bool B> struct TileShape<kT256x128, B> { static constexpr int BM = 256, BN = 128, BK = 64, S = 3, share = 1, waves = 8; };
 template <> struct TileShape<kT128, true> { static constexpr int BM = 128, BN = 128, BK = 64, S = 2, share = 2, waves = 4; };
 template <> struct TileShape<kT128, false> { static constexpr int BM = 128, BN = 128, BK = 32, S = 4, share = 2, waves = 4; };
 template <bool B> struct TileShape<kT128x64, B> { static constexpr int BM = 128, BN = 64, BK = 64, S = 3, share = 2, waves = 4; };
 template <bool B> struct TileShape<kT64, B> { static constexpr int BM = 64, BN = 64, BK = 64, S = 4, share = 2, waves = 4; };
 
+// LDS: S slabs of both operands, or (256 x 256) S slots of one slab each
+template <typename T> constexpr size_t tile_lds =
+    static_cast<size_t>(T::S) * (T::BN == 256 ? T::BM : T::BM + T::BN) * T::BK * sizeof(bf16_t);
+// rows of a wavefront's part of a tile: one row of the GeLU epilogue's column partials
+constexpr int kTileWaveRows[kNumRaggedTiles] = {128, 64, 64, 64, 32};
 template <int TILE> constexpr int tile_threads = TileShape<TILE, false>::waves * kWave;
 template <int TILE> constexpr int tile_waves_per_simd = TileShape<TILE, false>::share * TileShape<TILE, false>::waves / 4;
 
@@ -33,17 +38,16 @@ template <int TILE> constexpr int tile_waves_per_simd = TileShape<TILE, false>::
 // compute unit; `share` on every unit (then for all of them together).  `fixed`: what a round of
 // workgroups takes beside its contraction.
 //
-// The numbers are fitted to measurements, for forward products and for gradient pairs each: 169 products
-// and 178 pairs of layers with 64 to 16384 tokens and widths from 40 to 22000, every tile and every cut
-// of each timed, the constants chosen so that the tile and cut with the least predicted time lose as
-// little as possible against the fastest: 1.3 % and 2.8 % on average.  None of the products had an epilogue: the
-// store pass with bias, dropout and residual is not in the model (984 tokens of h 3016, 128 x 64 tiles, two projections and
-// one FC2: 12, 12 and 19.5 us predicted, 20.5 measured on average); for those the choice is that of the plain product.
+// The numbers are fitted to measurements, for forward products and for gradient pairs each: 589 products
+// and 582 pairs of layers with 64 to 16384 tokens and widths from 40 to 22000, every tile and nearly every cut
+// of each timed on operands in rotation, the constants chosen so that the tile and cut with the least predicted time
+// lose as little as possible against the fastest: 0.8 % and 2.0 % on average.  None of the products had an epilogue: the
+// store pass with bias, dropout and residual is not in the model; for those the choice is that of the plain product.
 struct TileCost {
   int bm, bn, share;
   double alone, one_each, full;
   double fixed;
-  // us per 32 indices of a round of n workgroups
+  // us per 32 indices of a round of n workgroups (n <= kUnits * share)
   double slab(double n) const {
     if (n <= kUnits) return alone + (one_each - alone) * n / kUnits;
     return one_each + (full - one_each) * (n - kUnits) / (kUnits * (share - 1));
@@ -51,13 +55,13 @@ struct TileCost {
   static constexpr int kUnits = 256;  // compute units
 };
 constexpr TileCost kProductCost[kNumRaggedTiles] = {
-    {256, 256, 1, 0.594, 0.726, 0.726, 7.4}, {256, 128, 2, 0.371, 0.832, 1.052, 4.8}, {128, 128, 2, 0.232, 0.416, 0.462, 6.4},
-    {128, 64, 2, 0.264, 0.264, 0.315, 5.3}, {64, 64, 2, 0.118, 0.129, 0.305, 3.7}};
+    {256, 256, 1, 0.469, 0.603, 0.603, 6.9}, {256, 128, 1, 0.289, 0.381, 0.381, 5.6}, {128, 128, 2, 0.262, 0.402, 0.477, 4.0},
+    {128, 64, 2, 0.090, 0.263, 0.290, 4.1}, {64, 64, 2, 0.095, 0.101, 0.616, 4.0}};
 constexpr TileCost kPairCost[kNumRaggedTiles] = {
-    {256, 256, 1, 0.640, 0.698, 0.698, 4.6}, {256, 128, 2, 0.370, 0.508, 1.289, 6.6}, {128, 128, 2, 0.284, 0.292, 0.520, 4.7},
-    {128, 64, 2, 0.172, 0.228, 0.538, 4.1}, {64, 64, 2, 0.140, 0.149, 0.246, 3.1}};
+    {256, 256, 1, 0.609, 0.611, 0.611, 4.4}, {256, 128, 1, 0.124, 0.416, 0.416, 8.3}, {128, 128, 2, 0.247, 0.253, 0.478, 4.4},
+    {128, 64, 2, 0.172, 0.228, 0.538, 4.1}, {64, 64, 2, 0.112, 0.081, 0.219, 3.2}};
 // the launch that adds the partial sums of a cut contraction (product / pair)
-constexpr double kFinishFixed[2] = {3.6, 3.0}, kFinishBytesPerUs[2] = {4.2e6, 2.0e6};
+constexpr double kFinishFixed[2] = {3.6, 2.7}, kFinishBytesPerUs[2] = {3.4e6, 1.9e6};
 
 constexpr int kMaxBK = 64;   // K ranges of a cut contraction are whole slabs of every tile
 constexpr int kCuts[] = {1, 2, 3, 4, 6, 8, 12, 16};   // K ranges considered
@@ -89,7 +93,8 @@ struct ProductPlan {
 
 ProductPlan search_product(int M, int N, int K) {
   ProductPlan best{kT64, range_of(K, 1), 1e30};
-  for (int t = 0; t < kNumRaggedTiles; ++t)
+  const bool far = K >= kFarStride;  // (both operands K-major)
+  for (int t = far ? kT64 : 0; t < kNumRaggedTiles; ++t)
     for (int want : kCuts) {
       if (want > 1 && K < kMinRange * want) break;
       const int k_per = range_of(K, want);
@@ -127,19 +132,19 @@ ProductPlan plan_product(const GemmDesc& d) {
 }
 
 // ---- kernels ------------------------------------------------------------------
-template <bool AK, bool BK_, int TILE>
+template <bool AK, bool BK_, int TILE, bool FAR>
 __global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
 gemm_ragged_kernel(MfmaGemmArgs g) {
   using T = TileShape<TILE, AK && BK_>;
-  if (g.k_splits > 1) gemm_tile<AK, BK_, T::BM, T::BN, true, T::S, true, T::BK, T::waves>(g, blockIdx.x, blockIdx.y);
-  else gemm_tile<AK, BK_, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(g, blockIdx.x, blockIdx.y);
+  if (g.k_splits > 1) gemm_tile<AK, BK_, T::BM, T::BN, true, T::S, true, T::BK, T::waves, false, FAR>(g, blockIdx.x, blockIdx.y);
+  else gemm_tile<AK, BK_, T::BM, T::BN, false, T::S, true, T::BK, T::waves, false, FAR>(g, blockIdx.x, blockIdx.y);
 }
 
 // Both products of a linear layer's backward in one launch: the first n_first workgroups belong to the one
 // whose tiles take longer, the others behind them fill what they leave idle.  (Weight gradient first
 // throughout: 237 us for 4000 tokens, 1600 inputs and 6400 outputs, whose input gradient has the longer
 // contraction; 198 this way.)
-template <int TILE>
+template <int TILE, bool FAR>
 __global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
 gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int dgrad_first) {
   using T = TileShape<TILE, false>;
@@ -149,19 +154,19 @@ gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int
   if (x >= n_first && x < n_pad) return;
   const int tile = x < n_first ? x : x - n_pad;
   if ((x < n_first) != (dgrad_first != 0)) {
-    if (wgrad.k_splits > 1) gemm_tile<false, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves>(wgrad, tile, 0);
-    else gemm_tile<false, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(wgrad, tile, 0);
+    if (wgrad.k_splits > 1) gemm_tile<false, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves, false, FAR>(wgrad, tile, 0);
+    else gemm_tile<false, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves, false, FAR>(wgrad, tile, 0);
   } else {
-    if (dgrad.k_splits > 1) gemm_tile<true, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves>(dgrad, tile, 0);
-    else gemm_tile<true, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves>(dgrad, tile, 0);
+    if (dgrad.k_splits > 1) gemm_tile<true, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
+    else gemm_tile<true, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
   }
 }
 
-template <bool AK, bool BK_, int TILE>
+template <bool AK, bool BK_, int TILE, bool FAR = false>
 hipError_t launch_ragged(MfmaGemmArgs a, hipStream_t st) {
   using T = TileShape<TILE, AK && BK_>;
-  constexpr size_t smem = static_cast<size_t>(T::S) * (T::BM + T::BN) * T::BK * sizeof(bf16_t);
-  auto kern = gemm_ragged_kernel<AK, BK_, TILE>;
+  constexpr size_t smem = tile_lds<T>;
+  auto kern = gemm_ragged_kernel<AK, BK_, TILE, FAR>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   a.tiles_m = ceil_div(a.M, T::BM);
   a.tiles_n = ceil_div(a.N, T::BN);
@@ -172,7 +177,8 @@ hipError_t launch_ragged(MfmaGemmArgs a, hipStream_t st) {
 }
 
 template <bool AK, bool BK_>
-hipError_t launch_tile(int tile, const MfmaGemmArgs& a, hipStream_t st) {
+hipError_t launch_tile(int tile, bool far, const MfmaGemmArgs& a, hipStream_t st) {
+  if (far) return launch_ragged<AK, BK_, kT64, true>(a, st);
   if constexpr (AK) {  // (both MN-major: attention, in tiles of at most 128 x 128)
     if (tile == kT256) return launch_ragged<AK, BK_, kT256>(a, st);
     if (tile == kT256x128) return launch_ragged<AK, BK_, kT256x128>(a, st);
@@ -189,18 +195,19 @@ hipError_t launch_tile(int tile, const MfmaGemmArgs& a, hipStream_t st) {
 // Latency of the whole contraction on a part of the chip bounds it; it is for workspaces that have no room for the
 // cut form.  128 tokens of h 5120 (QKV of width 1920, FC1 of 2560): 29 us each, cut 14 and 16; a step of that layer
 // 419 us against 268, of 512 tokens of h 3072 437 against 411, with both gradients of a layer as launches of their own.
-template <bool AK, bool BK_>
+template <bool AK, bool BK_, bool FAR>
 __global__ void __launch_bounds__((tile_threads<kT64>), (tile_waves_per_simd<kT64>)) gemm_serial_kernel(MfmaGemmArgs g) {
   using T = TileShape<kT64, AK && BK_>;
-  gemm_tile<AK, BK_, T::BM, T::BN, false, T::S, true, T::BK, T::waves, true>(g, blockIdx.x, 0);
+  gemm_tile<AK, BK_, T::BM, T::BN, false, T::S, true, T::BK, T::waves, true, FAR>(g, blockIdx.x, 0);
 }
 
-template <bool AK, bool BK_>
-hipError_t launch_serial(MfmaGemmArgs a, hipStream_t st) {
+template <bool AK, bool BK_, bool FAR = false>
+hipError_t launch_serial(bool far, MfmaGemmArgs a, hipStream_t st) {
+  if (far && !FAR) return launch_serial<AK, BK_, true>(far, a, st);
   using T = TileShape<kT64, AK && BK_>;
   static_assert(kMaxBK % T::BK == 0, "ranges are whole slabs");
-  constexpr size_t smem = static_cast<size_t>(T::S) * (T::BM + T::BN) * T::BK * sizeof(bf16_t);
-  auto kern = gemm_serial_kernel<AK, BK_>;
+  constexpr size_t smem = tile_lds<T>;
+  auto kern = gemm_serial_kernel<AK, BK_, FAR>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   a.tiles_m = ceil_div(a.M, T::BM);
   a.tiles_n = ceil_div(a.N, T::BN);
@@ -208,11 +215,11 @@ hipError_t launch_serial(MfmaGemmArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int TILE>
+template <int TILE, bool FAR = false>
 hipError_t launch_ragged_pair(MfmaGemmArgs w, MfmaGemmArgs d, hipStream_t st) {
   using T = TileShape<TILE, false>;
-  constexpr size_t smem = static_cast<size_t>(T::S) * (T::BM + T::BN) * T::BK * sizeof(bf16_t);
-  auto kern = gemm_ragged_pair_kernel<TILE>;
+  constexpr size_t smem = tile_lds<T>;
+  auto kern = gemm_ragged_pair_kernel<TILE, FAR>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   for (MfmaGemmArgs* g : {&w, &d}) {
     g->tiles_m = ceil_div(g->M, T::BM);
@@ -293,9 +300,9 @@ double pair_cost(const TileCost& t, const GemmDesc& w, int w_per, const GemmDesc
   const double n = nw + nd, round = static_cast<double>(TileCost::kUnits) * t.share;
   const double rate = t.slab(n < round ? n : round);            // of a round as full as this launch's
   const double at_once = n < round ? n : round;
-  const double even = (nw * sw + nd * sd) * rate / at_once + (n > round ? 0.49 * (sw < sd ? sw : sd) * rate : 0.0);
-  const double longest = (sw > sd ? sw : sd) * (n <= round ? rate : 0.44 * t.one_each + 0.56 * t.full);
-  double us = t.fixed * (1.0 + 0.54 * n / round) + (longest > even ? longest : even);
+  const double even = (nw * sw + nd * sd) * rate / at_once + (n > round ? 0.42 * (sw < sd ? sw : sd) * rate : 0.0);
+  const double longest = (sw > sd ? sw : sd) * (n <= round ? rate : 0.86 * t.one_each + 0.14 * t.full);
+  double us = t.fixed * (1.0 + 0.48 * n / round) + (longest > even ? longest : even);
   const double bytes = static_cast<double>(partial_bytes(w.M, w.N, ws) + partial_bytes(d.M, d.N, ds));
   if (bytes > 0.0) us += kFinishFixed[1] + bytes / kFinishBytesPerUs[1];
   return us;
@@ -305,17 +312,29 @@ RaggedPairPlan search_pair(const GemmDesc& w, const GemmDesc& d) {
   // (the GeLU epilogue's column sums are formed tile by tile, so such an input gradient is not cut)
   const bool cut_d = d.epi.kind == kEpiNone;
   RaggedPairPlan best{kT64, range_of(w.K, 1), range_of(d.K, 1), 1e30};
-  for (int t = 0; t < kNumRaggedTiles; ++t) {
-    if (t == kT128x64) continue;   // (no pair kernel of this tile)
-    for (int cw : kCuts) {
-      if (cw > 1 && w.K < kMinRange * cw) break;
-      for (int cd : kCuts) {
-        if (cd > 1 && (!cut_d || d.K < kMinRange * cd)) break;
-        const double us = pair_cost(kPairCost[t], w, range_of(w.K, cw), d, range_of(d.K, cd));
-        if (us < best.us) best = {t, range_of(w.K, cw), range_of(d.K, cd), us};
+  const bool far = w.M >= kFarStride || w.N >= kFarStride || d.N >= kFarStride || d.K >= kFarStride;  // the row strides
+  // Partial sums take at most three times what the tokens' side of both products does, or 8 MB: more of them named
+  // workspaces up to 1.7 times as large, and is not faster (582 pairs as above: 2.0 % over the fastest either way).
+  const size_t tokens_bytes = 2 * static_cast<size_t>(d.M) * (static_cast<size_t>(d.N) + d.K);
+  const size_t most_bytes = 3 * tokens_bytes > (8u << 20) ? 3 * tokens_bytes : (8u << 20);
+  int per[2][sizeof(kCuts) / sizeof(kCuts[0])], n[2] = {0, 0};  // the distinct ranges of the two contractions
+  for (int which = 0; which < 2; ++which)
+    for (int cut : kCuts) {
+      const int K = which == 0 ? w.K : d.K;
+      if (cut > 1 && (K < kMinRange * cut || (which == 1 && !cut_d))) break;
+      const int range = range_of(K, cut);
+      if (n[which] == 0 || range != per[which][n[which] - 1]) per[which][n[which]++] = range;
+    }
+  for (int iw = 0; iw < n[0]; ++iw)
+    for (int id = 0; id < n[1]; ++id) {
+      const int ws = ceil_div(w.K, per[0][iw]), ds = ceil_div(d.K, per[1][id]);
+      if (partial_bytes(w.M, w.N, ws) + partial_bytes(d.M, d.N, ds) > most_bytes) continue;
+      for (int t = far ? kT64 : 0; t < kNumRaggedTiles; ++t) {
+        if (t == kT128x64) continue;   // (no pair kernel of this tile)
+        const double us = pair_cost(kPairCost[t], w, per[0][iw], d, per[1][id]);
+        if (us < best.us) best = {t, per[0][iw], per[1][id], us};
       }
     }
-  }
   return best;
 }
 
@@ -328,12 +347,12 @@ RaggedPairPlan plan_pair_ragged(const GemmDesc& w, const GemmDesc& d) {
 
 RaggedChoice ragged_product(const GemmDesc& d) {
   const ProductPlan p = plan_product(d);
-  return {p.us, partial_bytes(d.M, d.N, p.splits(d.K)), 0, p.tile == kT256 && p.splits(d.K) == 1};
+  return {p.us, partial_bytes(d.M, d.N, p.splits(d.K)), 0};
 }
 
 hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st) {
   MfmaGemmArgs a = make_args(d);
-  const bool a_k = d.a_sk == 1, b_k = d.b_sk == 1;
+  const bool a_k = d.a_sk == 1, b_k = d.b_sk == 1, far = is_far(d);
   int tile;
   if (d.causal == kCausalNone && a.nz == 1) {
     const ProductPlan p = plan_product(d);
@@ -341,7 +360,7 @@ hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, 
     if (p.splits(d.K) > 1 && d.serial) {
       a.k_per = p.k_per;
       if (!a_k || !b_k) return hipErrorInvalidValue;  // (gradients come in pairs)
-      return launch_serial<true, true>(a, st);
+      return launch_serial<true, true>(far, a, st);
     }
     if (p.splits(d.K) > 1) {
       // the cut is part of the shape's summation order: no silent change where scratch is short
@@ -359,9 +378,9 @@ hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, 
     if (static_cast<long long>(ceil_div(d.M, t.bm)) * ceil_div(d.N, t.bn) * a.nz < TileCost::kUnits) tile = kT64;
   }
   hipError_t e;
-  if (a_k && b_k) e = launch_tile<true, true>(tile, a, st);
-  else if (a_k) e = launch_tile<true, false>(tile, a, st);
-  else if (!b_k) e = launch_tile<false, false>(tile, a, st);
+  if (a_k && b_k) e = launch_tile<true, true>(tile, far, a, st);
+  else if (a_k) e = launch_tile<true, false>(tile, far, a, st);
+  else if (!b_k) e = launch_tile<false, false>(tile, far, a, st);
   else return hipErrorInvalidValue;
   if (e != hipSuccess || a.k_splits == 1) return e;
   return launch_finish(&a, nullptr, st);
@@ -371,7 +390,7 @@ RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad) {
   const RaggedPairPlan p = plan_pair_ragged(wgrad, dgrad);
   const int ws = ceil_div(wgrad.K, p.w_per), ds = ceil_div(dgrad.K, p.d_per);
   return {p.us, partial_bytes(wgrad.M, wgrad.N, ws) + partial_bytes(dgrad.M, dgrad.N, ds),
-          ceil_div(dgrad.M, kPairCost[p.tile].bm / 2), p.tile == kT256 && ds == 1};
+          ceil_div(dgrad.M, kTileWaveRows[p.tile])};
 }
 
 hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
@@ -383,14 +402,16 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   d.k_splits = ceil_div(d.K, p.d_per);
   d.k_per = p.d_per;
   const size_t w_bytes = partial_bytes(w.M, w.N, w.k_splits), d_bytes = partial_bytes(d.M, d.N, d.k_splits);
-  const bool serial = dgrad.serial && w_bytes + d_bytes > 0;
+  const bool serial = dgrad.serial && w_bytes + d_bytes > 0, far = is_far(dgrad) || is_far(wgrad);
   if (w_bytes + d_bytes > 0 && !serial && (scratch == nullptr || scratch_bytes < w_bytes + d_bytes)) return hipErrorInvalidValue;
   hipError_t e;
   if (serial) {
-    // (the GeLU epilogue's column partials are a row per half tile: the plan's tile, whose contraction is whole)
+    // (the product that is not cut in the plan's tile: the GeLU epilogue's column partials depend on it)
+    const bool w_cut = w.k_splits > 1, d_cut = d.k_splits > 1;
     w.k_splits = d.k_splits = 1;
-    e = launch_serial<false, false>(w, st);
-    if (e == hipSuccess) e = dgrad.epi.kind == kEpiGeluBwd ? launch_tile<true, false>(p.tile, d, st) : launch_serial<true, false>(d, st);
+    const int w_tile = p.tile == kT256 || p.tile == kT256x128 ? kT128 : p.tile;  // (no larger one for two MN-major operands)
+    e = w_cut ? launch_serial<false, false>(far, w, st) : launch_tile<false, false>(w_tile, far, w, st);
+    if (e == hipSuccess) e = d_cut ? launch_serial<true, false>(far, d, st) : launch_tile<true, false>(p.tile, far, d, st);
   } else {
     w.partial = scratch;
     d.partial = scratch + w_bytes / sizeof(float);
@@ -398,7 +419,7 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
       case kT256: e = launch_ragged_pair<kT256>(w, d, st); break;
       case kT256x128: e = launch_ragged_pair<kT256x128>(w, d, st); break;
       case kT128: e = launch_ragged_pair<kT128>(w, d, st); break;
-      default: e = launch_ragged_pair<kT64>(w, d, st); break;
+      default: e = far ? launch_ragged_pair<kT64, true>(w, d, st) : launch_ragged_pair<kT64>(w, d, st); break;
     }
   }
   if (e != hipSuccess) return e;
@@ -406,7 +427,7 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   else if (w.k_splits > 1) e = launch_finish(&w, nullptr, st);
   else if (d.k_splits > 1) e = launch_finish(&d, nullptr, st);
   if (e != hipSuccess || dgrad.epi.kind != kEpiGeluBwd) return e;
-  return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, ceil_div(dgrad.M, kPairCost[p.tile].bm / 2), dgrad.N);
+  return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, ceil_div(dgrad.M, kTileWaveRows[p.tile]), dgrad.N);
 }
 
 }  // namespace lynx

@@ -7,12 +7,10 @@
 // "MN-major" (the contraction index is the row index: the weight in an input
 // gradient, both operands in a weight gradient).
 //
-// Design.  One workgroup of 4 wavefronts (one per SIMD, up to 512 registers
-// each) owns a BM x BN output tile (256 x 256 when it divides); each
-// wavefront owns a quarter of it, so every fragment read from LDS feeds four
-// MFMAs.  K is walked in slabs of 32.  Slabs travel global memory -> LDS
-// directly (global_load_lds_dwordx4, no staging registers) through a ring of
-// four LDS stages: while one slab is multiplied, three more are in flight,
+// Design.  One workgroup of 8 wavefronts (256 rows per tile; one workgroup per compute unit, see the loop) or of 4 (two
+// workgroups per unit) owns a BM x BN output tile, each wavefront a block of it, so every fragment read from LDS feeds
+// two to four MFMAs.  K is walked in slabs of 32 or 64.  Slabs travel global memory -> LDS directly (buffer_load_dwordx4
+// ... lds, no staging registers and no address arithmetic) through a ring that keeps one to three of them in flight,
 // which is what it takes to cover L2 latency at this MFMA rate.  Bank
 // conflicts are avoided by permuting 16-byte chunks, applied on the global
 // address side since a direct load writes lane i to LDS offset 16 i:
@@ -32,7 +30,11 @@
 namespace lynx {
 namespace {
 
-constexpr int kStages = 4;     // LDS ring depth
+constexpr int kStages = 4;     // LDS ring depth in slabs
+constexpr int kSlots = 5;      // ... of the 256 x 256 tile of eight wavefronts, in pieces of 32 KB (all of the LDS)
+
+// From this row stride (elements) on, a load's offset from the corner of its tile of up to 256 rows may take more than 32 bits.
+constexpr long long kFarStride = 1ll << 22;
 
 struct MfmaGemmArgs {
   const bf16_t* A; long long lda;
@@ -80,11 +82,13 @@ __device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
 // SERIAL: the K ranges (k_per indices, whole slabs) of a cut contraction one after the other: each is summed
 // from zero and added to the sum of those before it, which is what SPLITK and the launch that adds its partial
 // sums do, bit for bit, with registers in the place of the partial sums.
+//
+// FAR: a row stride of kFarStride elements or more.
 template <bool A_KMAJOR, bool B_KMAJOR, int BM, int BN, bool SPLITK = false, int STAGES = kStages, bool RAGGED = false,
-          int BK = kBK, int WAVES = kWaves, bool SERIAL = false>
+          int BK = kBK, int WAVES = kWaves, bool SERIAL = false, bool FAR = false>
 __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block_x, const int block_z) {
-  constexpr int kWavesN = WAVES / 2;
-  constexpr int WM = BM / 2, WN = BN / kWavesN;  // wavefronts in a grid of 2 x kWavesN
+  constexpr int kWavesN = WAVES == 8 ? BN / 64 : 2;
+  constexpr int WM = BM * kWavesN / WAVES, WN = BN / kWavesN;  // wavefronts in a grid of WAVES / kWavesN x kWavesN
   constexpr int TM = WM / 32, TN = WN / 32;
   using SA = Slab<BM, A_KMAJOR, BK, WAVES>;
   using SB = Slab<BN, B_KMAJOR, BK, WAVES>;
@@ -147,51 +151,62 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm0 = wave / kWavesN * WM, wn0 = wave % kWavesN * WN;
 
-  // this lane's global source of each direct load, at slab 0
-  const bf16_t* ga[SA::kLoadsPerWave];
-  const bf16_t* gb[SB::kLoadsPerWave];
+  // Where this lane's direct loads of slab 0 start: bytes from the corner of the operand's tile.  (FAR: more than 32
+  // bits of them, see kFarStride.)
+  using Offset = std::conditional_t<FAR, long long, uint32_t>;
+  Offset oa[SA::kLoadsPerWave], ob[SB::kLoadsPerWave];
 #pragma unroll
   for (int j = 0; j < SA::kLoadsPerWave; ++j) {
-    long long mn = m0 + SA::lane_mn(wave, j, lane);
-    const long long k = k_begin + SA::lane_k(wave, j, lane);
-    if (RAGGED) mn = min(mn, static_cast<long long>(g.M - (A_KMAJOR ? 1 : 8)));
-    ga[j] = Abase + (A_KMAJOR ? mn * g.lda + k : k * g.lda + mn);
+    int mn = SA::lane_mn(wave, j, lane);
+    if (RAGGED) mn = min(mn, g.M - m0 - (A_KMAJOR ? 1 : 8));
+    const long long k = SA::lane_k(wave, j, lane);
+    oa[j] = static_cast<Offset>(2 * (A_KMAJOR ? mn * g.lda + k : k * g.lda + mn));
   }
 #pragma unroll
   for (int j = 0; j < SB::kLoadsPerWave; ++j) {
-    long long mn = n0 + SB::lane_mn(wave, j, lane);
-    const long long k = k_begin + SB::lane_k(wave, j, lane);
-    if (RAGGED) mn = min(mn, static_cast<long long>(g.N - (B_KMAJOR ? 1 : 8)));
-    gb[j] = Bbase + (B_KMAJOR ? mn * g.ldb + k : k * g.ldb + mn);
+    int mn = SB::lane_mn(wave, j, lane);
+    if (RAGGED) mn = min(mn, g.N - n0 - (B_KMAJOR ? 1 : 8));
+    const long long k = SB::lane_k(wave, j, lane);
+    ob[j] = static_cast<Offset>(2 * (B_KMAJOR ? mn * g.ldb + k : k * g.ldb + mn));
   }
-  const long long a_step = A_KMAJOR ? BK : BK * g.lda;  // elements per slab
-  const long long b_step = B_KMAJOR ? BK : BK * g.ldb;
+  const char* const corner_a = reinterpret_cast<const char*>(Abase + (A_KMAJOR ? m0 * g.lda + k_begin : k_begin * g.lda + m0));
+  const char* const corner_b = reinterpret_cast<const char*>(Bbase + (B_KMAJOR ? n0 * g.ldb + k_begin : k_begin * g.ldb + n0));
+  const long long a_step = 2 * (A_KMAJOR ? BK : BK * g.lda);  // bytes per slab
+  const long long b_step = 2 * (B_KMAJOR ? BK : BK * g.ldb);
 
   const int nk = RAGGED ? (k_end - k_begin + BK - 1) / BK : (k_end - k_begin) / BK;
   // the slab that reaches beyond the contraction range (none: -1), and how many of its k exist
   const int k_rem = (k_end - k_begin) % BK;
   const int tail = RAGGED && k_rem != 0 ? nk - 1 : -1;
 
-  // j-th direct load of slab kt (A pieces first, then B) -> ring stage kt % STAGES
-  auto issue_load = [&](int kt, int j) {
-    bf16_t* sa = smem + (kt % STAGES) * kStageElems;
-    if (j < SA::kLoadsPerWave) {
-      const bf16_t* from = ga[j] + kt * a_step;
-      if (RAGGED && kt == tail && SA::lane_k(wave, j, lane) >= k_rem) from = reinterpret_cast<const bf16_t*>(&kZeroChunk);
-      __builtin_amdgcn_global_load_lds((global_void_ptr)(from),
-                                       (lds_void_ptr)(sa + SA::lds_offset(wave, j)), 16, 0, 0);
+  // Direct load j of an operand's slab kt to `to` (wavefront-uniform).  Steady: the slab is whole, and the load is a
+  // buffer load with the slab's corner in scalar registers, so that no vector instruction goes with it.  (Pointers
+  // of 64 bits, advanced in vector registers: 1206 TFLOP/s in the 256 x 256 tile where this gets 1255, and 1083 with
+  // the tail's condition on every load.)
+  auto load = [&](auto of_b_tag, auto steady_tag, int kt, int j, bf16_t* to) {
+    constexpr bool of_b = decltype(of_b_tag)::value;
+    const char* corner = of_b ? corner_b + kt * b_step : corner_a + kt * a_step;
+    const Offset offset = of_b ? ob[j] : oa[j];
+    if constexpr (decltype(steady_tag)::value && !FAR) {
+      buffer_load_to_lds(corner, offset, to);
     } else {
-      const int jb = j - SA::kLoadsPerWave;
-      const bf16_t* from = gb[jb] + kt * b_step;
-      if (RAGGED && kt == tail && SB::lane_k(wave, jb, lane) >= k_rem) from = reinterpret_cast<const bf16_t*>(&kZeroChunk);
-      __builtin_amdgcn_global_load_lds((global_void_ptr)(from),
-                                       (lds_void_ptr)(sa + SA::kElems + SB::lds_offset(wave, jb)), 16,
-                                       0, 0);
+      const char* from = corner + offset;
+      if (RAGGED && kt == tail && (of_b ? SB::lane_k(wave, j, lane) : SA::lane_k(wave, j, lane)) >= k_rem)
+        from = reinterpret_cast<const char*>(&kZeroChunk);
+      __builtin_amdgcn_global_load_lds((global_void_ptr)(from), (lds_void_ptr)(to), 16, 0, 0);
     }
+  };
+  constexpr std::integral_constant<bool, false> kA{}, kAny{};
+  constexpr std::integral_constant<bool, true> kB{};
+  // j-th direct load of slab kt (A's first, then B's) -> ring stage kt % STAGES
+  auto issue_load = [&](auto steady_tag, int kt, int j) {
+    bf16_t* sa = smem + (kt % STAGES) * kStageElems;
+    if (j < SA::kLoadsPerWave) load(kA, steady_tag, kt, j, sa + SA::lds_offset(wave, j));
+    else load(kB, steady_tag, kt, j - SA::kLoadsPerWave, sa + SA::kElems + SB::lds_offset(wave, j - SA::kLoadsPerWave));
   };
   auto issue_slab = [&](int kt) {
 #pragma unroll
-    for (int j = 0; j < kLoads; ++j) issue_load(kt, j);
+    for (int j = 0; j < kLoads; ++j) issue_load(kAny, kt, j);
   };
 
   floatx16_t acc[TN][TM];
@@ -202,6 +217,166 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
+  if constexpr (WAVES == 8) {
+    // Two groups of four wavefronts, one of each per SIMD, take turns: while one multiplies a chunk of 32
+    // contraction indices (2 TM TN matrix instructions back to back), the other reads its fragments of the next
+    // chunk, and a barrier swaps the roles.  Slabs of 64 indices, whole 128-byte lines of a K-major operand, so two
+    // chunks and four phases per slab; every compute phase issues a share of the loads, spread between its matrix
+    // instructions (all of a slab's loads in one compute phase: 1104 TFLOP/s where this gets 1255, in a phase
+    // that reads fragments 1091).  What bounds it: the clock that the power limit allows, then the issue of the loads.
+    //
+    // 256 x 256: a ring of five 32 KB slots that A and B slabs take in turn (piece 2 k: A's slab k, piece 2 k + 1:
+    // B's); while slab k is multiplied, A(k + 1), B(k + 1) and A(k + 2) are in flight or arriving.  Against eight
+    // wavefronts in step on slabs of 32 (ring of four; TFLOP/s, random operands in rotation so that none is cached):
+    // 16384 x 2560 x 5120, both K-major 1014 -> 1255; 8192 x 2048 x 8192 1137 -> 1365, with an MN-major B 1252 ->
+    // 1365, both MN-major 1252 -> 1364; all-zero operands 1740 -> 2091, 1907 -> 2179, 1827 -> 2153.
+    // 256 x 128: whole slabs in a ring of three.
+    static_assert(BM == 256 && (BN == 256 || BN == 128) && BK == 64 && !SERIAL, "tiles of eight wavefronts");
+    constexpr bool kInTurn = BN == 256;
+    static_assert(STAGES == (kInTurn ? kSlots : 3), "ring");
+    constexpr int kHalf = kLoads / 2;  // direct loads per wavefront per compute phase
+    // load j of the h-th half of a slab's loads (B's and then A's pieces, or A's loads followed by B's), to the
+    // ring position `at` (a slot, or a stage)
+    auto load_half = [&](auto h_tag, auto steady_tag, int kt, int at, int j) {
+      constexpr int h = decltype(h_tag)::value;
+      if constexpr (kInTurn) {
+        constexpr std::integral_constant<bool, h == 0> of_b{};
+        load(of_b, steady_tag, kt, j, smem + at * SA::kElems + SA::lds_offset(wave, j));
+      } else {
+        const int n = h * kHalf + j;
+        if (n < SA::kLoadsPerWave) load(kA, steady_tag, kt, n, smem + at * kStageElems + SA::lds_offset(wave, n));
+        else load(kB, steady_tag, kt, n - SA::kLoadsPerWave, smem + at * kStageElems + SA::kElems + SB::lds_offset(wave, n - SA::kLoadsPerWave));
+      }
+    };
+    constexpr std::integral_constant<int, 0> kFirst{};
+    constexpr std::integral_constant<int, 1> kSecond{};
+    auto load_all = [&](auto h_tag, int kt, int at) {
+#pragma unroll
+      for (int j = 0; j < kHalf; ++j) load_half(h_tag, kAny, kt, at, j);
+    };
+    // The order of halves: in turn, A0 | B0 A1 | B1 A2 | ...: `first half k` is B(k), `second half k` A(k + 1) with
+    // its slab counted as k + 1; otherwise the halves of slab k.  `kAhead` slabs after kt, a compute phase of the
+    // first group issues half c; the second group, half a slab later in time, has done half 0 a phase before and
+    // goes on to the next slab's.  Before the loop: what those phases assume done; then slab 0 has landed.
+    if constexpr (kInTurn) {
+      load_all(kSecond, 0, 0);
+      load_all(kFirst, 0, 1);
+      if (nk > 1) {
+        load_all(kSecond, 1, 2);
+        if (wave >= 4) load_all(kFirst, 1, 3);
+      }
+    } else {
+      load_all(kFirst, 0, 0);
+      load_all(kSecond, 0, 0);
+      if (nk > 1) {
+        load_all(kFirst, 1, 1);
+        load_all(kSecond, 1, 1);
+        if (wave >= 4 && nk > 2) load_all(kFirst, 2, 2);
+      }
+    }
+    constexpr int kNewer = kInTurn ? kHalf : 2 * kHalf;  // loads issued after slab kt + 1's when it is waited for
+    if (nk > 1) {
+      if (wave >= 4 && (kInTurn || nk > 2)) wait_vmcnt<kNewer + kHalf>();
+      else wait_vmcnt<kNewer>();
+    } else {
+      wait_vmcnt<0>();
+    }
+    block_barrier();
+    Frag<A_KMAJOR> fa[2][TM];
+    Frag<B_KMAJOR> fb[2][TN];
+    // (ragged: a wavefront whose part of the tile lies beyond the output loads and keeps the barriers, no more)
+    const bool works = !RAGGED || (m0 + wm0 < g.M && n0 + wn0 < g.N);
+    int slot_a = 0, slot_b = 1;  // in turn: of slab kt; otherwise slot_a: its stage
+    auto slab_step = [&](const int kt, auto group_tag, auto steady_tag, auto works_tag) {
+      constexpr int group = decltype(group_tag)::value;
+      constexpr bool steady = decltype(steady_tag)::value;  // no half asked for here is missing or has the tail
+      constexpr bool working = decltype(works_tag)::value;
+      const bf16_t* sa = smem + slot_a * (kInTurn ? SA::kElems : kStageElems);
+      const bf16_t* sb = kInTurn ? smem + slot_b * SA::kElems : sa + SA::kElems;
+      // what slab kt - 1 left: its slots, or its stage
+      const int free_a = kInTurn ? (slot_a >= 2 ? slot_a - 2 : slot_a - 2 + STAGES) : (slot_a >= 1 ? slot_a - 1 : STAGES - 1);
+      const int free_b = slot_b >= 2 ? slot_b - 2 : slot_b - 2 + STAGES;
+      // A compute phase's share of loads: which half, of which slab, to where.  Slab kt - 1 was last read one phase
+      // before the first group's first compute phase of slab kt, slab kt one before the second group's last.
+      constexpr int kHalf0 = kInTurn ? 1 : 2;  // half 0 in the first group's phases of slab kt is slab kt + kHalf0's
+      auto issue = [&](auto c_tag, int j) {
+        constexpr int c = decltype(c_tag)::value;
+        constexpr int h = group == 0 ? c : 1 - c;
+        constexpr std::integral_constant<int, h> h_tag{};
+        const int of = h == 1 ? kt + 2 : kt + kHalf0 + group;
+        const int at = kInTurn ? (group == 0 ? (c == 0 ? free_a : free_b) : (c == 0 ? free_b : slot_a))
+                               : (group == 1 && c == 1 ? slot_a : free_a);
+        if (steady || of < nk) load_half(h_tag, steady_tag, of, at, j);
+      };
+      auto chunk = [&](auto c_tag) {
+        constexpr int c = decltype(c_tag)::value;
+        if (working) {
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+#pragma unroll
+            for (int j = 0; j < TM; ++j) fa[u][j] = SA::fragment(sa, wm0 + 32 * j, 2 * c + u, lane);
+#pragma unroll
+            for (int i = 0; i < TN; ++i) fb[u][i] = SB::fragment(sb, wn0 + 32 * i, 2 * c + u, lane);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // Slab kt + 1 has landed, for the first group's next reading phase.  (The first group waits at the
+        // end of its compute phase, which is the same phase.)
+        if (group == 1 && c == 1) wait_vmcnt<steady ? kNewer : 0>();
+        wait_lgkmcnt0();
+        if (working) {
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+#pragma unroll
+            for (int j = 0; j < TM; ++j) fa[u][j].settle();
+#pragma unroll
+            for (int i = 0; i < TN; ++i) fb[u][i].settle();
+          }
+        }
+        block_barrier</*WAITED=*/true>();
+        __builtin_amdgcn_s_setprio(1);
+        constexpr int kMfmas = 2 * TM * TN;
+        constexpr int kEvery = kMfmas / 4;  // (at most four loads)
+#pragma unroll
+        for (int m = 0; m < kMfmas; ++m) {
+          if (working) {
+            const int u = m / (TM * TN), i = (m / TM) % TN, j = m % TM;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[u][i].operand(), fa[u][j].operand(), acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if (m % kEvery == 0 && m / kEvery < kHalf) issue(c_tag, m / kEvery);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (group == 0 && c == 1) wait_vmcnt<steady ? kNewer : 0>();
+        block_barrier</*WAITED=*/true>();  // (nothing of this phase is left to issue: see above)
+        __builtin_amdgcn_s_setprio(0);
+      };
+      chunk(kFirst);
+      chunk(kSecond);
+      if constexpr (kInTurn) {
+        slot_a = slot_a + 2 >= STAGES ? slot_a + 2 - STAGES : slot_a + 2;
+        slot_b = slot_b + 2 >= STAGES ? slot_b + 2 - STAGES : slot_b + 2;
+      } else {
+        slot_a = slot_a + 1 == STAGES ? 0 : slot_a + 1;
+      }
+    };
+    // (one phase apart: the second group starts, and the first ends, with a barrier more)
+    constexpr int kReach = kInTurn ? 3 : 4;  // a steady step asks for slabs up to kt + kReach - 1, none of them the last
+    auto contract = [&](auto group_tag, auto works_tag) {
+      if (decltype(group_tag)::value == 1) block_barrier();
+      int kt = 0;
+      for (; kt + kReach < nk; ++kt) slab_step(kt, group_tag, std::true_type{}, works_tag);
+      for (; kt < nk; ++kt) slab_step(kt, group_tag, std::false_type{}, works_tag);
+      if (decltype(group_tag)::value == 0) block_barrier();
+    };
+    if (works) {
+      if (wave < 4) contract(kFirst, std::true_type{});
+      else contract(kSecond, std::true_type{});
+    } else {
+      if (wave < 4) contract(kFirst, std::false_type{});
+      else contract(kSecond, std::false_type{});
+    }
+  } else {
   // prologue: STAGES - 1 slabs in flight, the first one landed
   constexpr int kAhead = STAGES - 1;
   static_assert(kAhead >= 1 && (kAhead - 1) * kLoads < 64, "ring depth");
@@ -255,7 +430,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
           if (op < TM) fa[nxt][op] = SA::fragment(sa, wm0 + 32 * op, u + 1, lane);
           else if (op < TM + TN) fb[nxt][op - TM] = SB::fragment(sb, wn0 + 32 * (op - TM), u + 1, lane);
           else if (op < kSide && u * kStepLoads + op - TM - TN < kLoads) {
-            if (refill) issue_load(kt + kAhead, u * kStepLoads + op - TM - TN);
+            if (refill) issue_load(steady_tag, kt + kAhead, u * kStepLoads + op - TM - TN);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -328,6 +503,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   for (; kt < nk; ++kt) {
     slab_step(kt, std::false_type{});
     end_range(kt);
+  }
   }
 
   // Epilogue.  acc[i][j][r] is the element n = wn0 + 32 i + 8 (r/4) + 4 (lane/32) + r%4,

@@ -172,7 +172,7 @@ struct GemmDesc {
   int causal;                              // CausalMode
   GemmEpilogue epi;                        // kind 0 (none) unless the matrix-core path is used
   // No room for the partial sums of a contraction that is cut for speed: one workgroup sums its ranges one after
-  // the other (slower, same bits).  In a pair, of both products; a pair of whole tiles keeps its cut and scratch.
+  // the other (slower, same bits).  In a pair, of both products.
   bool serial;
 };
 // Picks a kernel.  `scratch` (fp32, 16-byte aligned, gemm_scratch_bytes or more; null when that is 0)

@@ -55,6 +55,15 @@ __device__ __forceinline__ void block_barrier() {
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 typedef const __attribute__((address_space(1))) void* global_void_ptr;
 
+// Direct load of 16 bytes per lane from `base` (uniform) + offset to LDS at `to` (uniform) + 16 lane: a raw buffer that
+// starts at `base`, with no bound but that of the 32-bit offsets.
+__device__ __forceinline__ void buffer_load_to_lds(const void* base, uint32_t offset, bf16_t* to) {
+#if defined(__HIP_DEVICE_COMPILE__)  // (the host pass does not know the resource type)
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0xFFFFFFFF, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(to), 16, offset, 0, 0, 0);
+#endif
+}
+
 // An MFMA operand fragment as it arrives from LDS.  K-major slabs are read with plain
 // 16-byte loads, which the compiler tracks.  MN-major slabs are read with the transposing
 // LDS read, issued as inline assembly: the compiler's hazard tracking takes that read, as
