@@ -154,14 +154,22 @@ struct DropoutKey {
   float scale;                // 1 / (1 - p)
 };
 
+// a ^ b ^ c in one instruction (the compiler makes two, which were a third of a Philox call)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+  return a ^ b ^ c;
+#endif
+}
 __device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = static_cast<uint64_t>(0xD2511F53u) * c0;
     const uint64_t p1 = static_cast<uint64_t>(0xCD9E8D57u) * c2;
-    const uint32_t n0 = static_cast<uint32_t>(p1 >> 32) ^ c1 ^ k0;
-    const uint32_t n2 = static_cast<uint32_t>(p0 >> 32) ^ c3 ^ k1;
+    const uint32_t n0 = xor3(static_cast<uint32_t>(p1 >> 32), c1, k0);
+    const uint32_t n2 = xor3(static_cast<uint32_t>(p0 >> 32), c3, k1);
     c1 = static_cast<uint32_t>(p1);
     c3 = static_cast<uint32_t>(p0);
     c0 = n0;
@@ -194,16 +202,18 @@ __device__ __forceinline__ uint32_t dropout_keep8(const DropoutKey& k, uint64_t 
 __device__ __forceinline__ void dropout_apply8(const DropoutKey& k, uint64_t group, float (&v)[8]) {
   const uint4 w = philox4x32_10(static_cast<uint32_t>(group), static_cast<uint32_t>(group >> 32),
                                 k.stream0, k.stream1, k.key0, k.key1);
-  const uint32_t t = k.threshold;
+  // (the upper field against the shifted threshold, the lower as 16 bits: one compare each)
+  const uint32_t hi = k.threshold << 16;
+  const uint16_t lo = static_cast<uint16_t>(k.threshold);
   const float s = k.scale;
-  v[0] = ((w.x & 0xFFFFu) >= t) ? v[0] * s : 0.0f;
-  v[1] = ((w.x >> 16) >= t) ? v[1] * s : 0.0f;
-  v[2] = ((w.y & 0xFFFFu) >= t) ? v[2] * s : 0.0f;
-  v[3] = ((w.y >> 16) >= t) ? v[3] * s : 0.0f;
-  v[4] = ((w.z & 0xFFFFu) >= t) ? v[4] * s : 0.0f;
-  v[5] = ((w.z >> 16) >= t) ? v[5] * s : 0.0f;
-  v[6] = ((w.w & 0xFFFFu) >= t) ? v[6] * s : 0.0f;
-  v[7] = ((w.w >> 16) >= t) ? v[7] * s : 0.0f;
+  v[0] = static_cast<uint16_t>(w.x) >= lo ? v[0] * s : 0.0f;
+  v[1] = w.x >= hi ? v[1] * s : 0.0f;
+  v[2] = static_cast<uint16_t>(w.y) >= lo ? v[2] * s : 0.0f;
+  v[3] = w.y >= hi ? v[3] * s : 0.0f;
+  v[4] = static_cast<uint16_t>(w.z) >= lo ? v[4] * s : 0.0f;
+  v[5] = w.z >= hi ? v[5] * s : 0.0f;
+  v[6] = static_cast<uint16_t>(w.w) >= lo ? v[6] * s : 0.0f;
+  v[7] = w.w >= hi ? v[7] * s : 0.0f;
 }
 
 }  // namespace lynx

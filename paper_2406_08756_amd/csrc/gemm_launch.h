@@ -25,7 +25,8 @@ namespace {
 
 // Strides that only the tiles with 64-bit load offsets take (kFarStride).
 bool is_far(const GemmDesc& d) {
-  return (d.a_sk == 1 ? d.a_sm : d.a_sk) >= kFarStride || (d.b_sk == 1 ? d.b_sn : d.b_sk) >= kFarStride;
+  return (d.a_sk == 1 ? d.a_sm : d.a_sk) >= kFarStride || (d.b_sk == 1 ? d.b_sn : d.b_sk) >= kFarStride ||
+         d.c_sm >= kFarStride || (d.epi.kind != kEpiNone && d.epi.aux_ld >= kFarStride);
 }
 
 MfmaGemmArgs make_args(const GemmDesc& d) {
@@ -41,7 +42,6 @@ MfmaGemmArgs make_args(const GemmDesc& d) {
   a.nz = d.nz1 * d.nz2; a.nz2 = d.nz2; a.causal = d.causal;
   a.k_splits = 1; a.k_per = d.K; a.partial = nullptr;
   a.epi = d.epi.kind;
-  a.col0 = 0; a.row_len = d.N;
   if (d.epi.kind != kEpiNone) {
     a.aux = static_cast<const bf16_t*>(d.epi.aux); a.aux_ld = d.epi.aux_ld;
     a.vec = static_cast<const bf16_t*>(d.epi.vec);

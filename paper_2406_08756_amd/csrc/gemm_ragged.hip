@@ -93,7 +93,7 @@ struct ProductPlan {
 
 ProductPlan search_product(int M, int N, int K) {
   ProductPlan best{kT64, range_of(K, 1), 1e30};
-  const bool far = K >= kFarStride;  // (both operands K-major)
+  const bool far = K >= kFarStride || N >= kFarStride;  // the row strides
   for (int t = far ? kT64 : 0; t < kNumRaggedTiles; ++t)
     for (int want : kCuts) {
       if (want > 1 && K < kMinRange * want) break;
@@ -269,7 +269,7 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(MfmaGemmArgs a, Mfma
   if (g.plain != nullptr) store8(g.plain + static_cast<long long>(m) * g.ldc + n, s);
   load8(g.vec + n, vec);
   load8(g.aux + static_cast<long long>(m) * g.aux_ld + n, x);
-  bias_dropout_add8(s, vec, x, g.key, (static_cast<uint64_t>(m) * static_cast<uint64_t>(g.row_len) + n) >> 3, o);
+  bias_dropout_add8(s, vec, x, g.key, (static_cast<uint64_t>(m) * static_cast<uint64_t>(g.N) + n) >> 3, o);
   store8(c, o);
 }
 

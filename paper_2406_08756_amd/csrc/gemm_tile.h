@@ -53,11 +53,8 @@ struct MfmaGemmArgs {
   // sums in partial[split][M][N] instead of rounding into C
   int k_splits, k_per;
   float* partial;
-  // fused epilogue (GemmEpilogueKind).  aux / vec / plain are indexed with the absolute
-  // column col0 + n, so a launch that covers a column range of the output (edge strips)
-  // passes them unchanged; row_len is the full row length (the dropout element index).
+  // fused epilogue (GemmEpilogueKind)
   int epi;
-  int col0, row_len;
   const bf16_t* aux; long long aux_ld;
   const bf16_t* vec;
   bf16_t* plain;
@@ -528,19 +525,6 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
         }
     return;
   }
-  // The bias values of this wavefront's columns, requested in one batch (one exposed L2
-  // round trip instead of one per group of columns).
-  uint2 braw[TN][4];
-  if (g.bias != nullptr) {
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-      {
-        const int n = n0 + wn0 + 32 * i + 8 * q + 4 * (lane >> 5);
-        braw[i][q] = *reinterpret_cast<const uint2*>(g.bias + (RAGGED ? min(n, g.N - 4) : n));
-      }
-  }
   constexpr int kRowChunks = WN / 8;
   constexpr int kRowsPerStore = kWave / kRowChunks;
   constexpr int kIters = WM / kRowsPerStore;
@@ -550,11 +534,51 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   asm volatile("" : "+v"(elane));
   const int lr = elane / kRowChunks, lc = elane % kRowChunks;
   const long long row0 = m0 + wm0;
-  const int col = g.col0 + n0 + wn0 + lc * 8;  // absolute column of this lane's 8 outputs
+  const int col0 = n0 + wn0, col = col0 + lc * 8;  // first column, this lane's 8 outputs
   // (ragged: what this wavefront may store, relative to its first row and column)
   const int rows_in = RAGGED ? g.M - (m0 + wm0) : WM;
-  const bool col_in = !RAGGED || n0 + wn0 + lc * 8 < g.N;
-  auto stores = [&](int r) { return !RAGGED || (r < rows_in && col_in); };
+  const bool col_in = !RAGGED || col < g.N;
+  // Rows of [M, N] arrays, 16 bytes per lane, this wavefront's block: buffer accesses that end with the block's
+  // last row, so rows and columns that do not exist read zeros and are not written, without a branch, and an
+  // address is one 32-bit addition.  (With 64-bit products of row and stride, compares and branches per access
+  // instead, and two instructions for each three-way exclusive or of the dropout generator: a pass of the 13B-shaped
+  // shard, 16384 tokens, 5358 us where this takes 5276, of 8192 tokens of h 1024 1171 and 1151.)
+  struct Rows {
+    RowBuffer buffer;
+    const char* base;      // FAR
+    long long stride;      // bytes
+    uint32_t first, step;  // this lane's offset in access 0, from one access to the next
+  };
+  auto rows_of = [&](const bf16_t* p, long long ld) {
+    Rows v;
+    const bf16_t* corner = p + row0 * ld + col0;
+    v.base = reinterpret_cast<const char*>(corner);
+    v.stride = 2 * ld;
+    if constexpr (!FAR) {
+      v.buffer = row_buffer(corner, rows_in > 0 ? static_cast<uint32_t>(min(rows_in, WM)) * static_cast<uint32_t>(2 * ld) : 0u);
+      v.first = col_in ? static_cast<uint32_t>(lr) * static_cast<uint32_t>(2 * ld) + 16 * lc : 0x80000000u;
+      v.step = static_cast<uint32_t>(kRowsPerStore) * static_cast<uint32_t>(2 * ld);
+    }
+    return v;
+  };
+  auto row_load = [&](const Rows& v, int t) {
+    if constexpr (FAR) {
+      const int r = t * kRowsPerStore + lr;
+      uintx4_t x = {0u, 0u, 0u, 0u};
+      if (r < rows_in && col_in) x = *reinterpret_cast<const uintx4_t*>(v.base + r * v.stride + 16 * lc);
+      return x;
+    } else {
+      return row_buffer_load(v.buffer, v.first + static_cast<uint32_t>(t) * v.step);
+    }
+  };
+  auto row_store = [&](const Rows& v, int t, uintx4_t x) {
+    if constexpr (FAR) {
+      const int r = t * kRowsPerStore + lr;
+      if (r < rows_in && col_in) *reinterpret_cast<uintx4_t*>(const_cast<char*>(v.base) + r * v.stride + 16 * lc) = x;
+    } else {
+      row_buffer_store(v.buffer, v.first + static_cast<uint32_t>(t) * v.step, x);
+    }
+  };
   // Fused epilogues combine every 8 outputs with the same 8 elements of `aux`, fetched in
   // batches of 8 per lane, two batches in flight; the first is requested here, so it
   // arrives while the tile is rounded into LDS.
@@ -562,93 +586,125 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   constexpr int kBatches = kIters / kBatch;
   static_assert(kIters % kBatch == 0, "epilogue batches");
   uintx4_t ra0[kBatch], ra1[kBatch];
-  const bf16_t* auxp = g.epi != kEpiNone ? g.aux + row0 * g.aux_ld + (col_in ? col : g.col0) : nullptr;
+  const bool fused = g.epi != kEpiNone;
+  const Rows aux = rows_of(fused ? g.aux : Cbase, fused ? g.aux_ld : g.ldc);
   auto aux_load = [&](uintx4_t (&ra)[kBatch], int batch) {
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k)
-    {
-      const int r = (batch * kBatch + k) * kRowsPerStore + lr;
-      // (ragged: row rows_in - 1 of this wavefront, negative if it has none, is the last row of the operand)
-      ra[k] = *reinterpret_cast<const uintx4_t*>(auxp + static_cast<long long>(RAGGED ? min(r, rows_in - 1) : r) * g.aux_ld);
-    }
+    for (int k = 0; k < kBatch; ++k) ra[k] = row_load(aux, batch * kBatch + k);
   };
-  if (g.epi != kEpiNone) aux_load(ra0, 0);
-  block_barrier();  // every wavefront is done with the ring (no load is in flight any more)
+  if (fused) aux_load(ra0, 0);
   bf16_t* stage = smem + wave * (WM * WN);
+  auto round_to_stage = [&](auto bias_tag) {
+    constexpr bool with_bias = decltype(bias_tag)::value;
+    // (the bias values of this wavefront's columns in one batch: one exposed L2 round trip)
+    uint2 braw[with_bias ? TN : 1][4];
+    if constexpr (with_bias) {
 #pragma unroll
-  for (int i = 0; i < TN; ++i)
+      for (int i = 0; i < TN; ++i)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int nl = 32 * i + 8 * q + 4 * (lane >> 5);
-      float bv[4] = {0.f, 0.f, 0.f, 0.f};
-      if (g.bias != nullptr) {
-        const uint2 b = braw[i][q];
-        bv[0] = bf16_lo(b.x); bv[1] = bf16_hi(b.x); bv[2] = bf16_lo(b.y); bv[3] = bf16_hi(b.y);
-      }
-#pragma unroll
-      for (int j = 0; j < TM; ++j) {
-        const int ml = 32 * j + (lane & 31);
-        uint2 o;
-        o.x = pack_bf16(acc[i][j][4 * q + 0] + bv[0], acc[i][j][4 * q + 1] + bv[1]);
-        o.y = pack_bf16(acc[i][j][4 * q + 2] + bv[2], acc[i][j][4 * q + 3] + bv[3]);
-        const int chunk = (nl >> 3) ^ (ml & (kRowChunks - 1));
-        *reinterpret_cast<uint2*>(stage + ml * WN + chunk * 8 + (nl & 7)) = o;
-      }
+        for (int q = 0; q < 4; ++q) {
+          const int n = col0 + 32 * i + 8 * q + 4 * (lane >> 5);
+          braw[i][q] = *reinterpret_cast<const uint2*>(g.bias + (RAGGED ? min(n, g.N - 4) : n));
+        }
     }
-  bf16_t* cw = Cbase + static_cast<long long>(m0 + wm0) * g.ldc + n0 + wn0;
-  if (g.epi == kEpiNone) {
+    block_barrier();  // every wavefront is done with the ring (no load is in flight any more)
 #pragma unroll
-    for (int t = 0; t < kIters; ++t) {
-      const int r = t * kRowsPerStore + lr;
-      const uint4 v = *reinterpret_cast<const uint4*>(stage + r * WN + ((lc ^ (r & (kRowChunks - 1))) << 3));
-      if (stores(r)) *reinterpret_cast<uint4*>(cw + static_cast<long long>(r) * g.ldc + lc * 8) = v;
-    }
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int nl = 32 * i + 8 * q + 4 * (lane >> 5);
+        float bv[4] = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (with_bias) {
+          const uint2 b = braw[i][q];
+          bv[0] = bf16_lo(b.x); bv[1] = bf16_hi(b.x); bv[2] = bf16_lo(b.y); bv[3] = bf16_hi(b.y);
+        }
+        auto out = [&](int j, int k) { return with_bias ? acc[i][j][4 * q + k] + bv[k] : acc[i][j][4 * q + k]; };
+#pragma unroll
+        for (int j = 0; j < TM; ++j) {
+          const int ml = 32 * j + (lane & 31);
+          uint2 o;
+          o.x = pack_bf16(out(j, 0), out(j, 1));
+          o.y = pack_bf16(out(j, 2), out(j, 3));
+          const int chunk = (nl >> 3) ^ (ml & (kRowChunks - 1));
+          *reinterpret_cast<uint2*>(stage + ml * WN + chunk * 8 + (nl & 7)) = o;
+        }
+      }
+  };
+  if (g.bias != nullptr) round_to_stage(std::true_type{});
+  else round_to_stage(std::false_type{});
+  auto staged = [&](int t) {
+    const int r = t * kRowsPerStore + lr;
+    return *reinterpret_cast<const uintx4_t*>(stage + r * WN + ((lc ^ (r & (kRowChunks - 1))) << 3));
+  };
+  const Rows out = rows_of(Cbase, g.ldc);
+  if (!fused) {
+#pragma unroll
+    for (int t = 0; t < kIters; ++t) row_store(out, t, staged(t));
     return;
   }
-  float bv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (g.epi == kEpiBiasDropoutAdd) load8(g.vec + (col_in ? col : g.col0), bv);
-  float colacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto finish = [&](const uintx4_t (&ra)[kBatch], int batch) {
+  auto unpacked = [](uintx4_t raw, float (&v)[8]) {
+    Raw8<bf16_t> r;
+    r.v = make_uint4(raw[0], raw[1], raw[2], raw[3]);
+    unpack(r, v);
+  };
+  auto packed = [](const float (&v)[8]) {
+    return uintx4_t{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
+  };
+  auto all_batches = [&](auto&& finish) {
+    if (kBatches > 1) aux_load(ra1, 1);
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const int r = (batch * kBatch + k) * kRowsPerStore + lr;
-      Raw8<bf16_t> pv, xv;
-      pv.v = *reinterpret_cast<const uint4*>(stage + r * WN + ((lc ^ (r & (kRowChunks - 1))) << 3));
-      xv.v = make_uint4(ra[k][0], ra[k][1], ra[k][2], ra[k][3]);
-      float prod[8], x[8], o[8];
-      unpack(pv, prod);
-      unpack(xv, x);
-      if (g.epi == kEpiBiasDropoutAdd) {
-        if (g.plain != nullptr && stores(r))
-          *reinterpret_cast<uint4*>(g.plain + (row0 + r) * g.ldc + col) = pv.v;
-        const uint64_t elem = static_cast<uint64_t>(row0 + r) * static_cast<uint64_t>(g.row_len) + col;
-        bias_dropout_add8(prod, bv, x, g.key, elem >> 3, o);
-      } else {
-        gelu_bwd8<bf16_t>(prod, x, o);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) colacc[i] += !RAGGED || r < rows_in ? o[i] : 0.f;
+    for (int bt = 0; bt < kBatches; bt += 2) {
+      finish(ra0, bt);
+      if (bt + 2 < kBatches) aux_load(ra0, bt + 2);
+      if (bt + 1 < kBatches) {
+        finish(ra1, bt + 1);
+        if (bt + 3 < kBatches) aux_load(ra1, bt + 3);
       }
-      if (stores(r)) store8(cw + static_cast<long long>(r) * g.ldc + lc * 8, o);
     }
   };
-  if (kBatches > 1) aux_load(ra1, 1);
-  for (int bt = 0; bt < kBatches; bt += 2) {
-    finish(ra0, bt);
-    if (bt + 2 < kBatches) aux_load(ra0, bt + 2);
-    if (bt + 1 < kBatches) {
-      finish(ra1, bt + 1);
-      if (bt + 3 < kBatches) aux_load(ra1, bt + 3);
+  if (g.epi == kEpiBiasDropoutAdd) {
+    float bv[8];
+    load8(g.vec + (col_in ? col : 0), bv);
+    const bool keep_product = g.plain != nullptr;
+    const Rows plain = rows_of(keep_product ? g.plain : Cbase, g.ldc);
+    // dropout group (8 elements) of access 0, and groups from one access to the next
+    const uint64_t group0 = (static_cast<uint64_t>(row0 + lr) * static_cast<uint64_t>(g.N) + col) >> 3;
+    const uint64_t groups = static_cast<uint64_t>(kRowsPerStore) * static_cast<uint64_t>(g.N) >> 3;
+    all_batches([&](const uintx4_t (&ra)[kBatch], int batch) {
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const int t = batch * kBatch + k;
+        const uintx4_t p = staged(t);
+        float prod[8], x[8], o[8];
+        unpacked(p, prod);
+        unpacked(ra[k], x);
+        if (keep_product) row_store(plain, t, p);
+        bias_dropout_add8(prod, bv, x, g.key, group0 + static_cast<uint64_t>(t) * groups, o);
+        row_store(out, t, packed(o));
+      }
+    });
+    return;
+  }
+  float colacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  all_batches([&](const uintx4_t (&ra)[kBatch], int batch) {
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const int t = batch * kBatch + k;
+      float prod[8], x[8], o[8];
+      unpacked(staged(t), prod);
+      unpacked(ra[k], x);
+      gelu_bwd8<bf16_t>(prod, x, o);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) colacc[i] += !RAGGED || t * kRowsPerStore + lr < rows_in ? o[i] : 0.f;
+      row_store(out, t, packed(o));
     }
-  }
-  if (g.epi == kEpiGeluBwd) {
-    // column sums of this wavefront's WM rows: lanes with the same lc hold different rows
+  });
+  // column sums of this wavefront's WM rows: lanes with the same lc hold different rows
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int o = kRowChunks; o < kWave; o <<= 1) colacc[i] += __shfl_xor(colacc[i], o, kWave);
-    if (lane < kRowChunks && stores(0))
-      store8(g.colsum_partial + (row0 / WM) * g.row_len + col, colacc);
-  }
+    for (int o = kRowChunks; o < kWave; o <<= 1) colacc[i] += __shfl_xor(colacc[i], o, kWave);
+  if (lane < kRowChunks && rows_in > 0 && col_in) store8(g.colsum_partial + (row0 / WM) * g.N + col, colacc);
 }
 
 }  // namespace

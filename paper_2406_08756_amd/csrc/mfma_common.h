@@ -64,6 +64,33 @@ __device__ __forceinline__ void buffer_load_to_lds(const void* base, uint32_t of
 #endif
 }
 
+// `bytes` bytes from `base` (both uniform) as a raw buffer: 16-byte accesses at 32-bit offsets, of which those at or
+// beyond `bytes` read zeros and write nothing.
+struct RowBuffer {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __amdgpu_buffer_rsrc_t rsrc;
+#endif
+};
+__device__ __forceinline__ RowBuffer row_buffer(const void* base, uint32_t bytes) {
+  RowBuffer b;
+#if defined(__HIP_DEVICE_COMPILE__)
+  b.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+#endif
+  return b;
+}
+__device__ __forceinline__ uintx4_t row_buffer_load(const RowBuffer& b, uint32_t offset) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_raw_buffer_load_b128(b.rsrc, offset, 0, 0);
+#else
+  return uintx4_t{};
+#endif
+}
+__device__ __forceinline__ void row_buffer_store(const RowBuffer& b, uint32_t offset, uintx4_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_raw_buffer_store_b128(v, b.rsrc, offset, 0, 0);
+#endif
+}
+
 // An MFMA operand fragment as it arrives from LDS.  K-major slabs are read with plain
 // 16-byte loads, which the compiler tracks.  MN-major slabs are read with the transposing
 // LDS read, issued as inline assembly: the compiler's hazard tracking takes that read, as
