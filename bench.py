@@ -62,7 +62,7 @@ def slot_work(cfg):
         "b98_layernorm2_dropout_bwd": ("hbm", 5 * T * h * e),
         "b7_proj_dgrad_wgrad": ("mfma", 2 * lin(h, p)),
         "b6_dpd": ("mfma", att), "b6_dv": ("mfma", att), "b54_softmax_dropout_bwd": ("hbm", 3 * tri * e),
-        "b3_dq": ("mfma", att), "b3_dk": ("mfma", att), "b2_qkv_dgrad_wgrad": ("mfma", 2 * lin(3 * p, h)),
+        "b3_dq": ("mfma", att), "b3_dk": ("mfma", att), "b3_dq_dk": ("mfma", 2 * att), "b2_qkv_dgrad_wgrad": ("mfma", 2 * lin(3 * p, h)),
         "b2_bias_grad": ("hbm", T * 3 * p * e),
         "b1_layernorm1_bwd": ("hbm", 4 * T * h * e),
         # dPd = dC V^T with the dropout + softmax backward in its store pass: reads P, writes dS
@@ -525,7 +525,7 @@ def main():
                              "unit": "TFLOP/s", "frac": round(ach / mfma_peak, 4)}
             # the attention products move one seq x seq tensor (the causal triangle) for a contraction
             # of only head_dim: they sit on the HBM side of the ridge, so quote them against it too
-            if name.split("/")[-1] in ("op3_scores", "op6_context", "b6_dpd", "b6_dv", "b3_dq", "b3_dk"):
+            if name.split("/")[-1] in ("op3_scores", "op6_context", "b6_dpd", "b6_dv", "b3_dq", "b3_dk", "b3_dq_dk"):
                 tri_bytes = cfg.micro_batch * cfg.local_heads * cfg.seq * (cfg.seq + 1) // 2 * x.element_size()
                 gbs = tri_bytes / (ms * 1e-3) / 1e9
                 kernels[name].update({"hbm_achieved": round(gbs, 1), "hbm_unit": "GB/s of the causal triangle",

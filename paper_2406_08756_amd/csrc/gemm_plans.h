@@ -19,6 +19,8 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
                             ColumnSums* sums, hipStream_t st);
 // Products of attention (gemm_mfma.hip).
 hipError_t gemm_attention(const GemmDesc& d, hipStream_t st);
+// ... and (gemm_ragged.hip) a product over the rows and one over the columns of the same seq x seq operand in one launch.
+hipError_t gemm_attention_pair(const GemmDesc& rows, const GemmDesc& cols, hipStream_t st);
 
 // fp32 storage (gemm_f32.hip).
 bool gemm_f32_supported(const GemmDesc& d);

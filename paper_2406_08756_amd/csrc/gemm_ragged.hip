@@ -215,6 +215,46 @@ hipError_t launch_serial(bool far, MfmaGemmArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// The two products over a seq x seq gradient, dQ = dS K and dK = dS^T Q, in one launch: a workgroup of each in turn,
+// longest contractions first.  `by_slice`: slice z on XCD z % 8, one slice after the other, so that whichever of
+// the two comes second finds that slice of dS in the caches; otherwise all slices' longest tiles first.
+template <int TILE, bool FAR>
+__global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
+attn_gradients_kernel(MfmaGemmArgs rows, MfmaGemmArgs cols, int by_slice) {
+  using T = TileShape<TILE, false>;
+  const int x = static_cast<int>(blockIdx.x), per_slice = 2 * rows.tiles_m * rows.tiles_n;
+  int z, w;
+  if (by_slice) {
+    const int y = x >> 3;
+    z = y / per_slice * 8 + (x & 7);
+    w = y % per_slice;
+    if (z >= rows.nz) return;
+  } else {
+    w = x / rows.nz;
+    z = x - w * rows.nz;
+  }
+  const int tile = (w >> 1) * rows.nz + z;
+  if (w & 1) gemm_tile<false, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves, false, FAR>(cols, tile, 0);
+  else gemm_tile<true, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves, false, FAR>(rows, tile, 0);
+}
+
+template <int TILE, bool FAR = false>
+hipError_t launch_attn_gradients(MfmaGemmArgs rows, MfmaGemmArgs cols, hipStream_t st) {
+  using T = TileShape<TILE, false>;
+  constexpr size_t smem = tile_lds<T>;
+  auto kern = attn_gradients_kernel<TILE, FAR>;
+  LYNX_RAISE_LDS_LIMIT(kern, smem);
+  for (MfmaGemmArgs* g : {&rows, &cols}) {
+    g->tiles_m = ceil_div(g->M, T::BM);
+    g->tiles_n = ceil_div(g->N, T::BN);
+  }
+  const int per_slice = 2 * rows.tiles_m * rows.tiles_n;
+  const bool by_slice = rows.nz >= 32;
+  const int groups = by_slice ? 8 * ceil_div(rows.nz, 8) * per_slice : rows.nz * per_slice;
+  hipLaunchKernelGGL(kern, dim3(groups), dim3(T::waves * kWave), smem, st, rows, cols, by_slice ? 1 : 0);
+  return hipGetLastError();
+}
+
 template <int TILE, bool FAR = false>
 hipError_t launch_ragged_pair(MfmaGemmArgs w, MfmaGemmArgs d, hipStream_t st) {
   using T = TileShape<TILE, false>;
@@ -350,6 +390,22 @@ RaggedChoice ragged_product(const GemmDesc& d) {
   return {p.us, partial_bytes(d.M, d.N, p.splits(d.K)), 0};
 }
 
+int attention_tile(const GemmDesc& d, long long workgroups_per_tile) {
+  const int tile = d.causal == kCausalOutLower || d.N > 64 ? kT128 : kT128x64;
+  const TileCost& t = kProductCost[tile];
+  return ceil_div(d.M, t.bm) * ceil_div(d.N, t.bn) * workgroups_per_tile < TileCost::kUnits ? kT64 : tile;
+}
+
+hipError_t gemm_attention_pair(const GemmDesc& rows, const GemmDesc& cols, hipStream_t st) {
+  const MfmaGemmArgs r = make_args(rows), c = make_args(cols);
+  if (is_far(rows) || is_far(cols)) return launch_attn_gradients<kT64, true>(r, c, st);
+  switch (attention_tile(rows, r.nz)) {
+    case kT128: return launch_attn_gradients<kT128>(r, c, st);
+    case kT128x64: return launch_attn_gradients<kT128x64>(r, c, st);
+    default: return launch_attn_gradients<kT64>(r, c, st);
+  }
+}
+
 hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st) {
   MfmaGemmArgs a = make_args(d);
   const bool a_k = d.a_sk == 1, b_k = d.b_sk == 1, far = is_far(d);
@@ -373,9 +429,7 @@ hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, 
     // attention products: up to 128 rows (the zero padding of the seq x seq operands reaches the next
     // multiple of 128), a head dimension of up to 64 is half a tile wide, and where that leaves compute
     // units without a workgroup, 64 x 64 (21 slices of s = 328, d = 104: 10.2 us with 128 x 128 tiles)
-    tile = d.causal == kCausalOutLower || d.N > 64 ? kT128 : kT128x64;
-    const TileCost& t = kProductCost[tile];
-    if (static_cast<long long>(ceil_div(d.M, t.bm)) * ceil_div(d.N, t.bn) * a.nz < TileCost::kUnits) tile = kT64;
+    tile = attention_tile(d, a.nz);
   }
   hipError_t e;
   if (a_k && b_k) e = launch_tile<true, true>(tile, far, a, st);

@@ -164,7 +164,7 @@ struct Ctx {  // one pass (rehearsal or real) of a call
 enum BackwardSlot {
   kB13Dropout = 14, kB12Grads, kB11Gelu, kB10Grads, kB98LayerNormDropout, kB7Grads, kB6DPd,
   kB6DV, kB54Softmax, kB3DQ, kB3DK, kB2Grads, kB2BiasGrad, kB1LayerNorm, kB6RowDot, kB654DScores,
-  kOp36Fused, kB654DScoresFused, kB6DVFused, kColumnSums, kNumSlots
+  kOp36Fused, kB654DScoresFused, kB6DVFused, kColumnSums, kB3DQDK, kNumSlots
 };
 static_assert(kNumSlots <= LYNX_PROFILE_SLOTS, "profile slots");
 static_assert(LYNX_STATIC_WORKSPACE_BYTES == lynx::kStaticWorkspaceBytes, "header and library agree on the block size");
@@ -175,7 +175,7 @@ const char* const kSlotNames[kNumSlots] = {
     "b12_fc2_dgrad_wgrad", "b11_gelu_bwd", "b10_fc1_dgrad_wgrad",
     "b98_layernorm2_dropout_bwd", "b7_proj_dgrad_wgrad", "b6_dpd", "b6_dv", "b54_softmax_dropout_bwd", "b3_dq",
     "b3_dk", "b2_qkv_dgrad_wgrad", "b2_bias_grad", "b1_layernorm1_bwd", "b6_rowdot", "b654_dscores",
-    "op3456_attention_fused", "b654_dscores_fused", "b6_dv_fused", "b_column_sums"};
+    "op3456_attention_fused", "b654_dscores_fused", "b6_dv_fused", "b_column_sums", "b3_dq_dk"};
 
 char* act_ptr(const Ctx& cx, int i) {
   if (i == 0) return const_cast<char*>(static_cast<const char*>(cx.L->x));
@@ -765,12 +765,16 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   free_act(cx, 4);
   LYNX_TRY(tap(cx, 3, temp_ptr(cx, t_dpd)));
   // B3: S = Q K^T
-  LYNX_LAUNCH(cx, kB3DQ, lynx::gemm(dt, attn_rows(temp_ptr(cx, t_dpd), col_block(qkv, D, 1), 3 * D.p,
-                                           const_cast<char*>(col_block(dqkv, D, 0)), 3 * D.p, D),
-                             nullptr, 0, cx.st));
-  LYNX_LAUNCH(cx, kB3DK, lynx::gemm(dt, attn_cols(temp_ptr(cx, t_dpd), col_block(qkv, D, 0), 3 * D.p,
-                                           const_cast<char*>(col_block(dqkv, D, 1)), 3 * D.p, D),
-                             nullptr, 0, cx.st));
+  const GemmDesc dq = attn_rows(temp_ptr(cx, t_dpd), col_block(qkv, D, 1), 3 * D.p,
+                                const_cast<char*>(col_block(dqkv, D, 0)), 3 * D.p, D);
+  const GemmDesc dk = attn_cols(temp_ptr(cx, t_dpd), col_block(qkv, D, 0), 3 * D.p,
+                                const_cast<char*>(col_block(dqkv, D, 1)), 3 * D.p, D);
+  if (dt == LYNX_BF16) {
+    LYNX_LAUNCH(cx, kB3DQDK, lynx::gemm_seq_pair(dt, dq, dk, cx.st));
+  } else {
+    LYNX_LAUNCH(cx, kB3DQ, lynx::gemm(dt, dq, nullptr, 0, cx.st));
+    LYNX_LAUNCH(cx, kB3DK, lynx::gemm(dt, dk, nullptr, 0, cx.st));
+  }
   free_temp(cx, &t_dpd);
   free_act(cx, 3);
   LYNX_TRY(tap(cx, 2, dqkv));
