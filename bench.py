@@ -52,7 +52,7 @@ def slot_work(cfg):
     return {
         "op1_layernorm1": ("hbm", 2 * T * h * e), "op2_qkv_gemm": ("mfma", lin(3 * p, h)),
         "op3_scores": ("mfma", att), "op4_softmax_dropout": ("hbm", 3 * tri * e),
-        "op5_attn_dropout": ("hbm", 2 * tri * e), "op6_context": ("mfma", att),
+        "op5_attn_dropout": ("hbm", 2 * tri * e), "op345_scores_softmax": ("hbm", 2 * tri * e), "op6_context": ("mfma", att),
         "op7_attn_proj_gemm": ("mfma", lin(h, p)), "op8_bias_dropout_add1": ("hbm", 3 * T * h * e),
         "op9_layernorm2": ("hbm", 2 * T * h * e), "op10_fc1_gemm": ("mfma", lin(f, h)),
         "op11_gelu": ("hbm", 2 * T * f * e), "op12_fc2_gemm": ("mfma", lin(h, f)),
@@ -402,7 +402,10 @@ def main():
             B.lynx_layer_reset(prof)
             if k >= 2:
                 for name, v in ms.items():
-                    if name.startswith("op"):
+                    if name == "op345_scores_softmax":     # operators 3 to 5 in one launch: by the bytes each moves alone
+                        cost[2] += 0.2 * v / reps
+                        cost[3] += 0.8 * v / reps
+                    elif name.startswith("op"):
                         cost[int(name[2:].split("_")[0]) - 1] += v / reps
         B.lynx_layer_destroy(prof)
         del full_ws
@@ -519,6 +522,8 @@ def main():
         kind, amount = work[name.split("/")[-1]]
         if name == "fwd/op4_softmax_dropout" and not (mask >> 4) & 1:
             amount = amount * 2 // 3      # forward under this policy does not store P
+        if name.endswith("/op345_scores_softmax"):   # writes P unless forward need not keep it, Pd, and S if kept
+            amount = amount // 2 * ((name[:4] != "fwd/" or (mask >> 4) & 1) + 1 + ((mask >> 3) & 1))
         if kind == "mfma":
             ach = amount / (ms * 1e-3) / 1e12
             kernels[name] = {"ms": round(ms, 4), "bound": "mfma", "achieved": round(ach, 2),

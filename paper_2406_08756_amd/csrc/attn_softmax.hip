@@ -1,0 +1,331 @@
+// Operators 3 to 5 in one launch (bf16, s <= 2048, head dimension <= 128): S = Q K^T, P = softmax(S / sqrt(d)) over
+// j <= i, Pd = dropout(P).  S, P and Pd are written as far as somebody wants them; the bits of each are those of
+// the kernels that form them one after the other (attn_outer_kernel, softmax_dropout_fwd_kernel).
+//
+// What it saves is S's way through memory, a write and a read of b a s^2 values, and a launch.  What bounds it: the
+// vector ALU (exponentials, the dropout generator, rounding), about 90 cycles per 64 values, 32 more where exponentials
+// are formed twice (below), then its loads of K and its stores.  Separate kernels and this one, us: 40 slices of
+// s = 2048, d = 128, Pd alone 142 and 104, P and Pd 151 and 118; 64 slices 208 and 158, 250 and 187; 128 of 1024, d = 64,
+// S, P and Pd 128 and 98; 100 of 1000, d = 64, Pd 94 and 64, P and Pd 109 and 78; 8 of 384, a forward pass 43.8 and 41.2.
+//
+// A workgroup of WAVES wavefronts owns 32 rows of one slice.  Wavefront w takes the 64-column blocks w, w + WAVES, ...
+// up to the diagonal: it loads its rows of K into LDS by itself, 8 KB at a time, multiplies (products formed
+// transposed, so a lane holds 16 columns of one row per 32 x 32 tile, four consecutive ones at a time) and keeps the
+// rounded scores in registers, 16 per block.  Then the row maxima go round the wavefronts through LDS, then the
+// block sums (the canonical order of attn_math.h, whose group of 4 is a lane's four columns and whose tree of 8 a
+// lane's block), and every wavefront normalises its blocks, passes them through LDS into whole rows and stores those,
+// one dropout call per 8 columns.  At most two blocks per wavefront, of four wavefronts where s <= 512 and of eight beyond;
+// of rows longer than 1024 up to four blocks, whose exponentials are formed again for the normalisation instead of
+// being kept: at most 128 registers, and four wavefronts per SIMD cover each other's loads, transcendentals and stores.
+// (Four wavefronts of up to eight blocks, two per SIMD, 40 slices of s = 2048: 148 us with P, 119 without.)
+#include <mutex>
+
+#include "attn_math.h"
+#include "dropout_host.h"
+#include "gemm_launch.h"
+
+namespace lynx {
+namespace {
+
+constexpr int kRowsOfBlock = 32, kColsOfBlock = 64;
+constexpr int kMaxSeq = 2048;
+constexpr int kMaxBlocks = kMaxSeq / kColsOfBlock;
+constexpr int kStepElems = 4096;  // K of one step of one wavefront: 64 rows of head dimension 64, or 32 of 128
+
+struct ScoresSoftmaxArgs {
+  const bf16_t* q; const bf16_t* k;
+  long long ld;
+  bf16_t* S; bf16_t* P; bf16_t* Pd;  // nullable
+  int s, d, a, nz, row_blocks;
+  int global_heads, head0;
+  float scale;
+  DropoutKey key;
+  int stream_s, stream_p;  // streaming stores
+};
+
+// One 16-byte store per lane, streaming or not.
+__device__ __forceinline__ void store_row(const RowBuffer& b, uint32_t offset, uintx4_t v, bool streaming) {
+  if (streaming) row_buffer_store_streaming(b, offset, v);
+  else row_buffer_store(b, offset, v);
+}
+
+// NBW: most blocks per wavefront.
+template <int KD, bool RAGGED, int WAVES, int NBW>
+__global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_scores_softmax_kernel(ScoresSoftmaxArgs g) {
+  constexpr int kSlabs = KD / 64;
+  constexpr int kStepCols = kStepElems / KD, kSteps = kColsOfBlock / kStepCols;  // of a block
+  using SQ = Slab<kRowsOfBlock, true, 64, 1>;
+  using SK = Slab<kStepCols, true, 64, 1>;
+  constexpr bool kKeep = NBW <= 2;  // exponentials stay in registers
+  // longest rows first; slice z on XCD z % 8 where the slices are a multiple of 8
+  const int rb = g.row_blocks - 1 - static_cast<int>(blockIdx.x) / g.nz;
+  const int bz = static_cast<int>(blockIdx.x) % g.nz;
+  extern __shared__ __align__(1024) unsigned char smem_raw[];
+  bf16_t* sQ = reinterpret_cast<bf16_t*>(smem_raw);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  bf16_t* sK = sQ + kSlabs * SQ::kElems + wave * kStepElems;  // this wavefront's; later its staging area
+  float* row_max = reinterpret_cast<float*>(sQ + kSlabs * SQ::kElems + WAVES * kStepElems);  // [WAVES][32]
+  float* block_sum = row_max + WAVES * kRowsOfBlock;                                       // [kMaxBlocks][32]
+
+  const int z1 = bz / g.a, z2 = bz - z1 * g.a;
+  const long long slice = z1 * static_cast<long long>(g.s) * g.ld + static_cast<long long>(z2) * g.d;
+  const bf16_t* q = g.q + slice;
+  const bf16_t* k = g.k + slice;
+  const int r0 = rb * kRowsOfBlock;
+  const int rows_in = RAGGED ? min(kRowsOfBlock, g.s - r0) : kRowsOfBlock;
+  const int active = (r0 + rows_in - 1) / kColsOfBlock + 1;              // blocks up to the diagonal
+  const int padded = min(g.s, (r0 + rows_in + 127) / 128 * 128);         // columns written (zeros beyond the diagonal)
+  const int blocks = (padded + kColsOfBlock - 1) / kColsOfBlock;
+
+  // Slab sl (64 of the head dimension) of the rows from row0 on.  Whole ones through buffer loads: eight rows each, whose
+  // corner is uniform and whose lane offsets repeat every second load (the permutation of Slab has period 16 rows).
+  uint32_t lane_offset[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    lane_offset[j] = static_cast<uint32_t>(lane >> 3) * static_cast<uint32_t>(2 * g.ld) + 2 * static_cast<uint32_t>(SK::lane_k(0, j, lane));
+  auto load = [&](auto slab_tag, const bf16_t* base, int row0, int sl, bf16_t* to) {
+    using SL = decltype(slab_tag);
+    if (!RAGGED || (g.d == KD && row0 + 8 * SL::kLoadsPerWave <= g.s)) {
+#pragma unroll
+      for (int j = 0; j < SL::kLoadsPerWave; ++j)
+        buffer_load_to_lds(base + (row0 + 8 * j) * g.ld + sl * 64, lane_offset[j & 1], to + SL::lds_offset(0, j));
+      return;
+    }
+#pragma unroll
+    for (int j = 0; j < SL::kLoadsPerWave; ++j) {
+      const int row = min(row0 + SL::lane_mn(0, j, lane), g.s - 1);
+      const int kk = sl * 64 + SL::lane_k(0, j, lane);
+      const bf16_t* from = base + row * g.ld + kk;
+      if (kk >= g.d) from = reinterpret_cast<const bf16_t*>(&kZeroChunk);
+      __builtin_amdgcn_global_load_lds((global_void_ptr)(from), (lds_void_ptr)(to + SL::lds_offset(0, j)), 16, 0, 0);
+    }
+  };
+  auto load_k = [&](int col) {
+#pragma unroll
+    for (int sl = 0; sl < kSlabs; ++sl) load(SK{}, k, col, sl, sK + sl * SK::kElems);
+  };
+  if (wave < kSlabs) load(SQ{}, q, r0, wave, sQ + wave * SQ::kElems);
+  if (wave < active) load_k(wave * kColsOfBlock);
+  wait_vmcnt<0>();
+  block_barrier();
+
+  const int my_row = r0 + (lane & 31), half = lane >> 5;
+  // Staging, 32 rows of 64 columns, and the row layout it is read back in.  Two rows are as wide as the LDS banks: the
+  // 16-byte chunk is permuted by bits 1 to 3 of the row, the half of a chunk by bit 4, so that 32 rows' writes of 8
+  // bytes fall into different banks (the reader swaps the halves of rows 16 to 31 back).
+  const int lr = lane >> 3, lc = lane & 7;
+  bf16_t* const stage_to = sK + (lane & 31) * kColsOfBlock + 4 * (half ^ ((lane >> 4) & 1));
+  auto stage_write = [&](int i, int qd, uint2 v) {
+    *reinterpret_cast<uint2*>(stage_to + (((4 * i + qd) ^ ((lane >> 1) & 7)) << 3)) = v;
+  };
+  auto stage_read = [&](int u) {
+    const int row = u * 8 + lr;
+    const uintx4_t v = *reinterpret_cast<const uintx4_t*>(sK + row * kColsOfBlock + ((lc ^ ((row >> 1) & 7)) << 3));
+    return u < 2 ? v : uintx4_t{v[2], v[3], v[0], v[1]};
+  };
+  const long long out0 = (static_cast<long long>(bz) * g.s + r0) * g.s;
+  const uint32_t row_bytes = 2u * static_cast<uint32_t>(g.s), out_bytes = static_cast<uint32_t>(rows_in) * row_bytes;
+  auto offset_of = [&](int block, int u) {
+    const int col = block * kColsOfBlock + lc * 8;
+    const uint32_t at = static_cast<uint32_t>(u * 8 + lr) * row_bytes + 2u * static_cast<uint32_t>(col);
+    return !RAGGED || col < g.s ? at : 0x80000000u;
+  };
+
+  // scores, rounded and packed in pairs of columns: of the lane's row, columns 64 block + 32 i + 8 q + 4 half + 0..3
+  uint32_t sp[NBW][2][8];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < NBW; ++t) {
+    const int block = wave + WAVES * t;
+    if (block >= active) break;
+    const bool next = t + 1 < NBW && block + WAVES < active;
+    floatx16_t acc[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+#pragma unroll
+    for (int step = 0; step < kSteps; ++step) {
+      if (t > 0 || step > 0) wait_vmcnt<0>();
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int kk = 0; kk < KD / 16; ++kk) {
+        const Frag<true> fa = SQ::fragment(sQ + (kk >> 2) * SQ::kElems, 0, kk & 3, lane);
+#pragma unroll
+        for (int j = 0; j < 2 / kSteps; ++j) {
+          const Frag<true> fb = SK::fragment(sK + (kk >> 2) * SK::kElems, 32 * j, kk & 3, lane);
+          const int i = step * (2 / kSteps) + j;
+          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb.operand(), fa.operand(), acc[i], 0, 0, 0);
+        }
+      }
+      // this wavefront has read its K: the next rows may take its place (unless S is staged there first)
+      wait_lgkmcnt0();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (step + 1 < kSteps) load_k(block * kColsOfBlock + (step + 1) * kStepCols);
+      else if (next && g.S == nullptr) load_k((block + WAVES) * kColsOfBlock);
+    }
+    if (g.S != nullptr) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd)
+          stage_write(i, qd, make_uint2(pack_bf16(acc[i][4 * qd], acc[i][4 * qd + 1]), pack_bf16(acc[i][4 * qd + 2], acc[i][4 * qd + 3])));
+      const RowBuffer out = row_buffer(g.S + out0, out_bytes);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) store_row(out, offset_of(block, u), stage_read(u), g.stream_s != 0);
+      wait_lgkmcnt0();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (next) load_k((block + WAVES) * kColsOfBlock);
+    }
+    // columns beyond the diagonal, in its block only
+    if (block == active - 1) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int col = block * kColsOfBlock + 32 * i + 8 * (r >> 2) + 4 * half + (r & 3);
+          acc[i][r] = col <= my_row ? acc[i][r] : -INFINITY;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        mx = fmaxf(fmaxf(acc[i][2 * r], acc[i][2 * r + 1]), mx);
+        sp[t][i][r] = pack_bf16(acc[i][2 * r], acc[i][2 * r + 1]);
+      }
+  }
+  // Row maximum.  Rounding to storage and the positive scale are monotonic, so the largest logit is that of the
+  // largest score before rounding.
+  mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+  if (lane < 32) row_max[wave * kRowsOfBlock + lane] = mx;
+  block_barrier();
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) mx = fmaxf(mx, row_max[w * kRowsOfBlock + (lane & 31)]);
+  const float m = softmax_logit(round_to_storage(mx, static_cast<bf16_t*>(nullptr)), g.scale);
+  float e[kKeep ? NBW : 1][2][16];
+  auto exponentials = [&](int t, float (&x)[2][16]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        x[i][2 * r] = softmax_exp(softmax_logit(bf16_lo(sp[t][i][r]), g.scale), m);
+        x[i][2 * r + 1] = softmax_exp(softmax_logit(bf16_hi(sp[t][i][r]), g.scale), m);
+      }
+  };
+#pragma unroll
+  for (int t = 0; t < NBW; ++t) {
+    const int block = wave + WAVES * t;
+    if (block >= active) break;
+    float (&x)[2][16] = e[kKeep ? t : 0];
+    exponentials(t, x);
+    float v[8];
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      const int i = n >> 2, qd = n & 3;
+      v[n] = softmax_group4(x[i][4 * qd], x[i][4 * qd + 1], x[i][4 * qd + 2], x[i][4 * qd + 3]);
+    }
+    const float th = softmax_tree8(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]);
+    const float sum = th + __shfl_xor(th, 32, kWave);
+    if (lane < 32) block_sum[block * kRowsOfBlock + lane] = sum;
+  }
+  block_barrier();
+  // blocks alternately into two running sums, one per half of the wavefront
+  float sum = 0.f;
+  for (int b = 0; b < active; b += 2) {
+    const float x = block_sum[min(b + half, kMaxBlocks - 1) * kRowsOfBlock + (lane & 31)];
+    sum += b + half < active ? x : 0.f;
+  }
+  const float inv = softmax_inverse(sum + __shfl_xor(sum, 32, kWave));
+
+  const RowBuffer out_p = row_buffer(g.P + out0, g.P != nullptr ? out_bytes : 0u);
+  const RowBuffer out_pd = row_buffer(g.Pd + out0, g.Pd != nullptr ? out_bytes : 0u);
+  // dropout group (8 columns) of this lane in row lr, block 0
+  const uint64_t group0 = ((((static_cast<uint64_t>(z1) * g.global_heads + g.head0 + z2) * g.s + r0 + lr) * static_cast<uint64_t>(g.s)) >> 3) + lc;
+#pragma unroll
+  for (int t = 0; t < NBW; ++t) {
+    const int block = wave + WAVES * t;
+    if (block >= active) break;
+    if (!kKeep) exponentials(t, e[0]);
+    const float (&x)[2][16] = e[kKeep ? t : 0];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd)
+        stage_write(i, qd, make_uint2(pack_bf16(x[i][4 * qd] * inv, x[i][4 * qd + 1] * inv),
+                                      pack_bf16(x[i][4 * qd + 2] * inv, x[i][4 * qd + 3] * inv)));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uintx4_t raw = stage_read(u);
+      const uint32_t at = offset_of(block, u);
+      if (g.P != nullptr) store_row(out_p, at, raw, g.stream_p != 0);
+      if (g.Pd != nullptr) {
+        Raw8<bf16_t> r;
+        r.v = make_uint4(raw[0], raw[1], raw[2], raw[3]);
+        float p[8];
+        unpack(r, p);
+        dropout_apply8(g.key, group0 + static_cast<uint64_t>(u * g.s + block * (kColsOfBlock / 8)), p);
+        row_buffer_store(out_pd, at, uintx4_t{pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])});
+      }
+    }
+  }
+  // zeros between the diagonal's block and the next multiple of 128 columns (at most one block)
+  if (blocks > active && wave == (active & (WAVES - 1))) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uintx4_t zero = {0u, 0u, 0u, 0u};
+      if (g.P != nullptr) store_row(out_p, offset_of(active, u), zero, g.stream_p != 0);
+      if (g.Pd != nullptr) row_buffer_store(out_pd, offset_of(active, u), zero);
+    }
+  }
+}
+
+template <int KD, bool RAGGED, int WAVES, int NBW>
+hipError_t launch(const ScoresSoftmaxArgs& g, hipStream_t st) {
+  constexpr size_t smem = (kRowsOfBlock * KD + WAVES * kStepElems) * sizeof(bf16_t) + (WAVES + kMaxBlocks) * kRowsOfBlock * sizeof(float);
+  auto kern = attn_scores_softmax_kernel<KD, RAGGED, WAVES, NBW>;
+  LYNX_RAISE_LDS_LIMIT(kern, smem);
+  hipLaunchKernelGGL(kern, dim3(g.row_blocks * g.nz), dim3(WAVES * kWave), smem, st, g);
+  return hipGetLastError();
+}
+template <int KD, bool RAGGED>
+hipError_t launch(const ScoresSoftmaxArgs& g, hipStream_t st) {
+  // With so few workgroups that all run at once, one block per wavefront: the time of a workgroup is what counts.
+  const bool few = static_cast<long long>(g.row_blocks) * g.nz <= 512;
+  if (g.s <= 256 && few) return launch<KD, RAGGED, 4, 1>(g, st);
+  if (g.s <= 512) return few ? launch<KD, RAGGED, 8, 1>(g, st) : launch<KD, RAGGED, 4, 2>(g, st);
+  if (g.s <= 1024) return launch<KD, RAGGED, 8, 2>(g, st);
+  return launch<KD, RAGGED, 8, 4>(g, st);
+}
+
+}  // namespace
+
+bool attn_scores_softmax_supported(int dtype, int s, int d, long long ld) {
+  return dtype == 1 && s % 8 == 0 && s <= kMaxSeq && d % 8 == 0 && d <= 128 && ld % 8 == 0 && ld < (1ll << 28);
+}
+
+hipError_t attn_scores_softmax_fwd(const void* q, const void* k, long long ld, void* S, void* P, void* Pd, AttnShape sh, int d,
+                                   float scale, DropoutParams dp, hipStream_t st) {
+  if (!attn_scores_softmax_supported(1, sh.s, d, ld)) return hipErrorInvalidValue;
+  ScoresSoftmaxArgs g{};
+  g.q = static_cast<const bf16_t*>(q); g.k = static_cast<const bf16_t*>(k); g.ld = ld;
+  g.S = static_cast<bf16_t*>(S); g.P = static_cast<bf16_t*>(P); g.Pd = static_cast<bf16_t*>(Pd);
+  g.s = sh.s; g.d = d; g.a = sh.a; g.nz = sh.a * sh.b;
+  g.row_blocks = (sh.s + kRowsOfBlock - 1) / kRowsOfBlock;
+  g.global_heads = sh.global_heads; g.head0 = sh.head0;
+  g.scale = scale;
+  g.key = make_dropout_key(dp, 0);
+  // as in the kernels that this one replaces: S is not read again soon, nor is P where Pd is written too; rows that end
+  // inside a 128-byte line are left to the caches
+  const bool whole_lines = sh.s % 64 == 0;
+  g.stream_s = whole_lines;
+  g.stream_p = whole_lines && Pd != nullptr;
+  const bool whole = sh.s % kColsOfBlock == 0 && (d == 64 || d == 128);
+  if (d <= 64) return whole ? launch<64, false>(g, st) : launch<64, true>(g, st);
+  return whole ? launch<128, false>(g, st) : launch<128, true>(g, st);
+}
+
+}  // namespace lynx

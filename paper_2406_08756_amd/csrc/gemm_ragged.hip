@@ -249,7 +249,10 @@ hipError_t launch_attn_gradients(MfmaGemmArgs rows, MfmaGemmArgs cols, hipStream
     g->tiles_n = ceil_div(g->N, T::BN);
   }
   const int per_slice = 2 * rows.tiles_m * rows.tiles_n;
-  const bool by_slice = rows.nz >= 32;
+  // From eight slices per XCD on, the idle end of the last one is a small part.  Slice by slice and all at once: 64
+  // slices of s = 2048 142 and 161 us, 128 of 1024 59 and 63; but 40 of 2048 87 and 84, 32 of 2048 79 and 68.
+  // (Two launches: 182, 66, 97 and 89.)
+  const bool by_slice = rows.nz >= 64;
   const int groups = by_slice ? 8 * ceil_div(rows.nz, 8) * per_slice : rows.nz * per_slice;
   hipLaunchKernelGGL(kern, dim3(groups), dim3(T::waves * kWave), smem, st, rows, cols, by_slice ? 1 : 0);
   return hipGetLastError();

@@ -62,6 +62,11 @@ hipError_t layernorm_bwd_dropout_bwd(int dtype, const void* dy, const void* x, c
 // (i, round_up(i+1, 128)) of every written row are zero-filled.
 hipError_t softmax_dropout_fwd(int dtype, const void* S, void* P, void* Pd, AttnShape sh,
                                float scale, DropoutParams dp, hipStream_t st);
+// Operators 3 to 5 in one launch (attn_softmax.hip): q and k are [T, a * d] with row stride ld; S, P, Pd as the
+// separate kernels leave them, each written if not null.
+bool attn_scores_softmax_supported(int dtype, int s, int d, long long ld);
+hipError_t attn_scores_softmax_fwd(const void* q, const void* k, long long ld, void* S, void* P, void* Pd, AttnShape sh, int d,
+                                   float scale, DropoutParams dp, hipStream_t st);
 // Pd = keep * P * c from a resident P.
 hipError_t attn_dropout_fwd(int dtype, const void* P, void* Pd, AttnShape sh, DropoutParams dp,
                             hipStream_t st);

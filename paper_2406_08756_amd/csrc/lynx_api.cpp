@@ -164,7 +164,7 @@ struct Ctx {  // one pass (rehearsal or real) of a call
 enum BackwardSlot {
   kB13Dropout = 14, kB12Grads, kB11Gelu, kB10Grads, kB98LayerNormDropout, kB7Grads, kB6DPd,
   kB6DV, kB54Softmax, kB3DQ, kB3DK, kB2Grads, kB2BiasGrad, kB1LayerNorm, kB6RowDot, kB654DScores,
-  kOp36Fused, kB654DScoresFused, kB6DVFused, kColumnSums, kB3DQDK, kNumSlots
+  kOp36Fused, kB654DScoresFused, kB6DVFused, kColumnSums, kB3DQDK, kOp345, kNumSlots
 };
 static_assert(kNumSlots <= LYNX_PROFILE_SLOTS, "profile slots");
 static_assert(LYNX_STATIC_WORKSPACE_BYTES == lynx::kStaticWorkspaceBytes, "header and library agree on the block size");
@@ -175,7 +175,8 @@ const char* const kSlotNames[kNumSlots] = {
     "b12_fc2_dgrad_wgrad", "b11_gelu_bwd", "b10_fc1_dgrad_wgrad",
     "b98_layernorm2_dropout_bwd", "b7_proj_dgrad_wgrad", "b6_dpd", "b6_dv", "b54_softmax_dropout_bwd", "b3_dq",
     "b3_dk", "b2_qkv_dgrad_wgrad", "b2_bias_grad", "b1_layernorm1_bwd", "b6_rowdot", "b654_dscores",
-    "op3456_attention_fused", "b654_dscores_fused", "b6_dv_fused", "b_column_sums", "b3_dq_dk"};
+    "op3456_attention_fused", "b654_dscores_fused", "b6_dv_fused", "b_column_sums", "b3_dq_dk",
+    "op345_scores_softmax"};
 
 char* act_ptr(const Ctx& cx, int i) {
   if (i == 0) return const_cast<char*>(static_cast<const char*>(cx.L->x));
@@ -464,6 +465,27 @@ lynx_status run_fused_attention(Ctx& cx) {
   return LYNX_OK;
 }
 
+// Operators 3 and 4, and 5 where `with_pd`, as one launch (attn_softmax.hip): S is written only if the policy keeps it
+// (its place in the workspace is taken either way, so that every block lies where the separate operators put it),
+// P if `write_p`.
+bool can_fuse_scores(const Ctx& cx) {
+  const Dims& D = cx.L->D;
+  return lynx::attn_scores_softmax_supported(D.dtype, D.s, D.d, 3ll * D.p);
+}
+lynx_status run_fused_scores(Ctx& cx, bool write_p, bool with_pd) {
+  lynx_layer_s* L = cx.L;
+  const Dims& D = L->D;
+  const bool keep_s = (cx.bk->retain >> 3) & 1u;
+  LYNX_TRY(alloc_act(cx, 3));
+  if (write_p) LYNX_TRY(alloc_act(cx, 4));
+  if (with_pd) LYNX_TRY(alloc_act(cx, 5));
+  LYNX_LAUNCH(cx, kOp345, lynx::attn_scores_softmax_fwd(col_block(act_ptr(cx, 2), D, 0), col_block(act_ptr(cx, 2), D, 1), 3ll * D.p,
+                                               keep_s ? act_ptr(cx, 3) : nullptr, write_p ? act_ptr(cx, 4) : nullptr,
+                                               with_pd ? act_ptr(cx, 5) : nullptr, attn_shape(L), D.d,
+                                               1.0f / sqrtf(static_cast<float>(D.d)), dropout_params(L), cx.st));
+  return LYNX_OK;
+}
+
 lynx_status forward_pass(Ctx& cx, uint32_t retain) {
   Book& bk = *cx.bk;
   bk.retain = (retain & 0x3FFFu) | kCallerOwned;
@@ -476,6 +498,10 @@ lynx_status forward_pass(Ctx& cx, uint32_t retain) {
     if (bk.fused_attn && (i == 3 || i == 4)) continue;
     if (bk.fused_attn && i == 6) {
       LYNX_TRY(run_fused_attention(cx));
+    } else if (i == 3 && can_fuse_scores(cx)) {
+      LYNX_TRY(run_fused_scores(cx, /*write_p=*/(bk.retain >> 4) & 1u, /*with_pd=*/true));
+      done = 5;  // the launch covers OP4 and OP5 too
+      i = 4;
     } else if (i == 4) {
       LYNX_TRY(run_op(cx, 4, /*fuse_dropout=*/true, /*write_p=*/(bk.retain >> 4) & 1u));
       done = 5;  // OP4's launch covers OP5
@@ -557,6 +583,8 @@ lynx_status recompute_pass(Ctx& cx, uint32_t segment) {
     if (!((segment >> i) & 1u) || bk.live[i]) continue;
     if (bk.fused_attn && i == 6) {
       LYNX_TRY(run_fused_attention(cx));
+    } else if (i == 3 && ((segment >> 4) & 1u) && !bk.live[4] && can_fuse_scores(cx)) {
+      LYNX_TRY(run_fused_scores(cx, /*write_p=*/true, /*with_pd=*/((segment >> 5) & 1u) && !bk.live[5]));
     } else if (i == 4 && ((segment >> 5) & 1u) && !bk.live[5]) {
       LYNX_TRY(run_op(cx, 4, /*fuse_dropout=*/true));
     } else if ((i == 7 || i == 12) && ((segment >> (i + 1)) & 1u) && !bk.live[i + 1] &&

@@ -90,6 +90,12 @@ __device__ __forceinline__ void row_buffer_store(const RowBuffer& b, uint32_t of
   __builtin_amdgcn_raw_buffer_store_b128(v, b.rsrc, offset, 0, 0);
 #endif
 }
+// ... with the non-temporal hint
+__device__ __forceinline__ void row_buffer_store_streaming(const RowBuffer& b, uint32_t offset, uintx4_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_raw_buffer_store_b128(v, b.rsrc, offset, 0, 2);
+#endif
+}
 
 // An MFMA operand fragment as it arrives from LDS.  K-major slabs are read with plain
 // 16-byte loads, which the compiler tracks.  MN-major slabs are read with the transposing
