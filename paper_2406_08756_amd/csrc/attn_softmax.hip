@@ -49,6 +49,31 @@ __device__ __forceinline__ void store_row(const RowBuffer& b, uint32_t offset, u
   else row_buffer_store(b, offset, v);
 }
 
+// Slab sl (64 of the head dimension) of the rows from row0 on of a [s, d] operand with row stride ld.  Whole ones through
+// buffer loads: eight rows each, whose corner is uniform and whose lane offsets repeat every second load (the
+// permutation of Slab has period 16 rows).
+template <typename SL, int KD, bool RAGGED>
+__device__ __forceinline__ void load_rows(const bf16_t* base, long long ld, int s, int d, int row0, int sl, bf16_t* to, int lane) {
+  if (!RAGGED || (d == KD && row0 + 8 * SL::kLoadsPerWave <= s)) {
+    uint32_t offset[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      offset[j] = static_cast<uint32_t>(lane >> 3) * static_cast<uint32_t>(2 * ld) + 2 * static_cast<uint32_t>(SL::lane_k(0, j, lane));
+#pragma unroll
+    for (int j = 0; j < SL::kLoadsPerWave; ++j)
+      buffer_load_to_lds(base + (row0 + 8 * j) * ld + sl * 64, offset[j & 1], to + SL::lds_offset(0, j));
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < SL::kLoadsPerWave; ++j) {
+    const int row = min(row0 + SL::lane_mn(0, j, lane), s - 1);
+    const int kk = sl * 64 + SL::lane_k(0, j, lane);
+    const bf16_t* from = base + row * ld + kk;
+    if (kk >= d) from = reinterpret_cast<const bf16_t*>(&kZeroChunk);
+    __builtin_amdgcn_global_load_lds((global_void_ptr)(from), (lds_void_ptr)(to + SL::lds_offset(0, j)), 16, 0, 0);
+  }
+}
+
 // NBW: most blocks per wavefront.
 template <int KD, bool RAGGED, int WAVES, int NBW>
 __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_scores_softmax_kernel(ScoresSoftmaxArgs g) {
@@ -78,34 +103,11 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_scores
   const int padded = min(g.s, (r0 + rows_in + 127) / 128 * 128);         // columns written (zeros beyond the diagonal)
   const int blocks = (padded + kColsOfBlock - 1) / kColsOfBlock;
 
-  // Slab sl (64 of the head dimension) of the rows from row0 on.  Whole ones through buffer loads: eight rows each, whose
-  // corner is uniform and whose lane offsets repeat every second load (the permutation of Slab has period 16 rows).
-  uint32_t lane_offset[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-    lane_offset[j] = static_cast<uint32_t>(lane >> 3) * static_cast<uint32_t>(2 * g.ld) + 2 * static_cast<uint32_t>(SK::lane_k(0, j, lane));
-  auto load = [&](auto slab_tag, const bf16_t* base, int row0, int sl, bf16_t* to) {
-    using SL = decltype(slab_tag);
-    if (!RAGGED || (g.d == KD && row0 + 8 * SL::kLoadsPerWave <= g.s)) {
-#pragma unroll
-      for (int j = 0; j < SL::kLoadsPerWave; ++j)
-        buffer_load_to_lds(base + (row0 + 8 * j) * g.ld + sl * 64, lane_offset[j & 1], to + SL::lds_offset(0, j));
-      return;
-    }
-#pragma unroll
-    for (int j = 0; j < SL::kLoadsPerWave; ++j) {
-      const int row = min(row0 + SL::lane_mn(0, j, lane), g.s - 1);
-      const int kk = sl * 64 + SL::lane_k(0, j, lane);
-      const bf16_t* from = base + row * g.ld + kk;
-      if (kk >= g.d) from = reinterpret_cast<const bf16_t*>(&kZeroChunk);
-      __builtin_amdgcn_global_load_lds((global_void_ptr)(from), (lds_void_ptr)(to + SL::lds_offset(0, j)), 16, 0, 0);
-    }
-  };
   auto load_k = [&](int col) {
 #pragma unroll
-    for (int sl = 0; sl < kSlabs; ++sl) load(SK{}, k, col, sl, sK + sl * SK::kElems);
+    for (int sl = 0; sl < kSlabs; ++sl) load_rows<SK, KD, RAGGED>(k, g.ld, g.s, g.d, col, sl, sK + sl * SK::kElems, lane);
   };
-  if (wave < kSlabs) load(SQ{}, q, r0, wave, sQ + wave * SQ::kElems);
+  if (wave < kSlabs) load_rows<SQ, KD, RAGGED>(q, g.ld, g.s, g.d, r0, wave, sQ + wave * SQ::kElems, lane);
   if (wave < active) load_k(wave * kColsOfBlock);
   wait_vmcnt<0>();
   block_barrier();
@@ -301,6 +303,204 @@ hipError_t launch(const ScoresSoftmaxArgs& g, hipStream_t st) {
   return launch<KD, RAGGED, 8, 4>(g, st);
 }
 
+// ---- the gradient: dPd = dC V^T and the backward of dropout and softmax in one launch --------------------------------
+// dS = scale P (dP - sum_j dP P), dP = keep c round(dPd), for s <= 1024.  The same split of rows and blocks: a wavefront forms
+// its blocks of dPd, passes them through LDS into whole rows, where the dropout decisions are made, and keeps them,
+// dropped elements cleared, beside the same elements of P (16 registers each per block of at most two) until the row
+// sums are known.  dPd never goes through memory.  The sums are of the same terms as in softmax_dropout_bwd_kernel, which
+// takes what is longer.  What bounds it: reading P and writing dS, then the vector ALU.  Two kernels and this one, us:
+// 128 slices of 1024, d = 64, 112 and 83; 100 of 1000 101 and 72; 21 of 328, d = 104, 15 and 11; dQ and dK right behind it gain 5
+// more, since dV then runs before it.
+constexpr int kMaxGradientSeq = 1024;
+
+struct ScoreGradientArgs {
+  const bf16_t* dc; const bf16_t* v;
+  long long lddc, ldv;
+  const bf16_t* P; bf16_t* dS;
+  int s, d, a, nz, row_blocks;
+  int global_heads, head0;
+  float scale;
+  DropoutKey key;
+};
+
+template <int KD, bool RAGGED, int WAVES, int NBW>
+__global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_gradient_kernel(ScoreGradientArgs g) {
+  constexpr int kSlabs = KD / 64;
+  constexpr int kStepCols = kStepElems / KD, kSteps = kColsOfBlock / kStepCols;
+  using SQ = Slab<kRowsOfBlock, true, 64, 1>;
+  using SK = Slab<kStepCols, true, 64, 1>;
+  const int rb = g.row_blocks - 1 - static_cast<int>(blockIdx.x) / g.nz;
+  const int bz = static_cast<int>(blockIdx.x) % g.nz;
+  extern __shared__ __align__(1024) unsigned char smem_raw[];
+  bf16_t* sQ = reinterpret_cast<bf16_t*>(smem_raw);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  bf16_t* sK = sQ + kSlabs * SQ::kElems + wave * kStepElems;
+  float* row_sum = reinterpret_cast<float*>(sQ + kSlabs * SQ::kElems + WAVES * kStepElems);  // [WAVES][32]
+  const int z1 = bz / g.a, z2 = bz - z1 * g.a;
+  const bf16_t* dc = g.dc + z1 * static_cast<long long>(g.s) * g.lddc + static_cast<long long>(z2) * g.d;
+  const bf16_t* v = g.v + z1 * static_cast<long long>(g.s) * g.ldv + static_cast<long long>(z2) * g.d;
+  const int r0 = rb * kRowsOfBlock;
+  const int rows_in = RAGGED ? min(kRowsOfBlock, g.s - r0) : kRowsOfBlock;
+  const int active = (r0 + rows_in - 1) / kColsOfBlock + 1;
+  const int padded = min(g.s, (r0 + rows_in + 127) / 128 * 128);
+  const int blocks = (padded + kColsOfBlock - 1) / kColsOfBlock;
+
+  auto load_v = [&](int col) {
+#pragma unroll
+    for (int sl = 0; sl < kSlabs; ++sl) load_rows<SK, KD, RAGGED>(v, g.ldv, g.s, g.d, col, sl, sK + sl * SK::kElems, lane);
+  };
+  if (wave < kSlabs) load_rows<SQ, KD, RAGGED>(dc, g.lddc, g.s, g.d, r0, wave, sQ + wave * SQ::kElems, lane);
+  if (wave < active) load_v(wave * kColsOfBlock);
+  wait_vmcnt<0>();
+  block_barrier();
+
+  const int my_row = r0 + (lane & 31), half = lane >> 5;
+  const int lr = lane >> 3, lc = lane & 7;
+  // (staging as above)
+  bf16_t* const stage_to = sK + (lane & 31) * kColsOfBlock + 4 * (half ^ ((lane >> 4) & 1));
+  auto stage_read = [&](int u) {
+    const int row = u * 8 + lr;
+    const uintx4_t x = *reinterpret_cast<const uintx4_t*>(sK + row * kColsOfBlock + ((lc ^ ((row >> 1) & 7)) << 3));
+    return u < 2 ? x : uintx4_t{x[2], x[3], x[0], x[1]};
+  };
+  const long long out0 = (static_cast<long long>(bz) * g.s + r0) * g.s;
+  const uint32_t row_bytes = 2u * static_cast<uint32_t>(g.s), out_bytes = static_cast<uint32_t>(rows_in) * row_bytes;
+  auto offset_of = [&](int block, int u) {
+    const int col = block * kColsOfBlock + lc * 8;
+    const uint32_t at = static_cast<uint32_t>(u * 8 + lr) * row_bytes + 2u * static_cast<uint32_t>(col);
+    return !RAGGED || col < g.s ? at : 0x80000000u;
+  };
+  const RowBuffer in_p = row_buffer(g.P + out0, out_bytes), out = row_buffer(g.dS + out0, out_bytes);
+  const uint64_t group0 = ((((static_cast<uint64_t>(z1) * g.global_heads + g.head0 + z2) * g.s + r0 + lr) * static_cast<uint64_t>(g.s)) >> 3) + lc;
+
+  uintx4_t dpd[NBW][4], pr[NBW][4];  // dPd (dropped elements cleared) and P in rows
+  float dot[4] = {0.f, 0.f, 0.f, 0.f};
+  auto unpacked = [](uintx4_t raw, float (&x)[8]) {
+    Raw8<bf16_t> r;
+    r.v = make_uint4(raw[0], raw[1], raw[2], raw[3]);
+    unpack(r, x);
+  };
+  // dP of eight elements: cleared ones stay zero
+  auto gradient8 = [&](uintx4_t raw, float (&x)[8]) {
+    unpacked(raw, x);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] *= g.key.scale;
+  };
+  DropoutKey keep_only = g.key;  // (1 or 0 of each element: the raw value, or cleared)
+  keep_only.scale = 1.0f;
+#pragma unroll
+  for (int t = 0; t < NBW; ++t) {
+    const int block = wave + WAVES * t;
+    if (block >= active) break;
+    const bool next = t + 1 < NBW && block + WAVES < active;
+    floatx16_t acc[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+#pragma unroll
+    for (int step = 0; step < kSteps; ++step) {
+      if (t > 0 || step > 0) wait_vmcnt<0>();
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int kk = 0; kk < KD / 16; ++kk) {
+        const Frag<true> fa = SQ::fragment(sQ + (kk >> 2) * SQ::kElems, 0, kk & 3, lane);
+#pragma unroll
+        for (int j = 0; j < 2 / kSteps; ++j) {
+          const Frag<true> fb = SK::fragment(sK + (kk >> 2) * SK::kElems, 32 * j, kk & 3, lane);
+          const int i = step * (2 / kSteps) + j;
+          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb.operand(), fa.operand(), acc[i], 0, 0, 0);
+        }
+      }
+      wait_lgkmcnt0();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (step + 1 < kSteps) load_v(block * kColsOfBlock + (step + 1) * kStepCols);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) pr[t][u] = row_buffer_load(in_p, offset_of(block, u));
+    if (block == active - 1) {  // nothing beyond the diagonal
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int col = block * kColsOfBlock + 32 * i + 8 * (r >> 2) + 4 * half + (r & 3);
+          acc[i][r] = col <= my_row ? acc[i][r] : 0.f;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd)
+        *reinterpret_cast<uint2*>(stage_to + (((4 * i + qd) ^ ((lane >> 1) & 7)) << 3)) =
+            make_uint2(pack_bf16(acc[i][4 * qd], acc[i][4 * qd + 1]), pack_bf16(acc[i][4 * qd + 2], acc[i][4 * qd + 3]));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) dpd[t][u] = stage_read(u);
+    wait_lgkmcnt0();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (next) load_v((block + WAVES) * kColsOfBlock);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float x[8], p[8];
+      unpacked(dpd[t][u], x);
+      dropout_apply8(keep_only, group0 + static_cast<uint64_t>(u * g.s + block * (kColsOfBlock / 8)), x);
+      dpd[t][u] = uintx4_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])};
+      unpacked(pr[t][u], p);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) dot[u] += (x[i] * g.key.scale) * p[i];
+    }
+  }
+  // row sums: over a row's eight lanes, then over the wavefronts in order
+#pragma unroll
+  for (int u = 0; u < 4; ++u) dot[u] = group8_sum(dot[u]);
+  if (lc == 0)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) row_sum[wave * kRowsOfBlock + u * 8 + lr] = dot[u];
+  block_barrier();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    dot[u] = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) dot[u] += row_sum[w * kRowsOfBlock + u * 8 + lr];
+  }
+#pragma unroll
+  for (int t = 0; t < NBW; ++t) {
+    const int block = wave + WAVES * t;
+    if (block >= active) break;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float x[8], p[8];
+      gradient8(dpd[t][u], x);
+      unpacked(pr[t][u], p);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = softmax_bwd(p[i], x[i], dot[u], g.scale);
+      row_buffer_store(out, offset_of(block, u), uintx4_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])});
+    }
+  }
+  if (blocks > active && wave == (active & (WAVES - 1))) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) row_buffer_store(out, offset_of(active, u), uintx4_t{0u, 0u, 0u, 0u});
+  }
+}
+
+template <int KD, bool RAGGED, int WAVES, int NBW>
+hipError_t launch(const ScoreGradientArgs& g, hipStream_t st) {
+  constexpr size_t smem = (kRowsOfBlock * KD + WAVES * kStepElems) * sizeof(bf16_t) + WAVES * kRowsOfBlock * sizeof(float);
+  auto kern = attn_score_gradient_kernel<KD, RAGGED, WAVES, NBW>;
+  LYNX_RAISE_LDS_LIMIT(kern, smem);
+  hipLaunchKernelGGL(kern, dim3(g.row_blocks * g.nz), dim3(WAVES * kWave), smem, st, g);
+  return hipGetLastError();
+}
+template <int KD, bool RAGGED>
+hipError_t launch(const ScoreGradientArgs& g, hipStream_t st) {
+  const bool few = static_cast<long long>(g.row_blocks) * g.nz <= 512;
+  if (g.s <= 256 && few) return launch<KD, RAGGED, 4, 1>(g, st);
+  if (g.s <= 512) return few ? launch<KD, RAGGED, 8, 1>(g, st) : launch<KD, RAGGED, 4, 2>(g, st);
+  return launch<KD, RAGGED, 8, 2>(g, st);
+}
+
 }  // namespace
 
 bool attn_scores_softmax_supported(int dtype, int s, int d, long long ld) {
@@ -323,6 +523,27 @@ hipError_t attn_scores_softmax_fwd(const void* q, const void* k, long long ld, v
   const bool whole_lines = sh.s % 64 == 0;
   g.stream_s = whole_lines;
   g.stream_p = whole_lines && Pd != nullptr;
+  const bool whole = sh.s % kColsOfBlock == 0 && (d == 64 || d == 128);
+  if (d <= 64) return whole ? launch<64, false>(g, st) : launch<64, true>(g, st);
+  return whole ? launch<128, false>(g, st) : launch<128, true>(g, st);
+}
+
+bool attn_score_gradient_supported(int dtype, int s, int d, long long ld) {
+  return s <= kMaxGradientSeq && attn_scores_softmax_supported(dtype, s, d, ld);
+}
+
+hipError_t attn_score_gradient(const void* dc, long long lddc, const void* v, long long ldv, const void* P, void* dS, AttnShape sh,
+                               int d, float scale, DropoutParams dp, hipStream_t st) {
+  if (!attn_score_gradient_supported(1, sh.s, d, ldv) || lddc > ldv) return hipErrorInvalidValue;
+  ScoreGradientArgs g{};
+  g.dc = static_cast<const bf16_t*>(dc); g.lddc = lddc;
+  g.v = static_cast<const bf16_t*>(v); g.ldv = ldv;
+  g.P = static_cast<const bf16_t*>(P); g.dS = static_cast<bf16_t*>(dS);
+  g.s = sh.s; g.d = d; g.a = sh.a; g.nz = sh.a * sh.b;
+  g.row_blocks = (sh.s + kRowsOfBlock - 1) / kRowsOfBlock;
+  g.global_heads = sh.global_heads; g.head0 = sh.head0;
+  g.scale = scale;
+  g.key = make_dropout_key(dp, 0);
   const bool whole = sh.s % kColsOfBlock == 0 && (d == 64 || d == 128);
   if (d <= 64) return whole ? launch<64, false>(g, st) : launch<64, true>(g, st);
   return whole ? launch<128, false>(g, st) : launch<128, true>(g, st);

@@ -67,6 +67,11 @@ hipError_t softmax_dropout_fwd(int dtype, const void* S, void* P, void* Pd, Attn
 bool attn_scores_softmax_supported(int dtype, int s, int d, long long ld);
 hipError_t attn_scores_softmax_fwd(const void* q, const void* k, long long ld, void* S, void* P, void* Pd, AttnShape sh, int d,
                                    float scale, DropoutParams dp, hipStream_t st);
+// dS = scale P (dP - sum_j dP P), dP = keep c round(dC V^T), in one launch (s <= 1024): dc [T, a * d] with row stride lddc,
+// v with ldv.
+bool attn_score_gradient_supported(int dtype, int s, int d, long long ld);
+hipError_t attn_score_gradient(const void* dc, long long lddc, const void* v, long long ldv, const void* P, void* dS, AttnShape sh,
+                               int d, float scale, DropoutParams dp, hipStream_t st);
 // Pd = keep * P * c from a resident P.
 hipError_t attn_dropout_fwd(int dtype, const void* P, void* Pd, AttnShape sh, DropoutParams dp,
                             hipStream_t st);

@@ -743,9 +743,11 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   dpd.epi.global_heads = D.a * L->cfg.tp_size;
   dpd.epi.head0 = L->cfg.tp_rank * D.a;
   const bool fused_ds = lynx::gemm_supported(dt, dpd);
-  // dV = Pd^T dC.  With the one-pass dS kernel it goes first, so that dQ and dK read dS right
+  // (elsewhere, up to s = 1024, the dot products are formed from dPd itself, in the launch that forms dPd)
+  const bool rows_ds = !fused_ds && lynx::attn_score_gradient_supported(dt, D.s, D.d, 3ll * D.p);
+  // dV = Pd^T dC.  With the one-pass dS kernels it goes first, so that dQ and dK read dS right
   // after it is written, while much of it is still in the caches (measured: dQ 0.070 -> 0.05x ms).
-  const bool dv_first = fused_ds && !cx.bk->fused_attn;
+  const bool dv_first = (fused_ds || rows_ds) && !cx.bk->fused_attn;
   auto launch_dv = [&]() -> lynx_status {
     LYNX_LAUNCH(cx, kB6DV, lynx::gemm(dt, attn_cols(act_ptr(cx, 5), temp_ptr(cx, t_dc), D.p,
                                              const_cast<char*>(col_block(dqkv, D, 2)), 3 * D.p, D),
@@ -769,6 +771,10 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
                                                  reinterpret_cast<float*>(temp_ptr(cx, t_rowdot)), D.b, D.a, D.s,
                                                  D.d, D.p, cx.st));
     LYNX_LAUNCH(cx, kB654DScores, lynx::gemm(dt, dpd, nullptr, 0, cx.st));
+  } else if (rows_ds) {
+    LYNX_LAUNCH(cx, kB654DScores, lynx::attn_score_gradient(temp_ptr(cx, t_dc), D.p, col_block(qkv, D, 2), 3ll * D.p,
+                                                            act_ptr(cx, 4), temp_ptr(cx, t_dpd), attn_shape(L), D.d,
+                                                            dpd.epi.scale, dropout_params(L), cx.st));
   } else {
     dpd.epi = lynx::GemmEpilogue{};
     LYNX_LAUNCH(cx, kB6DPd, lynx::gemm(dt, dpd, nullptr, 0, cx.st));
@@ -784,7 +790,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   free_temp(cx, &t_dc);
   free_act(cx, 5);
   free_act(cx, 6);
-  if (!fused_ds && !cx.bk->fused_attn) {
+  if (!fused_ds && !rows_ds && !cx.bk->fused_attn) {
     LYNX_LAUNCH(cx, kB54Softmax, lynx::softmax_dropout_bwd(dt, temp_ptr(cx, t_dpd), act_ptr(cx, 4),
                                               temp_ptr(cx, t_dpd), attn_shape(L),
                                               1.0f / sqrtf(static_cast<float>(D.d)), dropout_params(L),
