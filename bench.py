@@ -61,7 +61,7 @@ def slot_work(cfg):
         "b11_gelu_bwd": ("hbm", 3 * T * f * e), "b10_fc1_dgrad_wgrad": ("mfma", 2 * lin(f, h)),
         "b98_layernorm2_dropout_bwd": ("hbm", 5 * T * h * e),
         "b7_proj_dgrad_wgrad": ("mfma", 2 * lin(h, p)),
-        "b6_dpd": ("mfma", att), "b6_dv": ("mfma", att), "b54_softmax_dropout_bwd": ("hbm", 3 * tri * e),
+        "b6_dpd": ("mfma", att), "b6_dv": ("mfma", att), "b6_dpd_dv": ("mfma", 2 * att), "b54_softmax_dropout_bwd": ("hbm", 3 * tri * e),
         "b3_dq": ("mfma", att), "b3_dk": ("mfma", att), "b3_dq_dk": ("mfma", 2 * att), "b2_qkv_dgrad_wgrad": ("mfma", 2 * lin(3 * p, h)),
         "b2_bias_grad": ("hbm", T * 3 * p * e),
         "b1_layernorm1_bwd": ("hbm", 4 * T * h * e),
@@ -104,7 +104,9 @@ def phase_flops(cfg, retain_mask):
     if 6 in ops and 5 not in ops and not (retain_mask >> 5) & 1:
         ops = ops + [3]    # operator 6 ran fused with operators 3-5: the score product is part of what it regenerates
     rec = sum(w[op_slot[i]][1] for i in ops if i in op_slot)
-    bwd = sum(v for n, (kind, v) in w.items() if n.startswith("b") and kind == "mfma" and not n.endswith("_fused"))
+    joint = ("b3_dq_dk", "b6_dpd_dv")   # launches of two products that are listed on their own too
+    bwd = sum(v for n, (kind, v) in w.items()
+              if n.startswith("b") and kind == "mfma" and not n.endswith("_fused") and n not in joint)
     return fwd, rec, bwd
 
 
@@ -530,7 +532,7 @@ def main():
                              "unit": "TFLOP/s", "frac": round(ach / mfma_peak, 4)}
             # the attention products move one seq x seq tensor (the causal triangle) for a contraction
             # of only head_dim: they sit on the HBM side of the ridge, so quote them against it too
-            if name.split("/")[-1] in ("op3_scores", "op6_context", "b6_dpd", "b6_dv", "b3_dq", "b3_dk", "b3_dq_dk"):
+            if name.split("/")[-1] in ("op3_scores", "op6_context", "b6_dpd", "b6_dv", "b3_dq", "b3_dk", "b3_dq_dk", "b6_dpd_dv"):
                 tri_bytes = cfg.micro_batch * cfg.local_heads * cfg.seq * (cfg.seq + 1) // 2 * x.element_size()
                 gbs = tri_bytes / (ms * 1e-3) / 1e9
                 kernels[name].update({"hbm_achieved": round(gbs, 1), "hbm_unit": "GB/s of the causal triangle",

@@ -59,12 +59,12 @@ hipError_t gemm(int dtype, const GemmDesc& d, float* scratch, size_t scratch_byt
   return gemm_ragged(d, scratch, scratch_bytes, st);
 }
 
-hipError_t gemm_seq_pair(int dtype, const GemmDesc& rows, const GemmDesc& cols, hipStream_t st) {
-  if (dtype != 1 || !gemm_supported(dtype, rows) || !gemm_supported(dtype, cols)) return hipErrorInvalidValue;
-  if (rows.causal != kCausalKLeM || cols.causal != kCausalKGeM || rows.M != cols.M || rows.N != cols.N ||
-      rows.nz1 != cols.nz1 || rows.nz2 != cols.nz2)
-    return hipErrorInvalidValue;
-  return gemm_attention_pair(rows, cols, st);
+hipError_t gemm_seq_pair(int dtype, const GemmDesc& first, const GemmDesc& cols, hipStream_t st) {
+  if (!gemm_supported(dtype, first) || !gemm_supported(dtype, cols)) return hipErrorInvalidValue;
+  if (cols.causal != kCausalKGeM || first.nz1 != cols.nz1 || first.nz2 != cols.nz2) return hipErrorInvalidValue;
+  if (dtype != 1) return gemm_f32_two(first, cols, st);
+  if (first.causal != kCausalKLeM || first.M != cols.M || first.N != cols.N) return hipErrorInvalidValue;
+  return gemm_attention_pair(first, cols, st);
 }
 
 bool gemm_pair_supported(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {

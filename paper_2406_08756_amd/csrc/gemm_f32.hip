@@ -325,6 +325,17 @@ __global__ void __launch_bounds__(kThreads) gemm_f32_pair_kernel(GemmDesc wgrad,
   else f32_tile<true, false, BM>(dgrad, key, tile, 0);
 }
 
+// Two products of attention that do not need each other (batched alike) in one launch: few tiles each, and a launch of
+// either leaves half of the chip's wavefronts out.  Workgroups of both in turn as long as both have some.
+template <bool AK1, bool BK1, bool AK2, bool BK2, int BM>
+__global__ void __launch_bounds__(kThreads) gemm_f32_two_kernel(GemmDesc d1, GemmDesc d2, int n1, int n2) {
+  const int x = static_cast<int>(blockIdx.x), both = 2 * min(n1, n2);
+  const bool second = x < both ? (x & 1) != 0 : n2 > n1;
+  const int tile = x < both ? x >> 1 : x - both / 2;
+  if (second) f32_tile<AK2, BK2, BM>(d2, DropoutKey{}, tile, blockIdx.y);
+  else f32_tile<AK1, BK1, BM>(d1, DropoutKey{}, tile, blockIdx.y);
+}
+
 long long tiles(const GemmDesc& d, int bm) {
   const long long tm = (d.M + bm - 1) / bm, tn = (d.N + bm - 1) / bm;
   return d.causal == kCausalOutLower ? tm * (tm + 1) / 2 : tm * tn;
@@ -349,6 +360,16 @@ hipError_t launch(const GemmDesc& d, hipStream_t st) {
 template <bool AK, bool BK>
 hipError_t launch(const GemmDesc& d, hipStream_t st) {
   return small_tiles(tiles(d, 64) * d.nz1 * d.nz2) ? launch<AK, BK, 32>(d, st) : launch<AK, BK, 64>(d, st);
+}
+
+template <bool AK1, bool BK1, bool AK2, bool BK2>
+hipError_t launch_two(const GemmDesc& a, const GemmDesc& b, hipStream_t st) {
+  const int bm = small_tiles((tiles(a, 64) + tiles(b, 64)) * a.nz1 * a.nz2) ? 32 : 64;
+  const int n1 = static_cast<int>(tiles(a, bm)), n2 = static_cast<int>(tiles(b, bm));
+  const dim3 grid(n1 + n2, a.nz1 * a.nz2);
+  if (bm == 32) hipLaunchKernelGGL((gemm_f32_two_kernel<AK1, BK1, AK2, BK2, 32>), grid, dim3(kThreads), kLdsBytes, st, a, b, n1, n2);
+  else hipLaunchKernelGGL((gemm_f32_two_kernel<AK1, BK1, AK2, BK2, 64>), grid, dim3(kThreads), kLdsBytes, st, a, b, n1, n2);
+  return hipGetLastError();
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -380,6 +401,12 @@ hipError_t gemm_f32(const GemmDesc& d, hipStream_t st) {
   if (d.epi.kind == kEpiGeluBwd) return hipErrorInvalidValue;  // in a pair only
   if (d.a_sk != 1) return launch<false, false>(d, st);
   return d.b_sk == 1 ? launch<true, true>(d, st) : launch<true, false>(d, st);
+}
+
+hipError_t gemm_f32_two(const GemmDesc& a, const GemmDesc& b, hipStream_t st) {
+  if (a.nz1 != b.nz1 || a.nz2 != b.nz2 || a.epi.kind != kEpiNone || b.epi.kind != kEpiNone || a.a_sk != 1 || b.a_sk == 1)
+    return hipErrorInvalidValue;
+  return a.b_sk == 1 ? launch_two<true, true, false, false>(a, b, st) : launch_two<true, false, false, false>(a, b, st);
 }
 
 size_t gemm_f32_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad) {

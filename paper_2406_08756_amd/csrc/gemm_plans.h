@@ -25,6 +25,8 @@ hipError_t gemm_attention_pair(const GemmDesc& rows, const GemmDesc& cols, hipSt
 // fp32 storage (gemm_f32.hip).
 bool gemm_f32_supported(const GemmDesc& d);
 hipError_t gemm_f32(const GemmDesc& d, hipStream_t st);
+// two products of attention, the second with both operands MN-major, in one launch
+hipError_t gemm_f32_two(const GemmDesc& a, const GemmDesc& b, hipStream_t st);
 size_t gemm_f32_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad);
 hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, ColumnSums* sums, hipStream_t st);
 

@@ -164,7 +164,7 @@ struct Ctx {  // one pass (rehearsal or real) of a call
 enum BackwardSlot {
   kB13Dropout = 14, kB12Grads, kB11Gelu, kB10Grads, kB98LayerNormDropout, kB7Grads, kB6DPd,
   kB6DV, kB54Softmax, kB3DQ, kB3DK, kB2Grads, kB2BiasGrad, kB1LayerNorm, kB6RowDot, kB654DScores,
-  kOp36Fused, kB654DScoresFused, kB6DVFused, kColumnSums, kB3DQDK, kOp345, kNumSlots
+  kOp36Fused, kB654DScoresFused, kB6DVFused, kColumnSums, kB3DQDK, kOp345, kB6DPdDV, kNumSlots
 };
 static_assert(kNumSlots <= LYNX_PROFILE_SLOTS, "profile slots");
 static_assert(LYNX_STATIC_WORKSPACE_BYTES == lynx::kStaticWorkspaceBytes, "header and library agree on the block size");
@@ -176,7 +176,7 @@ const char* const kSlotNames[kNumSlots] = {
     "b98_layernorm2_dropout_bwd", "b7_proj_dgrad_wgrad", "b6_dpd", "b6_dv", "b54_softmax_dropout_bwd", "b3_dq",
     "b3_dk", "b2_qkv_dgrad_wgrad", "b2_bias_grad", "b1_layernorm1_bwd", "b6_rowdot", "b654_dscores",
     "op3456_attention_fused", "b654_dscores_fused", "b6_dv_fused", "b_column_sums", "b3_dq_dk",
-    "op345_scores_softmax"};
+    "op345_scores_softmax", "b6_dpd_dv"};
 
 char* act_ptr(const Ctx& cx, int i) {
   if (i == 0) return const_cast<char*>(static_cast<const char*>(cx.L->x));
@@ -748,10 +748,10 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   // dV = Pd^T dC.  With the one-pass dS kernels it goes first, so that dQ and dK read dS right
   // after it is written, while much of it is still in the caches (measured: dQ 0.070 -> 0.05x ms).
   const bool dv_first = (fused_ds || rows_ds) && !cx.bk->fused_attn;
+  const GemmDesc dv = attn_cols(act_ptr(cx, 5), temp_ptr(cx, t_dc), D.p, const_cast<char*>(col_block(dqkv, D, 2)), 3 * D.p, D);
+  const bool dpd_with_dv = dt == LYNX_F32;  // one launch
   auto launch_dv = [&]() -> lynx_status {
-    LYNX_LAUNCH(cx, kB6DV, lynx::gemm(dt, attn_cols(act_ptr(cx, 5), temp_ptr(cx, t_dc), D.p,
-                                             const_cast<char*>(col_block(dqkv, D, 2)), 3 * D.p, D),
-                               nullptr, 0, cx.st));
+    LYNX_LAUNCH(cx, kB6DV, lynx::gemm(dt, dv, nullptr, 0, cx.st));
     return LYNX_OK;
   };
   if (dv_first) {
@@ -777,14 +777,18 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
                                                             dpd.epi.scale, dropout_params(L), cx.st));
   } else {
     dpd.epi = lynx::GemmEpilogue{};
-    LYNX_LAUNCH(cx, kB6DPd, lynx::gemm(dt, dpd, nullptr, 0, cx.st));
+    if (dpd_with_dv) {
+      LYNX_LAUNCH(cx, kB6DPdDV, lynx::gemm_seq_pair(dt, dpd, dv, cx.st));
+    } else {
+      LYNX_LAUNCH(cx, kB6DPd, lynx::gemm(dt, dpd, nullptr, 0, cx.st));
+    }
   }
   free_temp(cx, &t_rowdot);
   if (cx.bk->fused_attn) {
     LYNX_LAUNCH(cx, kB6DVFused, lynx::attn_fused_bwd_dv(qkv, 3 * D.p, temp_ptr(cx, t_dc), D.p, attn_stats_ptr(cx), dqkv,
                                                    3 * D.p, attn_shape(L), D.d, 1.0f / sqrtf(static_cast<float>(D.d)),
                                                    dropout_params(L), cx.st));
-  } else if (!dv_first) {
+  } else if (!dv_first && !dpd_with_dv) {
     LYNX_TRY(launch_dv());
   }
   free_temp(cx, &t_dc);
@@ -803,12 +807,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
                                 const_cast<char*>(col_block(dqkv, D, 0)), 3 * D.p, D);
   const GemmDesc dk = attn_cols(temp_ptr(cx, t_dpd), col_block(qkv, D, 0), 3 * D.p,
                                 const_cast<char*>(col_block(dqkv, D, 1)), 3 * D.p, D);
-  if (dt == LYNX_BF16) {
-    LYNX_LAUNCH(cx, kB3DQDK, lynx::gemm_seq_pair(dt, dq, dk, cx.st));
-  } else {
-    LYNX_LAUNCH(cx, kB3DQ, lynx::gemm(dt, dq, nullptr, 0, cx.st));
-    LYNX_LAUNCH(cx, kB3DK, lynx::gemm(dt, dk, nullptr, 0, cx.st));
-  }
+  LYNX_LAUNCH(cx, kB3DQDK, lynx::gemm_seq_pair(dt, dq, dk, cx.st));
   free_temp(cx, &t_dpd);
   free_act(cx, 3);
   LYNX_TRY(tap(cx, 2, dqkv));
