@@ -164,7 +164,7 @@ struct Ctx {  // one pass (rehearsal or real) of a call
 enum BackwardSlot {
   kB13Dropout = 14, kB12Grads, kB11Gelu, kB10Grads, kB98LayerNormDropout, kB7Grads, kB6DPd,
   kB6DV, kB54Softmax, kB3DQ, kB3DK, kB2Grads, kB2BiasGrad, kB1LayerNorm, kB6RowDot, kB654DScores,
-  kOp36Fused, kB654DScoresFused, kB6DVFused, kColumnSums, kB3DQDK, kOp345, kB6DPdDV, kNumSlots
+  kOp36Fused, kB654DScoresFused, kB6DVFused, kColumnSums, kNumSlots
 };
 static_assert(kNumSlots <= LYNX_PROFILE_SLOTS, "profile slots");
 static_assert(LYNX_STATIC_WORKSPACE_BYTES == lynx::kStaticWorkspaceBytes, "header and library agree on the block size");
@@ -175,8 +175,7 @@ const char* const kSlotNames[kNumSlots] = {
     "b12_fc2_dgrad_wgrad", "b11_gelu_bwd", "b10_fc1_dgrad_wgrad",
     "b98_layernorm2_dropout_bwd", "b7_proj_dgrad_wgrad", "b6_dpd", "b6_dv", "b54_softmax_dropout_bwd", "b3_dq",
     "b3_dk", "b2_qkv_dgrad_wgrad", "b2_bias_grad", "b1_layernorm1_bwd", "b6_rowdot", "b654_dscores",
-    "op3456_attention_fused", "b654_dscores_fused", "b6_dv_fused", "b_column_sums", "b3_dq_dk",
-    "op345_scores_softmax", "b6_dpd_dv"};
+    "op3456_attention_fused", "b654_dscores_fused", "b6_dv_fused", "b_column_sums"};
 
 char* act_ptr(const Ctx& cx, int i) {
   if (i == 0) return const_cast<char*>(static_cast<const char*>(cx.L->x));
@@ -467,7 +466,7 @@ lynx_status run_fused_attention(Ctx& cx) {
 
 // Operators 3 and 4, and 5 where `with_pd`, as one launch (attn_softmax.hip): S is written only if the policy keeps it
 // (its place in the workspace is taken either way, so that every block lies where the separate operators put it),
-// P if `write_p`.
+// P if `write_p`.  Timed in slot 4.
 bool can_fuse_scores(const Ctx& cx) {
   const Dims& D = cx.L->D;
   return lynx::attn_scores_softmax_supported(D.dtype, D.s, D.d, 3ll * D.p);
@@ -479,7 +478,7 @@ lynx_status run_fused_scores(Ctx& cx, bool write_p, bool with_pd) {
   LYNX_TRY(alloc_act(cx, 3));
   if (write_p) LYNX_TRY(alloc_act(cx, 4));
   if (with_pd) LYNX_TRY(alloc_act(cx, 5));
-  LYNX_LAUNCH(cx, kOp345, lynx::attn_scores_softmax_fwd(col_block(act_ptr(cx, 2), D, 0), col_block(act_ptr(cx, 2), D, 1), 3ll * D.p,
+  LYNX_LAUNCH(cx, 4, lynx::attn_scores_softmax_fwd(col_block(act_ptr(cx, 2), D, 0), col_block(act_ptr(cx, 2), D, 1), 3ll * D.p,
                                                keep_s ? act_ptr(cx, 3) : nullptr, write_p ? act_ptr(cx, 4) : nullptr,
                                                with_pd ? act_ptr(cx, 5) : nullptr, attn_shape(L), D.d,
                                                1.0f / sqrtf(static_cast<float>(D.d)), dropout_params(L), cx.st));
@@ -778,7 +777,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   } else {
     dpd.epi = lynx::GemmEpilogue{};
     if (dpd_with_dv) {
-      LYNX_LAUNCH(cx, kB6DPdDV, lynx::gemm_seq_pair(dt, dpd, dv, cx.st));
+      LYNX_LAUNCH(cx, kB6DPd, lynx::gemm_seq_pair(dt, dpd, dv, cx.st));
     } else {
       LYNX_LAUNCH(cx, kB6DPd, lynx::gemm(dt, dpd, nullptr, 0, cx.st));
     }
@@ -807,7 +806,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
                                 const_cast<char*>(col_block(dqkv, D, 0)), 3 * D.p, D);
   const GemmDesc dk = attn_cols(temp_ptr(cx, t_dpd), col_block(qkv, D, 0), 3 * D.p,
                                 const_cast<char*>(col_block(dqkv, D, 1)), 3 * D.p, D);
-  LYNX_LAUNCH(cx, kB3DQDK, lynx::gemm_seq_pair(dt, dq, dk, cx.st));
+  LYNX_LAUNCH(cx, kB3DQ, lynx::gemm_seq_pair(dt, dq, dk, cx.st));
   free_temp(cx, &t_dpd);
   free_act(cx, 3);
   LYNX_TRY(tap(cx, 2, dqkv));
