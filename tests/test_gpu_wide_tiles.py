@@ -15,9 +15,10 @@ B = pytest.importorskip("paper_2406_08756_amd.binding")
 
 pytestmark = pytest.mark.gpu
 
-# (hidden, heads, head_dim, ffn, seq, micro_batch), bf16
+# (hidden, heads, head_dim, ffn, seq, micro_batch), bf16; the last: rows of 2^22 elements and more, which the tile with
+# 64-bit load offsets takes
 SHAPES = ([(h, 8, 64, 1032, 128, 64) for h in (64, 72, 128, 136, 192, 200, 256, 264, 328, 392)] +
-          [(h, 8, 64, 2656, 248, 12) for h in (520, 576, 584)])
+          [(h, 8, 64, 2656, 248, 12) for h in (520, 576, 584)] + [(8, 1, 8, (1 << 22) + 72, 24, 1)])
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "h%d_f%d" % (s[0], s[3]))
