@@ -96,11 +96,14 @@ struct Book {
   // sum of backward at once (each is finished before the next); 2, also the partial sums of contractions that
   // are cut for speed (their ranges are summed one after the other); 3, also the fusion of operators 7 + 8 and
   // 12 + 13, which places the activations after them elsewhere; 4, also backward's scratch lies at the upper end,
-  // where it leaves the holes to the blocks after it.  It can change within a run (two_pass) and differ from one
-  // policy to the next, so no value may depend on it: every level sums in the same order.
+  // where it leaves the holes to the blocks after it; 5, of all these only the partial sums of cut
+  // contractions (the column sums' own blocks are small and fit holes that one scratch for them all does not).
+  // It can change within a run (two_pass) and differ from one policy to the next, so no value may depend on it:
+  // every level sums in the same order.
   int thrift = 0;
 };
-constexpr int kNoDeferredSums = 1, kSerial = 2, kUnfused = 3, kScratchHigh = 4, kMaxThrift = kScratchHigh;
+constexpr int kNoDeferredSums = 1, kSerial = 2, kUnfused = 3, kScratchHigh = 4, kSerialOnly = 5,
+              kMaxThrift = kSerialOnly;
 
 }  // namespace
 
@@ -436,7 +439,7 @@ GemmDesc fused_linear_desc(Ctx& cx, int lin, bool keep_product) {
 }
 bool can_fuse_linear(const Ctx& cx, int lin) {
   const Dims& D = cx.L->D;
-  if (cx.bk->thrift >= kUnfused) return false;
+  if (cx.bk->thrift >= kUnfused && cx.bk->thrift != kSerialOnly) return false;
   // shapes only (pointers are 256-byte aligned arena blocks or checked caller buffers)
   GemmDesc g = linear_fwd(reinterpret_cast<const void*>(256), reinterpret_cast<const void*>(256), nullptr,
                           reinterpret_cast<void*>(256), D.T, D.h, lin == 7 ? D.p : D.f);
@@ -610,7 +613,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   const int widest = D.h > 3 * D.p ? (D.h > D.f ? D.h : D.f) : (3 * D.p > D.f ? 3 * D.p : D.f);
   // The second stage of the eight column sums (bias and LayerNorm gradients) is one launch at the end;
   // without the room for all their partial sums, each producer reuses `scr` and is finished at once.
-  const bool defer = cx.bk->thrift < kNoDeferredSums;
+  const bool defer = cx.bk->thrift < kNoDeferredSums || cx.bk->thrift == kSerialOnly;
   lynx::ColumnSums sums;
   size_t scratch_bytes = 0;
   if (!defer) {
@@ -632,7 +635,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
       }
   }
   Temp scratch, t_dv2, t_du, t_dy2, t_dx2, t_do, t_dc, t_dpd, t_dqkv, t_dy1;
-  LYNX_TRY(alloc_temp(cx, scratch_bytes, &scratch, cx.bk->thrift >= kScratchHigh));
+  LYNX_TRY(alloc_temp(cx, scratch_bytes, &scratch, cx.bk->thrift == kScratchHigh));
   float* scr = reinterpret_cast<float*>(temp_ptr(cx, scratch));
   Temp t_part[4];  // partial sums of: b2, b1 (two producers), LayerNorm 2 with bo, bqkv and LayerNorm 1
   float* part = scr;
