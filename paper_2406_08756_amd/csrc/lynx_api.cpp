@@ -872,14 +872,16 @@ int thrift_for(lynx_layer_s* L, uint32_t retain) {
 
 // Rehearse on a copy, then run for real.  The run's thrift was chosen for forward -> backward, and segments in
 // between move the blocks: a call that does not fit at that level is tried at those above it and then at those
-// below it (more thrift is another placement, not always a smaller one).  No value depends on the level.
+// below it (more thrift is another placement, not always a smaller one), at kSerialOnly last unless the run began
+// there: it is for what fits no other level.  No value depends on the level.
 template <typename F>
 lynx_status two_pass(lynx_layer_s* L, hipStream_t st, F&& body) {
   const int base = L->book.thrift;
   lynx_status s = LYNX_ERR_OOM;
   int level = base;
+  const int top = base == kSerialOnly ? kSerialOnly : kScratchHigh;
   for (int k = 0; s == LYNX_ERR_OOM && k <= kMaxThrift; ++k) {
-    level = base + k <= kMaxThrift ? base + k : kMaxThrift - k;
+    level = base + k <= top ? base + k : k <= top ? top - k : kSerialOnly;
     Book copy = L->book;
     copy.thrift = level;
     Ctx rehearsal{L, &copy, false, st};
