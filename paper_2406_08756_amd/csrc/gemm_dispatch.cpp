@@ -96,6 +96,12 @@ size_t gemm_pair_colsum_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& 
   return static_cast<size_t>(rows) * static_cast<size_t>(dgrad.N) * sizeof(float);
 }
 
+size_t gemm_pair_colsum_least_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  if (dtype != 1) return gemm_f32_pair_colsum_bytes(dgrad, wgrad);
+  const int cols = (dgrad.N / 8 + 3) / 4 * 8;  // a quarter of the columns, in octets
+  return static_cast<size_t>(ragged_pair(dgrad, wgrad).colsum_rows) * static_cast<size_t>(cols) * sizeof(float);
+}
+
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,
                      size_t scratch_bytes, ColumnSums* sums, hipStream_t st) {
   if (!gemm_pair_supported(dtype, dgrad, wgrad)) return hipErrorInvalidValue;

@@ -459,15 +459,40 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   d.k_splits = ceil_div(d.K, p.d_per);
   d.k_per = p.d_per;
   const size_t w_bytes = partial_bytes(w.M, w.N, w.k_splits), d_bytes = partial_bytes(d.M, d.N, d.k_splits);
-  const bool serial = dgrad.serial && w_bytes + d_bytes > 0, far = is_far(dgrad) || is_far(wgrad);
+  const int colsum_rows = ceil_div(dgrad.M, kTileWaveRows[p.tile]);
+  // columns whose GeLU partials have room at once
+  int at_once = dgrad.N;
+  if (dgrad.epi.kind == kEpiGeluBwd) {
+    const size_t room = dgrad.epi.colsum_bytes / (static_cast<size_t>(colsum_rows) * sizeof(float));
+    if (room < static_cast<size_t>(dgrad.N)) at_once = static_cast<int>(room) / 8 * 8;
+    if (at_once == 0) return hipErrorInvalidValue;
+    if (at_once < dgrad.N && at_once > 256) at_once = at_once / 256 * 256;  // whole tiles
+  }
+  const bool in_parts = at_once < dgrad.N, far = is_far(dgrad) || is_far(wgrad);
+  const bool serial = dgrad.serial && w_bytes + d_bytes > 0;
+  if (in_parts && !dgrad.serial && w_bytes > 0) return hipErrorInvalidValue;
   if (w_bytes + d_bytes > 0 && !serial && (scratch == nullptr || scratch_bytes < w_bytes + d_bytes)) return hipErrorInvalidValue;
   hipError_t e;
-  if (serial) {
+  if (serial || in_parts) {
     // (the product that is not cut in the plan's tile: the GeLU epilogue's column partials depend on it)
     const bool w_cut = w.k_splits > 1, d_cut = d.k_splits > 1;
     w.k_splits = d.k_splits = 1;
     const int w_tile = p.tile == kT256 || p.tile == kT256x128 ? kT128 : p.tile;  // (no larger one for two MN-major operands)
     e = w_cut ? launch_serial<false, false>(far, w, st) : launch_tile<false, false>(w_tile, far, w, st);
+    if (in_parts) {
+      for (int n0 = 0; e == hipSuccess && n0 < dgrad.N; n0 += at_once) {
+        MfmaGemmArgs part = d;
+        part.N = n0 + at_once < dgrad.N ? at_once : dgrad.N - n0;
+        part.B = d.B + n0;
+        part.C = d.C + n0;
+        part.aux = d.aux + n0;
+        e = launch_tile<true, false>(p.tile, far, part, st);
+        ColumnSums of_part;
+        if (e == hipSuccess) e = of_part.add(part.colsum_partial, static_cast<bf16_t*>(dgrad.epi.colsum_out) + n0, colsum_rows, part.N);
+        if (e == hipSuccess) e = finish_column_sums(1, &of_part, st);
+      }
+      return e;
+    }
     if (e == hipSuccess) e = d_cut ? launch_serial<true, false>(far, d, st) : launch_tile<true, false>(p.tile, far, d, st);
   } else {
     w.partial = scratch;
@@ -484,7 +509,7 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   else if (w.k_splits > 1) e = launch_finish(&w, nullptr, st);
   else if (d.k_splits > 1) e = launch_finish(&d, nullptr, st);
   if (e != hipSuccess || dgrad.epi.kind != kEpiGeluBwd) return e;
-  return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, ceil_div(dgrad.M, kTileWaveRows[p.tile]), dgrad.N);
+  return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, colsum_rows, dgrad.N);
 }
 
 }  // namespace lynx

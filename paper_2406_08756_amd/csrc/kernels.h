@@ -145,8 +145,9 @@ enum GemmEpilogueKind : int {
   // stride = c_sm).  Bit-identical to bias_dropout_add_fwd run on a stored P.
   kEpiBiasDropoutAdd = 1,
   // GeLU backward (input gradient of FC2 only, inside gemm_pair): C = P gelu'(aux) and
-  // colsum_out[n] = sum_m C[m, n] (the FC1 bias gradient): partial sums to `colsum_partial`
-  // (gemm_pair_colsum_bytes), second stage to the pair's `sums`.
+  // colsum_out[n] = sum_m C[m, n] (the FC1 bias gradient): partial sums to `colsum_partial`, second stage to the
+  // pair's `sums`.  With room for gemm_pair_colsum_bytes (`colsum_bytes`) in one launch; with less (at least
+  // gemm_pair_colsum_least_bytes) in ranges of columns, each with both of its stages before the next: the same bits.
   kEpiGeluBwd = 2,
   // dropout + softmax backward (B5 + B4) on the score-shaped product dPd = dC V^T (causal,
   // batched): C = dS = scale aux (keep c P - rowdot), aux = the softmax output P in the layout
@@ -163,6 +164,7 @@ struct GemmEpilogue {
   int site;               // (1)
   DropoutParams dp;       // (1)
   float* colsum_partial;  // (2)
+  size_t colsum_bytes;    // (2)
   void* colsum_out;       // (2) [N], storage dtype
   const float* rowdot;    // (4)
   float scale;            // (4)
@@ -204,5 +206,6 @@ size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc&
 // Whether the input gradient should carry the GeLU backward (kEpiGeluBwd): supported, and it pays.
 bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);
 size_t gemm_pair_colsum_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // its column partials
+size_t gemm_pair_colsum_least_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);
 
 }  // namespace lynx

@@ -92,18 +92,37 @@ struct Book {
   // the policy keeps none of S, P, Pd and the shape is one the fused attention kernels take:
   // operators 3-5 never run, operator 6 reads QKV alone
   bool fused_attn = false;
-  // what the run goes without because the workspace has no room for it: 1, partial sums of every column
-  // sum of backward at once (each is finished before the next); 2, also the partial sums of contractions that
-  // are cut for speed (their ranges are summed one after the other); 3, also the fusion of operators 7 + 8 and
-  // 12 + 13, which places the activations after them elsewhere; 4, also backward's scratch lies at the upper end,
-  // where it leaves the holes to the blocks after it; 5, of all these only the partial sums of cut
-  // contractions (the column sums' own blocks are small and fit holes that one scratch for them all does not).
-  // It can change within a run (two_pass) and differ from one policy to the next, so no value may depend on it:
-  // every level sums in the same order.
+  // Index into kGoesWithout: what the run goes without because the workspace has no room for it.  It can change
+  // within a run (two_pass) and differ from one policy to the next, so no value may depend on it: every level sums
+  // in the same order.
   int thrift = 0;
 };
-constexpr int kNoDeferredSums = 1, kSerial = 2, kUnfused = 3, kScratchHigh = 4, kSerialOnly = 5,
-              kMaxThrift = kSerialOnly;
+
+enum Thrift : unsigned {
+  kSumsApart = 1,     // partial sums of every column sum of backward at once: each is finished before the next
+  kSerial = 2,        // partial sums of contractions that are cut for speed: their ranges are summed one after the other
+  kUnfused = 4,       // the fusion of operators 7 + 8 and 12 + 13, which places the activations after them elsewhere
+  kScratchHigh = 8,   // backward's scratch at the lower end: at the upper one it leaves the holes to the blocks after it
+  kGeluInParts = 16,  // the column partials of the GeLU store pass at once, held until all column sums are finished
+  kEarlyHigh = 32,    // dV2, dY2 and dO, which are gone before dS takes its place, at the lower end
+};
+// The levels.  Less is not always a smaller placement: contractions in series beside deferred column sums, whose own
+// blocks are small and fit holes that one scratch for them all does not, fit where nothing before them does.  A run
+// begins at one of the first five (thrift_for); the others are for a call that fits none of those.  The GeLU partials
+// depend on the tile that FC2's gradients are computed in, so without those of kGeluInParts a workspace that was large
+// enough for one choice of tiles would be too small for another.
+constexpr unsigned kGoesWithout[] = {0,
+                                     kSumsApart,
+                                     kSumsApart | kSerial,
+                                     kSumsApart | kSerial | kUnfused,
+                                     kSumsApart | kSerial | kUnfused | kScratchHigh,
+                                     kSerial,
+                                     kSerial | kGeluInParts,
+                                     kSerial | kUnfused | kGeluInParts,
+                                     kSerial | kGeluInParts | kEarlyHigh};
+constexpr int kLevels = sizeof(kGoesWithout) / sizeof(kGoesWithout[0]);
+constexpr int kLevelSerial = 2, kLevelScratchHigh = 4;
+bool without(const Book& bk, Thrift what) { return (kGoesWithout[bk.thrift] & what) != 0; }
 
 }  // namespace
 
@@ -127,8 +146,8 @@ struct lynx_layer_s {
   // parity aid: where backward copies the gradient with respect to activation A_i (null: nowhere)
   void* grad_tap[LYNX_NUM_ACTIVATIONS] = {};
   int static_device = -1;  // >= 0: the workspace is that device's built-in block
-  // per retain mask (bits 1..12) the least Book::thrift at which forward -> backward fits the workspace, -1: not
-  // rehearsed yet.  A byte for each of the 4096 masks: a caller may change policy from one micro-batch to the next.
+  // per retain mask (bits 1..12) the Book::thrift that thrift_for has found, -1: not rehearsed yet.  A byte for each of
+  // the 4096 masks: a caller may change policy from one micro-batch to the next.
   signed char thrift[1 << 12];
   lynx_layer_s() { memset(thrift, -1, sizeof(thrift)); }
 };
@@ -326,7 +345,7 @@ GemmDesc attn_cols(const void* sq, const void* y, long long ldy, void* out, long
 // One linear product, with scratch of its own for the partial sums of a cut contraction.
 lynx_status run_linear(Ctx& cx, int slot, GemmDesc g) {
   const int dt = cx.L->D.dtype;
-  g.serial = cx.bk->thrift >= kSerial;
+  g.serial = without(*cx.bk, kSerial);
   const size_t bytes = lynx::gemm_scratch_bytes(dt, g);
   Temp scratch;
   if (bytes > 0) LYNX_TRY(alloc_temp(cx, bytes, &scratch));
@@ -439,7 +458,7 @@ GemmDesc fused_linear_desc(Ctx& cx, int lin, bool keep_product) {
 }
 bool can_fuse_linear(const Ctx& cx, int lin) {
   const Dims& D = cx.L->D;
-  if (cx.bk->thrift >= kUnfused && cx.bk->thrift != kSerialOnly) return false;
+  if (without(*cx.bk, kUnfused)) return false;
   // shapes only (pointers are 256-byte aligned arena blocks or checked caller buffers)
   GemmDesc g = linear_fwd(reinterpret_cast<const void*>(256), reinterpret_cast<const void*>(256), nullptr,
                           reinterpret_cast<void*>(256), D.T, D.h, lin == 7 ? D.p : D.f);
@@ -613,7 +632,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   const int widest = D.h > 3 * D.p ? (D.h > D.f ? D.h : D.f) : (3 * D.p > D.f ? 3 * D.p : D.f);
   // The second stage of the eight column sums (bias and LayerNorm gradients) is one launch at the end;
   // without the room for all their partial sums, each producer reuses `scr` and is finished at once.
-  const bool defer = cx.bk->thrift < kNoDeferredSums || cx.bk->thrift == kSerialOnly;
+  const bool defer = !without(*cx.bk, kSumsApart);
   lynx::ColumnSums sums;
   size_t scratch_bytes = 0;
   if (!defer) {
@@ -629,14 +648,15 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
         GemmDesc d = linear_dgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
         GemmDesc g = linear_wgrad(nullptr, nullptr, nullptr, D.T, nk[0], nk[1]);
         d.epi.kind = gelu ? lynx::kEpiGeluBwd : lynx::kEpiNone;
-        d.serial = g.serial = cx.bk->thrift >= kSerial;
+        d.serial = g.serial = without(*cx.bk, kSerial);
         const size_t b = lynx::gemm_pair_scratch_bytes(dt, d, g);
         if (b > scratch_bytes) scratch_bytes = b;
       }
   }
   Temp scratch, t_dv2, t_du, t_dy2, t_dx2, t_do, t_dc, t_dpd, t_dqkv, t_dy1;
-  LYNX_TRY(alloc_temp(cx, scratch_bytes, &scratch, cx.bk->thrift == kScratchHigh));
+  LYNX_TRY(alloc_temp(cx, scratch_bytes, &scratch, without(*cx.bk, kScratchHigh)));
   float* scr = reinterpret_cast<float*>(temp_ptr(cx, scratch));
+  const bool early_high = without(*cx.bk, kEarlyHigh);
   Temp t_part[4];  // partial sums of: b2, b1 (two producers), LayerNorm 2 with bo, bqkv and LayerNorm 1
   float* part = scr;
   auto alloc_partials = [&](int i, size_t bytes) -> lynx_status {
@@ -645,74 +665,76 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
     part = reinterpret_cast<float*>(temp_ptr(cx, t_part[i]));
     return LYNX_OK;
   };
-  // after a producer's launch, and timed with it: its sums, where they cannot wait
-  auto summed = [&](hipError_t e) { return e != hipSuccess || defer ? e : lynx::finish_column_sums(dt, &sums, cx.st); };
+  // after a producer's launch, and timed with it: the sums asked for so far, where they cannot wait
+  auto summed = [&](hipError_t e, bool waits) { return e != hipSuccess || waits ? e : lynx::finish_column_sums(dt, &sums, cx.st); };
   // both gradients of a linear layer
-  auto launch_pair = [&](int slot, GemmDesc dg, GemmDesc wg) -> lynx_status {
-    dg.serial = wg.serial = cx.bk->thrift >= kSerial;
-    LYNX_LAUNCH(cx, slot, summed(lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, &sums, cx.st)));
+  auto launch_pair = [&](int slot, GemmDesc dg, GemmDesc wg, bool waits) -> lynx_status {
+    dg.serial = wg.serial = without(*cx.bk, kSerial);
+    LYNX_LAUNCH(cx, slot, summed(lynx::gemm_pair(dt, dg, wg, scr, scratch_bytes, &sums, cx.st), waits));
     return LYNX_OK;
   };
   const size_t th = static_cast<size_t>(D.T) * D.h * e, tf = static_cast<size_t>(D.T) * D.f * e;
 
   // B13: OUT = X2 + keep2 (V2 + b2) c
-  LYNX_TRY(alloc_temp(cx, th, &t_dv2));
+  LYNX_TRY(alloc_temp(cx, th, &t_dv2, early_high));
   LYNX_TRY(alloc_partials(0, lynx::colsum_scratch_bytes(D.T, D.h)));
   LYNX_LAUNCH(cx, kB13Dropout, summed(lynx::dropout_bwd(dt, d_out, temp_ptr(cx, t_dv2), gr->b2, part, D.T, D.h, 2,
-                                    dropout_params(L), &sums, cx.st)));
+                                    dropout_params(L), &sums, cx.st), defer));
   LYNX_TRY(tap(cx, 12, temp_ptr(cx, t_dv2)));
   // B12: V2 = G W2^T, and B11: G = gelu(U).  Where it pays, the store pass of the input gradient
   // multiplies by gelu'(U) and sums the columns (the FC1 bias gradient), so dG is never written and
   // the GeLU backward never runs as a kernel; elsewhere that kernel replaces dG by dU in place.
   LYNX_TRY(alloc_temp(cx, tf, &t_du));
+  const bool gelu_in_parts = without(*cx.bk, kGeluInParts), gelu_waits = defer && !gelu_in_parts;
   {
     GemmDesc dg = linear_dgrad(temp_ptr(cx, t_dv2), w.w2, temp_ptr(cx, t_du), D.T, D.h, D.f);
     GemmDesc wg = linear_wgrad(temp_ptr(cx, t_dv2), act_ptr(cx, 11), gr->w2, D.T, D.h, D.f);
     dg.epi.kind = lynx::kEpiGeluBwd;
-    dg.serial = wg.serial = cx.bk->thrift >= kSerial;
+    dg.serial = wg.serial = without(*cx.bk, kSerial);
     dg.epi.aux = act_ptr(cx, 10);
     dg.epi.aux_ld = D.f;
     dg.epi.colsum_partial = scr;
     dg.epi.colsum_out = gr->b1;
     if (lynx::gemm_pair_absorbs_gelu(dt, dg, wg)) {
       // (not in `scr` where the same launch leaves the partial sums of a cut weight gradient there)
-      const size_t colsum_bytes = lynx::gemm_pair_colsum_bytes(dt, dg, wg);
-      if (defer || colsum_bytes > scratch_bytes || lynx::gemm_pair_scratch_bytes(dt, dg, wg) > 0) {
-        LYNX_TRY(alloc_temp(cx, colsum_bytes, &t_part[1]));
+      dg.epi.colsum_bytes = gelu_in_parts ? lynx::gemm_pair_colsum_least_bytes(dt, dg, wg) : lynx::gemm_pair_colsum_bytes(dt, dg, wg);
+      if (defer || dg.epi.colsum_bytes > scratch_bytes || lynx::gemm_pair_scratch_bytes(dt, dg, wg) > 0) {
+        LYNX_TRY(alloc_temp(cx, dg.epi.colsum_bytes, &t_part[1]));
         dg.epi.colsum_partial = reinterpret_cast<float*>(temp_ptr(cx, t_part[1]));
       }
-      LYNX_TRY(launch_pair(kB12Grads, dg, wg));
-      if (!defer) free_temp(cx, &t_part[1]);
+      LYNX_TRY(launch_pair(kB12Grads, dg, wg, gelu_waits));
+      if (!gelu_waits) free_temp(cx, &t_part[1]);
       free_temp(cx, &t_dv2);
       free_act(cx, 11);
     } else {
       dg.epi = lynx::GemmEpilogue{};
-      LYNX_TRY(launch_pair(kB12Grads, dg, wg));
+      LYNX_TRY(launch_pair(kB12Grads, dg, wg, defer));
       free_temp(cx, &t_dv2);
       free_act(cx, 11);
       LYNX_TRY(alloc_partials(1, lynx::colsum_scratch_bytes(D.T, D.f)));
       LYNX_LAUNCH(cx, kB11Gelu, summed(lynx::gelu_bwd(dt, temp_ptr(cx, t_du), act_ptr(cx, 10), temp_ptr(cx, t_du),
-                                               gr->b1, part, D.T, D.f, &sums, cx.st)));
+                                               gr->b1, part, D.T, D.f, &sums, cx.st), gelu_waits));
+      if (!gelu_waits) free_temp(cx, &t_part[1]);
     }
   }
   free_act(cx, 10);
   LYNX_TRY(tap(cx, 10, temp_ptr(cx, t_du)));
   // B10: U = Y2 W1^T + b1
-  LYNX_TRY(alloc_temp(cx, th, &t_dy2));
+  LYNX_TRY(alloc_temp(cx, th, &t_dy2, early_high));
   LYNX_TRY(launch_pair(kB10Grads, linear_dgrad(temp_ptr(cx, t_du), w.w1, temp_ptr(cx, t_dy2), D.T, D.f, D.h),
-                       linear_wgrad(temp_ptr(cx, t_du), act_ptr(cx, 9), gr->w1, D.T, D.f, D.h)));
+                       linear_wgrad(temp_ptr(cx, t_du), act_ptr(cx, 9), gr->w1, D.T, D.f, D.h), defer));
   free_temp(cx, &t_du);
   LYNX_TRY(tap(cx, 9, temp_ptr(cx, t_dy2)));
   // B9: Y2 = LN2(X2); dX2 = dOUT + dLN.  B8 in the same pass: X2 = X + keep1 (O + bo) c,
   // so dO = keep1 c dX2 and dbo = its column sums
   LYNX_TRY(alloc_temp(cx, th, &t_dx2));
-  LYNX_TRY(alloc_temp(cx, th, &t_do));
+  LYNX_TRY(alloc_temp(cx, th, &t_do, early_high));
   LYNX_TRY(alloc_partials(2, lynx::layernorm_bwd_scratch_bytes(D.T, D.h, true)));
   LYNX_LAUNCH(cx, kB98LayerNormDropout,
               summed(lynx::layernorm_bwd_dropout_bwd(dt, temp_ptr(cx, t_dy2), act_ptr(cx, 8), stats_ptr(cx, 9),
                                               stats_ptr(cx, 9) + D.T, w.g2, d_out, temp_ptr(cx, t_dx2), gr->g2,
                                               gr->be2, temp_ptr(cx, t_do), gr->bo, part, D.T, D.h, 1,
-                                              dropout_params(L), &sums, cx.st)));
+                                              dropout_params(L), &sums, cx.st), defer));
   LYNX_TRY(tap(cx, 8, temp_ptr(cx, t_dx2)));
   LYNX_TRY(tap(cx, 7, temp_ptr(cx, t_do)));
   free_temp(cx, &t_dy2);
@@ -721,7 +743,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   // B7: O = C Wo^T
   LYNX_TRY(alloc_temp(cx, static_cast<size_t>(D.T) * D.p * e, &t_dc));
   LYNX_TRY(launch_pair(kB7Grads, linear_dgrad(temp_ptr(cx, t_do), w.wo, temp_ptr(cx, t_dc), D.T, D.h, D.p),
-                       linear_wgrad(temp_ptr(cx, t_do), act_ptr(cx, 6), gr->wo, D.T, D.h, D.p)));
+                       linear_wgrad(temp_ptr(cx, t_do), act_ptr(cx, 6), gr->wo, D.T, D.h, D.p), defer));
   free_temp(cx, &t_do);
   LYNX_TRY(tap(cx, 6, temp_ptr(cx, t_dc)));
   // B6: C = Pd V (C itself is read once more below, for the row dot products)
@@ -816,10 +838,10 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   // B2: QKV = Y1 Wqkv^T + bqkv
   LYNX_TRY(alloc_temp(cx, th, &t_dy1));
   LYNX_TRY(launch_pair(kB2Grads, linear_dgrad(dqkv, w.wqkv, temp_ptr(cx, t_dy1), D.T, 3 * D.p, D.h),
-                       linear_wgrad(dqkv, act_ptr(cx, 1), gr->wqkv, D.T, 3 * D.p, D.h)));
+                       linear_wgrad(dqkv, act_ptr(cx, 1), gr->wqkv, D.T, 3 * D.p, D.h), defer));
   const size_t bqkv_bytes = Arena::round_up(lynx::colsum_scratch_bytes(D.T, 3 * D.p));
   LYNX_TRY(alloc_partials(3, bqkv_bytes + lynx::layernorm_bwd_scratch_bytes(D.T, D.h, false)));
-  LYNX_LAUNCH(cx, kB2BiasGrad, summed(lynx::column_sum(dt, dqkv, gr->bqkv, part, D.T, 3 * D.p, &sums, cx.st)));
+  LYNX_LAUNCH(cx, kB2BiasGrad, summed(lynx::column_sum(dt, dqkv, gr->bqkv, part, D.T, 3 * D.p, &sums, cx.st), defer));
   if (defer) part += bqkv_bytes / sizeof(float);
   free_temp(cx, &t_dqkv);
   free_act(cx, 2);
@@ -827,7 +849,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   // B1: Y1 = LN1(X); dX = dX2 + dLN
   LYNX_LAUNCH(cx, kB1LayerNorm, summed(lynx::layernorm_bwd(dt, temp_ptr(cx, t_dy1), act_ptr(cx, 0), stats_ptr(cx, 1),
                                       stats_ptr(cx, 1) + D.T, w.g1, temp_ptr(cx, t_dx2), d_x, gr->g1,
-                                      gr->be1, part, D.T, D.h, &sums, cx.st)));
+                                      gr->be1, part, D.T, D.h, &sums, cx.st), defer));
   if (defer) LYNX_LAUNCH(cx, kColumnSums, lynx::finish_column_sums(dt, &sums, cx.st));
   for (Temp& t : t_part) free_temp(cx, &t);
   free_temp(cx, &t_dy1);
@@ -849,15 +871,16 @@ bool grads_ok(const lynx_grads* g) {
   return true;
 }
 
-// The least thrift at which forward(retain) -> backward fits the workspace (none: kSerial, for the forward's sake).
+// The first of the levels up to kLevelScratchHigh at which forward(retain) -> backward fits the workspace (none:
+// kLevelSerial, for the forward's sake).
 int thrift_for(lynx_layer_s* L, uint32_t retain) {
   signed char& thrift = L->thrift[(retain >> 1) & 0xFFFu];
   if (thrift < 0) {
     // (placeholders, non-null and aligned: the rehearsal takes the kernel path a real call takes)
     void* const fake = reinterpret_cast<void*>(static_cast<uintptr_t>(Arena::kAlign));
     const lynx_grads g{fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake, fake};
-    thrift = kSerial;
-    for (int level = 0; level <= kMaxThrift; ++level) {
+    thrift = kLevelSerial;
+    for (int level = 0; level <= kLevelScratchHigh; ++level) {
       Book book;
       book.arena = Arena(L->book.arena.capacity());
       book.thrift = level;
@@ -872,16 +895,15 @@ int thrift_for(lynx_layer_s* L, uint32_t retain) {
 
 // Rehearse on a copy, then run for real.  The run's thrift was chosen for forward -> backward, and segments in
 // between move the blocks: a call that does not fit at that level is tried at those above it and then at those
-// below it (more thrift is another placement, not always a smaller one), at kSerialOnly last unless the run began
-// there: it is for what fits no other level.  No value depends on the level.
+// below it (more thrift is another placement, not always a smaller one), the levels beyond kLevelScratchHigh after
+// these.  No value depends on the level.
 template <typename F>
 lynx_status two_pass(lynx_layer_s* L, hipStream_t st, F&& body) {
   const int base = L->book.thrift;
   lynx_status s = LYNX_ERR_OOM;
   int level = base;
-  const int top = base == kSerialOnly ? kSerialOnly : kScratchHigh;
-  for (int k = 0; s == LYNX_ERR_OOM && k <= kMaxThrift; ++k) {
-    level = base + k <= top ? base + k : k <= top ? top - k : kSerialOnly;
+  for (int k = 0; s == LYNX_ERR_OOM && k < kLevels; ++k) {
+    level = k > kLevelScratchHigh ? k : base + k <= kLevelScratchHigh ? base + k : kLevelScratchHigh - k;
     Book copy = L->book;
     copy.thrift = level;
     Ctx rehearsal{L, &copy, false, st};
@@ -974,7 +996,7 @@ lynx_status lynx_layer_create_static(const lynx_layer_config* cfg, lynx_layer_t*
   if (!make_dims(cfg, &D)) return LYNX_ERR_SHAPE;
   // the leanest schedule of this shape (keep the input only) must fit the block
   size_t least = 0;
-  for (int thrift = 0; thrift <= kUnfused; ++thrift) {
+  for (int thrift = 0; thrift < kLevelScratchHigh; ++thrift) {
     const size_t need = workspace_need(cfg, LYNX_RETAIN_FULL_RECOMPUTE, nullptr, thrift);
     if (thrift == 0 || need < least) least = need;
   }
