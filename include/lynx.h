@@ -166,10 +166,10 @@ lynx_status lynx_layer_destroy(lynx_layer_t layer);
  * kernel reads workspace memory it has not written), and one layer at a time
  * may live in it per GPU: two would overwrite each other, so a second create on
  * the same device before the first is destroyed fails with STATE.  Errors:
- * INVALID_ARG, SHAPE, OOM when even the leanest schedule of this shape
- * (input retained only, none of those partial sums) exceeds the block -
- * later calls return OOM as usual when a richer retain mask does not fit -,
- * HIP when the block's address cannot be obtained. */
+ * INVALID_ARG, SHAPE, OOM when even the leanest schedule of this shape (input
+ * retained only) does not run in the block - later calls return OOM as usual
+ * when a richer retain mask does not fit -, HIP when the block's address cannot
+ * be obtained. */
 #define LYNX_STATIC_WORKSPACE_BYTES ((size_t)64 << 20)
 lynx_status lynx_layer_create_static(const lynx_layer_config* cfg, lynx_layer_t* out_layer);
 

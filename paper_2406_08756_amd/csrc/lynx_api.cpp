@@ -935,12 +935,11 @@ struct Rehearsal {
   }
 };
 
-// The workspace a call sequence reaches into: forward, the phases, backward.
-size_t workspace_need(const lynx_layer_config* cfg, uint32_t retain_mask, const uint32_t* phase_masks, int thrift) {
+// The workspace a call sequence reaches into, with room for everything: forward, the phases, backward.
+size_t workspace_need(const lynx_layer_config* cfg, uint32_t retain_mask, const uint32_t* phase_masks) {
   Dims D;
   if (!make_dims(cfg, &D) || (retain_mask & ~0x3FFFu)) return 0;
   Rehearsal r(*cfg, D, static_cast<size_t>(1) << 60);
-  r.L.book.thrift = thrift;
   Ctx cx{&r.L, &r.L.book, false, nullptr};
   if (forward_pass(cx, retain_mask) != LYNX_OK) return 0;
   for (int t = 0; phase_masks != nullptr && t < 4; ++t)
@@ -994,13 +993,9 @@ lynx_status lynx_layer_create_static(const lynx_layer_config* cfg, lynx_layer_t*
   if (cfg == nullptr || out_layer == nullptr) return LYNX_ERR_INVALID_ARG;
   Dims D;
   if (!make_dims(cfg, &D)) return LYNX_ERR_SHAPE;
-  // the leanest schedule of this shape (keep the input only) must fit the block
-  size_t least = 0;
-  for (int thrift = 0; thrift < kLevelScratchHigh; ++thrift) {
-    const size_t need = workspace_need(cfg, LYNX_RETAIN_FULL_RECOMPUTE, nullptr, thrift);
-    if (thrift == 0 || need < least) least = need;
-  }
-  if (least == 0 || least > lynx::kStaticWorkspaceBytes) return LYNX_ERR_OOM;
+  // the leanest schedule of this shape (keep the input only) must fit the block, at whichever level
+  const uint32_t no_phases[4] = {0, 0, 0, 0};
+  if (!sequence_fits(cfg, LYNX_RETAIN_FULL_RECOMPUTE, no_phases, lynx::kStaticWorkspaceBytes)) return LYNX_ERR_OOM;
   lynx_layer_s* L = new (std::nothrow) lynx_layer_s;
   if (L == nullptr) return LYNX_ERR_OOM;
   void* base = nullptr;
@@ -1128,11 +1123,11 @@ lynx_status lynx_layer_activation(lynx_layer_t L, int act_id, const void** devic
 
 size_t lynx_workspace_bytes_for_schedule(const lynx_layer_config* cfg, uint32_t retain_mask,
                                          const uint32_t* phase_masks) {
-  const size_t need = workspace_need(cfg, retain_mask, phase_masks, 0);
+  const size_t need = workspace_need(cfg, retain_mask, phase_masks);
   // A run starts at the thrift that forward -> backward alone needs.  Where phases leave less room than that takes,
   // this can be another placement than the one just rehearsed; with the room of both it is the same.
   if (need == 0 || phase_masks == nullptr || sequence_fits(cfg, retain_mask, phase_masks, need)) return need;
-  const size_t alone = workspace_need(cfg, retain_mask, nullptr, 0);
+  const size_t alone = workspace_need(cfg, retain_mask, nullptr);
   return alone > need ? alone : need;
 }
 
