@@ -503,13 +503,15 @@ hipError_t launch(const ScoreGradientArgs& g, hipStream_t st) {
 
 }  // namespace
 
-bool attn_scores_softmax_supported(int dtype, int s, int d, long long ld) {
-  return dtype == 1 && s % 8 == 0 && s <= kMaxSeq && d % 8 == 0 && d <= 128 && ld % 8 == 0 && ld < (1ll << 28);
+// (32 rows per workgroup: with 2^23 of them and more the kernels of 128 rows may still be launched)
+bool attn_scores_softmax_supported(int dtype, int s, int d, long long ld, long long slices) {
+  return dtype == 1 && s % 8 == 0 && s <= kMaxSeq && d % 8 == 0 && d <= 128 && ld % 8 == 0 && ld < (1ll << 28) &&
+         fits_grid((s + kRowsOfBlock - 1) / kRowsOfBlock * slices, 8 * kWave);
 }
 
 hipError_t attn_scores_softmax_fwd(const void* q, const void* k, long long ld, void* S, void* P, void* Pd, AttnShape sh, int d,
                                    float scale, DropoutParams dp, hipStream_t st) {
-  if (!attn_scores_softmax_supported(1, sh.s, d, ld)) return hipErrorInvalidValue;
+  if (!attn_scores_softmax_supported(1, sh.s, d, ld, static_cast<long long>(sh.a) * sh.b)) return hipErrorInvalidValue;
   ScoresSoftmaxArgs g{};
   g.q = static_cast<const bf16_t*>(q); g.k = static_cast<const bf16_t*>(k); g.ld = ld;
   g.S = static_cast<bf16_t*>(S); g.P = static_cast<bf16_t*>(P); g.Pd = static_cast<bf16_t*>(Pd);
@@ -528,13 +530,13 @@ hipError_t attn_scores_softmax_fwd(const void* q, const void* k, long long ld, v
   return whole ? launch<128, false>(g, st) : launch<128, true>(g, st);
 }
 
-bool attn_score_gradient_supported(int dtype, int s, int d, long long ld) {
-  return s <= kMaxGradientSeq && attn_scores_softmax_supported(dtype, s, d, ld);
+bool attn_score_gradient_supported(int dtype, int s, int d, long long ld, long long slices) {
+  return s <= kMaxGradientSeq && attn_scores_softmax_supported(dtype, s, d, ld, slices);
 }
 
 hipError_t attn_score_gradient(const void* dc, long long lddc, const void* v, long long ldv, const void* P, void* dS, AttnShape sh,
                                int d, float scale, DropoutParams dp, hipStream_t st) {
-  if (!attn_score_gradient_supported(1, sh.s, d, ldv) || lddc > ldv) return hipErrorInvalidValue;
+  if (!attn_score_gradient_supported(1, sh.s, d, ldv, static_cast<long long>(sh.a) * sh.b) || lddc > ldv) return hipErrorInvalidValue;
   ScoreGradientArgs g{};
   g.dc = static_cast<const bf16_t*>(dc); g.lddc = lddc;
   g.v = static_cast<const bf16_t*>(v); g.ldv = ldv;

@@ -20,7 +20,9 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
 // Products of attention (gemm_mfma.hip).
 hipError_t gemm_attention(const GemmDesc& d, hipStream_t st);
 // ... and (gemm_ragged.hip) a product over the rows and one over the columns of the same seq x seq operand in one launch.
+// (two where one would have more threads than a launch may)
 hipError_t gemm_attention_pair(const GemmDesc& rows, const GemmDesc& cols, hipStream_t st);
+bool gemm_attention_pair_joint(const GemmDesc& rows);
 
 // fp32 storage (gemm_f32.hip).
 bool gemm_f32_supported(const GemmDesc& d);

@@ -399,8 +399,18 @@ int attention_tile(const GemmDesc& d, long long workgroups_per_tile) {
   return ceil_div(d.M, t.bm) * ceil_div(d.N, t.bn) * workgroups_per_tile < TileCost::kUnits ? kT64 : tile;
 }
 
+bool gemm_attention_pair_joint(const GemmDesc& rows) {
+  const long long slices = static_cast<long long>(rows.nz1) * rows.nz2;
+  const TileCost& t = kProductCost[is_far(rows) ? kT64 : attention_tile(rows, slices)];
+  return fits_grid((slices + 7) / 8 * 16 * ceil_div(rows.M, t.bm) * ceil_div(rows.N, t.bn), 4 * kWave);
+}
+
 hipError_t gemm_attention_pair(const GemmDesc& rows, const GemmDesc& cols, hipStream_t st) {
   const MfmaGemmArgs r = make_args(rows), c = make_args(cols);
+  if (!gemm_attention_pair_joint(rows)) {
+    const hipError_t e = gemm_attention(rows, st);
+    return e != hipSuccess ? e : gemm_attention(cols, st);
+  }
   if (is_far(rows) || is_far(cols)) return launch_attn_gradients<kT64, true>(r, c, st);
   switch (attention_tile(rows, r.nz)) {
     case kT128: return launch_attn_gradients<kT128>(r, c, st);

@@ -8,6 +8,9 @@
 
 namespace lynx {
 
+// Whether a launch of so many workgroups of so many threads is one that HIP takes (fewer than 2^32 threads per dimension).
+inline bool fits_grid(long long workgroups, int threads) { return workgroups * threads < (1ll << 32); }
+
 struct DropoutParams {
   uint64_t seed;
   uint64_t step;
@@ -64,12 +67,12 @@ hipError_t softmax_dropout_fwd(int dtype, const void* S, void* P, void* Pd, Attn
                                float scale, DropoutParams dp, hipStream_t st);
 // Operators 3 to 5 in one launch (attn_softmax.hip): q and k are [T, a * d] with row stride ld; S, P, Pd as the
 // separate kernels leave them, each written if not null.
-bool attn_scores_softmax_supported(int dtype, int s, int d, long long ld);
+bool attn_scores_softmax_supported(int dtype, int s, int d, long long ld, long long slices);
 hipError_t attn_scores_softmax_fwd(const void* q, const void* k, long long ld, void* S, void* P, void* Pd, AttnShape sh, int d,
                                    float scale, DropoutParams dp, hipStream_t st);
 // dS = scale P (dP - sum_j dP P), dP = keep c round(dC V^T), in one launch (s <= 1024): dc [T, a * d] with row stride lddc,
 // v with ldv.
-bool attn_score_gradient_supported(int dtype, int s, int d, long long ld);
+bool attn_score_gradient_supported(int dtype, int s, int d, long long ld, long long slices);
 hipError_t attn_score_gradient(const void* dc, long long lddc, const void* v, long long ldv, const void* P, void* dS, AttnShape sh,
                                int d, float scale, DropoutParams dp, hipStream_t st);
 // Pd = keep * P * c from a resident P.

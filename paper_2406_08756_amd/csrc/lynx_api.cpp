@@ -491,7 +491,7 @@ lynx_status run_fused_attention(Ctx& cx) {
 // P if `write_p`.  Timed in slot 4.
 bool can_fuse_scores(const Ctx& cx) {
   const Dims& D = cx.L->D;
-  return lynx::attn_scores_softmax_supported(D.dtype, D.s, D.d, 3ll * D.p);
+  return lynx::attn_scores_softmax_supported(D.dtype, D.s, D.d, 3ll * D.p, static_cast<long long>(D.b) * D.a);
 }
 lynx_status run_fused_scores(Ctx& cx, bool write_p, bool with_pd) {
   lynx_layer_s* L = cx.L;
@@ -768,7 +768,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   dpd.epi.head0 = L->cfg.tp_rank * D.a;
   const bool fused_ds = lynx::gemm_supported(dt, dpd);
   // (elsewhere, up to s = 1024, the dot products are formed from dPd itself, in the launch that forms dPd)
-  const bool rows_ds = !fused_ds && lynx::attn_score_gradient_supported(dt, D.s, D.d, 3ll * D.p);
+  const bool rows_ds = !fused_ds && lynx::attn_score_gradient_supported(dt, D.s, D.d, 3ll * D.p, static_cast<long long>(D.b) * D.a);
   // dV = Pd^T dC.  With the one-pass dS kernels it goes first, so that dQ and dK read dS right
   // after it is written, while much of it is still in the caches (measured: dQ 0.070 -> 0.05x ms).
   const bool dv_first = (fused_ds || rows_ds) && !cx.bk->fused_attn;
