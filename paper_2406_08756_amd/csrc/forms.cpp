@@ -20,4 +20,46 @@ unsigned lynx_form_attention(int s, int d, long long ld, int batch, int heads) {
          (gemm_attention_pair_joint(rows) ? 4u : 0u);
 }
 
+// Tiles per workgroup of the score-shaped products (S where it is formed alone, dPd).
+int lynx_form_score_run(int s, int slices) { return lynx::attention_score_run(s, slices); }
+
+// The bf16 product [M, N] over K of a forward linear layer: {rows and columns of the tile, ranges of the contraction}.
+void lynx_form_product(int M, int N, int K, int* out) {
+  lynx::GemmDesc d{};
+  d.M = M; d.N = N; d.K = K;
+  const lynx::RaggedChoice c = lynx::ragged_product(d);
+  out[0] = c.tile_m; out[1] = c.tile_n; out[2] = c.ranges;
+}
+
+// Both bf16 gradients of a linear layer of `inputs` to `outputs`: {rows and columns of the tile, ranges of the weight
+// gradient's contraction, of the input gradient's, whether that one carries the GeLU backward}, which `gelu` (FC2) asks
+// for where it pays.
+void lynx_form_pair(int tokens, int outputs, int inputs, int gelu, int* out) {
+  void* const some = reinterpret_cast<void*>(256);  // (aligned; nothing is read)
+  lynx::GemmDesc d{}, w{};
+  d.M = tokens; d.N = inputs; d.K = outputs;
+  d.a_sm = outputs; d.a_sk = 1;
+  d.b_sk = inputs; d.b_sn = 1;
+  w.M = outputs; w.N = inputs; w.K = tokens;
+  w.a_sm = 1; w.a_sk = outputs;
+  w.b_sk = inputs; w.b_sn = 1;
+  for (lynx::GemmDesc* g : {&d, &w}) {
+    g->A = g->B = some;
+    g->C = some;
+    g->c_sm = inputs;
+    g->nz1 = g->nz2 = 1;
+  }
+  if (gelu) {
+    d.epi.kind = lynx::kEpiGeluBwd;
+    d.epi.aux = some;
+    d.epi.aux_ld = inputs;
+    d.epi.colsum_partial = static_cast<float*>(some);
+    d.epi.colsum_out = some;
+    if (!lynx::gemm_pair_absorbs_gelu(1, d, w)) d.epi = lynx::GemmEpilogue{};
+  }
+  const lynx::RaggedChoice c = lynx::ragged_pair(d, w);
+  out[0] = c.tile_m; out[1] = c.tile_n; out[2] = c.ranges; out[3] = c.dgrad_ranges;
+  out[4] = d.epi.kind == lynx::kEpiGeluBwd;
+}
+
 }  // extern "C"

@@ -397,6 +397,8 @@ hipError_t scores(const MfmaGemmArgs& a, hipStream_t st) {
 
 }  // namespace
 
+int attention_score_run(int s, int slices) { return attn_run((s + 127) / 128, slices); }
+
 // Attention: score-shaped (S = Q K^T, dPd = dC V^T and dS in its place) and contraction-restricted.
 hipError_t gemm_attention(const GemmDesc& d, hipStream_t st) {
   const MfmaGemmArgs a = make_args(d);

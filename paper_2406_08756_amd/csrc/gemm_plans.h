@@ -6,11 +6,14 @@
 namespace lynx {
 
 // What the ragged kernels would do with a product (or a pair): estimated time, fp32 scratch for the
-// partial sums of cut contractions, and (pair) rows of column partials of the GeLU epilogue.
+// partial sums of cut contractions, (pair) rows of column partials of the GeLU epilogue, the tile, and the ranges that
+// the contraction (pair: of the weight gradient, of the input gradient) is cut into.
 struct RaggedChoice {
   double us;
   size_t scratch_bytes;
   int colsum_rows;
+  int tile_m, tile_n;
+  int ranges, dgrad_ranges;
 };
 RaggedChoice ragged_product(const GemmDesc& d);
 RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad);
@@ -19,6 +22,7 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
                             ColumnSums* sums, hipStream_t st);
 // Products of attention (gemm_mfma.hip).
 hipError_t gemm_attention(const GemmDesc& d, hipStream_t st);
+int attention_score_run(int s, int slices);  // score-shaped ones: tiles per workgroup
 // ... and (gemm_ragged.hip) a product over the rows and one over the columns of the same seq x seq operand in one launch.
 // (two where one would have more threads than a launch may)
 hipError_t gemm_attention_pair(const GemmDesc& rows, const GemmDesc& cols, hipStream_t st);

@@ -390,7 +390,8 @@ RaggedPairPlan plan_pair_ragged(const GemmDesc& w, const GemmDesc& d) {
 
 RaggedChoice ragged_product(const GemmDesc& d) {
   const ProductPlan p = plan_product(d);
-  return {p.us, partial_bytes(d.M, d.N, p.splits(d.K)), 0};
+  const int splits = p.splits(d.K);
+  return {p.us, partial_bytes(d.M, d.N, splits), 0, kProductCost[p.tile].bm, kProductCost[p.tile].bn, splits, 1};
 }
 
 int attention_tile(const GemmDesc& d, long long workgroups_per_tile) {
@@ -457,7 +458,7 @@ RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad) {
   const RaggedPairPlan p = plan_pair_ragged(wgrad, dgrad);
   const int ws = ceil_div(wgrad.K, p.w_per), ds = ceil_div(dgrad.K, p.d_per);
   return {p.us, partial_bytes(wgrad.M, wgrad.N, ws) + partial_bytes(dgrad.M, dgrad.N, ds),
-          ceil_div(dgrad.M, kTileWaveRows[p.tile])};
+          ceil_div(dgrad.M, kTileWaveRows[p.tile]), kPairCost[p.tile].bm, kPairCost[p.tile].bn, ws, ds};
 }
 
 hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,

@@ -1,19 +1,11 @@
 """Launches of attention with more threads than HIP takes (2^32 in a dimension): so many slices that a launch for two
 products, or with a workgroup per 32 rows, has too many, go by the kernels that have fewer."""
-import ctypes
-
 import pytest
 
-B = pytest.importorskip("paper_2406_08756_amd.binding")
+pytest.importorskip("paper_2406_08756_amd.binding")
 
-_lib = ctypes.CDLL(B.LIB_PATH)
-_lib.lynx_form_attention.restype = ctypes.c_uint
-_lib.lynx_form_attention.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
-SCORES, GRADIENT, JOINT = 1, 2, 4
-
-
-def form(seq, head_dim, micro_batch, heads):
-    return _lib.lynx_form_attention(seq, head_dim, 3 * heads * head_dim, micro_batch, heads)
+from forms import GRADIENT, JOINT, SCORES
+from forms import attention as form
 
 
 def test_ordinary_sizes():

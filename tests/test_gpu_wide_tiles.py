@@ -1,7 +1,8 @@
-"""The 256-row tiles of eight wavefronts: contractions of one to six slabs of 64 and one octet more or less (prologue,
-steady loop and last slabs of the ring), an output whose last tile is one octet wide (wavefronts with nothing to
-compute).  The cost model gives the 256 x 256 tile to FC1 of the first kind of layer below and 256 x 128 to that of the
-second.  Against the fp64 oracle at the suite's tolerance, and under full recomputation with the same bits."""
+"""The 256-row tiles of eight wavefronts in forward products: contractions of one to six slabs of 64 and one octet more or
+less (prologue, steady loop and last slabs of the ring of 256 x 256), of nine and ten (256 x 128, which the cost model
+gives nothing shorter), an output whose last tile is one octet wide (wavefronts with nothing to compute).  FC1 takes the
+256 x 256 tile in the first kind of layer below and 256 x 128 in the second.  Against the fp64 oracle at the suite's
+tolerance, and under full recomputation with the same bits."""
 import numpy as np
 import pytest
 
@@ -12,8 +13,7 @@ from harness import GpuLayer, rel_err
 from test_gpu_product_edges import TOL, run
 
 B = pytest.importorskip("paper_2406_08756_amd.binding")
-
-pytestmark = pytest.mark.gpu
+import forms
 
 # (hidden, heads, head_dim, ffn, seq, micro_batch), bf16; the last: rows of 2^22 elements and more, which the tile with
 # 64-bit load offsets takes
@@ -21,6 +21,12 @@ SHAPES = ([(h, 8, 64, 1032, 128, 64) for h in (64, 72, 128, 136, 192, 200, 256, 
           [(h, 8, 64, 2656, 248, 12) for h in (520, 576, 584)] + [(8, 1, 8, (1 << 22) + 72, 24, 1)])
 
 
+@pytest.mark.parametrize("shape", SHAPES[:-1], ids=lambda s: "h%d_f%d" % (s[0], s[3]))
+def test_form(shape):
+    assert forms.of_layer(shape, "fc1") == (256, 256 if shape[3] == 1032 else 128, 1)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "h%d_f%d" % (s[0], s[3]))
 def test_layer(shape):
     cfg = synth.LayerConfig(synth.BF16, *shape, tp_size=2, tp_rank=1, seed=7, layer_id=3)

@@ -14,6 +14,7 @@ from harness import GpuLayer, rel_err
 from test_host_runtime import FAKE, FDOUT, FDX, FOUT, FX, dry_layer
 
 B = pytest.importorskip("paper_2406_08756_amd.binding")
+import forms
 
 MASKS = (pm.FULL_RECOMPUTE, pm.ATTENTION_ONLY, pm.STORE_ALL)
 # name: (dtype, hidden, heads, head_dim, ffn, seq, micro_batch), bytes under each mask
@@ -219,10 +220,17 @@ CUT_GRADIENTS = {
     "input_gradients": (5120, 5, 128, 2560, 128, 1),       # GeLU backward as a kernel, in place
     "few_rows": (2056, 1, 64, 4104, 24, 1),
     "weight_gradients": (432, 1, 40, 216, 640, 2),
-    "gelu_in_128_tiles": (128, 2, 64, 640, 1152, 5),       # its column partials: a row per half tile
-    "gelu_in_256_tiles": (136, 5, 128, 1992, 1224, 4),
-    "whole_tiles": (384, 2, 64, 3072, 768, 3),             # (this cut has scratch in every workspace)
+    "gelu_in_64_tiles": (128, 2, 64, 640, 1152, 5),        # its column partials: a row per half tile
+    "gelu_in_128_tiles": (136, 5, 128, 1992, 1224, 4),
+    "gelu_in_256_tiles": (16, 1, 8, 4400, 856, 6),
+    "whole_tiles": (384, 2, 64, 3072, 768, 3),
 }
+
+
+@pytest.mark.parametrize("name,tile", [("gelu_in_64_tiles", 64), ("gelu_in_128_tiles", 128), ("gelu_in_256_tiles", 256)])
+def test_gelu_forms(name, tile):
+    rows, cols, weight_ranges, input_ranges, gelu = forms.of_layer(CUT_GRADIENTS[name], "fc2_grads")
+    assert (rows, cols) == (tile, tile) and weight_ranges > 1 and input_ranges == 1 and gelu
 
 
 @pytest.mark.gpu
