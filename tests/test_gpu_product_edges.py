@@ -24,6 +24,7 @@ SHAPES = {
     "one_under_64_f32": (synth.F32, 56, 1, 56, 120, 56, 2),
     "one_over_64_f32": (synth.F32, 72, 2, 72, 136, 136, 1),
     "large_tiles_f32": (synth.F32, 520, 2, 72, 1096, 328, 2),   # 64 x 64 tiles, tails everywhere
+    "far_strides_f32": (synth.F32, 8, 1, 8, (1 << 23) + 72, 8, 1),  # rows of 2^23 elements and more: 64-bit load addresses
     "octets_bf16": (synth.BF16, 8, 1, 8, 8, 8, 1),
     "one_over_64": (synth.BF16, 72, 1, 72, 136, 72, 1),
     "one_under_128": (synth.BF16, 120, 1, 120, 248, 120, 2),
