@@ -389,15 +389,21 @@ def main():
     segments = [B.LYNX_SEG_ALL_MISSING]
     heu = None
     if args.heu:
-        # C_i: each forward operator's time under store-all, from the library's event pairs
-        full_ws = torch.empty(B.lynx_workspace_bytes(cfg, POLICIES["store_all"]) + 256, dtype=torch.uint8, device="cuda")
-        prof = B.lynx_layer_create(cfg, (full_ws.data_ptr() + 255) // 256 * 256, full_ws.numel() - 256)
+        # C_i: each operator's time alone, from the library's event pairs: regenerated by a segment that names no other,
+        # so that none is covered by the launch of its neighbour (segments that name several run them in fewer launches)
+        alone = cfg.with_(flags=0)
+        nbytes = B.lynx_workspace_bytes(alone, POLICIES["store_all"]) + sum(B.lynx_activation_bytes(alone, i) for i in range(1, 13))
+        full_ws = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+        prof = B.lynx_layer_create(alone, (full_ws.data_ptr() + 255) // 256 * 256, nbytes)
         B.lynx_layer_set_params(prof, params)
         B.lynx_layer_set_profiling(prof, True)
         cost = [0.0] * 13
         reps = 5
         for k in range(reps + 2):
-            B.lynx_layer_forward(prof, x, out, POLICIES["store_all"], k, stream)
+            B.lynx_layer_forward(prof, x, out, POLICIES["full"], k, stream)
+            B.lynx_layer_profile_ms(prof)
+            for op in range(1, 13):
+                B.lynx_recompute(prof, 1 << op, stream)
             ms = B.lynx_layer_profile_ms(prof)
             B.lynx_layer_reset(prof)
             if k >= 2:
@@ -406,20 +412,7 @@ def main():
                         cost[int(name[2:].split("_")[0]) - 1] += v / reps
         B.lynx_layer_destroy(prof)
         del full_ws
-        # OP3 to OP5 run as one launch where the shape allows (its time is under OP4): by the bytes each moves alone
-        if cost[2] == 0.0:
-            cost[2], cost[3] = 0.2 * cost[3], 0.8 * cost[3]
-        # the store-all forward runs OP4 and OP5 as one kernel (its time is under OP4): split it evenly
-        cost[3], cost[4] = 0.5 * cost[3], 0.5 * cost[3]
-        # OP7+OP8 and OP12+OP13 run as one launch each where the matrix-core kernel applies (the
-        # time is under the linear operator); run on its own, the bias + dropout + residual
-        # operator moves 3 T h e bytes: price it at 5.5 TB/s, what the stand-alone kernel reaches
-        # (and take about two thirds of that off the fused launch: it does the same work minus a
-        # write and a read of the product)
-        for lin in (7, 12):
-            if cost[lin] == 0.0:
-                cost[lin] = 3.0 * cfg.tokens * cfg.hidden * (2 if cfg.dtype == 1 else 4) / 5.5e9
-                cost[lin - 1] = max(cost[lin - 1] - 0.65 * cost[lin], 0.5 * cost[lin - 1])
+        cost[12] = cost[7]  # (operator 13, whose output the caller holds, is the kernel of operator 8 on the same sizes)
         M = [B.lynx_activation_bytes(cfg, i) for i in range(14)]
         budget = M[13] + args.budget_frac * sum(M[1:13])
         ctime = [float(v) for v in args.ctime_ms.split(",")]
