@@ -135,8 +135,8 @@ size_t lynx_activation_bytes(const lynx_layer_config* cfg, int act_id);
  * Where few tokens leave the chip idle, the size includes fp32 partial sums of
  * contractions that are cut into ranges.  A smaller workspace that the sequence
  * fits without them is accepted too: the ranges are then summed one after the
- * other (slower, the same bits).  (A weight gradient over 2048 tokens or more
- * that is cut into two keeps its partial sums in every workspace.) */
+ * other, and where that is not enough the FC1 bias gradient is formed in ranges
+ * of columns (slower, the same bits). */
 size_t lynx_workspace_bytes(const lynx_layer_config* cfg, uint32_t retain_mask);
 
 /* The same for a schedule with explicit regeneration phases (Sec. 4.2: the

@@ -16,7 +16,8 @@
 // lane's block), and every wavefront normalises its blocks, passes them through LDS into whole rows and stores those,
 // one dropout call per 8 columns.  At most two blocks per wavefront, of four wavefronts where s <= 512 and of eight beyond;
 // of rows longer than 1024 up to four blocks, whose exponentials are formed again for the normalisation instead of
-// being kept: at most 128 registers, and four wavefronts per SIMD cover each other's loads, transcendentals and stores.
+// being kept: at most 128 registers (forms of ragged shapes with four blocks, and two of the gradient with two, spill one or
+// two more), and four wavefronts per SIMD cover each other's loads, transcendentals and stores.
 // (Four wavefronts of up to eight blocks, two per SIMD, 40 slices of s = 2048: 148 us with P, 119 without.)
 #include <mutex>
 

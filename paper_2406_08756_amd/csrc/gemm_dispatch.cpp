@@ -23,11 +23,13 @@ bool gemm_mfma_supported(int dtype, const GemmDesc& d) {
     case kEpiNone:
       return true;
     case kEpiSoftmaxBwd:
-      // Only the row-block kernel of the score-shaped products carries it: head dimension 128, whole tiles.  (Its
-      // row dot products come from the rounded C; the separate kernel's, from the dPd that it differentiates,
-      // cancel that tensor's rounding.  At other lengths and head dimensions the one launch made the error of the QKV
-      // weight gradient against 64 bits 0.4 to 2.1 % larger, and a step of 14 drawn layers 0.98 to 1.03 times as fast,
-      // 1.000 on average; of 1000 and of 1024 tokens at head dimension 64 1.02.)
+      // Only the row-block kernel of the score-shaped products carries it: head dimension 128, whole tiles, at every
+      // length.  Elsewhere attn_score_gradient forms the row dot products from the dPd that it differentiates (up to
+      // s = 1024), or softmax_dropout_bwd does (beyond); those cancel that tensor's rounding, while these come from the
+      // rounded C, which made the error of the QKV weight gradient against 64 bits 0.4 to 2.1 % larger at other shapes.
+      // The line is older than attn_score_gradient, which takes head dimension 128 too.  This one with attn_rowdot / that
+      // one, us: 4 slices of s = 128 8.1 / 4.6, 8 of 384 8.8 / 6.1, 64 of 384 16.4 / 10.3, 128 of 512 33.6 / 30.9, 64 of 768
+      // 38.0 / 33.4, 32 of 1024 29.7 / 26.4, 128 of 1024 101 / 109: it is in the wrong place below about 1000.
       return d.causal == kCausalOutLower && d.bias == nullptr && d.M % 128 == 0 && d.K == 128 && a_k && b_k &&
              d.epi.aux != nullptr && aligned(d.epi.aux, 16) && d.epi.rowdot != nullptr;
     case kEpiBiasDropoutAdd:

@@ -41,8 +41,12 @@ template <int TILE> constexpr int tile_waves_per_simd = TileShape<TILE, false>::
 // The numbers are fitted to measurements, for forward products and for gradient pairs each: 589 products
 // and 582 pairs of layers with 64 to 16384 tokens and widths from 40 to 22000, every tile and nearly every cut
 // of each timed on operands in rotation, the constants chosen so that the tile and cut with the least predicted time
-// lose as little as possible against the fastest: 0.8 % and 2.0 % on average.  None of the products had an epilogue: the
-// store pass with bias, dropout and residual is not in the model; for those the choice is that of the plain product.
+// lose as little as possible against the fastest: 0.8 % and 2.0 % on average.  What decides no choice is not pinned by
+// that: single constants are no times of anything (pairs of 64 x 64 tiles: 0.112 alone, 0.081 with one on every unit), and
+// they say little beyond those sizes.  None of the products had an epilogue, nor had the pairs: the store pass with bias,
+// dropout and residual is not in the model, and for those the choice is that of the plain product; neither is the GeLU
+// pass (984 tokens of h 3016, f 1544: 51 us in 64 x 64 tiles, 47 in the 128 x 128 ones of the model before; of 60 layers'
+// FC2 gradients the one that got slower with this model, the others 1.00 to 2.45 times as fast, 1.13 on average).
 struct TileCost {
   int bm, bn, share;
   double alone, one_each, full;

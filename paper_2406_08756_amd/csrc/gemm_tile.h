@@ -14,8 +14,8 @@
 // which is what it takes to cover L2 latency at this MFMA rate.  Bank
 // conflicts are avoided by permuting 16-byte chunks, applied on the global
 // address side since a direct load writes lane i to LDS offset 16 i:
-//   K-major slab  [mn][32]: chunk ^= (row >> 2) & 3
-//   MN-major slab [32][mn]: chunk ^= (k & 3) << 2, read with the transposing
+//   K-major slab  [mn][64]: chunk ^= (row >> 1) & 7, [mn][32]: chunk ^= (row >> 2) & 3
+//   MN-major slab [k][mn]: chunk ^= (k & 3) << 2 (of 64 columns: ((k >> 1) & 1) << 2), read with the transposing
 //     LDS read (ds_read_b64_tr_b16) that hands each lane four consecutive k.
 // The product is formed transposed (B fragment as the first MFMA operand) so
 // each lane ends with four consecutive n of one row m; the epilogue passes the

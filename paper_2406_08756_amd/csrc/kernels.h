@@ -197,9 +197,10 @@ size_t gemm_scratch_bytes(int dtype, const GemmDesc& d);  // shapes and `serial`
 // Sizes multiples of 8, operands 16-byte aligned and contiguous along one index, an epilogue this
 // product can carry: everything the layer asks for except fp32 with kEpiSoftmaxBwd.
 bool gemm_supported(int dtype, const GemmDesc& d);
-// Two products that do not need each other in one launch, with the bits of gemm() on each: C = sq y (kCausalKLeM) and
-// C' = sq^T y' (kCausalKGeM) over the same seq x seq operand (dQ and dK from dS); fp32 also a score-shaped product
-// (kCausalOutLower) in the place of the first (dPd and dV).
+// Two products that do not need each other in one launch: C = sq y (kCausalKLeM) and C' = sq^T y' (kCausalKGeM) over the
+// same seq x seq operand (dQ and dK from dS); fp32 also a score-shaped product (kCausalOutLower) in the place of the first
+// (dPd and dV).  bf16: the bits of gemm() on each.  fp32: the tile, and with it whether a contraction is one sum or four,
+// is chosen for both together.
 hipError_t gemm_seq_pair(int dtype, const GemmDesc& first, const GemmDesc& cols, hipStream_t st);
 // Input gradient and weight gradient of one linear layer in one launch.  `scratch` as above
 // (gemm_pair_scratch_bytes).
