@@ -2,6 +2,8 @@
 asserts it."""
 import ctypes
 
+import torch  # noqa: F401  (first, so that the library shares its HIP runtime)
+
 from paper_2406_08756_amd import binding as B
 
 _lib = ctypes.CDLL(B.LIB_PATH)

@@ -1,6 +1,7 @@
 """Launches of attention with more threads than HIP takes (2^32 in a dimension): so many slices that a launch for two
 products, or with a workgroup per 32 rows, has too many, go by the kernels that have fewer."""
 import pytest
+import torch  # noqa: F401  (first, so that the library shares its HIP runtime)
 
 pytest.importorskip("paper_2406_08756_amd.binding")
 
