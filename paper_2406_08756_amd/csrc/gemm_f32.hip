@@ -4,7 +4,7 @@
 // each operand per lane, so the contraction index can run in octets: lane half hb of a fragment holds
 // indices 8 c + 4 hb + 0..3 of its row, and instruction j of the octet multiplies element j of both halves.
 //
-// Contraction slabs travel through a four-stage LDS ring filled by direct global -> LDS loads; LDS and
+// Contraction slabs travel through an LDS ring of three or four stages filled by direct global -> LDS loads; LDS and
 // the loads have time to spare, so no large tile is needed.  What bounds it: the matrix pipe and what is issued between
 // its instructions; with buffer loads instead of checked 64-bit pointers and two sums instead of one chain, 1024 tokens,
 // 1024 x 4096: 96.5 -> 83.3 us, 4096 x 1024 86.5 -> 78.8; pairs with the longer contraction first 125 -> 111 (QKV), a
@@ -75,10 +75,15 @@ struct SlabF {
 
 constexpr int kLarge = 64, kSmall = 32;   // tile sides
 constexpr long long kFarStride = 1ll << 23;  // row strides (elements) from which on 32 bits may not hold a load's offset in bytes
-constexpr int kStages = 4;
+// Ring stages of 16 KB.  64 x 64: three, so that three workgroups share a compute unit and cover each other's barriers,
+// fills and store passes; with four (two workgroups) a step of 1024 tokens of h 1024 takes 808 us where this takes 786, with
+// two (five workgroups, one slab ahead) 899.  32 x 32: four; such launches do not fill the chip, and a layer of 256 tokens
+// of h 256 takes 141.2 us this way, 142.5 with three.
+template <int BM> constexpr int kStages = BM == kLarge ? 3 : 4;
 constexpr int kPitchPad = 4;              // floats: keeps the 16-byte accesses of the staged tile off each other's banks
-constexpr size_t kLdsBytes = kStages * 2 * 2048 * sizeof(float);
-static_assert(kLdsBytes >= kWaves * 32 * (kSmall + kPitchPad) * sizeof(float) && kLdsBytes >= kLarge * (kLarge + kPitchPad) * sizeof(float),
+template <int BM> constexpr size_t kLdsBytes = kStages<BM> * 2 * 2048 * sizeof(float);
+static_assert(kLdsBytes<kSmall> >= kWaves * 32 * (kSmall + kPitchPad) * sizeof(float) &&
+                  kLdsBytes<kLarge> >= kLarge * (kLarge + kPitchPad) * sizeof(float),
               "the staged tile fits the ring");
 
 // Where a tile lies and what it contracts over.
@@ -188,7 +193,7 @@ __device__ __forceinline__ void store_tile(const GemmDesc& d, const DropoutKey& 
 
 template <bool AK, bool BK, int BM>
 __device__ __forceinline__ void f32_tile(const GemmDesc& d, const DropoutKey& key, int block_x, int block_z) {
-  constexpr int S = kStages, kAhead = S - 1;
+  constexpr int S = kStages<BM>, kAhead = S - 1;
   using SA = SlabF<BM, AK>;
   using SB = SlabF<BM, BK>;
   constexpr bool kShareTile = BM == kSmall;  // the wavefronts divide the contraction, not the tile
@@ -354,7 +359,7 @@ DropoutKey epilogue_key(const GemmDesc& d) {
 template <bool AK, bool BK, int BM>
 hipError_t launch(const GemmDesc& d, hipStream_t st) {
   hipLaunchKernelGGL((gemm_f32_kernel<AK, BK, BM>), dim3(static_cast<unsigned>(tiles(d, BM)), d.nz1 * d.nz2), dim3(kThreads),
-                     kLdsBytes, st, d, epilogue_key(d));
+                     kLdsBytes<BM>, st, d, epilogue_key(d));
   return hipGetLastError();
 }
 template <bool AK, bool BK>
@@ -367,8 +372,8 @@ hipError_t launch_two(const GemmDesc& a, const GemmDesc& b, hipStream_t st) {
   const int bm = small_tiles((tiles(a, 64) + tiles(b, 64)) * a.nz1 * a.nz2) ? 32 : 64;
   const int n1 = static_cast<int>(tiles(a, bm)), n2 = static_cast<int>(tiles(b, bm));
   const dim3 grid(n1 + n2, a.nz1 * a.nz2);
-  if (bm == 32) hipLaunchKernelGGL((gemm_f32_two_kernel<AK1, BK1, AK2, BK2, 32>), grid, dim3(kThreads), kLdsBytes, st, a, b, n1, n2);
-  else hipLaunchKernelGGL((gemm_f32_two_kernel<AK1, BK1, AK2, BK2, 64>), grid, dim3(kThreads), kLdsBytes, st, a, b, n1, n2);
+  if (bm == 32) hipLaunchKernelGGL((gemm_f32_two_kernel<AK1, BK1, AK2, BK2, 32>), grid, dim3(kThreads), kLdsBytes<32>, st, a, b, n1, n2);
+  else hipLaunchKernelGGL((gemm_f32_two_kernel<AK1, BK1, AK2, BK2, 64>), grid, dim3(kThreads), kLdsBytes<64>, st, a, b, n1, n2);
   return hipGetLastError();
 }
 
@@ -421,10 +426,10 @@ hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, ColumnSum
   const bool dgrad_first = dgrad.K > wgrad.K;
   const int n_first = dgrad_first ? n_d : n_w;
   if (small)
-    hipLaunchKernelGGL((gemm_f32_pair_kernel<32>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes, st, wgrad, dgrad,
+    hipLaunchKernelGGL((gemm_f32_pair_kernel<32>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes<32>, st, wgrad, dgrad,
                        DropoutKey{}, n_first, dgrad_first ? 1 : 0);
   else
-    hipLaunchKernelGGL((gemm_f32_pair_kernel<64>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes, st, wgrad, dgrad,
+    hipLaunchKernelGGL((gemm_f32_pair_kernel<64>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes<64>, st, wgrad, dgrad,
                        DropoutKey{}, n_first, dgrad_first ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || dgrad.epi.kind != kEpiGeluBwd) return e;
