@@ -1,6 +1,7 @@
 // Which form of a kernel would run, answered on the host, so that a test that means to reach a form can say so and fail
 // when it no longer does.  Exported, but not part of the C ABI that lynx.h declares.
 #include "gemm_plans.h"
+#include "quotient.h"
 
 extern "C" {
 
@@ -18,6 +19,13 @@ unsigned lynx_form_attention(int s, int d, long long ld, int batch, int heads) {
   rows.causal = kCausalKLeM;
   return (attn_scores_softmax_supported(1, s, d, ld, slices) ? 1u : 0u) | (attn_score_gradient_supported(1, s, d, ld, slices) ? 2u : 0u) |
          (gemm_attention_pair_joint(rows) ? 4u : 0u);
+}
+
+// x / d as the kernels form it, for x up to `most`, and whether by the inverse.
+int lynx_form_quotient(int x, int d, long long most, int* by_inverse) {
+  const uint32_t inv = lynx::inverse(d, most);
+  *by_inverse = inv != 0;
+  return lynx::quotient(x, d, inv);
 }
 
 // Tiles per workgroup of the score-shaped products (S where it is formed alone, dPd).

@@ -12,7 +12,7 @@ namespace {
 // unit (one loads while the other stores).
 template <bool A_KMAJOR>
 __global__ void __launch_bounds__(kThreads, 2) attn_product_kernel(MfmaGemmArgs g) {
-  gemm_tile<A_KMAJOR, false, 128, 128>(g, blockIdx.x, 0);
+  gemm_tile<A_KMAJOR, false, 128, 128, true>(g, blockIdx.x, 0);
 }
 
 // Work items of the score-shaped row-block kernels: row block tm (128 rows) owns tiles
@@ -369,8 +369,7 @@ hipError_t launch_attn_product(MfmaGemmArgs a, hipStream_t st) {
   constexpr size_t smem = static_cast<size_t>(kStages) * (128 + 128) * kBK * sizeof(bf16_t);
   auto kern = attn_product_kernel<AK>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
-  a.tiles_m = a.M / 128;
-  a.tiles_n = a.N / 128;
+  set_tiles(&a, 128, 128);
   hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n * a.nz), dim3(kThreads), smem, st, a);
   return hipGetLastError();
 }

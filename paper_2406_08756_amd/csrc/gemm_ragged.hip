@@ -136,12 +136,12 @@ ProductPlan plan_product(const GemmDesc& d) {
 }
 
 // ---- kernels ------------------------------------------------------------------
-template <bool AK, bool BK_, int TILE, bool FAR>
+template <bool AK, bool BK_, int TILE, bool FAR, bool SEQ>
 __global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
 gemm_ragged_kernel(MfmaGemmArgs g) {
   using T = TileShape<TILE, AK && BK_>;
-  if (g.k_splits > 1) gemm_tile<AK, BK_, T::BM, T::BN, true, T::S, true, T::BK, T::waves, false, FAR>(g, blockIdx.x, blockIdx.y);
-  else gemm_tile<AK, BK_, T::BM, T::BN, false, T::S, true, T::BK, T::waves, false, FAR>(g, blockIdx.x, blockIdx.y);
+  if (!SEQ && g.k_splits > 1) gemm_tile<AK, BK_, T::BM, T::BN, false, true, T::S, true, T::BK, T::waves, false, FAR>(g, blockIdx.x, 0);
+  else gemm_tile<AK, BK_, T::BM, T::BN, SEQ, false, T::S, true, T::BK, T::waves, false, FAR>(g, blockIdx.x, SEQ ? blockIdx.y : 0);
 }
 
 // Both products of a linear layer's backward in one launch: the first n_first workgroups belong to the one
@@ -158,22 +158,21 @@ gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int
   if (x >= n_first && x < n_pad) return;
   const int tile = x < n_first ? x : x - n_pad;
   if ((x < n_first) != (dgrad_first != 0)) {
-    if (wgrad.k_splits > 1) gemm_tile<false, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves, false, FAR>(wgrad, tile, 0);
-    else gemm_tile<false, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves, false, FAR>(wgrad, tile, 0);
+    if (wgrad.k_splits > 1) gemm_tile<false, false, T::BM, T::BN, false, true, T::S, true, T::BK, T::waves, false, FAR>(wgrad, tile, 0);
+    else gemm_tile<false, false, T::BM, T::BN, false, false, T::S, true, T::BK, T::waves, false, FAR>(wgrad, tile, 0);
   } else {
-    if (dgrad.k_splits > 1) gemm_tile<true, false, T::BM, T::BN, true, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
-    else gemm_tile<true, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
+    if (dgrad.k_splits > 1) gemm_tile<true, false, T::BM, T::BN, false, true, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
+    else gemm_tile<true, false, T::BM, T::BN, false, false, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
   }
 }
 
-template <bool AK, bool BK_, int TILE, bool FAR = false>
+template <bool AK, bool BK_, int TILE, bool FAR, bool SEQ>
 hipError_t launch_ragged(MfmaGemmArgs a, hipStream_t st) {
   using T = TileShape<TILE, AK && BK_>;
   constexpr size_t smem = tile_lds<T>;
-  auto kern = gemm_ragged_kernel<AK, BK_, TILE, FAR>;
+  auto kern = gemm_ragged_kernel<AK, BK_, TILE, FAR, SEQ>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
-  a.tiles_m = ceil_div(a.M, T::BM);
-  a.tiles_n = ceil_div(a.N, T::BN);
+  set_tiles(&a, T::BM, T::BN);
   const int ntiles = a.causal == kCausalOutLower ? a.tiles_m * (a.tiles_m + 1) / 2 : a.tiles_m * a.tiles_n * a.k_splits;
   const bool flat = a.causal == kCausalKLeM || a.causal == kCausalKGeM;  // (tile, matrix) in x
   hipLaunchKernelGGL(kern, flat ? dim3(ntiles * a.nz) : dim3(ntiles, a.nz), dim3(T::waves * kWave), smem, st, a);
@@ -182,15 +181,23 @@ hipError_t launch_ragged(MfmaGemmArgs a, hipStream_t st) {
 
 template <bool AK, bool BK_>
 hipError_t launch_tile(int tile, bool far, const MfmaGemmArgs& a, hipStream_t st) {
-  if (far) return launch_ragged<AK, BK_, kT64, true>(a, st);
-  if constexpr (AK) {  // (both MN-major: attention, in tiles of at most 128 x 128)
-    if (tile == kT256) return launch_ragged<AK, BK_, kT256>(a, st);
-    if (tile == kT256x128) return launch_ragged<AK, BK_, kT256x128>(a, st);
+  if (a.causal != kCausalNone) {  // attention, in tiles of at most 128 x 128
+    if (far) return launch_ragged<AK, BK_, kT64, true, true>(a, st);
+    switch (tile) {
+      case kT128: return launch_ragged<AK, BK_, kT128, false, true>(a, st);
+      case kT128x64: return launch_ragged<AK, BK_, kT128x64, false, true>(a, st);
+      default: return launch_ragged<AK, BK_, kT64, false, true>(a, st);
+    }
+  }
+  if (far) return launch_ragged<AK, BK_, kT64, true, false>(a, st);
+  if constexpr (AK) {  // (no larger one for two MN-major operands)
+    if (tile == kT256) return launch_ragged<AK, BK_, kT256, false, false>(a, st);
+    if (tile == kT256x128) return launch_ragged<AK, BK_, kT256x128, false, false>(a, st);
   }
   switch (tile) {
-    case kT128: return launch_ragged<AK, BK_, kT128>(a, st);
-    case kT128x64: return launch_ragged<AK, BK_, kT128x64>(a, st);
-    default: return launch_ragged<AK, BK_, kT64>(a, st);
+    case kT128: return launch_ragged<AK, BK_, kT128, false, false>(a, st);
+    case kT128x64: return launch_ragged<AK, BK_, kT128x64, false, false>(a, st);
+    default: return launch_ragged<AK, BK_, kT64, false, false>(a, st);
   }
 }
 
@@ -202,7 +209,7 @@ hipError_t launch_tile(int tile, bool far, const MfmaGemmArgs& a, hipStream_t st
 template <bool AK, bool BK_, bool FAR>
 __global__ void __launch_bounds__((tile_threads<kT64>), (tile_waves_per_simd<kT64>)) gemm_serial_kernel(MfmaGemmArgs g) {
   using T = TileShape<kT64, AK && BK_>;
-  gemm_tile<AK, BK_, T::BM, T::BN, false, T::S, true, T::BK, T::waves, true, FAR>(g, blockIdx.x, 0);
+  gemm_tile<AK, BK_, T::BM, T::BN, false, false, T::S, true, T::BK, T::waves, true, FAR>(g, blockIdx.x, 0);
 }
 
 template <bool AK, bool BK_, bool FAR = false>
@@ -213,8 +220,7 @@ hipError_t launch_serial(bool far, MfmaGemmArgs a, hipStream_t st) {
   constexpr size_t smem = tile_lds<T>;
   auto kern = gemm_serial_kernel<AK, BK_, FAR>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
-  a.tiles_m = ceil_div(a.M, T::BM);
-  a.tiles_n = ceil_div(a.N, T::BN);
+  set_tiles(&a, T::BM, T::BN);
   hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n), dim3(T::waves * kWave), smem, st, a);
   return hipGetLastError();
 }
@@ -238,8 +244,8 @@ attn_gradients_kernel(MfmaGemmArgs rows, MfmaGemmArgs cols, int by_slice) {
     z = x - w * rows.nz;
   }
   const int tile = (w >> 1) * rows.nz + z;
-  if (w & 1) gemm_tile<false, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves, false, FAR>(cols, tile, 0);
-  else gemm_tile<true, false, T::BM, T::BN, false, T::S, true, T::BK, T::waves, false, FAR>(rows, tile, 0);
+  if (w & 1) gemm_tile<false, false, T::BM, T::BN, true, false, T::S, true, T::BK, T::waves, false, FAR>(cols, tile, 0);
+  else gemm_tile<true, false, T::BM, T::BN, true, false, T::S, true, T::BK, T::waves, false, FAR>(rows, tile, 0);
 }
 
 template <int TILE, bool FAR = false>
@@ -249,8 +255,7 @@ hipError_t launch_attn_gradients(MfmaGemmArgs rows, MfmaGemmArgs cols, hipStream
   auto kern = attn_gradients_kernel<TILE, FAR>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   for (MfmaGemmArgs* g : {&rows, &cols}) {
-    g->tiles_m = ceil_div(g->M, T::BM);
-    g->tiles_n = ceil_div(g->N, T::BN);
+    set_tiles(g, T::BM, T::BN);
   }
   const int per_slice = 2 * rows.tiles_m * rows.tiles_n;
   // From eight slices per XCD on, the idle end of the last one is a small part.  Slice by slice and all at once: 64
@@ -269,8 +274,7 @@ hipError_t launch_ragged_pair(MfmaGemmArgs w, MfmaGemmArgs d, hipStream_t st) {
   auto kern = gemm_ragged_pair_kernel<TILE, FAR>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   for (MfmaGemmArgs* g : {&w, &d}) {
-    g->tiles_m = ceil_div(g->M, T::BM);
-    g->tiles_n = ceil_div(g->N, T::BN);
+    set_tiles(g, T::BM, T::BN);
   }
   const int n_w = w.tiles_m * w.tiles_n * w.k_splits, n_d = d.tiles_m * d.tiles_n * d.k_splits;
   const bool dgrad_first = d.k_per > w.k_per;

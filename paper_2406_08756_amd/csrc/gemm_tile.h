@@ -26,6 +26,7 @@
 #include "kernels.h"
 #include "mfma_common.h"
 #include "pointwise_math.h"
+#include "quotient.h"
 
 namespace lynx {
 namespace {
@@ -48,6 +49,8 @@ struct MfmaGemmArgs {
   int nz, nz2;
   int causal;  // CausalMode
   int run;     // score-shaped row-block kernels: tiles per workgroup
+  // for quotient(): of tiles_m tiles_n, of a band of tile rows (8 tiles_n), of the rows of the last band, and of nz, tiles_n and nz2
+  uint32_t inv_tiles, inv_band, inv_last, inv_nz, inv_tiles_n, inv_nz2;
   // split contraction: workgroup x computes K range x / (tiles_m tiles_n) of k_splits ranges of
   // k_per indices (whole slabs; the last range may be shorter, none is empty) and leaves its fp32
   // sums in partial[split][M][N] instead of rounding into C
@@ -66,6 +69,22 @@ struct MfmaGemmArgs {
   int global_heads, head0;
 };
 
+constexpr int kBand = 8;  // tile rows of a band, see gemm_tile
+
+// Tiles of bm x bn, and the inverses of what their indices are divided by.
+inline void set_tiles(MfmaGemmArgs* g, int bm, int bn) {
+  g->tiles_m = (g->M + bm - 1) / bm;
+  g->tiles_n = (g->N + bn - 1) / bn;
+  const long long tiles = static_cast<long long>(g->tiles_m) * g->tiles_n;
+  g->inv_tiles = inverse(tiles, tiles * g->k_splits - 1);
+  g->inv_band = inverse(static_cast<long long>(kBand) * g->tiles_n, tiles - 1);
+  const int last = g->tiles_m % kBand;
+  g->inv_last = last != 0 ? inverse(last, static_cast<long long>(last) * g->tiles_n - 1) : 0u;
+  g->inv_nz = inverse(g->nz, tiles * g->nz - 1);
+  g->inv_tiles_n = inverse(g->tiles_n, tiles - 1);
+  g->inv_nz2 = inverse(g->nz2, g->nz - 1);
+}
+
 // 16 bytes of zeros: what a ragged tile multiplies in place of contraction indices beyond K.
 __device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
 
@@ -81,7 +100,9 @@ __device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
 // sums do, bit for bit, with registers in the place of the partial sums.
 //
 // FAR: a row stride of kFarStride elements or more.
-template <bool A_KMAJOR, bool B_KMAJOR, int BM, int BN, bool SPLITK = false, int STAGES = kStages, bool RAGGED = false,
+//
+// SEQ: one of a batch of matrices, with CausalMode (attention); otherwise g is a single product.
+template <bool A_KMAJOR, bool B_KMAJOR, int BM, int BN, bool SEQ, bool SPLITK = false, int STAGES = kStages, bool RAGGED = false,
           int BK = kBK, int WAVES = kWaves, bool SERIAL = false, bool FAR = false>
 __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block_x, const int block_z) {
   constexpr int kWavesN = WAVES == 8 ? BN / 64 : 2;
@@ -95,18 +116,18 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   bf16_t* smem = reinterpret_cast<bf16_t*>(smem_raw);
 
   // workgroup -> output tile
-  int tm, tn, bz = block_z;
-  if (g.causal == kCausalKLeM || g.causal == kCausalKGeM) {
+  int tm, tn, bz = block_z, split = 0;
+  if (SEQ && (g.causal == kCausalKLeM || g.causal == kCausalKGeM)) {
     // One-dimensional grid over (tile, matrix), longest contraction first: tile row tm
     // contracts over tm + 1 (k <= m) or tiles_m - tm (k >= m) row blocks, and a launch
     // that ends on the long tiles leaves most compute units idle meanwhile.  Matrix z
     // stays on XCD z % 8, whose L2 then keeps its small operand.
-    const int t = block_x / g.nz;
+    const int t = quotient(block_x, g.nz, g.inv_nz);
     bz = block_x - t * g.nz;
-    const int row = t / g.tiles_n;
+    const int row = quotient(t, g.tiles_n, g.inv_tiles_n);
     tn = t - row * g.tiles_n;
     tm = g.causal == kCausalKLeM ? g.tiles_m - 1 - row : row;
-  } else if (g.causal == kCausalOutLower) {
+  } else if (SEQ) {
     // square output, only tiles on or below the diagonal: t = tm (tm + 1) / 2 + tn
     const int t = block_x;
     tm = static_cast<int>((sqrtf(8.0f * static_cast<float>(t) + 1.0f) - 1.0f) * 0.5f);
@@ -119,30 +140,35 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
     // panels stay in that XCD's L2.
     const int ntiles = g.tiles_m * g.tiles_n;
     int tile = block_x;
-    if (SPLITK) tile = block_x % ntiles;
+    if (SPLITK) {
+      split = quotient(block_x, ntiles, g.inv_tiles);
+      tile = block_x - split * ntiles;
+    }
     const int per_xcd = ntiles / 8;
     if (tile < per_xcd * 8) tile = (tile & 7) * per_xcd + (tile >> 3);
-    constexpr int kBand = 8;
-    const int band = tile / (kBand * g.tiles_n);
-    const int band_rows = min(kBand, g.tiles_m - band * kBand);
+    const int band = quotient(tile, kBand * g.tiles_n, g.inv_band);
     const int in_band = tile - band * kBand * g.tiles_n;
-    tm = band * kBand + in_band % band_rows;
-    tn = in_band / band_rows;
+    const int band_rows = min(kBand, g.tiles_m - band * kBand);
+    tn = band_rows == kBand ? in_band / kBand : quotient(in_band, band_rows, g.inv_last);
+    tm = band * kBand + in_band - tn * band_rows;
   }
   const int m0 = tm * BM, n0 = tn * BN;
   // contraction range: causal products skip the slabs that are identically zero
   int k_begin = 0, k_end = g.K;
-  if (g.causal == kCausalKLeM) k_end = min(g.K, m0 + BM);
-  if (g.causal == kCausalKGeM) k_begin = m0;
-  const int split = SPLITK ? block_x / (g.tiles_m * g.tiles_n) : 0;
+  if (SEQ && g.causal == kCausalKLeM) k_end = min(g.K, m0 + BM);
+  if (SEQ && g.causal == kCausalKGeM) k_begin = m0;
   if (SPLITK) {
     k_begin = split * g.k_per;
     k_end = min(g.K, k_begin + g.k_per);
   }
-  const int z1 = bz / g.nz2, z2 = bz - z1 * g.nz2;
-  const bf16_t* Abase = g.A + z1 * g.a_z1 + z2 * g.a_z2;
-  const bf16_t* Bbase = g.B + z1 * g.b_z1 + z2 * g.b_z2;
-  bf16_t* Cbase = g.C + z1 * g.c_z1 + z2 * g.c_z2;
+  const bf16_t *Abase = g.A, *Bbase = g.B;
+  bf16_t* Cbase = g.C;
+  if (SEQ) {
+    const int z1 = quotient(bz, g.nz2, g.inv_nz2), z2 = bz - z1 * g.nz2;
+    Abase += z1 * g.a_z1 + z2 * g.a_z2;
+    Bbase += z1 * g.b_z1 + z2 * g.b_z2;
+    Cbase += z1 * g.c_z1 + z2 * g.c_z2;
+  }
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -175,6 +201,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   // the slab that reaches beyond the contraction range (none: -1), and how many of its k exist
   const int k_rem = (k_end - k_begin) % BK;
   const int tail = RAGGED && k_rem != 0 ? nk - 1 : -1;
+  const int whole = FAR ? 0 : (tail < 0 ? nk : tail);  // slabs that buffer loads fetch
 
   // Direct load j of an operand's slab kt to `to` (wavefront-uniform).  Steady: the slab is whole, and the load is a
   // buffer load with the slab's corner in scalar registers, so that no vector instruction goes with it.  (Pointers
@@ -194,17 +221,32 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
     }
   };
   constexpr std::integral_constant<bool, false> kA{}, kAny{};
-  constexpr std::integral_constant<bool, true> kB{};
+  constexpr std::integral_constant<bool, true> kB{}, kSteady{};
   // j-th direct load of slab kt (A's first, then B's) -> ring stage kt % STAGES
   auto issue_load = [&](auto steady_tag, int kt, int j) {
     bf16_t* sa = smem + (kt % STAGES) * kStageElems;
     if (j < SA::kLoadsPerWave) load(kA, steady_tag, kt, j, sa + SA::lds_offset(wave, j));
     else load(kB, steady_tag, kt, j - SA::kLoadsPerWave, sa + SA::kElems + SB::lds_offset(wave, j - SA::kLoadsPerWave));
   };
-  auto issue_slab = [&](int kt) {
+  auto issue_slab = [&](auto steady_tag, int kt) {
 #pragma unroll
-    for (int j = 0; j < kLoads; ++j) issue_load(kAny, kt, j);
+    for (int j = 0; j < kLoads; ++j) issue_load(steady_tag, kt, j);
   };
+
+  // Bias of this wavefront's columns.  Tiles of four wavefronts request it ahead of the contraction (larger ones have no
+  // registers to spare and do so in one batch behind it: one exposed round trip to L2).
+  constexpr bool kBiasEarly = WAVES == 4 && !SEQ && !SPLITK;
+  uint2 braw[TN][4];
+  auto request_bias = [&] {
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int n = n0 + wn0 + 32 * i + 8 * q + 4 * (lane >> 5);
+        braw[i][q] = *reinterpret_cast<const uint2*>(g.bias + (RAGGED ? min(n, g.N - 4) : n));
+      }
+  };
+  if (kBiasEarly && g.bias != nullptr) request_bias();
 
   floatx16_t acc[TN][TM];
 #pragma unroll
@@ -247,30 +289,35 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
     };
     constexpr std::integral_constant<int, 0> kFirst{};
     constexpr std::integral_constant<int, 1> kSecond{};
-    auto load_all = [&](auto h_tag, int kt, int at) {
+    auto load_all = [&](auto h_tag, auto steady_tag, int kt, int at) {
 #pragma unroll
-      for (int j = 0; j < kHalf; ++j) load_half(h_tag, kAny, kt, at, j);
+      for (int j = 0; j < kHalf; ++j) load_half(h_tag, steady_tag, kt, at, j);
     };
     // The order of halves: in turn, A0 | B0 A1 | B1 A2 | ...: `first half k` is B(k), `second half k` A(k + 1) with
     // its slab counted as k + 1; otherwise the halves of slab k.  `kAhead` slabs after kt, a compute phase of the
     // first group issues half c; the second group, half a slab later in time, has done half 0 a phase before and
     // goes on to the next slab's.  Before the loop: what those phases assume done; then slab 0 has landed.
-    if constexpr (kInTurn) {
-      load_all(kSecond, 0, 0);
-      load_all(kFirst, 0, 1);
-      if (nk > 1) {
-        load_all(kSecond, 1, 2);
-        if (wave >= 4) load_all(kFirst, 1, 3);
+    auto first_loads = [&](auto steady_tag) {
+      constexpr bool steady = decltype(steady_tag)::value;
+      if constexpr (kInTurn) {
+        load_all(kSecond, steady_tag, 0, 0);
+        load_all(kFirst, steady_tag, 0, 1);
+        if (steady || nk > 1) {
+          load_all(kSecond, steady_tag, 1, 2);
+          if (wave >= 4) load_all(kFirst, steady_tag, 1, 3);
+        }
+      } else {
+        load_all(kFirst, steady_tag, 0, 0);
+        load_all(kSecond, steady_tag, 0, 0);
+        if (steady || nk > 1) {
+          load_all(kFirst, steady_tag, 1, 1);
+          load_all(kSecond, steady_tag, 1, 1);
+          if (wave >= 4 && (steady || nk > 2)) load_all(kFirst, steady_tag, 2, 2);
+        }
       }
-    } else {
-      load_all(kFirst, 0, 0);
-      load_all(kSecond, 0, 0);
-      if (nk > 1) {
-        load_all(kFirst, 1, 1);
-        load_all(kSecond, 1, 1);
-        if (wave >= 4 && nk > 2) load_all(kFirst, 2, 2);
-      }
-    }
+    };
+    if (whole > 2) first_loads(kSteady);
+    else first_loads(kAny);
     constexpr int kNewer = kInTurn ? kHalf : 2 * kHalf;  // loads issued after slab kt + 1's when it is waited for
     if (nk > 1) {
       if (wave >= 4 && (kInTurn || nk > 2)) wait_vmcnt<kNewer + kHalf>();
@@ -379,9 +426,14 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   // prologue: STAGES - 1 slabs in flight, the first one landed
   constexpr int kAhead = STAGES - 1;
   static_assert(kAhead >= 1 && (kAhead - 1) * kLoads < 64, "ring depth");
+  if (kAhead <= whole) {
 #pragma unroll
-  for (int i = 0; i < kAhead; ++i)
-    if (i < nk) issue_slab(i);
+    for (int i = 0; i < kAhead; ++i) issue_slab(kSteady, i);
+  } else {
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+      if (i < nk) issue_slab(kAny, i);
+  }
   wait_slabs<kLoads, kAhead - 1>(nk - 1);
   block_barrier();
 
@@ -495,7 +547,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   wait_lgkmcnt0();
   settle(0);
   int kt = 0;
-  for (; kt + kAhead < (tail < 0 ? nk : tail); ++kt) {
+  for (; kt + kAhead < whole; ++kt) {
     slab_step(kt, std::true_type{});
     end_range(kt);
   }
@@ -598,17 +650,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   bf16_t* stage = smem + wave * (WM * WN);
   auto round_to_stage = [&](auto bias_tag) {
     constexpr bool with_bias = decltype(bias_tag)::value;
-    // (the bias values of this wavefront's columns in one batch: one exposed L2 round trip)
-    uint2 braw[with_bias ? TN : 1][4];
-    if constexpr (with_bias) {
-#pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int n = col0 + 32 * i + 8 * q + 4 * (lane >> 5);
-          braw[i][q] = *reinterpret_cast<const uint2*>(g.bias + (RAGGED ? min(n, g.N - 4) : n));
-        }
-    }
+    if (with_bias && !kBiasEarly) request_bias();
     block_barrier();  // every wavefront is done with the ring (no load is in flight any more)
 #pragma unroll
     for (int i = 0; i < TN; ++i)

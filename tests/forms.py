@@ -21,6 +21,12 @@ def score_run(seq, slices):
     return _lib.lynx_form_score_run(seq, slices)
 
 
+def quotient(x, d, most):
+    """(x / d as tile indices are divided, by the inverse or not)"""
+    by_inverse = ctypes.c_int()
+    return _lib.lynx_form_quotient(x, d, ctypes.c_longlong(most), ctypes.byref(by_inverse)), bool(by_inverse.value)
+
+
 def product(M, N, K):
     """(rows, columns of the tile, K ranges)"""
     out = (ctypes.c_int * 3)()
