@@ -223,11 +223,12 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   constexpr std::integral_constant<bool, false> kA{}, kAny{};
   constexpr std::integral_constant<bool, true> kB{}, kSteady{};
   // j-th direct load of slab kt (A's first, then B's) -> ring stage kt % STAGES
-  auto issue_load = [&](auto steady_tag, int kt, int j) {
-    bf16_t* sa = smem + (kt % STAGES) * kStageElems;
+  auto stage_load = [&](auto steady_tag, int kt, int stage, int j) {
+    bf16_t* sa = smem + stage * kStageElems;
     if (j < SA::kLoadsPerWave) load(kA, steady_tag, kt, j, sa + SA::lds_offset(wave, j));
     else load(kB, steady_tag, kt, j - SA::kLoadsPerWave, sa + SA::kElems + SB::lds_offset(wave, j - SA::kLoadsPerWave));
   };
+  auto issue_load = [&](auto steady_tag, int kt, int j) { stage_load(steady_tag, kt, kt % STAGES, j); };
   auto issue_slab = [&](auto steady_tag, int kt) {
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) issue_load(steady_tag, kt, j);
@@ -423,6 +424,119 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
       else contract(kSecond, std::false_type{});
     }
   } else {
+  static_assert(!(SERIAL && SPLITK), "ranges one after the other, or one each");
+  floatx16_t total[SERIAL ? TN : 1][SERIAL ? TM : 1];  // SERIAL: sum of the ranges that are complete
+  if constexpr (SERIAL) {
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) total[i][j][r] = -0.f;  // (-0 + x has the bits of x)
+  }
+  const int range_slabs = SERIAL ? g.k_per / BK : 0;
+  auto end_range = [&](int kt) {
+    if constexpr (SERIAL) {
+      if (kt + 1 < nk && (kt + 1) % range_slabs != 0) return;
+#pragma unroll
+      for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            total[i][j][r] += acc[i][j][r];
+            acc[i][j][r] = kt + 1 < nk ? 0.f : total[i][j][r];
+          }
+    }
+  };
+  if constexpr (A_KMAJOR && B_KMAJOR && TM * TN <= 2) {
+    // Little to multiply per slab (four or eight matrix instructions of a wavefront): what counts is the chain from slab
+    // to slab.  All fragments of the next slab are requested at once, right behind the barrier that says it has landed, and
+    // arrive while this slab's are multiplied; the barrier also frees this slab's stage, whose fragments every
+    // wavefront has in registers, so STAGES slabs are in flight.  (With a request and a wait per 16 indices, the loop below, a
+    // forward pass of 128 tokens of h 5120 takes 63.6 us where this takes 62.6; with MN-major operands, whose requests are
+    // twice as many instructions, that loop is the faster one: small_bf16_store_all 118.8 and 120.3.)
+    constexpr int kSteps = BK / 16;
+    constexpr int kMfmas = kSteps * TM * TN;
+    auto first_slabs = [&](auto steady_tag) {
+      constexpr bool steady = decltype(steady_tag)::value;
+#pragma unroll
+      for (int i = 0; i < STAGES; ++i)
+        if (steady || i < nk)
+#pragma unroll
+          for (int j = 0; j < kLoads; ++j) stage_load(steady_tag, i, i, j);
+    };
+    if (STAGES <= whole) first_slabs(kSteady);
+    else first_slabs(kAny);
+    wait_slabs<kLoads, STAGES - 1>(nk - 1);
+    block_barrier();
+    Frag<A_KMAJOR> fa[2][kSteps][TM];
+    Frag<B_KMAJOR> fb[2][kSteps][TN];
+    auto request = [&](auto set_tag, int stage) {
+      constexpr int set = decltype(set_tag)::value;
+      const bf16_t* sa = smem + stage * kStageElems;
+#pragma unroll
+      for (int u = 0; u < kSteps; ++u) {
+#pragma unroll
+        for (int j = 0; j < TM; ++j) fa[set][u][j] = SA::fragment(sa, wm0 + 32 * j, u, lane);
+#pragma unroll
+        for (int i = 0; i < TN; ++i) fb[set][u][i] = SB::fragment(sa + SA::kElems, wn0 + 32 * i, u, lane);
+      }
+    };
+    auto arrived = [&](auto set_tag) {
+      constexpr int set = decltype(set_tag)::value;
+      wait_lgkmcnt0();
+#pragma unroll
+      for (int u = 0; u < kSteps; ++u) {
+#pragma unroll
+        for (int j = 0; j < TM; ++j) fa[set][u][j].settle();
+#pragma unroll
+        for (int i = 0; i < TN; ++i) fb[set][u][i].settle();
+      }
+    };
+    constexpr std::integral_constant<int, 0> kEven{};
+    constexpr std::integral_constant<int, 1> kOdd{};
+    request(kEven, 0);
+    arrived(kEven);
+    int stage = 0;
+    auto slab_step = [&](int kt, auto set_tag, auto steady_tag) {
+      constexpr int set = decltype(set_tag)::value;
+      constexpr bool steady = decltype(steady_tag)::value;
+      constexpr std::integral_constant<int, 1 - set> kNext{};
+      const int freed = stage;
+      stage = stage + 1 == STAGES ? 0 : stage + 1;
+      const bool more = steady || kt + 1 < nk;
+      if (more) {
+        if (steady) wait_vmcnt<(STAGES - 2) * kLoads>();
+        else wait_slabs<kLoads, STAGES - 2>(nk - 2 - kt);
+        block_barrier</*WAITED=*/true>();
+        request(kNext, stage);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int m = 0; m < kMfmas; ++m) {
+        const int u = m / (TM * TN), i = m / TM % TN, j = m % TM;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][u][i].operand(), fa[set][u][j].operand(), acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (m == 0 && (steady || kt + STAGES < nk)) {
+#pragma unroll
+          for (int j2 = 0; j2 < kLoads; ++j2) stage_load(steady_tag, kt + STAGES, freed, j2);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (more) arrived(kNext);
+      end_range(kt);
+    };
+    int kt = 0;
+    for (; kt + 1 + STAGES < whole; kt += 2) {
+      slab_step(kt, kEven, std::true_type{});
+      slab_step(kt + 1, kOdd, std::true_type{});
+    }
+    for (; kt < nk; kt += 2) {
+      slab_step(kt, kEven, std::false_type{});
+      if (kt + 1 < nk) slab_step(kt + 1, kOdd, std::false_type{});
+    }
+  } else {
   // prologue: STAGES - 1 slabs in flight, the first one landed
   constexpr int kAhead = STAGES - 1;
   static_assert(kAhead >= 1 && (kAhead - 1) * kLoads < 64, "ring depth");
@@ -519,31 +633,6 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
     wait_lgkmcnt0();  // the next slab's first fragments have arrived
     if (more) settle(last ^ 1);
   };
-  static_assert(!(SERIAL && SPLITK), "ranges one after the other, or one each");
-  floatx16_t total[SERIAL ? TN : 1][SERIAL ? TM : 1];  // SERIAL: sum of the ranges that are complete
-  if constexpr (SERIAL) {
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) total[i][j][r] = -0.f;  // (-0 + x has the bits of x)
-  }
-  const int range_slabs = SERIAL ? g.k_per / BK : 0;
-  auto end_range = [&](int kt) {
-    if constexpr (SERIAL) {
-      if (kt + 1 < nk && (kt + 1) % range_slabs != 0) return;
-#pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            total[i][j][r] += acc[i][j][r];
-            acc[i][j][r] = kt + 1 < nk ? 0.f : total[i][j][r];
-          }
-    }
-  };
   wait_lgkmcnt0();
   settle(0);
   int kt = 0;
@@ -554,6 +643,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   for (; kt < nk; ++kt) {
     slab_step(kt, std::false_type{});
     end_range(kt);
+  }
   }
   }
 
