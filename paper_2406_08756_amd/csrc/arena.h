@@ -36,6 +36,23 @@ class Arena {
     return false;
   }
 
+  // The block at `offset` (a multiple of kAlign); false unless all of it is free.
+  bool alloc_at(size_t offset, size_t bytes) {
+    const size_t need = round_up(bytes == 0 ? 1 : bytes);
+    auto it = free_.upper_bound(offset);
+    if (it == free_.begin()) return false;
+    --it;
+    const size_t first = it->first, end = it->first + it->second;
+    if (offset + need > end) return false;
+    free_.erase(it);
+    if (offset > first) free_[first] = offset - first;
+    if (end > offset + need) free_[offset + need] = end - (offset + need);
+    used_[offset] = need;
+    in_use_ += need;
+    if (offset + need > extent_peak_) extent_peak_ = offset + need;
+    return true;
+  }
+
   // The upper end of the highest block that fits.
   bool alloc_high(size_t bytes, size_t* offset) {
     const size_t need = round_up(bytes == 0 ? 1 : bytes);

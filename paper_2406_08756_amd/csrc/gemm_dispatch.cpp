@@ -35,6 +35,8 @@ bool gemm_mfma_supported(int dtype, const GemmDesc& d) {
     case kEpiBiasDropoutAdd:
       return unbatched(d) && d.bias == nullptr && d.epi.aux != nullptr && aligned(d.epi.aux, 16) &&
              d.epi.aux_ld % 8 == 0 && d.epi.vec != nullptr && aligned(d.epi.vec, 16) && aligned(d.epi.plain, 16);
+    case kEpiGelu:
+      return unbatched(d) && a_k && b_k && aligned(d.epi.plain, 16);
     case kEpiGeluBwd:  // inside a pair only
       return unbatched(d) && d.bias == nullptr && d.epi.aux != nullptr && aligned(d.epi.aux, 16) &&
              d.epi.aux_ld % 8 == 0 && d.epi.colsum_partial != nullptr && aligned(d.epi.colsum_partial, 16) &&
@@ -54,8 +56,21 @@ size_t gemm_scratch_bytes(int dtype, const GemmDesc& d) {
   return ragged_product(d).scratch_bytes;
 }
 
+// Tiles of four wavefronts, two workgroups per unit, or a cut contraction's second launch: GeLU costs next to nothing there
+// and saves a launch and U's way back, a pass of the fp32 block of 256 tokens of h 256 141.2 -> 138.1 us, of 768 tokens of
+// h 512 118.9 -> 116.4, of 984 of h 3016 440.3 -> 433.5, of a drawn small layer 136.8 -> 132.2.  A tile of eight wavefronts has its unit to
+// itself, so GeLU adds its 8 us per round to the launch, what the kernel of its own takes: 4000 tokens of h 1600 1206.8
+// and 1208.8, 8192 of h 1024 1062.7 and 1062.3, a drawn large layer 1354 and 1373.
+bool gemm_absorbs_gelu(int dtype, const GemmDesc& d) {
+  if (!gemm_supported(dtype, d)) return false;
+  if (dtype != 1) return true;
+  const RaggedChoice c = ragged_product(d);
+  return c.tile_m <= 128 || c.ranges > 1;
+}
+
 hipError_t gemm(int dtype, const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st) {
   if (!gemm_supported(dtype, d) || d.epi.kind == kEpiGeluBwd) return hipErrorInvalidValue;
+  if (d.epi.kind == kEpiGelu && !gemm_absorbs_gelu(dtype, d)) return hipErrorInvalidValue;
   if (dtype != 1) return gemm_f32(d, st);
   if (d.causal != kCausalNone) return gemm_attention(d, st);
   return gemm_ragged(d, scratch, scratch_bytes, st);

@@ -156,9 +156,14 @@ __device__ __forceinline__ void store_tile(const GemmDesc& d, const DropoutKey& 
       }
     }
     float* c = t.C + m * d.c_sm + n;
-    if (d.epi.kind == kEpiNone) {
+    if (d.epi.kind == kEpiNone || d.epi.kind == kEpiGelu) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[i] += bias[i];
+      if (d.epi.kind == kEpiGelu) {
+        if (d.epi.plain != nullptr) store8(static_cast<float*>(d.epi.plain) + m * d.c_sm + n, v);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = gelu_f(v[i]);
+      }
       store8(c, v);
     } else {
       float x[8], o[8];
@@ -391,6 +396,7 @@ bool gemm_f32_supported(const GemmDesc& d) {
   if (!aligned16(d.A) || !aligned16(d.B) || !aligned16(d.C) || !aligned16(d.bias)) return false;
   switch (d.epi.kind) {
     case kEpiNone: return true;
+    case kEpiGelu: return d.causal == kCausalNone && d.nz1 * d.nz2 == 1 && aligned16(d.epi.plain);
     case kEpiBiasDropoutAdd:
       return d.causal == kCausalNone && d.nz1 * d.nz2 == 1 && d.bias == nullptr && d.epi.aux != nullptr &&
              aligned16(d.epi.aux) && d.epi.aux_ld % 4 == 0 && d.epi.vec != nullptr && aligned16(d.epi.vec) &&

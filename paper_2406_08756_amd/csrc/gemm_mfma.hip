@@ -12,7 +12,7 @@ namespace {
 // unit (one loads while the other stores).
 template <bool A_KMAJOR>
 __global__ void __launch_bounds__(kThreads, 2) attn_product_kernel(MfmaGemmArgs g) {
-  gemm_tile<A_KMAJOR, false, 128, 128, true>(g, blockIdx.x, 0);
+  gemm_tile<A_KMAJOR, false, 128, 128, kOfSequence>(g, blockIdx.x, 0);
 }
 
 // Work items of the score-shaped row-block kernels: row block tm (128 rows) owns tiles

@@ -136,12 +136,12 @@ ProductPlan plan_product(const GemmDesc& d) {
 }
 
 // ---- kernels ------------------------------------------------------------------
-template <bool AK, bool BK_, int TILE, bool FAR, bool SEQ>
+template <bool AK, bool BK_, int TILE, bool FAR, TileForm FORM>
 __global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
 gemm_ragged_kernel(MfmaGemmArgs g) {
   using T = TileShape<TILE, AK && BK_>;
-  if (!SEQ && g.k_splits > 1) gemm_tile<AK, BK_, T::BM, T::BN, false, true, T::S, true, T::BK, T::waves, false, FAR>(g, blockIdx.x, 0);
-  else gemm_tile<AK, BK_, T::BM, T::BN, SEQ, false, T::S, true, T::BK, T::waves, false, FAR>(g, blockIdx.x, SEQ ? blockIdx.y : 0);
+  if (FORM == kSingle && g.k_splits > 1) gemm_tile<AK, BK_, T::BM, T::BN, kSingle, true, T::S, true, T::BK, T::waves, false, FAR>(g, blockIdx.x, 0);
+  else gemm_tile<AK, BK_, T::BM, T::BN, FORM, false, T::S, true, T::BK, T::waves, false, FAR>(g, blockIdx.x, FORM == kOfSequence ? blockIdx.y : 0);
 }
 
 // Both products of a linear layer's backward in one launch: the first n_first workgroups belong to the one
@@ -158,19 +158,19 @@ gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int
   if (x >= n_first && x < n_pad) return;
   const int tile = x < n_first ? x : x - n_pad;
   if ((x < n_first) != (dgrad_first != 0)) {
-    if (wgrad.k_splits > 1) gemm_tile<false, false, T::BM, T::BN, false, true, T::S, true, T::BK, T::waves, false, FAR>(wgrad, tile, 0);
-    else gemm_tile<false, false, T::BM, T::BN, false, false, T::S, true, T::BK, T::waves, false, FAR>(wgrad, tile, 0);
+    if (wgrad.k_splits > 1) gemm_tile<false, false, T::BM, T::BN, kSingle, true, T::S, true, T::BK, T::waves, false, FAR>(wgrad, tile, 0);
+    else gemm_tile<false, false, T::BM, T::BN, kSingle, false, T::S, true, T::BK, T::waves, false, FAR>(wgrad, tile, 0);
   } else {
-    if (dgrad.k_splits > 1) gemm_tile<true, false, T::BM, T::BN, false, true, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
-    else gemm_tile<true, false, T::BM, T::BN, false, false, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
+    if (dgrad.k_splits > 1) gemm_tile<true, false, T::BM, T::BN, kSingle, true, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
+    else gemm_tile<true, false, T::BM, T::BN, kSingle, false, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
   }
 }
 
-template <bool AK, bool BK_, int TILE, bool FAR, bool SEQ>
+template <bool AK, bool BK_, int TILE, bool FAR, TileForm FORM>
 hipError_t launch_ragged(MfmaGemmArgs a, hipStream_t st) {
   using T = TileShape<TILE, AK && BK_>;
   constexpr size_t smem = tile_lds<T>;
-  auto kern = gemm_ragged_kernel<AK, BK_, TILE, FAR, SEQ>;
+  auto kern = gemm_ragged_kernel<AK, BK_, TILE, FAR, FORM>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   set_tiles(&a, T::BM, T::BN);
   const int ntiles = a.causal == kCausalOutLower ? a.tiles_m * (a.tiles_m + 1) / 2 : a.tiles_m * a.tiles_n * a.k_splits;
@@ -182,22 +182,33 @@ hipError_t launch_ragged(MfmaGemmArgs a, hipStream_t st) {
 template <bool AK, bool BK_>
 hipError_t launch_tile(int tile, bool far, const MfmaGemmArgs& a, hipStream_t st) {
   if (a.causal != kCausalNone) {  // attention, in tiles of at most 128 x 128
-    if (far) return launch_ragged<AK, BK_, kT64, true, true>(a, st);
+    if (far) return launch_ragged<AK, BK_, kT64, true, kOfSequence>(a, st);
     switch (tile) {
-      case kT128: return launch_ragged<AK, BK_, kT128, false, true>(a, st);
-      case kT128x64: return launch_ragged<AK, BK_, kT128x64, false, true>(a, st);
-      default: return launch_ragged<AK, BK_, kT64, false, true>(a, st);
+      case kT128: return launch_ragged<AK, BK_, kT128, false, kOfSequence>(a, st);
+      case kT128x64: return launch_ragged<AK, BK_, kT128x64, false, kOfSequence>(a, st);
+      default: return launch_ragged<AK, BK_, kT64, false, kOfSequence>(a, st);
     }
   }
-  if (far) return launch_ragged<AK, BK_, kT64, true, false>(a, st);
+  if constexpr (AK && BK_) {  // GeLU in the store pass, in tiles of four wavefronts
+    if (a.epi == kEpiGelu && a.k_splits == 1) {
+      if (far) return launch_ragged<AK, BK_, kT64, true, kWithGelu>(a, st);
+      switch (tile) {
+        case kT128: return launch_ragged<AK, BK_, kT128, false, kWithGelu>(a, st);
+        case kT128x64: return launch_ragged<AK, BK_, kT128x64, false, kWithGelu>(a, st);
+        case kT64: return launch_ragged<AK, BK_, kT64, false, kWithGelu>(a, st);
+        default: return hipErrorInvalidValue;
+      }
+    }
+  }
+  if (far) return launch_ragged<AK, BK_, kT64, true, kSingle>(a, st);
   if constexpr (AK) {  // (no larger one for two MN-major operands)
-    if (tile == kT256) return launch_ragged<AK, BK_, kT256, false, false>(a, st);
-    if (tile == kT256x128) return launch_ragged<AK, BK_, kT256x128, false, false>(a, st);
+    if (tile == kT256) return launch_ragged<AK, BK_, kT256, false, kSingle>(a, st);
+    if (tile == kT256x128) return launch_ragged<AK, BK_, kT256x128, false, kSingle>(a, st);
   }
   switch (tile) {
-    case kT128: return launch_ragged<AK, BK_, kT128, false, false>(a, st);
-    case kT128x64: return launch_ragged<AK, BK_, kT128x64, false, false>(a, st);
-    default: return launch_ragged<AK, BK_, kT64, false, false>(a, st);
+    case kT128: return launch_ragged<AK, BK_, kT128, false, kSingle>(a, st);
+    case kT128x64: return launch_ragged<AK, BK_, kT128x64, false, kSingle>(a, st);
+    default: return launch_ragged<AK, BK_, kT64, false, kSingle>(a, st);
   }
 }
 
@@ -206,19 +217,21 @@ hipError_t launch_tile(int tile, bool far, const MfmaGemmArgs& a, hipStream_t st
 // Latency of the whole contraction on a part of the chip bounds it; it is for workspaces that have no room for the
 // cut form.  128 tokens of h 5120 (QKV of width 1920, FC1 of 2560): 29 us each, cut 14 and 16; a step of that layer
 // 419 us against 268, of 512 tokens of h 3072 437 against 411, with both gradients of a layer as launches of their own.
-template <bool AK, bool BK_, bool FAR>
+template <bool AK, bool BK_, bool FAR, TileForm FORM>
 __global__ void __launch_bounds__((tile_threads<kT64>), (tile_waves_per_simd<kT64>)) gemm_serial_kernel(MfmaGemmArgs g) {
   using T = TileShape<kT64, AK && BK_>;
-  gemm_tile<AK, BK_, T::BM, T::BN, false, false, T::S, true, T::BK, T::waves, true, FAR>(g, blockIdx.x, 0);
+  gemm_tile<AK, BK_, T::BM, T::BN, FORM, false, T::S, true, T::BK, T::waves, true, FAR>(g, blockIdx.x, 0);
 }
 
-template <bool AK, bool BK_, bool FAR = false>
+template <bool AK, bool BK_, bool FAR = false, TileForm FORM = kSingle>
 hipError_t launch_serial(bool far, MfmaGemmArgs a, hipStream_t st) {
   if (far && !FAR) return launch_serial<AK, BK_, true>(far, a, st);
+  if constexpr (AK && BK_ && FORM == kSingle)
+    if (a.epi == kEpiGelu) return launch_serial<AK, BK_, FAR, kWithGelu>(far, a, st);
   using T = TileShape<kT64, AK && BK_>;
   static_assert(kMaxBK % T::BK == 0, "ranges are whole slabs");
   constexpr size_t smem = tile_lds<T>;
-  auto kern = gemm_serial_kernel<AK, BK_, FAR>;
+  auto kern = gemm_serial_kernel<AK, BK_, FAR, FORM>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   set_tiles(&a, T::BM, T::BN);
   hipLaunchKernelGGL(kern, dim3(a.tiles_m * a.tiles_n), dim3(T::waves * kWave), smem, st, a);
@@ -244,8 +257,8 @@ attn_gradients_kernel(MfmaGemmArgs rows, MfmaGemmArgs cols, int by_slice) {
     z = x - w * rows.nz;
   }
   const int tile = (w >> 1) * rows.nz + z;
-  if (w & 1) gemm_tile<false, false, T::BM, T::BN, true, false, T::S, true, T::BK, T::waves, false, FAR>(cols, tile, 0);
-  else gemm_tile<true, false, T::BM, T::BN, true, false, T::S, true, T::BK, T::waves, false, FAR>(rows, tile, 0);
+  if (w & 1) gemm_tile<false, false, T::BM, T::BN, kOfSequence, false, T::S, true, T::BK, T::waves, false, FAR>(cols, tile, 0);
+  else gemm_tile<true, false, T::BM, T::BN, kOfSequence, false, T::S, true, T::BK, T::waves, false, FAR>(rows, tile, 0);
 }
 
 template <int TILE, bool FAR = false>
@@ -284,7 +297,7 @@ hipError_t launch_ragged_pair(MfmaGemmArgs w, MfmaGemmArgs d, hipStream_t st) {
 }
 
 // C = round(sum over the K ranges, in range order, of partial[range][m][n] (+ bias)), and what the
-// product's epilogue does with it (GemmEpilogueKind: none, or bias + dropout + residual), for one or
+// product's epilogue does with it (GemmEpilogueKind: none, GeLU, or bias + dropout + residual), for one or
 // two products: the first `n0` workgroups belong to `a`, the rest to `b`.
 __global__ void __launch_bounds__(256) splitk_finish_kernel(MfmaGemmArgs a, MfmaGemmArgs b, int n0) {
   const bool second = static_cast<int>(blockIdx.x) >= n0;
@@ -318,6 +331,12 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(MfmaGemmArgs a, Mfma
 #pragma unroll
   for (int i = 0; i < 8; ++i) s[i] = round_to_storage(s[i], static_cast<bf16_t*>(nullptr));
   if (g.plain != nullptr) store8(g.plain + static_cast<long long>(m) * g.ldc + n, s);
+  if (g.epi == kEpiGelu) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i] = gelu_f(s[i]);
+    store8(c, o);
+    return;
+  }
   load8(g.vec + n, vec);
   load8(g.aux + static_cast<long long>(m) * g.aux_ld + n, x);
   bias_dropout_add8(s, vec, x, g.key, (static_cast<uint64_t>(m) * static_cast<uint64_t>(g.N) + n) >> 3, o);

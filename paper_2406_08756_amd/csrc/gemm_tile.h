@@ -101,10 +101,13 @@ __device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
 //
 // FAR: a row stride of kFarStride elements or more.
 //
-// SEQ: one of a batch of matrices, with CausalMode (attention); otherwise g is a single product.
-template <bool A_KMAJOR, bool B_KMAJOR, int BM, int BN, bool SEQ, bool SPLITK = false, int STAGES = kStages, bool RAGGED = false,
+// FORM: a single product, one that carries GeLU (in kernels of its own: with it behind a branch of the epilogue the others
+// took 0.2 us longer each, of 7 to 13), or one of a batch of matrices with CausalMode (attention).
+enum TileForm { kSingle, kWithGelu, kOfSequence };
+template <bool A_KMAJOR, bool B_KMAJOR, int BM, int BN, TileForm FORM, bool SPLITK = false, int STAGES = kStages, bool RAGGED = false,
           int BK = kBK, int WAVES = kWaves, bool SERIAL = false, bool FAR = false>
 __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block_x, const int block_z) {
+  constexpr bool SEQ = FORM == kOfSequence;
   constexpr int kWavesN = WAVES == 8 ? BN / 64 : 2;
   constexpr int WM = BM * kWavesN / WAVES, WN = BN / kWavesN;  // wavefronts in a grid of WAVES / kWavesN x kWavesN
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -730,7 +733,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   constexpr int kBatches = kIters / kBatch;
   static_assert(kIters % kBatch == 0, "epilogue batches");
   uintx4_t ra0[kBatch], ra1[kBatch];
-  const bool fused = g.epi != kEpiNone;
+  const bool fused = FORM != kWithGelu && g.epi != kEpiNone;
   const Rows aux = rows_of(fused ? g.aux : Cbase, fused ? g.aux_ld : g.ldc);
   auto aux_load = [&](uintx4_t (&ra)[kBatch], int batch) {
 #pragma unroll
@@ -771,7 +774,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
     return *reinterpret_cast<const uintx4_t*>(stage + r * WN + ((lc ^ (r & (kRowChunks - 1))) << 3));
   };
   const Rows out = rows_of(Cbase, g.ldc);
-  if (!fused) {
+  if (FORM != kWithGelu && !fused) {
 #pragma unroll
     for (int t = 0; t < kIters; ++t) row_store(out, t, staged(t));
     return;
@@ -784,6 +787,22 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
   auto packed = [](const float (&v)[8]) {
     return uintx4_t{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
   };
+  if constexpr (FORM == kWithGelu) {
+    // U, where somebody wants it, and G
+    const bool keep_u = g.plain != nullptr;
+    const Rows plain = rows_of(keep_u ? g.plain : Cbase, g.ldc);
+#pragma unroll
+    for (int t = 0; t < kIters; ++t) {
+      const uintx4_t p = staged(t);
+      if (keep_u) row_store(plain, t, p);
+      float u[8];
+      unpacked(p, u);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) u[i] = gelu_f(u[i]);
+      row_store(out, t, packed(u));
+    }
+    return;
+  }
   auto all_batches = [&](auto&& finish) {
     if (kBatches > 1) aux_load(ra1, 1);
 #pragma unroll

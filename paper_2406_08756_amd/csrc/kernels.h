@@ -152,6 +152,9 @@ enum GemmEpilogueKind : int {
   // pair's `sums`.  With room for gemm_pair_colsum_bytes (`colsum_bytes`) in one launch; with less (at least
   // gemm_pair_colsum_least_bytes) in ranges of columns, each with both of its stages before the next: the same bits.
   kEpiGeluBwd = 2,
+  // GeLU (operators 10 + 11): U = the product with its bias, rounded, is stored to `plain` unless that is null, and C =
+  // gelu(U).  Bit-identical to gelu_fwd run on a stored U.
+  kEpiGelu = 3,
   // dropout + softmax backward (B5 + B4) on the score-shaped product dPd = dC V^T (causal,
   // batched): C = dS = scale aux (keep c P - rowdot), aux = the softmax output P in the layout
   // of C, rowdot[z * M + i] the row's sum_j dP_ij P_ij (attn_rowdot), dropout site 0 with the
@@ -163,7 +166,7 @@ struct GemmEpilogue {
   const void* aux;        // [M, N], row stride aux_ld: the residual (1) or U (2)
   long long aux_ld;
   const void* vec;        // (1) bias[N]
-  void* plain;            // (1) nullable
+  void* plain;            // (1) (3) nullable
   int site;               // (1)
   DropoutParams dp;       // (1)
   float* colsum_partial;  // (2)
@@ -202,6 +205,8 @@ bool gemm_supported(int dtype, const GemmDesc& d);
 // (dPd and dV).  bf16: the bits of gemm() on each.  fp32: the tile, and with it whether a contraction is one sum or four,
 // is chosen for both together.
 hipError_t gemm_seq_pair(int dtype, const GemmDesc& first, const GemmDesc& cols, hipStream_t st);
+// Whether a forward product should carry GeLU (kEpiGelu): supported, and it pays.
+bool gemm_absorbs_gelu(int dtype, const GemmDesc& d);
 // Input gradient and weight gradient of one linear layer in one launch.  `scratch` as above
 // (gemm_pair_scratch_bytes).
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,

@@ -475,6 +475,68 @@ lynx_status run_fused_linear(Ctx& cx, int lin) {
   return run_linear(cx, lin, fused_linear_desc(cx, lin, keep_product));
 }
 
+// OP10 + OP11 as one launch: G, and U if `keep_u` (its place is taken either way).  Same bits as the two.  The two
+// operators may put G where Y2 or the partial sums of a cut contraction were; plan_fused_gelu says whether it lies where
+// nothing is in the way, at `g_off`, and whether the partial sums have room below what the two operators reach.
+// Then every block lies where it did, and a workspace is large enough for one form exactly when it is for the other.
+// `y2_goes`: whether Y2 is released once U is there.  `passes`: neither G nor V2 outlives the forward pass, so that G may
+// lie wherever there is room for it, U, Y2 and the partial sums, and afterwards for those of operator 12.
+struct FusedGelu {
+  size_t g_off = 0;
+};
+GemmDesc fused_gelu_desc(const Ctx& cx, const void* y2, const void* w1, const void* b1, void* u, void* g_out) {
+  const Dims& D = cx.L->D;
+  GemmDesc g = linear_fwd(y2, w1, b1, g_out, D.T, D.f, D.h);
+  g.epi.kind = lynx::kEpiGelu;
+  g.epi.plain = u;
+  g.serial = without(*cx.bk, kSerial);
+  return g;
+}
+bool plan_fused_gelu(const Ctx& cx, bool y2_goes, bool passes, FusedGelu* plan) {
+  const Dims& D = cx.L->D;
+  // (shapes only: aligned addresses, as the blocks and the caller's buffers have)
+  void* const some = reinterpret_cast<void*>(256);
+  const GemmDesc g = fused_gelu_desc(cx, some, some, some, some, some);
+  if (!lynx::gemm_absorbs_gelu(D.dtype, g)) return false;
+  const size_t scratch_bytes = lynx::gemm_scratch_bytes(D.dtype, g);
+  const size_t g_bytes = Arena::round_up(act_bytes(D, 11)), y2_bytes = Arena::round_up(act_bytes(D, 9));
+  Arena apart = cx.bk->arena;  // as the two operators go about it
+  size_t u_off, scratch_off = 0;
+  if (!apart.alloc(act_bytes(D, 10), &u_off)) return false;
+  if (scratch_bytes > 0) {
+    if (!apart.alloc(scratch_bytes, &scratch_off)) return false;
+    apart.release(scratch_off);
+  }
+  if (y2_goes) apart.release(cx.bk->off[9]);
+  if (!apart.alloc(act_bytes(D, 11), &plan->g_off)) return false;
+  const bool on_y2 = y2_goes && plan->g_off < cx.bk->off[9] + y2_bytes && cx.bk->off[9] < plan->g_off + g_bytes;
+  Arena joint = cx.bk->arena;
+  if (!on_y2 && joint.alloc(act_bytes(D, 10), &u_off) && joint.alloc_at(plan->g_off, act_bytes(D, 11)) &&
+      (scratch_bytes == 0 || (joint.alloc(scratch_bytes, &scratch_off) && joint.extent_peak() <= apart.extent_peak())))
+    return true;
+  if (!passes || !can_fuse_linear(cx, 12)) return false;
+  joint = cx.bk->arena;
+  if (!joint.alloc(act_bytes(D, 10), &u_off) || !joint.alloc(act_bytes(D, 11), &plan->g_off)) return false;
+  if (scratch_bytes > 0) {
+    if (!joint.alloc(scratch_bytes, &scratch_off)) return false;
+    joint.release(scratch_off);
+  }
+  if (y2_goes) joint.release(cx.bk->off[9]);
+  if (!((cx.bk->retain >> 10) & 1u)) joint.release(u_off);
+  GemmDesc fc2 = linear_fwd(some, some, nullptr, some, D.T, D.h, D.f);
+  fc2.serial = without(*cx.bk, kSerial);
+  const size_t fc2_bytes = lynx::gemm_scratch_bytes(D.dtype, fc2);
+  return fc2_bytes == 0 || joint.alloc(fc2_bytes, &scratch_off);
+}
+lynx_status run_fused_gelu(Ctx& cx, const FusedGelu& plan, bool keep_u) {
+  LYNX_TRY(alloc_act(cx, 10));
+  if (!cx.bk->arena.alloc_at(plan.g_off, act_bytes(cx.L->D, 11))) return LYNX_ERR_OOM;
+  cx.bk->off[11] = plan.g_off;
+  cx.bk->live[11] = true;
+  return run_linear(cx, 10, fused_gelu_desc(cx, act_ptr(cx, 9), cx.L->params.w1, cx.L->params.b1,
+                                            keep_u ? act_ptr(cx, 10) : nullptr, act_ptr(cx, 11)));
+}
+
 // Operators 3-6 as one launch (attn_fused.hip): C and its row statistics from QKV.
 lynx_status run_fused_attention(Ctx& cx) {
   lynx_layer_s* L = cx.L;
@@ -513,6 +575,7 @@ lynx_status forward_pass(Ctx& cx, uint32_t retain) {
   bk.live[0] = true;
   bk.fused_attn = (cx.L->cfg.flags & LYNX_FLAG_FUSED_ATTENTION) && !(bk.retain & 0x38u) &&
                   lynx::attn_fused_supported(cx.L->D.dtype, cx.L->D.s, cx.L->D.d);
+  FusedGelu gelu;
   for (int i = 1; i <= kNumOps; ++i) {
     if (i == 5) continue;  // emitted by OP4's kernel
     int done = i;
@@ -529,6 +592,9 @@ lynx_status forward_pass(Ctx& cx, uint32_t retain) {
     } else if ((i == 7 || i == 12) && can_fuse_linear(cx, i)) {
       LYNX_TRY(run_fused_linear(cx, i));
       done = ++i;  // the launch covers the bias + dropout + residual operator too
+    } else if (i == 10 && plan_fused_gelu(cx, /*y2_goes=*/!((bk.retain >> 9) & 1u), /*passes=*/!(bk.retain & 0x1800u), &gelu)) {
+      LYNX_TRY(run_fused_gelu(cx, gelu, /*keep_u=*/(bk.retain >> 10) & 1u));
+      done = ++i;  // the launch covers OP11 too
     } else {
       LYNX_TRY(run_op(cx, i));
     }
@@ -600,6 +666,7 @@ lynx_status recompute_pass(Ctx& cx, uint32_t segment) {
       have[i] = true;
     }
   }
+  FusedGelu gelu;
   for (int i = 1; i <= kNumOps; ++i) {
     if (!((segment >> i) & 1u) || bk.live[i]) continue;
     if (bk.fused_attn && i == 6) {
@@ -611,6 +678,9 @@ lynx_status recompute_pass(Ctx& cx, uint32_t segment) {
     } else if ((i == 7 || i == 12) && ((segment >> (i + 1)) & 1u) && !bk.live[i + 1] &&
                can_fuse_linear(cx, i)) {
       LYNX_TRY(run_fused_linear(cx, i));
+      ++i;
+    } else if (i == 10 && ((segment >> 11) & 1u) && !bk.live[11] && plan_fused_gelu(cx, /*y2_goes=*/false, /*passes=*/false, &gelu)) {
+      LYNX_TRY(run_fused_gelu(cx, gelu, /*keep_u=*/true));
       ++i;
     } else {
       LYNX_TRY(run_op(cx, i));
