@@ -48,6 +48,22 @@ __device__ __forceinline__ float softmax_prob(float e, float inv) {
 #pragma clang fp contract(off)
   return round_to_storage(e * inv, static_cast<T*>(nullptr));
 }
+// The dot product of two rows of a head, one of 16 consecutive lanes each (lane l of them: vectors l, l + 16, ... of 8):
+// sum_dd dC[dd] C[dd] = sum_j dP_j P_j of the softmax backward.  Every lane ends with it.
+template <typename LoadX, typename LoadY>
+__device__ __forceinline__ float row_dot16(int l, int d, LoadX&& load_x, LoadY&& load_y) {
+  float acc = 0.f;
+  for (int v = l; v * 8 < d; v += 16) {
+    float x[8], y[8];
+    load_x(v, x);
+    load_y(v, y);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc = __builtin_fmaf(x[k], y[k], acc);
+  }
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 16);
+  return acc;
+}
 // dS = scale P (dP - dot) (B4 with the scale of B3 folded in), dP already masked and scaled.
 __device__ __forceinline__ float softmax_bwd(float p, float dp, float dot, float scale) {
 #pragma clang fp contract(off)

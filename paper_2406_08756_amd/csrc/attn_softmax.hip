@@ -312,10 +312,14 @@ hipError_t launch(const ScoresSoftmaxArgs& g, hipStream_t st) {
 // takes what is longer.  What bounds it: reading P and writing dS, then the vector ALU.  Two kernels and this one, us:
 // 128 slices of 1024, d = 64, 112 and 83; 100 of 1000 101 and 72; 21 of 328, d = 104, 15 and 11; dQ and dK right behind it gain 5
 // more, since dV then runs before it.
+//
+// FROM_C (head dimension 128, whole tiles): the row sums are known beforehand, as sum_dd dC[i, dd] C[i, dd], so that a block
+// is finished and stored as soon as it is multiplied.  The bits of attn_rowdot and attn_dscores_kernel.
 constexpr int kMaxGradientSeq = 1024;
 
 struct ScoreGradientArgs {
   const bf16_t* dc; const bf16_t* v;
+  const bf16_t* c;  // FROM_C; row stride lddc
   long long lddc, ldv;
   const bf16_t* P; bf16_t* dS;
   int s, d, a, nz, row_blocks;
@@ -324,7 +328,7 @@ struct ScoreGradientArgs {
   DropoutKey key;
 };
 
-template <int KD, bool RAGGED, int WAVES, int NBW>
+template <int KD, bool RAGGED, int WAVES, int NBW, bool FROM_C>
 __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_gradient_kernel(ScoreGradientArgs g) {
   constexpr int kSlabs = KD / 64;
   constexpr int kStepCols = kStepElems / KD, kSteps = kColsOfBlock / kStepCols;
@@ -337,7 +341,7 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   bf16_t* sK = sQ + kSlabs * SQ::kElems + wave * kStepElems;
-  float* row_sum = reinterpret_cast<float*>(sQ + kSlabs * SQ::kElems + WAVES * kStepElems);  // [WAVES][32]
+  float* row_sum = reinterpret_cast<float*>(sQ + kSlabs * SQ::kElems + WAVES * kStepElems);  // [WAVES][32], FROM_C: [32]
   const int z1 = bz / g.a, z2 = bz - z1 * g.a;
   const bf16_t* dc = g.dc + z1 * static_cast<long long>(g.s) * g.lddc + static_cast<long long>(z2) * g.d;
   const bf16_t* v = g.v + z1 * static_cast<long long>(g.s) * g.ldv + static_cast<long long>(z2) * g.d;
@@ -353,6 +357,17 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
   };
   if (wave < kSlabs) load_rows<SQ, KD, RAGGED>(dc, g.lddc, g.s, g.d, r0, wave, sQ + wave * SQ::kElems, lane);
   if (wave < active) load_v(wave * kColsOfBlock);
+  if constexpr (FROM_C) {
+    const bf16_t* c = g.c + z1 * static_cast<long long>(g.s) * g.lddc + static_cast<long long>(z2) * g.d;
+#pragma unroll
+    for (int i = 0; i < kRowsOfBlock / (4 * WAVES); ++i) {
+      const int row = 4 * (wave + WAVES * i) + (lane >> 4);
+      const long long at = (r0 + row) * g.lddc;
+      const float dot = row_dot16(lane & 15, KD, [&](int v8, float (&x)[8]) { load8(dc + at + v8 * 8, x); },
+                                  [&](int v8, float (&x)[8]) { load8_streaming(c + at + v8 * 8, x); });
+      if ((lane & 15) == 0) row_sum[row] = dot;
+    }
+  }
   wait_vmcnt<0>();
   block_barrier();
 
@@ -375,8 +390,13 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
   const RowBuffer in_p = row_buffer(g.P + out0, out_bytes), out = row_buffer(g.dS + out0, out_bytes);
   const uint64_t group0 = ((((static_cast<uint64_t>(z1) * g.global_heads + g.head0 + z2) * g.s + r0 + lr) * static_cast<uint64_t>(g.s)) >> 3) + lc;
 
-  uintx4_t dpd[NBW][4], pr[NBW][4];  // dPd (dropped elements cleared) and P in rows
+  constexpr int kHeld = FROM_C ? 1 : NBW;
+  uintx4_t dpd[kHeld][4], pr[kHeld][4];  // dPd (dropped elements cleared) and P in rows
   float dot[4] = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (FROM_C) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) dot[u] = row_sum[u * 8 + lr];
+  }
   auto unpacked = [](uintx4_t raw, float (&x)[8]) {
     Raw8<bf16_t> r;
     r.v = make_uint4(raw[0], raw[1], raw[2], raw[3]);
@@ -390,11 +410,8 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
   };
   DropoutKey keep_only = g.key;  // (1 or 0 of each element: the raw value, or cleared)
   keep_only.scale = 1.0f;
-#pragma unroll
-  for (int t = 0; t < NBW; ++t) {
-    const int block = wave + WAVES * t;
-    if (block >= active) break;
-    const bool next = t + 1 < NBW && block + WAVES < active;
+  // block `block` of the slice, the t-th of this wavefront
+  auto block_step = [&](const int t, const int block, const bool next) {
     floatx16_t acc[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -402,7 +419,9 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
       for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
 #pragma unroll
     for (int step = 0; step < kSteps; ++step) {
-      if (t > 0 || step > 0) wait_vmcnt<0>();
+      // (FROM_C: V was asked for ahead of the four stores of the block before)
+      if (step > 0 || (!FROM_C && block != wave)) wait_vmcnt<0>();
+      else if (block != wave) wait_vmcnt<4>();
       asm volatile("" ::: "memory");
 #pragma unroll
       for (int kk = 0; kk < KD / 16; ++kk) {
@@ -446,13 +465,31 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
     for (int u = 0; u < 4; ++u) {
       float x[8], p[8];
       unpacked(dpd[t][u], x);
+      if constexpr (FROM_C) {
+        dropout_apply8(g.key, group0 + static_cast<uint64_t>(u * g.s + block * (kColsOfBlock / 8)), x);
+        unpacked(pr[t][u], p);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = softmax_bwd(p[i], x[i], dot[u], g.scale);
+        row_buffer_store(out, offset_of(block, u), uintx4_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])});
+        continue;
+      }
       dropout_apply8(keep_only, group0 + static_cast<uint64_t>(u * g.s + block * (kColsOfBlock / 8)), x);
       dpd[t][u] = uintx4_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])};
       unpacked(pr[t][u], p);
 #pragma unroll
       for (int i = 0; i < 8; ++i) dot[u] += (x[i] * g.key.scale) * p[i];
     }
-  }
+  };
+  if constexpr (FROM_C) {
+#pragma unroll 1
+    for (int block = wave; block < active; block += WAVES) block_step(0, block, block + WAVES < active);
+  } else {
+#pragma unroll
+    for (int t = 0; t < NBW; ++t) {
+      const int block = wave + WAVES * t;
+      if (block >= active) break;
+      block_step(t, block, t + 1 < NBW && block + WAVES < active);
+    }
   // row sums: over a row's eight lanes, then over the wavefronts in order
 #pragma unroll
   for (int u = 0; u < 4; ++u) dot[u] = group8_sum(dot[u]);
@@ -480,16 +517,17 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
       row_buffer_store(out, offset_of(block, u), uintx4_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])});
     }
   }
+  }
   if (blocks > active && wave == (active & (WAVES - 1))) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) row_buffer_store(out, offset_of(active, u), uintx4_t{0u, 0u, 0u, 0u});
   }
 }
 
-template <int KD, bool RAGGED, int WAVES, int NBW>
+template <int KD, bool RAGGED, int WAVES, int NBW, bool FROM_C = false>
 hipError_t launch(const ScoreGradientArgs& g, hipStream_t st) {
   constexpr size_t smem = (kRowsOfBlock * KD + WAVES * kStepElems) * sizeof(bf16_t) + WAVES * kRowsOfBlock * sizeof(float);
-  auto kern = attn_score_gradient_kernel<KD, RAGGED, WAVES, NBW>;
+  auto kern = attn_score_gradient_kernel<KD, RAGGED, WAVES, NBW, FROM_C>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   hipLaunchKernelGGL(kern, dim3(g.row_blocks * g.nz), dim3(WAVES * kWave), smem, st, g);
   return hipGetLastError();
@@ -535,18 +573,37 @@ bool attn_score_gradient_supported(int dtype, int s, int d, long long ld, long l
   return s <= kMaxGradientSeq && attn_scores_softmax_supported(dtype, s, d, ld, slices);
 }
 
-hipError_t attn_score_gradient(const void* dc, long long lddc, const void* v, long long ldv, const void* P, void* dS, AttnShape sh,
-                               int d, float scale, DropoutParams dp, hipStream_t st) {
-  if (!attn_score_gradient_supported(1, sh.s, d, ldv, static_cast<long long>(sh.a) * sh.b) || lddc > ldv) return hipErrorInvalidValue;
+// Head dimension 128 and whole tiles of 128 rows, where attn_rowdot and attn_dscores_kernel are the alternative, up to
+// 2^26 elements of dS.  Those two walk tiles of 128 rows and so read V a quarter as often, which is what counts once P and
+// dS, 256 MB together, outgrow the memory-side cache; this one is a launch less and has four times the workgroups.  Those two
+// and this one with the launch of dQ and dK behind it, us: 8 slices of s = 384 19.2 and 15.7, 32 of 1024 52 and 49, 64 of 768
+// 66 and 64, 128 of 512 72 and 72, 16 of 2048 92 and 89; beyond: 32 of 1536 105 and 101, 128 of 1024 189 and 198, 40 of
+// 2048 194 and 198, 64 of 2048 310 and 329.
+bool attn_score_gradient_from_c(int dtype, int s, int d, long long ld, long long slices) {
+  return d == 128 && s % 128 == 0 && s <= kMaxSeq && slices * s * s <= (1ll << 26) &&
+         attn_scores_softmax_supported(dtype, s, d, ld, slices);
+}
+
+hipError_t attn_score_gradient(const void* dc, long long lddc, const void* v, long long ldv, const void* c, const void* P, void* dS,
+                               AttnShape sh, int d, float scale, DropoutParams dp, hipStream_t st) {
+  const long long slices = static_cast<long long>(sh.a) * sh.b;
+  const bool from_c = c != nullptr;
+  if (lddc > ldv || !(from_c ? attn_score_gradient_from_c(1, sh.s, d, ldv, slices) : attn_score_gradient_supported(1, sh.s, d, ldv, slices)))
+    return hipErrorInvalidValue;
   ScoreGradientArgs g{};
   g.dc = static_cast<const bf16_t*>(dc); g.lddc = lddc;
   g.v = static_cast<const bf16_t*>(v); g.ldv = ldv;
+  g.c = static_cast<const bf16_t*>(c);
   g.P = static_cast<const bf16_t*>(P); g.dS = static_cast<bf16_t*>(dS);
   g.s = sh.s; g.d = d; g.a = sh.a; g.nz = sh.a * sh.b;
   g.row_blocks = (sh.s + kRowsOfBlock - 1) / kRowsOfBlock;
   g.global_heads = sh.global_heads; g.head0 = sh.head0;
   g.scale = scale;
   g.key = make_dropout_key(dp, 0);
+  if (from_c) {
+    if (sh.s <= 256 && static_cast<long long>(g.row_blocks) * g.nz <= 512) return launch<128, false, 4, 1, true>(g, st);
+    return launch<128, false, 8, 1, true>(g, st);
+  }
   const bool whole = sh.s % kColsOfBlock == 0 && (d == 64 || d == 128);
   if (d <= 64) return whole ? launch<64, false>(g, st) : launch<64, true>(g, st);
   return whole ? launch<128, false>(g, st) : launch<128, true>(g, st);

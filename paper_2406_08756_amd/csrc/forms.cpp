@@ -6,7 +6,8 @@
 extern "C" {
 
 // Attention of bf16 layers, with row stride ld of QKV; bits: 1, operators 3 to 5
-// in one launch; 2, the score gradient in one launch that keeps dPd in registers; 4, dQ and dK in one launch.
+// in one launch; 2, the score gradient in one launch that keeps dPd in registers; 4, dQ and dK in one launch; 8, the score
+// gradient in one launch with its row sums from C.
 unsigned lynx_form_attention(int s, int d, long long ld, int batch, int heads) {
   using namespace lynx;
   const long long slices = static_cast<long long>(batch) * heads;
@@ -18,7 +19,7 @@ unsigned lynx_form_attention(int s, int d, long long ld, int batch, int heads) {
   rows.nz1 = batch; rows.nz2 = heads;
   rows.causal = kCausalKLeM;
   return (attn_scores_softmax_supported(1, s, d, ld, slices) ? 1u : 0u) | (attn_score_gradient_supported(1, s, d, ld, slices) ? 2u : 0u) |
-         (gemm_attention_pair_joint(rows) ? 4u : 0u);
+         (gemm_attention_pair_joint(rows) ? 4u : 0u) | (attn_score_gradient_from_c(1, s, d, ld, slices) ? 8u : 0u);
 }
 
 // x / d as the kernels form it, for x up to `most`, and whether by the inverse.

@@ -27,9 +27,7 @@ bool gemm_mfma_supported(int dtype, const GemmDesc& d) {
       // length.  Elsewhere attn_score_gradient forms the row dot products from the dPd that it differentiates (up to
       // s = 1024), or softmax_dropout_bwd does (beyond); those cancel that tensor's rounding, while these come from the
       // rounded C, which made the error of the QKV weight gradient against 64 bits 0.4 to 2.1 % larger at other shapes.
-      // The line is older than attn_score_gradient, which takes head dimension 128 too.  This one with attn_rowdot / that
-      // one, us: 4 slices of s = 128 8.1 / 4.6, 8 of 384 8.8 / 6.1, 64 of 384 16.4 / 10.3, 128 of 512 33.6 / 30.9, 64 of 768
-      // 38.0 / 33.4, 32 of 1024 29.7 / 26.4, 128 of 1024 101 / 109: it is in the wrong place below about 1000.
+      // (Up to 2^26 elements attn_score_gradient_from_c takes these shapes too, with the same dot products.)
       return d.causal == kCausalOutLower && d.bias == nullptr && d.M % 128 == 0 && d.K == 128 && a_k && b_k &&
              d.epi.aux != nullptr && aligned(d.epi.aux, 16) && d.epi.rowdot != nullptr;
     case kEpiBiasDropoutAdd:

@@ -71,10 +71,11 @@ bool attn_scores_softmax_supported(int dtype, int s, int d, long long ld, long l
 hipError_t attn_scores_softmax_fwd(const void* q, const void* k, long long ld, void* S, void* P, void* Pd, AttnShape sh, int d,
                                    float scale, DropoutParams dp, hipStream_t st);
 // dS = scale P (dP - sum_j dP P), dP = keep c round(dC V^T), in one launch (s <= 1024): dc [T, a * d] with row stride lddc,
-// v with ldv.
+// v with ldv.  With `c` (C, row stride lddc; attn_score_gradient_from_c) the sums come from it, as attn_rowdot forms them.
 bool attn_score_gradient_supported(int dtype, int s, int d, long long ld, long long slices);
-hipError_t attn_score_gradient(const void* dc, long long lddc, const void* v, long long ldv, const void* P, void* dS, AttnShape sh,
-                               int d, float scale, DropoutParams dp, hipStream_t st);
+bool attn_score_gradient_from_c(int dtype, int s, int d, long long ld, long long slices);
+hipError_t attn_score_gradient(const void* dc, long long lddc, const void* v, long long ldv, const void* c, const void* P, void* dS,
+                               AttnShape sh, int d, float scale, DropoutParams dp, hipStream_t st);
 // Pd = keep * P * c from a resident P.
 hipError_t attn_dropout_fwd(int dtype, const void* P, void* Pd, AttnShape sh, DropoutParams dp,
                             hipStream_t st);

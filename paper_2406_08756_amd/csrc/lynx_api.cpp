@@ -860,13 +860,17 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
     LYNX_LAUNCH(cx, kB654DScoresFused, lynx::attn_fused_bwd_ds(qkv, 3 * D.p, temp_ptr(cx, t_dc), D.p, attn_stats_ptr(cx),
                                                           rowdot, temp_ptr(cx, t_dpd), attn_shape(L), D.d,
                                                           dpd.epi.scale, dropout_params(L), cx.st));
+  } else if (fused_ds && lynx::attn_score_gradient_from_c(dt, D.s, D.d, 3ll * D.p, static_cast<long long>(D.b) * D.a)) {
+    LYNX_LAUNCH(cx, kB654DScores, lynx::attn_score_gradient(temp_ptr(cx, t_dc), D.p, col_block(qkv, D, 2), 3ll * D.p, act_ptr(cx, 6),
+                                                            act_ptr(cx, 4), temp_ptr(cx, t_dpd), attn_shape(L), D.d,
+                                                            dpd.epi.scale, dropout_params(L), cx.st));
   } else if (fused_ds) {
     LYNX_LAUNCH(cx, kB6RowDot, lynx::attn_rowdot(dt, temp_ptr(cx, t_dc), act_ptr(cx, 6),
                                                  reinterpret_cast<float*>(temp_ptr(cx, t_rowdot)), D.b, D.a, D.s,
                                                  D.d, D.p, cx.st));
     LYNX_LAUNCH(cx, kB654DScores, lynx::gemm(dt, dpd, nullptr, 0, cx.st));
   } else if (rows_ds) {
-    LYNX_LAUNCH(cx, kB654DScores, lynx::attn_score_gradient(temp_ptr(cx, t_dc), D.p, col_block(qkv, D, 2), 3ll * D.p,
+    LYNX_LAUNCH(cx, kB654DScores, lynx::attn_score_gradient(temp_ptr(cx, t_dc), D.p, col_block(qkv, D, 2), 3ll * D.p, nullptr,
                                                             act_ptr(cx, 4), temp_ptr(cx, t_dpd), attn_shape(L), D.d,
                                                             dpd.epi.scale, dropout_params(L), cx.st));
   } else {

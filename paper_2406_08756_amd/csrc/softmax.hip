@@ -209,23 +209,16 @@ attn_rowdot_kernel(const T* __restrict__ x, const T* __restrict__ y, float* __re
                    int d, long long ld, long long pairs) {
   const long long q = static_cast<long long>(blockIdx.x) * 16 + (threadIdx.x >> 4);
   const int l = threadIdx.x & 15;
-  float acc = 0.f;
   long long t = 0;
   int hd = 0;
   if (q < pairs) {
     t = q / a;
     hd = static_cast<int>(q - t * a);
-    const size_t base = static_cast<size_t>(t) * ld + static_cast<size_t>(hd) * d;
-    for (int v = l; v * 8 < d; v += 16) {
-      float xv[8], yv[8];
-      load8(x + base + v * 8, xv);            // dC: the kernels that follow read it again
-      load8_streaming(y + base + v * 8, yv);  // C: its last use
-#pragma unroll
-      for (int k = 0; k < 8; ++k) acc += xv[k] * yv[k];
-    }
   }
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 16);
+  const size_t base = static_cast<size_t>(t) * ld + static_cast<size_t>(hd) * d;
+  const float acc = row_dot16(l, q < pairs ? d : 0,
+                              [&](int v, float (&xv)[8]) { load8(x + base + v * 8, xv); },            // dC: the kernels that follow read it again
+                              [&](int v, float (&yv)[8]) { load8_streaming(y + base + v * 8, yv); });  // C: its last use
   if (q < pairs && l == 0) {
     const long long bi = t / s, i = t - bi * s;
     out[(bi * a + hd) * s + i] = acc;

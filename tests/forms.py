@@ -9,11 +9,11 @@ from paper_2406_08756_amd import binding as B
 _lib = ctypes.CDLL(B.LIB_PATH)
 _lib.lynx_form_attention.restype = ctypes.c_uint
 _lib.lynx_form_attention.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
-SCORES, GRADIENT, JOINT = 1, 2, 4
+SCORES, GRADIENT, JOINT, FROM_C = 1, 2, 4, 8
 
 
 def attention(seq, head_dim, micro_batch, heads):
-    """Bits SCORES, GRADIENT, JOINT: what runs as one launch."""
+    """Bits SCORES, GRADIENT, JOINT, FROM_C: what runs as one launch."""
     return _lib.lynx_form_attention(seq, head_dim, 3 * heads * head_dim, micro_batch, heads)
 
 
