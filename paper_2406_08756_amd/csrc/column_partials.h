@@ -1,0 +1,67 @@
+// First stage of a plain column sum as a guest in another kernel's launch (the QKV bias gradient in that of the QKV
+// weight and input gradients, which read the same tensor): its workgroups come last and run where the products' last
+// round leaves units idle.
+#pragma once
+#include "device_common.h"
+#include "kernels.h"
+
+namespace lynx {
+
+constexpr int kPartialRows = 32;  // rows of one partial, as in rows_colsum_kernel
+
+struct ColumnPartials {
+  const void* x;  // [rows, cols]
+  float* part;    // [ceil(rows / 32), cols]
+  int rows, cols;
+  int tiles;      // of 32 rows x 64 vectors, one per wavefront; 0: none
+  int first;      // workgroup
+};
+// The guest of a launch of `first` workgroups of so many wavefronts; *groups: its own workgroups.
+inline ColumnPartials guest_partials(const ColumnSumInput* in, int first, int waves, int* groups) {
+  ColumnPartials c{};
+  c.first = first;
+  *groups = 0;
+  if (in == nullptr) return c;
+  c.x = in->x; c.part = in->part;
+  c.rows = in->rows; c.cols = in->cols;
+  c.tiles = (in->rows + kPartialRows - 1) / kPartialRows * ((in->cols / 8 + kWave - 1) / kWave);
+  *groups = (c.tiles + waves - 1) / waves;
+  return c;
+}
+
+// Tile `tile`, one vector of 8 columns per lane.  A lane has all 32 rows of its columns, so nothing goes through LDS,
+// which belongs to the products; the order of the sums is that of rows_colsum_kernel: rows r, r + 4, ... of the tile
+// form one sum, of four.  8192 rows of 6144 columns (100 MB) take 16.8 us as a launch of their own; behind the 448
+// workgroups of the products a pass gets 11 to 15 us shorter.
+template <typename T>
+__device__ __forceinline__ void column_partials(const ColumnPartials& c, int tile) {
+  if (tile >= c.tiles) return;
+  const int vecs = c.cols >> 3, wide = (vecs + kWave - 1) / kWave;
+  const int block = tile / wide, vec = (tile - block * wide) * kWave + static_cast<int>(threadIdx.x & (kWave - 1));
+  if (vec >= vecs) return;
+  const int r0 = block * kPartialRows;
+  const T* x = static_cast<const T*>(c.x) + static_cast<size_t>(r0) * c.cols + static_cast<size_t>(vec) * 8;
+  float sum[4][8] = {};
+  constexpr int kAtOnce = sizeof(T) == 2 ? 16 : 8;  // (64 registers, within what the products take)
+#pragma unroll
+  for (int h = 0; h < kPartialRows; h += kAtOnce) {
+    Raw8<T> raw[kAtOnce];
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k)
+      if (r0 + h + k < c.rows) load_raw_streaming(x + static_cast<size_t>(h + k) * c.cols, raw[k]);
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) {
+      if (r0 + h + k >= c.rows) break;
+      float v[8];
+      unpack(raw[k], v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) sum[k & 3][i] += v[i];
+    }
+  }
+  float total[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) total[i] = (sum[0][i] + sum[1][i]) + (sum[2][i] + sum[3][i]);
+  store8(c.part + static_cast<size_t>(block) * c.cols + static_cast<size_t>(vec) * 8, total);
+}
+
+}  // namespace lynx

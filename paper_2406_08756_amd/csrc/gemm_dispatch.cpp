@@ -120,8 +120,15 @@ size_t gemm_pair_colsum_least_bytes(int dtype, const GemmDesc& dgrad, const Gemm
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,
                      size_t scratch_bytes, ColumnSums* sums, hipStream_t st) {
   if (!gemm_pair_supported(dtype, dgrad, wgrad)) return hipErrorInvalidValue;
-  if (dtype != 1) return gemm_f32_pair(dgrad, wgrad, sums, st);
-  return gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, sums, st);
+  if (dtype != 1) return gemm_f32_pair(dgrad, wgrad, nullptr, sums, st);
+  return gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, nullptr, sums, st);
+}
+
+hipError_t gemm_pair_column_sum(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
+                                const ColumnSumInput& in, ColumnSums* sums, hipStream_t st) {
+  if (!gemm_pair_supported(dtype, dgrad, wgrad) || in.cols % 8) return hipErrorInvalidValue;
+  if (dtype != 1) return gemm_f32_pair(dgrad, wgrad, &in, sums, st);
+  return gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, &in, sums, st);
 }
 
 }  // namespace lynx

@@ -15,6 +15,7 @@
 //
 // Sizes are multiples of 8, so chunks of four elements never straddle an edge.  Rows and columns beyond
 // the operands repeat the last ones and are not stored, contraction indices beyond K read zeros.
+#include "column_partials.h"
 #include "device_common.h"
 #include "dropout_host.h"
 #include "kernels.h"
@@ -329,10 +330,22 @@ __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmDesc d, DropoutK
 // Input and weight gradient of a linear layer in one launch, so that together they fill the chip: the first n_first
 // workgroups belong to the one with the longer contraction, the others fill what it leaves idle.
 template <int BM>
-__global__ void __launch_bounds__(kThreads) gemm_f32_pair_kernel(GemmDesc wgrad, GemmDesc dgrad, DropoutKey key, int n_first, int dgrad_first) {
+__device__ __forceinline__ void f32_pair_tile(const GemmDesc& wgrad, const GemmDesc& dgrad, const DropoutKey& key, int n_first, int dgrad_first) {
   const int x = static_cast<int>(blockIdx.x), tile = x < n_first ? x : x - n_first;
   if ((x < n_first) != (dgrad_first != 0)) f32_tile<false, false, BM>(wgrad, key, tile, 0);
   else f32_tile<true, false, BM>(dgrad, key, tile, 0);
+}
+template <int BM>
+__global__ void __launch_bounds__(kThreads) gemm_f32_pair_kernel(GemmDesc wgrad, GemmDesc dgrad, DropoutKey key, int n_first, int dgrad_first) {
+  f32_pair_tile<BM>(wgrad, dgrad, key, n_first, dgrad_first);
+}
+// ... and a column sum besides, in workgroups behind them
+template <int BM>
+__global__ void __launch_bounds__(kThreads)
+gemm_f32_pair_guest_kernel(GemmDesc wgrad, GemmDesc dgrad, DropoutKey key, int n_first, int dgrad_first, ColumnPartials guest) {
+  const int x = static_cast<int>(blockIdx.x);
+  if (x >= guest.first) column_partials<float>(guest, (x - guest.first) * kWaves + static_cast<int>(threadIdx.x) / kWave);
+  else f32_pair_tile<BM>(wgrad, dgrad, key, n_first, dgrad_first);
 }
 
 // Two products of attention that do not need each other (batched alike) in one launch: few tiles each, and a launch of
@@ -425,19 +438,28 @@ size_t gemm_f32_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad) 
   return static_cast<size_t>((dgrad.M + bm - 1) / bm) * dgrad.N * sizeof(float);
 }
 
-hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, ColumnSums* sums, hipStream_t st) {
+hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, const ColumnSumInput* in, ColumnSums* sums, hipStream_t st) {
   const bool small = small_tiles(tiles(dgrad, 64) + tiles(wgrad, 64));
   const int bm = small ? 32 : 64;
   const int n_w = static_cast<int>(tiles(wgrad, bm)), n_d = static_cast<int>(tiles(dgrad, bm));
   const bool dgrad_first = dgrad.K > wgrad.K;
   const int n_first = dgrad_first ? n_d : n_w;
-  if (small)
-    hipLaunchKernelGGL((gemm_f32_pair_kernel<32>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes<32>, st, wgrad, dgrad,
-                       DropoutKey{}, n_first, dgrad_first ? 1 : 0);
-  else
-    hipLaunchKernelGGL((gemm_f32_pair_kernel<64>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes<64>, st, wgrad, dgrad,
-                       DropoutKey{}, n_first, dgrad_first ? 1 : 0);
+  auto launch_pair = [&](auto bm_tag) {
+    constexpr int BM = decltype(bm_tag)::value;
+    if (in != nullptr) {
+      int n_guest;
+      const ColumnPartials guest = guest_partials(in, n_w + n_d, kWaves, &n_guest);
+      hipLaunchKernelGGL((gemm_f32_pair_guest_kernel<BM>), dim3(n_w + n_d + n_guest), dim3(kThreads), kLdsBytes<BM>, st, wgrad, dgrad,
+                         DropoutKey{}, n_first, dgrad_first ? 1 : 0, guest);
+    } else {
+      hipLaunchKernelGGL((gemm_f32_pair_kernel<BM>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes<BM>, st, wgrad, dgrad, DropoutKey{},
+                         n_first, dgrad_first ? 1 : 0);
+    }
+  };
+  if (small) launch_pair(std::integral_constant<int, kSmall>{});
+  else launch_pair(std::integral_constant<int, kLarge>{});
   hipError_t e = hipGetLastError();
+  if (e == hipSuccess && in != nullptr) e = sums->add(in->part, in->out, (in->rows + kPartialRows - 1) / kPartialRows, in->cols);
   if (e != hipSuccess || dgrad.epi.kind != kEpiGeluBwd) return e;
   return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, (dgrad.M + bm - 1) / bm, dgrad.N);
 }

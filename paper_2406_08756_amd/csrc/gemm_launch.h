@@ -2,6 +2,7 @@
 #pragma once
 #include <mutex>
 
+#include "column_partials.h"
 #include "dropout_host.h"
 #include "gemm_plans.h"
 #include "gemm_tile.h"

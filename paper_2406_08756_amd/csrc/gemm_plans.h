@@ -18,8 +18,9 @@ struct RaggedChoice {
 RaggedChoice ragged_product(const GemmDesc& d);
 RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad);
 hipError_t gemm_ragged(const GemmDesc& d, float* scratch, size_t scratch_bytes, hipStream_t st);
+// (with a column sum, nullable: gemm_pair_column_sum)
 hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
-                            ColumnSums* sums, hipStream_t st);
+                            const ColumnSumInput* in, ColumnSums* sums, hipStream_t st);
 // Products of attention (gemm_mfma.hip).
 hipError_t gemm_attention(const GemmDesc& d, hipStream_t st);
 int attention_score_run(int s, int slices);  // score-shaped ones: tiles per workgroup
@@ -34,6 +35,6 @@ hipError_t gemm_f32(const GemmDesc& d, hipStream_t st);
 // two products of attention, the second with both operands MN-major, in one launch
 hipError_t gemm_f32_two(const GemmDesc& a, const GemmDesc& b, hipStream_t st);
 size_t gemm_f32_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad);
-hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, ColumnSums* sums, hipStream_t st);
+hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, const ColumnSumInput* in, ColumnSums* sums, hipStream_t st);
 
 }  // namespace lynx

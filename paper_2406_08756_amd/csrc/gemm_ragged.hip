@@ -149,8 +149,7 @@ gemm_ragged_kernel(MfmaGemmArgs g) {
 // throughout: 237 us for 4000 tokens, 1600 inputs and 6400 outputs, whose input gradient has the longer
 // contraction; 198 this way.)
 template <int TILE, bool FAR>
-__global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
-gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int dgrad_first) {
+__device__ __forceinline__ void pair_tile(const MfmaGemmArgs& wgrad, const MfmaGemmArgs& dgrad, int n_first, int dgrad_first) {
   using T = TileShape<TILE, false>;
   // the second product starts at a multiple of 8 workgroups, as its tile order, which takes the workgroup
   // id mod 8 for the XCD, needs it; the few workgroups in between idle
@@ -164,6 +163,21 @@ gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int
     if (dgrad.k_splits > 1) gemm_tile<true, false, T::BM, T::BN, kSingle, true, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
     else gemm_tile<true, false, T::BM, T::BN, kSingle, false, T::S, true, T::BK, T::waves, false, FAR>(dgrad, tile, 0);
   }
+}
+template <int TILE, bool FAR>
+__global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
+gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int dgrad_first) {
+  pair_tile<TILE, FAR>(wgrad, dgrad, n_first, dgrad_first);
+}
+// ... and a column sum besides, in workgroups behind them
+template <int TILE, bool FAR>
+__global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
+gemm_ragged_pair_guest_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int dgrad_first, ColumnPartials guest) {
+  const int x = static_cast<int>(blockIdx.x);
+  if (x >= guest.first)
+    column_partials<bf16_t>(guest, (x - guest.first) * TileShape<TILE, false>::waves + static_cast<int>(threadIdx.x) / kWave);
+  else
+    pair_tile<TILE, FAR>(wgrad, dgrad, n_first, dgrad_first);
 }
 
 template <bool AK, bool BK_, int TILE, bool FAR, TileForm FORM>
@@ -281,18 +295,27 @@ hipError_t launch_attn_gradients(MfmaGemmArgs rows, MfmaGemmArgs cols, hipStream
 }
 
 template <int TILE, bool FAR = false>
-hipError_t launch_ragged_pair(MfmaGemmArgs w, MfmaGemmArgs d, hipStream_t st) {
+hipError_t launch_ragged_pair(MfmaGemmArgs w, MfmaGemmArgs d, const ColumnSumInput* in, hipStream_t st) {
   using T = TileShape<TILE, false>;
   constexpr size_t smem = tile_lds<T>;
+  for (MfmaGemmArgs* g : {&w, &d}) set_tiles(g, T::BM, T::BN);
+  const int n_w = w.tiles_m * w.tiles_n * w.k_splits, n_d = d.tiles_m * d.tiles_n * d.k_splits;
+  const int dgrad_first = d.k_per > w.k_per;
+  const int n_first = dgrad_first ? n_d : n_w, n_pad = (n_first + 7) & ~7;
+  const int n = n_pad + n_w + n_d - n_first;
+  if constexpr (TILE != kT128) {
+    if (in != nullptr) {
+      auto kern = gemm_ragged_pair_guest_kernel<TILE, FAR>;
+      LYNX_RAISE_LDS_LIMIT(kern, smem);
+      int n_guest;
+      const ColumnPartials guest = guest_partials(in, n, T::waves, &n_guest);
+      hipLaunchKernelGGL(kern, dim3(n + n_guest), dim3(T::waves * kWave), smem, st, w, d, n_first, dgrad_first, guest);
+      return hipGetLastError();
+    }
+  }
   auto kern = gemm_ragged_pair_kernel<TILE, FAR>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
-  for (MfmaGemmArgs* g : {&w, &d}) {
-    set_tiles(g, T::BM, T::BN);
-  }
-  const int n_w = w.tiles_m * w.tiles_n * w.k_splits, n_d = d.tiles_m * d.tiles_n * d.k_splits;
-  const bool dgrad_first = d.k_per > w.k_per;
-  const int n_first = dgrad_first ? n_d : n_w, n_pad = (n_first + 7) & ~7;
-  hipLaunchKernelGGL(kern, dim3(n_pad + n_w + n_d - n_first), dim3(T::waves * kWave), smem, st, w, d, n_first, dgrad_first);
+  hipLaunchKernelGGL(kern, dim3(n), dim3(T::waves * kWave), smem, st, w, d, n_first, dgrad_first);
   return hipGetLastError();
 }
 
@@ -489,7 +512,7 @@ RaggedChoice ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad) {
 }
 
 hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
-                            ColumnSums* sums, hipStream_t st) {
+                            const ColumnSumInput* in, ColumnSums* sums, hipStream_t st) {
   const RaggedPairPlan p = plan_pair_ragged(wgrad, dgrad);
   MfmaGemmArgs d = make_args(dgrad), w = make_args(wgrad);
   w.k_splits = ceil_div(w.K, p.w_per);
@@ -508,9 +531,16 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   }
   const bool in_parts = at_once < dgrad.N, far = is_far(dgrad) || is_far(wgrad);
   const bool serial = dgrad.serial && w_bytes + d_bytes > 0;
-  if (in_parts && !dgrad.serial && w_bytes > 0) return hipErrorInvalidValue;
+  if (in_parts && (in != nullptr || (!dgrad.serial && w_bytes > 0))) return hipErrorInvalidValue;
   if (w_bytes + d_bytes > 0 && !serial && (scratch == nullptr || scratch_bytes < w_bytes + d_bytes)) return hipErrorInvalidValue;
   hipError_t e;
+  // A column sum goes with the products, whose last round of workgroups leaves units idle (10 to 15 us of a pass of 8192
+  // tokens of h 2048 or 4096, 1 to 2 of the small layers in 64 x 64 tiles), but not with 128 x 128 tiles: their kernel
+  // needs its registers (984 tokens of h 3016 426.6 us with a launch of its own, 427.9 this way; 192 of 2048 241.7 and 244.6).
+  // (A launch of its own comes after them: ahead of them its streaming loads take x out of the caches, 3 us.)
+  const bool sum_apart = in != nullptr && (serial || p.tile == kT128);
+  const ColumnSumInput* const sum_after = sum_apart ? in : nullptr;
+  if (sum_apart) in = nullptr;
   if (serial || in_parts) {
     // (the product that is not cut in the plan's tile: the GeLU epilogue's column partials depend on it)
     const bool w_cut = w.k_splits > 1, d_cut = d.k_splits > 1;
@@ -529,23 +559,26 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
         if (e == hipSuccess) e = of_part.add(part.colsum_partial, static_cast<bf16_t*>(dgrad.epi.colsum_out) + n0, colsum_rows, part.N);
         if (e == hipSuccess) e = finish_column_sums(1, &of_part, st);
       }
-      return e;
+      return e;  // (FC2's gradients: no column sum besides)
     }
     if (e == hipSuccess) e = d_cut ? launch_serial<true, false>(far, d, st) : launch_tile<true, false>(p.tile, far, d, st);
   } else {
     w.partial = scratch;
     d.partial = scratch + w_bytes / sizeof(float);
     switch (p.tile) {
-      case kT256: e = launch_ragged_pair<kT256>(w, d, st); break;
-      case kT256x128: e = launch_ragged_pair<kT256x128>(w, d, st); break;
-      case kT128: e = launch_ragged_pair<kT128>(w, d, st); break;
-      default: e = far ? launch_ragged_pair<kT64, true>(w, d, st) : launch_ragged_pair<kT64>(w, d, st); break;
+      case kT256: e = launch_ragged_pair<kT256>(w, d, in, st); break;
+      case kT256x128: e = launch_ragged_pair<kT256x128>(w, d, in, st); break;
+      case kT128: e = launch_ragged_pair<kT128>(w, d, nullptr, st); break;
+      default: e = far ? launch_ragged_pair<kT64, true>(w, d, in, st) : launch_ragged_pair<kT64>(w, d, in, st); break;
     }
+    if (e == hipSuccess && in != nullptr) e = sums->add(in->part, in->out, (in->rows + kPartialRows - 1) / kPartialRows, in->cols);
   }
   if (e != hipSuccess) return e;
   if (w.k_splits > 1 && d.k_splits > 1) e = launch_finish(&w, &d, st);
   else if (w.k_splits > 1) e = launch_finish(&w, nullptr, st);
   else if (d.k_splits > 1) e = launch_finish(&d, nullptr, st);
+  if (e == hipSuccess && sum_after != nullptr)
+    e = column_sum(1, sum_after->x, sum_after->out, sum_after->part, sum_after->rows, sum_after->cols, sums, st);
   if (e != hipSuccess || dgrad.epi.kind != kEpiGeluBwd) return e;
   return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, colsum_rows, dgrad.N);
 }

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import forms
 import lynx_synth as synth
 from harness import GpuLayer
 
@@ -44,3 +45,20 @@ def test_bias_gradients_are_summed_in_one_order(dtype, h, s, b):
     np.testing.assert_array_equal(got["b2"], column_sum(dOUT, dtype))
     dQKV = dQKV.float().cpu().numpy().reshape(cfg.tokens, 3 * cfg.proj)
     np.testing.assert_array_equal(got["bqkv"], column_sum(dQKV, dtype))
+
+
+# (hidden, heads, head_dim, ffn, seq, micro_batch), side of the products' tile: the QKV bias gradient in the launch of the
+# products (64, 256) or behind it (128); whole and part tiles of 64 vectors, last blocks of less than 32 rows
+@pytest.mark.parametrize("shape,side", [((264, 5, 104, 64, 72, 3), 64), ((512, 4, 128, 64, 384, 2), 64),
+                                        ((3016, 7, 104, 64, 328, 3), 128), ((2048, 16, 128, 64, 1000, 4), 256)])
+def test_qkv_bias_gradient_beside_the_products(shape, side):
+    assert forms.of_layer(shape, "qkv_grads")[1] == side
+    cfg = synth.LayerConfig(synth.BF16, *shape, dropout_p=0.0)
+    layer = GpuLayer(cfg, synth.make_params(cfg))
+    dQKV = layer.tap_gradients(["dQKV"])["dQKV"]
+    layer.forward(synth.make_x(cfg), B.LYNX_RETAIN_STORE_ALL)
+    layer.backward(synth.make_dout(cfg))
+    torch.cuda.synchronize()
+    got = layer.grads["bqkv"].float().cpu().numpy()
+    layer.close()
+    np.testing.assert_array_equal(got, column_sum(dQKV.float().cpu().numpy().reshape(cfg.tokens, 3 * cfg.proj), synth.BF16))
