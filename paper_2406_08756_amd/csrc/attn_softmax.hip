@@ -312,14 +312,11 @@ hipError_t launch(const ScoresSoftmaxArgs& g, hipStream_t st) {
 // takes what is longer.  What bounds it: reading P and writing dS, then the vector ALU.  Two kernels and this one, us:
 // 128 slices of 1024, d = 64, 112 and 83; 100 of 1000 101 and 72; 21 of 328, d = 104, 15 and 11; dQ and dK right behind it gain 5
 // more, since dV then runs before it.
-//
-// FROM_C (head dimension 128, whole tiles): the row sums are known beforehand, as sum_dd dC[i, dd] C[i, dd], so that a block
-// is finished and stored as soon as it is multiplied.  The bits of attn_rowdot and attn_dscores_kernel.
 constexpr int kMaxGradientSeq = 1024;
 
 struct ScoreGradientArgs {
   const bf16_t* dc; const bf16_t* v;
-  const bf16_t* c;  // FROM_C; row stride lddc
+  const bf16_t* c;  // (row sums from C) row stride lddc
   long long lddc, ldv;
   const bf16_t* P; bf16_t* dS;
   int s, d, a, nz, row_blocks;
@@ -328,7 +325,7 @@ struct ScoreGradientArgs {
   DropoutKey key;
 };
 
-template <int KD, bool RAGGED, int WAVES, int NBW, bool FROM_C>
+template <int KD, bool RAGGED, int WAVES, int NBW>
 __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_gradient_kernel(ScoreGradientArgs g) {
   constexpr int kSlabs = KD / 64;
   constexpr int kStepCols = kStepElems / KD, kSteps = kColsOfBlock / kStepCols;
@@ -341,7 +338,7 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   bf16_t* sK = sQ + kSlabs * SQ::kElems + wave * kStepElems;
-  float* row_sum = reinterpret_cast<float*>(sQ + kSlabs * SQ::kElems + WAVES * kStepElems);  // [WAVES][32], FROM_C: [32]
+  float* row_sum = reinterpret_cast<float*>(sQ + kSlabs * SQ::kElems + WAVES * kStepElems);  // [WAVES][32]
   const int z1 = bz / g.a, z2 = bz - z1 * g.a;
   const bf16_t* dc = g.dc + z1 * static_cast<long long>(g.s) * g.lddc + static_cast<long long>(z2) * g.d;
   const bf16_t* v = g.v + z1 * static_cast<long long>(g.s) * g.ldv + static_cast<long long>(z2) * g.d;
@@ -357,17 +354,6 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
   };
   if (wave < kSlabs) load_rows<SQ, KD, RAGGED>(dc, g.lddc, g.s, g.d, r0, wave, sQ + wave * SQ::kElems, lane);
   if (wave < active) load_v(wave * kColsOfBlock);
-  if constexpr (FROM_C) {
-    const bf16_t* c = g.c + z1 * static_cast<long long>(g.s) * g.lddc + static_cast<long long>(z2) * g.d;
-#pragma unroll
-    for (int i = 0; i < kRowsOfBlock / (4 * WAVES); ++i) {
-      const int row = 4 * (wave + WAVES * i) + (lane >> 4);
-      const long long at = (r0 + row) * g.lddc;
-      const float dot = row_dot16(lane & 15, KD, [&](int v8, float (&x)[8]) { load8(dc + at + v8 * 8, x); },
-                                  [&](int v8, float (&x)[8]) { load8_streaming(c + at + v8 * 8, x); });
-      if ((lane & 15) == 0) row_sum[row] = dot;
-    }
-  }
   wait_vmcnt<0>();
   block_barrier();
 
@@ -390,13 +376,8 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
   const RowBuffer in_p = row_buffer(g.P + out0, out_bytes), out = row_buffer(g.dS + out0, out_bytes);
   const uint64_t group0 = ((((static_cast<uint64_t>(z1) * g.global_heads + g.head0 + z2) * g.s + r0 + lr) * static_cast<uint64_t>(g.s)) >> 3) + lc;
 
-  constexpr int kHeld = FROM_C ? 1 : NBW;
-  uintx4_t dpd[kHeld][4], pr[kHeld][4];  // dPd (dropped elements cleared) and P in rows
+  uintx4_t dpd[NBW][4], pr[NBW][4];  // dPd (dropped elements cleared) and P in rows
   float dot[4] = {0.f, 0.f, 0.f, 0.f};
-  if constexpr (FROM_C) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) dot[u] = row_sum[u * 8 + lr];
-  }
   auto unpacked = [](uintx4_t raw, float (&x)[8]) {
     Raw8<bf16_t> r;
     r.v = make_uint4(raw[0], raw[1], raw[2], raw[3]);
@@ -410,8 +391,11 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
   };
   DropoutKey keep_only = g.key;  // (1 or 0 of each element: the raw value, or cleared)
   keep_only.scale = 1.0f;
-  // block `block` of the slice, the t-th of this wavefront
-  auto block_step = [&](const int t, const int block, const bool next) {
+#pragma unroll
+  for (int t = 0; t < NBW; ++t) {
+    const int block = wave + WAVES * t;
+    if (block >= active) break;
+    const bool next = t + 1 < NBW && block + WAVES < active;
     floatx16_t acc[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -419,9 +403,7 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
       for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
 #pragma unroll
     for (int step = 0; step < kSteps; ++step) {
-      // (FROM_C: V was asked for ahead of the four stores of the block before)
-      if (step > 0 || (!FROM_C && block != wave)) wait_vmcnt<0>();
-      else if (block != wave) wait_vmcnt<4>();
+      if (t > 0 || step > 0) wait_vmcnt<0>();
       asm volatile("" ::: "memory");
 #pragma unroll
       for (int kk = 0; kk < KD / 16; ++kk) {
@@ -465,31 +447,13 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
     for (int u = 0; u < 4; ++u) {
       float x[8], p[8];
       unpacked(dpd[t][u], x);
-      if constexpr (FROM_C) {
-        dropout_apply8(g.key, group0 + static_cast<uint64_t>(u * g.s + block * (kColsOfBlock / 8)), x);
-        unpacked(pr[t][u], p);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = softmax_bwd(p[i], x[i], dot[u], g.scale);
-        row_buffer_store(out, offset_of(block, u), uintx4_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])});
-        continue;
-      }
       dropout_apply8(keep_only, group0 + static_cast<uint64_t>(u * g.s + block * (kColsOfBlock / 8)), x);
       dpd[t][u] = uintx4_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])};
       unpacked(pr[t][u], p);
 #pragma unroll
       for (int i = 0; i < 8; ++i) dot[u] += (x[i] * g.key.scale) * p[i];
     }
-  };
-  if constexpr (FROM_C) {
-#pragma unroll 1
-    for (int block = wave; block < active; block += WAVES) block_step(0, block, block + WAVES < active);
-  } else {
-#pragma unroll
-    for (int t = 0; t < NBW; ++t) {
-      const int block = wave + WAVES * t;
-      if (block >= active) break;
-      block_step(t, block, t + 1 < NBW && block + WAVES < active);
-    }
+  }
   // row sums: over a row's eight lanes, then over the wavefronts in order
 #pragma unroll
   for (int u = 0; u < 4; ++u) dot[u] = group8_sum(dot[u]);
@@ -517,6 +481,134 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
       row_buffer_store(out, offset_of(block, u), uintx4_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])});
     }
   }
+  if (blocks > active && wave == (active & (WAVES - 1))) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) row_buffer_store(out, offset_of(active, u), uintx4_t{0u, 0u, 0u, 0u});
+  }
+}
+
+// Head dimension 128, whole tiles of 128 rows, the row sums known beforehand: as sum_dd dC[i, dd] C[i, dd], with the bits of
+// attn_rowdot and attn_dscores_kernel.  A block is finished and stored as soon as it is multiplied.  (A kernel of its own: as a
+// form of the one above it took that one's registers, 128 slices of 1024, d = 64, 86 -> 135 us.)
+template <int WAVES>
+__global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_gradient_from_c_kernel(ScoreGradientArgs g) {
+  constexpr int KD = 128, kSlabs = KD / 64, kStepCols = kStepElems / KD, kSteps = kColsOfBlock / kStepCols;
+  using SQ = Slab<kRowsOfBlock, true, 64, 1>;
+  using SK = Slab<kStepCols, true, 64, 1>;
+  const int rb = g.row_blocks - 1 - static_cast<int>(blockIdx.x) / g.nz;
+  const int bz = static_cast<int>(blockIdx.x) % g.nz;
+  extern __shared__ __align__(1024) unsigned char smem_raw[];
+  bf16_t* sQ = reinterpret_cast<bf16_t*>(smem_raw);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  bf16_t* sK = sQ + kSlabs * SQ::kElems + wave * kStepElems;
+  float* row_sum = reinterpret_cast<float*>(sQ + kSlabs * SQ::kElems + WAVES * kStepElems);  // [32]
+  const int z1 = bz / g.a, z2 = bz - z1 * g.a;
+  const long long head = z1 * static_cast<long long>(g.s) * g.lddc + static_cast<long long>(z2) * KD;
+  const bf16_t* dc = g.dc + head;
+  const bf16_t* v = g.v + z1 * static_cast<long long>(g.s) * g.ldv + static_cast<long long>(z2) * KD;
+  const int r0 = rb * kRowsOfBlock;
+  const int active = (r0 + kRowsOfBlock - 1) / kColsOfBlock + 1;
+  const int blocks = (r0 + kRowsOfBlock + 127) / 128 * 128 / kColsOfBlock;
+
+  auto load_v = [&](int col) {
+#pragma unroll
+    for (int sl = 0; sl < kSlabs; ++sl) load_rows<SK, KD, false>(v, g.ldv, g.s, KD, col, sl, sK + sl * SK::kElems, lane);
+  };
+  if (wave < kSlabs) load_rows<SQ, KD, false>(dc, g.lddc, g.s, KD, r0, wave, sQ + wave * SQ::kElems, lane);
+  if (wave < active) load_v(wave * kColsOfBlock);
+#pragma unroll
+  for (int i = 0; i < kRowsOfBlock / (4 * WAVES); ++i) {
+    const int row = 4 * (wave + WAVES * i) + (lane >> 4);
+    const long long at = (r0 + row) * g.lddc;
+    const float dot = row_dot16(lane & 15, KD, [&](int v8, float (&x)[8]) { load8(dc + at + v8 * 8, x); },
+                                [&](int v8, float (&x)[8]) { load8_streaming(g.c + head + at + v8 * 8, x); });
+    if ((lane & 15) == 0) row_sum[row] = dot;
+  }
+  wait_vmcnt<0>();
+  block_barrier();
+
+  const int my_row = r0 + (lane & 31), half = lane >> 5;
+  const int lr = lane >> 3, lc = lane & 7;
+  // (staging as above)
+  bf16_t* const stage_to = sK + (lane & 31) * kColsOfBlock + 4 * (half ^ ((lane >> 4) & 1));
+  auto stage_read = [&](int u) {
+    const int row = u * 8 + lr;
+    const uintx4_t x = *reinterpret_cast<const uintx4_t*>(sK + row * kColsOfBlock + ((lc ^ ((row >> 1) & 7)) << 3));
+    return u < 2 ? x : uintx4_t{x[2], x[3], x[0], x[1]};
+  };
+  const long long out0 = (static_cast<long long>(bz) * g.s + r0) * g.s;
+  const uint32_t row_bytes = 2u * static_cast<uint32_t>(g.s), out_bytes = kRowsOfBlock * row_bytes;
+  auto offset_of = [&](int block, int u) {
+    return static_cast<uint32_t>(u * 8 + lr) * row_bytes + 2u * static_cast<uint32_t>(block * kColsOfBlock + lc * 8);
+  };
+  const RowBuffer in_p = row_buffer(g.P + out0, out_bytes), out = row_buffer(g.dS + out0, out_bytes);
+  const uint64_t group0 = ((((static_cast<uint64_t>(z1) * g.global_heads + g.head0 + z2) * g.s + r0 + lr) * static_cast<uint64_t>(g.s)) >> 3) + lc;
+  float dot[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) dot[u] = row_sum[u * 8 + lr];
+#pragma unroll 1
+  for (int block = wave; block < active; block += WAVES) {
+    floatx16_t acc[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+#pragma unroll
+    for (int step = 0; step < kSteps; ++step) {
+      // (V was asked for ahead of the four stores of the block before)
+      if (step > 0) wait_vmcnt<0>();
+      else if (block != wave) wait_vmcnt<4>();
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int kk = 0; kk < KD / 16; ++kk) {
+        const Frag<true> fa = SQ::fragment(sQ + (kk >> 2) * SQ::kElems, 0, kk & 3, lane);
+        const Frag<true> fb = SK::fragment(sK + (kk >> 2) * SK::kElems, 0, kk & 3, lane);
+        acc[step] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb.operand(), fa.operand(), acc[step], 0, 0, 0);
+      }
+      wait_lgkmcnt0();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (step + 1 < kSteps) load_v(block * kColsOfBlock + (step + 1) * kStepCols);
+    }
+    uintx4_t pr[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) pr[u] = row_buffer_load(in_p, offset_of(block, u));
+    if (block == active - 1) {  // nothing beyond the diagonal
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int col = block * kColsOfBlock + 32 * i + 8 * (r >> 2) + 4 * half + (r & 3);
+          acc[i][r] = col <= my_row ? acc[i][r] : 0.f;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd)
+        *reinterpret_cast<uint2*>(stage_to + (((4 * i + qd) ^ ((lane >> 1) & 7)) << 3)) =
+            make_uint2(pack_bf16(acc[i][4 * qd], acc[i][4 * qd + 1]), pack_bf16(acc[i][4 * qd + 2], acc[i][4 * qd + 3]));
+    uintx4_t rows[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) rows[u] = stage_read(u);
+    wait_lgkmcnt0();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (block + WAVES < active) load_v((block + WAVES) * kColsOfBlock);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      Raw8<bf16_t> raw_x, raw_p;
+      raw_x.v = make_uint4(rows[u][0], rows[u][1], rows[u][2], rows[u][3]);
+      raw_p.v = make_uint4(pr[u][0], pr[u][1], pr[u][2], pr[u][3]);
+      float x[8], p[8];
+      unpack(raw_x, x);
+      unpack(raw_p, p);
+      dropout_apply8(g.key, group0 + static_cast<uint64_t>(u * g.s + block * (kColsOfBlock / 8)), x);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = softmax_bwd(p[i], x[i], dot[u], g.scale);
+      row_buffer_store(out, offset_of(block, u), uintx4_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])});
+    }
   }
   if (blocks > active && wave == (active & (WAVES - 1))) {
 #pragma unroll
@@ -524,10 +616,19 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
   }
 }
 
-template <int KD, bool RAGGED, int WAVES, int NBW, bool FROM_C = false>
+template <int WAVES>
+hipError_t launch_from_c(const ScoreGradientArgs& g, hipStream_t st) {
+  constexpr size_t smem = (kRowsOfBlock * 128 + WAVES * kStepElems) * sizeof(bf16_t) + kRowsOfBlock * sizeof(float);
+  auto kern = attn_score_gradient_from_c_kernel<WAVES>;
+  LYNX_RAISE_LDS_LIMIT(kern, smem);
+  hipLaunchKernelGGL(kern, dim3(g.row_blocks * g.nz), dim3(WAVES * kWave), smem, st, g);
+  return hipGetLastError();
+}
+
+template <int KD, bool RAGGED, int WAVES, int NBW>
 hipError_t launch(const ScoreGradientArgs& g, hipStream_t st) {
   constexpr size_t smem = (kRowsOfBlock * KD + WAVES * kStepElems) * sizeof(bf16_t) + WAVES * kRowsOfBlock * sizeof(float);
-  auto kern = attn_score_gradient_kernel<KD, RAGGED, WAVES, NBW, FROM_C>;
+  auto kern = attn_score_gradient_kernel<KD, RAGGED, WAVES, NBW>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
   hipLaunchKernelGGL(kern, dim3(g.row_blocks * g.nz), dim3(WAVES * kWave), smem, st, g);
   return hipGetLastError();
@@ -601,8 +702,8 @@ hipError_t attn_score_gradient(const void* dc, long long lddc, const void* v, lo
   g.scale = scale;
   g.key = make_dropout_key(dp, 0);
   if (from_c) {
-    if (sh.s <= 256 && static_cast<long long>(g.row_blocks) * g.nz <= 512) return launch<128, false, 4, 1, true>(g, st);
-    return launch<128, false, 8, 1, true>(g, st);
+    if (sh.s <= 256 && static_cast<long long>(g.row_blocks) * g.nz <= 512) return launch_from_c<4>(g, st);
+    return launch_from_c<8>(g, st);
   }
   const bool whole = sh.s % kColsOfBlock == 0 && (d == 64 || d == 128);
   if (d <= 64) return whole ? launch<64, false>(g, st) : launch<64, true>(g, st);
