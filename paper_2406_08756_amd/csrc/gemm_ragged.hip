@@ -112,7 +112,7 @@ ProductPlan search_product(int M, int N, int K) {
 // thread keeps the last ones it worked out.
 template <typename Plan, int KEYS>
 struct PlanCache {
-  static constexpr int kSlots = 32;
+  static constexpr int kSlots = 256;  // (with 32, the products of one layer in six fell on one another)
   struct Entry { int key[KEYS]; Plan plan; bool used; } entry[kSlots] = {};
   template <typename F>
   const Plan& get(const int (&key)[KEYS], F&& search) {
