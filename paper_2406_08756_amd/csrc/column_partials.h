@@ -31,8 +31,7 @@ inline ColumnPartials guest_partials(const ColumnSumInput* in, int first, int wa
 
 // Tile `tile`, one vector of 8 columns per lane.  A lane has all 32 rows of its columns, so nothing goes through LDS,
 // which belongs to the products; the order of the sums is that of rows_colsum_kernel: rows r, r + 4, ... of the tile
-// form one sum, of four.  8192 rows of 6144 columns (100 MB) take 16.8 us as a launch of their own; behind the 448
-// workgroups of the products a pass gets 11 to 15 us shorter.
+// form one sum, of four.
 template <typename T>
 __device__ __forceinline__ void column_partials(const ColumnPartials& c, int tile) {
   if (tile >= c.tiles) return;

@@ -303,7 +303,7 @@ hipError_t launch_ragged_pair(MfmaGemmArgs w, MfmaGemmArgs d, const ColumnSumInp
   const int dgrad_first = d.k_per > w.k_per;
   const int n_first = dgrad_first ? n_d : n_w, n_pad = (n_first + 7) & ~7;
   const int n = n_pad + n_w + n_d - n_first;
-  if constexpr (TILE != kT128) {
+  if constexpr (TILE == kT64) {
     if (in != nullptr) {
       auto kern = gemm_ragged_pair_guest_kernel<TILE, FAR>;
       LYNX_RAISE_LDS_LIMIT(kern, smem);
@@ -534,11 +534,12 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   if (in_parts && (in != nullptr || (!dgrad.serial && w_bytes > 0))) return hipErrorInvalidValue;
   if (w_bytes + d_bytes > 0 && !serial && (scratch == nullptr || scratch_bytes < w_bytes + d_bytes)) return hipErrorInvalidValue;
   hipError_t e;
-  // A column sum goes with the products, whose last round of workgroups leaves units idle (10 to 15 us of a pass of 8192
-  // tokens of h 2048 or 4096, 1 to 2 of the small layers in 64 x 64 tiles), but not with 128 x 128 tiles: their kernel
-  // needs its registers (984 tokens of h 3016 426.6 us with a launch of its own, 427.9 this way; 192 of 2048 241.7 and 244.6).
-  // (A launch of its own comes after them: ahead of them its streaming loads take x out of the caches, 3 us.)
-  const bool sum_apart = in != nullptr && (serial || p.tile == kT128);
+  // A column sum goes with products in 64 x 64 tiles: layers of which every launch is a hundredth (a pass of 768 tokens of h
+  // 512 113.6 -> 112.4 us, of a drawn one 132.1 -> 130.0).  Larger tiles keep the launch of its own: with 256 x 256 it gained
+  // 0 to 0.4 % of a pass, with 128 x 128 it lost 0.3 to 1.2 % (registers), and behind 263 workgroups of 256 x 128, seven
+  // more than there are units, the launch took 125 us where the two take 107.
+  // (That launch comes after the products: ahead of them its streaming loads take x out of the caches, 3 us.)
+  const bool sum_apart = in != nullptr && (serial || p.tile != kT64);
   const ColumnSumInput* const sum_after = sum_apart ? in : nullptr;
   if (sum_apart) in = nullptr;
   if (serial || in_parts) {
@@ -566,8 +567,8 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
     w.partial = scratch;
     d.partial = scratch + w_bytes / sizeof(float);
     switch (p.tile) {
-      case kT256: e = launch_ragged_pair<kT256>(w, d, in, st); break;
-      case kT256x128: e = launch_ragged_pair<kT256x128>(w, d, in, st); break;
+      case kT256: e = launch_ragged_pair<kT256>(w, d, nullptr, st); break;
+      case kT256x128: e = launch_ragged_pair<kT256x128>(w, d, nullptr, st); break;
       case kT128: e = launch_ragged_pair<kT128>(w, d, nullptr, st); break;
       default: e = far ? launch_ragged_pair<kT64, true>(w, d, in, st) : launch_ragged_pair<kT64>(w, d, in, st); break;
     }

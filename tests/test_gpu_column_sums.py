@@ -48,7 +48,7 @@ def test_bias_gradients_are_summed_in_one_order(dtype, h, s, b):
 
 
 # (hidden, heads, head_dim, ffn, seq, micro_batch), side of the products' tile: the QKV bias gradient in the launch of the
-# products (64, 256) or behind it (128); whole and part tiles of 64 vectors, last blocks of less than 32 rows
+# products (64) or behind it; whole and part tiles of 64 vectors, last blocks of less than 32 rows
 @pytest.mark.parametrize("shape,side", [((264, 5, 104, 64, 72, 3), 64), ((512, 4, 128, 64, 384, 2), 64),
                                         ((3016, 7, 104, 64, 328, 3), 128), ((2048, 16, 128, 64, 1000, 4), 256)])
 def test_qkv_bias_gradient_beside_the_products(shape, side):
