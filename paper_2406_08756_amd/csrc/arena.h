@@ -95,6 +95,11 @@ class Arena {
     free_[off] = len;
   }
 
+  // As if a block up to `end` had been handed out.
+  void reach(size_t end) {
+    if (end > extent_peak_) extent_peak_ = end;
+  }
+
   size_t in_use() const { return in_use_; }
   size_t extent_peak() const { return extent_peak_; }  // highest byte ever handed out
   size_t capacity() const { return capacity_; }

@@ -475,14 +475,17 @@ lynx_status run_fused_linear(Ctx& cx, int lin) {
   return run_linear(cx, lin, fused_linear_desc(cx, lin, keep_product));
 }
 
-// OP10 + OP11 as one launch: G, and U if `keep_u` (its place is taken either way).  Same bits as the two.  The two
-// operators may put G where Y2 or the partial sums of a cut contraction were; plan_fused_gelu says whether it lies where
-// nothing is in the way, at `g_off`, and whether the partial sums have room below what the two operators reach.
-// Then every block lies where it did, and a workspace is large enough for one form exactly when it is for the other.
-// `y2_goes`: whether Y2 is released once U is there.  `passes`: neither G nor V2 outlives the forward pass, so that G may
-// lie wherever there is room for it, U, Y2 and the partial sums, and afterwards for those of operator 12.
+// OP10 + OP11 as one launch: G, and U if `keep_u`.  Same bits as the two.  The two operators may put G where Y2 or the
+// partial sums of a cut contraction were, which one launch cannot.  plan_fused_gelu follows their allocations and says
+// whether one launch finds room below what they reach, with every block that outlives it where they put it: then a
+// workspace is large enough for one form exactly when it is for the other, and the peak is theirs (`reach`).
+//   - G lies where the two operators put it, if neither Y2 nor the partial sums are in the way; U has its place either way.
+//   - `passes`, neither G nor V2 outlives the forward pass: G lies wherever there is room beside what operators 10 to 12 need,
+//     and U has a place only if it is kept (otherwise G takes that place).
+// `y2_goes`: whether Y2 is released once U is there.
 struct FusedGelu {
-  size_t g_off = 0;
+  size_t g_off = 0, reach = 0;
+  bool u_has_place = true;
 };
 GemmDesc fused_gelu_desc(const Ctx& cx, const void* y2, const void* w1, const void* b1, void* u, void* g_out) {
   const Dims& D = cx.L->D;
@@ -492,45 +495,51 @@ GemmDesc fused_gelu_desc(const Ctx& cx, const void* y2, const void* w1, const vo
   g.serial = without(*cx.bk, kSerial);
   return g;
 }
-bool plan_fused_gelu(const Ctx& cx, bool y2_goes, bool passes, FusedGelu* plan) {
+bool plan_fused_gelu(const Ctx& cx, bool y2_goes, bool passes, bool keep_u, FusedGelu* plan) {
   const Dims& D = cx.L->D;
   // (shapes only: aligned addresses, as the blocks and the caller's buffers have)
   void* const some = reinterpret_cast<void*>(256);
   const GemmDesc g = fused_gelu_desc(cx, some, some, some, some, some);
   if (!lynx::gemm_absorbs_gelu(D.dtype, g)) return false;
   const size_t scratch_bytes = lynx::gemm_scratch_bytes(D.dtype, g);
-  const size_t g_bytes = Arena::round_up(act_bytes(D, 11)), y2_bytes = Arena::round_up(act_bytes(D, 9));
+  const size_t u_bytes = act_bytes(D, 10), g_bytes = act_bytes(D, 11);
+  const size_t y2_off = cx.bk->off[9];
+  size_t u_off, scratch_off;
+  auto passing_scratch = [&](Arena& a, size_t bytes) {
+    if (bytes == 0) return true;
+    if (!a.alloc(bytes, &scratch_off)) return false;
+    a.release(scratch_off);
+    return true;
+  };
   Arena apart = cx.bk->arena;  // as the two operators go about it
-  size_t u_off, scratch_off = 0;
-  if (!apart.alloc(act_bytes(D, 10), &u_off)) return false;
-  if (scratch_bytes > 0) {
-    if (!apart.alloc(scratch_bytes, &scratch_off)) return false;
-    apart.release(scratch_off);
-  }
-  if (y2_goes) apart.release(cx.bk->off[9]);
-  if (!apart.alloc(act_bytes(D, 11), &plan->g_off)) return false;
-  const bool on_y2 = y2_goes && plan->g_off < cx.bk->off[9] + y2_bytes && cx.bk->off[9] < plan->g_off + g_bytes;
+  if (!apart.alloc(u_bytes, &u_off) || !passing_scratch(apart, scratch_bytes)) return false;
+  if (y2_goes) apart.release(y2_off);
+  if (!apart.alloc(g_bytes, &plan->g_off)) return false;
   Arena joint = cx.bk->arena;
-  if (!on_y2 && joint.alloc(act_bytes(D, 10), &u_off) && joint.alloc_at(plan->g_off, act_bytes(D, 11)) &&
-      (scratch_bytes == 0 || (joint.alloc(scratch_bytes, &scratch_off) && joint.extent_peak() <= apart.extent_peak())))
+  const bool on_y2 = y2_goes && plan->g_off < y2_off + act_bytes(D, 9) && y2_off < plan->g_off + g_bytes;
+  plan->u_has_place = true;
+  plan->reach = apart.extent_peak();
+  if (!on_y2 && (scratch_bytes == 0 || (joint.alloc(u_bytes, &u_off) && joint.alloc_at(plan->g_off, g_bytes) &&
+                                        passing_scratch(joint, scratch_bytes) && joint.extent_peak() <= plan->reach)))
     return true;
   if (!passes || !can_fuse_linear(cx, 12)) return false;
-  joint = cx.bk->arena;
-  if (!joint.alloc(act_bytes(D, 10), &u_off) || !joint.alloc(act_bytes(D, 11), &plan->g_off)) return false;
-  if (scratch_bytes > 0) {
-    if (!joint.alloc(scratch_bytes, &scratch_off)) return false;
-    joint.release(scratch_off);
-  }
-  if (y2_goes) joint.release(cx.bk->off[9]);
-  if (!((cx.bk->retain >> 10) & 1u)) joint.release(u_off);
   GemmDesc fc2 = linear_fwd(some, some, nullptr, some, D.T, D.h, D.f);
   fc2.serial = without(*cx.bk, kSerial);
   const size_t fc2_bytes = lynx::gemm_scratch_bytes(D.dtype, fc2);
-  return fc2_bytes == 0 || joint.alloc(fc2_bytes, &scratch_off);
+  if (!keep_u) apart.release(u_off);
+  if (!passing_scratch(apart, fc2_bytes)) return false;
+  joint = cx.bk->arena;
+  if ((keep_u && !joint.alloc(u_bytes, &u_off)) || !joint.alloc(g_bytes, &plan->g_off) || !passing_scratch(joint, scratch_bytes))
+    return false;
+  if (y2_goes) joint.release(y2_off);
+  plan->u_has_place = keep_u;
+  plan->reach = apart.extent_peak();
+  return passing_scratch(joint, fc2_bytes) && joint.extent_peak() <= plan->reach;
 }
 lynx_status run_fused_gelu(Ctx& cx, const FusedGelu& plan, bool keep_u) {
-  LYNX_TRY(alloc_act(cx, 10));
+  if (plan.u_has_place) LYNX_TRY(alloc_act(cx, 10));
   if (!cx.bk->arena.alloc_at(plan.g_off, act_bytes(cx.L->D, 11))) return LYNX_ERR_OOM;
+  cx.bk->arena.reach(plan.reach);
   cx.bk->off[11] = plan.g_off;
   cx.bk->live[11] = true;
   return run_linear(cx, 10, fused_gelu_desc(cx, act_ptr(cx, 9), cx.L->params.w1, cx.L->params.b1,
@@ -576,6 +585,7 @@ lynx_status forward_pass(Ctx& cx, uint32_t retain) {
   bk.fused_attn = (cx.L->cfg.flags & LYNX_FLAG_FUSED_ATTENTION) && !(bk.retain & 0x38u) &&
                   lynx::attn_fused_supported(cx.L->D.dtype, cx.L->D.s, cx.L->D.d);
   FusedGelu gelu;
+  const bool keep_u = (bk.retain >> 10) & 1u;
   for (int i = 1; i <= kNumOps; ++i) {
     if (i == 5) continue;  // emitted by OP4's kernel
     int done = i;
@@ -592,8 +602,8 @@ lynx_status forward_pass(Ctx& cx, uint32_t retain) {
     } else if ((i == 7 || i == 12) && can_fuse_linear(cx, i)) {
       LYNX_TRY(run_fused_linear(cx, i));
       done = ++i;  // the launch covers the bias + dropout + residual operator too
-    } else if (i == 10 && plan_fused_gelu(cx, /*y2_goes=*/!((bk.retain >> 9) & 1u), /*passes=*/!(bk.retain & 0x1800u), &gelu)) {
-      LYNX_TRY(run_fused_gelu(cx, gelu, /*keep_u=*/(bk.retain >> 10) & 1u));
+    } else if (i == 10 && plan_fused_gelu(cx, /*y2_goes=*/!((bk.retain >> 9) & 1u), /*passes=*/!(bk.retain & 0x1800u), keep_u, &gelu)) {
+      LYNX_TRY(run_fused_gelu(cx, gelu, keep_u));
       done = ++i;  // the launch covers OP11 too
     } else {
       LYNX_TRY(run_op(cx, i));
@@ -679,7 +689,7 @@ lynx_status recompute_pass(Ctx& cx, uint32_t segment) {
                can_fuse_linear(cx, i)) {
       LYNX_TRY(run_fused_linear(cx, i));
       ++i;
-    } else if (i == 10 && ((segment >> 11) & 1u) && !bk.live[11] && plan_fused_gelu(cx, /*y2_goes=*/false, /*passes=*/false, &gelu)) {
+    } else if (i == 10 && ((segment >> 11) & 1u) && !bk.live[11] && plan_fused_gelu(cx, /*y2_goes=*/false, /*passes=*/false, /*keep_u=*/true, &gelu)) {
       LYNX_TRY(run_fused_gelu(cx, gelu, /*keep_u=*/true));
       ++i;
     } else {
