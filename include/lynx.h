@@ -264,8 +264,8 @@ lynx_status lynx_layer_set_dry_run(lynx_layer_t layer, int on);
  * dropout in one launch), OP8 by slot 7, OP13 by slot 12, and in small tiles OP11 by slot 10.  The
  * rest are the backward kernels (likewise the GeLU backward may run inside
  * the FC2 gradient launch, dPd with the softmax backward as one launch, dK in the
- * launch and slot of dQ, in fp32 dV in those of dPd, and the first stage of the QKV bias
- * gradient in those of the QKV gradients).
+ * launch and slot of dQ, in fp32 dV in those of dPd, and, in fp32 and in bf16 products of
+ * small tiles, the first stage of the QKV bias gradient in those of the QKV gradients).
  * The second stage of the column sums (bias and LayerNorm gradients) is one launch
  * at the end, with a slot of its own; a run whose workspace has no room for all their
  * partial sums finishes each in the slot of the kernel that forms them.

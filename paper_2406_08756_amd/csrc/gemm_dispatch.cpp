@@ -124,9 +124,20 @@ hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, fl
   return gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, nullptr, sums, st);
 }
 
+// In 64 x 64 tiles: layers of which every launch is a hundredth (a pass of 768 tokens of h 512 113.6 -> 112.4 us, of a drawn
+// one 132.1 -> 130.0).  Larger tiles keep the launch of its own: with 256 x 256 it gained 0 to 0.4 % of a pass, with
+// 128 x 128 it lost 0.3 to 1.2 % (registers), and behind 263 workgroups of 256 x 128, seven more than there are units, the
+// launch took 125 us where the two take 107.
+bool gemm_pair_takes_column_sum(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  if (!gemm_pair_supported(dtype, dgrad, wgrad)) return false;
+  if (dtype != 1) return true;
+  const RaggedChoice c = ragged_pair(dgrad, wgrad);
+  return c.tile_m == 64 && c.tile_n == 64 && dgrad.epi.kind == kEpiNone && !(dgrad.serial && c.scratch_bytes > 0);
+}
+
 hipError_t gemm_pair_column_sum(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
                                 const ColumnSumInput& in, ColumnSums* sums, hipStream_t st) {
-  if (!gemm_pair_supported(dtype, dgrad, wgrad) || in.cols % 8) return hipErrorInvalidValue;
+  if (!gemm_pair_takes_column_sum(dtype, dgrad, wgrad) || in.cols % 8) return hipErrorInvalidValue;
   if (dtype != 1) return gemm_f32_pair(dgrad, wgrad, &in, sums, st);
   return gemm_ragged_pair(dgrad, wgrad, scratch, scratch_bytes, &in, sums, st);
 }

@@ -531,17 +531,10 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   }
   const bool in_parts = at_once < dgrad.N, far = is_far(dgrad) || is_far(wgrad);
   const bool serial = dgrad.serial && w_bytes + d_bytes > 0;
-  if (in_parts && (in != nullptr || (!dgrad.serial && w_bytes > 0))) return hipErrorInvalidValue;
+  if (in_parts && !dgrad.serial && w_bytes > 0) return hipErrorInvalidValue;
+  if (in != nullptr && (serial || in_parts || p.tile != kT64)) return hipErrorInvalidValue;
   if (w_bytes + d_bytes > 0 && !serial && (scratch == nullptr || scratch_bytes < w_bytes + d_bytes)) return hipErrorInvalidValue;
   hipError_t e;
-  // A column sum goes with products in 64 x 64 tiles: layers of which every launch is a hundredth (a pass of 768 tokens of h
-  // 512 113.6 -> 112.4 us, of a drawn one 132.1 -> 130.0).  Larger tiles keep the launch of its own: with 256 x 256 it gained
-  // 0 to 0.4 % of a pass, with 128 x 128 it lost 0.3 to 1.2 % (registers), and behind 263 workgroups of 256 x 128, seven
-  // more than there are units, the launch took 125 us where the two take 107.
-  // (That launch comes after the products: ahead of them its streaming loads take x out of the caches, 3 us.)
-  const bool sum_apart = in != nullptr && (serial || p.tile != kT64);
-  const ColumnSumInput* const sum_after = sum_apart ? in : nullptr;
-  if (sum_apart) in = nullptr;
   if (serial || in_parts) {
     // (the product that is not cut in the plan's tile: the GeLU epilogue's column partials depend on it)
     const bool w_cut = w.k_splits > 1, d_cut = d.k_splits > 1;
@@ -560,7 +553,7 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
         if (e == hipSuccess) e = of_part.add(part.colsum_partial, static_cast<bf16_t*>(dgrad.epi.colsum_out) + n0, colsum_rows, part.N);
         if (e == hipSuccess) e = finish_column_sums(1, &of_part, st);
       }
-      return e;  // (FC2's gradients: no column sum besides)
+      return e;
     }
     if (e == hipSuccess) e = d_cut ? launch_serial<true, false>(far, d, st) : launch_tile<true, false>(p.tile, far, d, st);
   } else {
@@ -578,8 +571,6 @@ hipError_t gemm_ragged_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, float*
   if (w.k_splits > 1 && d.k_splits > 1) e = launch_finish(&w, &d, st);
   else if (w.k_splits > 1) e = launch_finish(&w, nullptr, st);
   else if (d.k_splits > 1) e = launch_finish(&d, nullptr, st);
-  if (e == hipSuccess && sum_after != nullptr)
-    e = column_sum(1, sum_after->x, sum_after->out, sum_after->part, sum_after->rows, sum_after->cols, sums, st);
   if (e != hipSuccess || dgrad.epi.kind != kEpiGeluBwd) return e;
   return sums->add(dgrad.epi.colsum_partial, dgrad.epi.colsum_out, colsum_rows, dgrad.N);
 }

@@ -212,8 +212,8 @@ bool gemm_absorbs_gelu(int dtype, const GemmDesc& d);
 // (gemm_pair_scratch_bytes).
 hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch,
                      size_t scratch_bytes, ColumnSums* sums, hipStream_t st);
-// The same, and the column sums of x [rows, cols]: partial sums to `part` (not part of `scratch`), second stage to `sums`; in
-// the same launch where that pays.  The bits of column_sum.
+// The same, and the column sums of x [rows, cols] in the same launch, where gemm_pair_takes_column_sum: partial sums to `part`
+// (not part of `scratch`), second stage to `sums`.  The bits of column_sum.
 struct ColumnSumInput {
   const void* x;
   void* out;
@@ -222,6 +222,7 @@ struct ColumnSumInput {
 };
 hipError_t gemm_pair_column_sum(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, float* scratch, size_t scratch_bytes,
                                 const ColumnSumInput& in, ColumnSums* sums, hipStream_t st);
+bool gemm_pair_takes_column_sum(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);
 size_t gemm_pair_scratch_bytes(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);  // shapes, epilogue and `serial` only
 // Whether the input gradient should carry the GeLU backward (kEpiGeluBwd): supported, and it pays.
 bool gemm_pair_absorbs_gelu(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad);

@@ -925,16 +925,17 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   GemmDesc qkv_wg = linear_wgrad(dqkv, act_ptr(cx, 1), gr->wqkv, D.T, 3 * D.p, D.h);
   const size_t bqkv_bytes = Arena::round_up(lynx::colsum_scratch_bytes(D.T, 3 * D.p));
   LYNX_TRY(alloc_partials(3, bqkv_bytes + lynx::layernorm_bwd_scratch_bytes(D.T, D.h, false)));
-  if (defer) {
+  qkv_dg.serial = qkv_wg.serial = without(*cx.bk, kSerial);
+  if (defer && lynx::gemm_pair_takes_column_sum(dt, qkv_dg, qkv_wg)) {
     // the bias gradient in the same launch (its partial sums are apart from `scr`, which the pair may use)
-    qkv_dg.serial = qkv_wg.serial = without(*cx.bk, kSerial);
     const lynx::ColumnSumInput bqkv{dqkv, gr->bqkv, part, D.T, 3 * D.p};
     LYNX_LAUNCH(cx, kB2Grads, lynx::gemm_pair_column_sum(dt, qkv_dg, qkv_wg, scr, scratch_bytes, bqkv, &sums, cx.st));
-    part += bqkv_bytes / sizeof(float);
   } else {
+    // (after the products: ahead of them its streaming loads take dQKV out of the caches, 3 us)
     LYNX_TRY(launch_pair(kB2Grads, qkv_dg, qkv_wg, defer));
     LYNX_LAUNCH(cx, kB2BiasGrad, summed(lynx::column_sum(dt, dqkv, gr->bqkv, part, D.T, 3 * D.p, &sums, cx.st), defer));
   }
+  if (defer) part += bqkv_bytes / sizeof(float);
   free_temp(cx, &t_dqkv);
   free_act(cx, 2);
   LYNX_TRY(tap(cx, 1, temp_ptr(cx, t_dy1)));

@@ -62,3 +62,18 @@ def test_qkv_bias_gradient_beside_the_products(shape, side):
     got = layer.grads["bqkv"].float().cpu().numpy()
     layer.close()
     np.testing.assert_array_equal(got, column_sum(dQKV.float().cpu().numpy().reshape(cfg.tokens, 3 * cfg.proj), synth.BF16))
+
+
+# a profile names the QKV bias gradient wherever it is a launch of its own, and the products' slot covers the products
+@pytest.mark.parametrize("shape,side,apart", [((512, 4, 128, 64, 384, 2), 64, False), ((3016, 7, 104, 64, 328, 3), 128, True),
+                                              ((2048, 16, 128, 64, 1000, 4), 256, True)])
+def test_qkv_bias_gradient_in_the_profile(shape, side, apart):
+    assert forms.of_layer(shape, "qkv_grads")[1] == side
+    cfg = synth.LayerConfig(synth.BF16, *shape)
+    layer = GpuLayer(cfg, synth.make_params(cfg))
+    B.lynx_layer_set_profiling(layer.handle, True)
+    layer.forward(synth.make_x(cfg), B.LYNX_RETAIN_STORE_ALL)
+    layer.backward(synth.make_dout(cfg))
+    slots = B.lynx_layer_profile_ms(layer.handle)
+    layer.close()
+    assert "b2_qkv_dgrad_wgrad" in slots and ("b2_bias_grad" in slots) == apart
