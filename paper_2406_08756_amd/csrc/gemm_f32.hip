@@ -339,7 +339,9 @@ template <int BM>
 __global__ void __launch_bounds__(kThreads) gemm_f32_pair_kernel(GemmDesc wgrad, GemmDesc dgrad, DropoutKey key, int n_first, int dgrad_first) {
   f32_pair_tile<BM>(wgrad, dgrad, key, n_first, dgrad_first);
 }
-// ... and a column sum besides, in workgroups behind them
+// ... and a column sum besides, in workgroups behind them.  The rows that the guest has in flight raise the registers of all
+// (VGPRs and AGPRs) from 100 (64 x 64) and 84 to 140; three wavefronts per SIMD, as the ring of 64 x 64 tiles is made
+// for, may have 168.  (No bound says so: given one, the compiler spends 128 and waits between the guest's loads.)
 template <int BM>
 __global__ void __launch_bounds__(kThreads)
 gemm_f32_pair_guest_kernel(GemmDesc wgrad, GemmDesc dgrad, DropoutKey key, int n_first, int dgrad_first, ColumnPartials guest) {
