@@ -107,3 +107,50 @@ def test_score_gradient(shape):
         if value != 3e38:
             assert bool((spoilt | ~lower)[touched].all()), (j, value)
     layer.close()
+
+
+# (head dimension 128 and whole tiles: the row sums come from C, so a row of V spoils its column only, a row of C its row;
+# four and eight wavefronts, one and several blocks each)
+@pytest.mark.parametrize("shape", [(2, 128, 128, 1), (9, 128, 256, 9), (1, 128, 640, 2), (1, 128, 2048, 1)],
+                         ids=lambda s: "a%d_d%d_s%d_b%d" % s)
+def test_score_gradient_with_row_sums_from_c(shape):
+    a, d, s, b = shape
+    cfg, layer = setup(shape)
+    assert forms.attention(s, d, b, a) & forms.FROM_C
+    X, dOUT = synth.make_x(cfg), synth.make_dout(cfg)
+    keep = torch.empty(b, a, s, s, dtype=torch.uint8, device="cuda")
+    B.lynx_dropout_mask(cfg, 3, 0, keep)
+    tap = layer.tap_gradients(["dS"])["dS"]
+    lower = torch.tril(torch.ones(s, s, dtype=torch.bool, device="cuda"))
+
+    def context():
+        addr, _ = B.lynx_layer_activation(layer.handle, 6)
+        off = addr - layer.workspace.data_ptr()
+        return layer.workspace[off:off + cfg.tokens * cfg.proj * 2].view(torch.bfloat16).view(b, s, a, d)
+
+    def gradient(spoil):
+        layer.workspace.fill_(0xFF)
+        layer.forward(X, pm.STORE_ALL, step=3)
+        spoil()
+        layer.backward(dOUT)
+        torch.cuda.synchronize()
+        return tap.view(b, a, s, s).clone()
+
+    clean = gradient(lambda: None)
+    assert bool(torch.isfinite(clean.float()[..., lower]).all())
+
+    def check(got, touched, what, spoils=True):
+        unchanged = (got.view(torch.int16) == clean.view(torch.int16)) | ~lower
+        assert bool((unchanged | touched).all()), what
+        if spoils:
+            assert bool((~torch.isfinite(got.float()) | ~(touched & lower)).all()), what
+
+    # (3e38: a product overflows or not by its own values)
+    for j, value in ((0, INF), (s // 2, float("nan")), (s - 1, -INF), (s // 3, 3e38)):
+        touched = torch.zeros(b, a, s, s, dtype=torch.bool, device="cuda")
+        touched[0, 0, j:, j] = keep[0, 0, j:, j] != 0      # a dropped element has no part in the gradient
+        check(gradient(lambda: qkv(layer, cfg)[0, j, 2, 0].fill_(value)), touched, ("V", j, value), value != 3e38)
+        touched.zero_()
+        touched[0, a - 1, j] = True
+        check(gradient(lambda: context()[0, j, a - 1, 5].fill_(value)), touched, ("C", j, value), value != 3e38)
+    layer.close()

@@ -44,3 +44,28 @@ def test_bits_of_the_kernels_with_row_sums_of_their_own(shape):
                                                           (1024, 13, 5, False), (1000, 1, 1, False), (2176, 1, 1, False)])
 def test_the_line(seq, micro_batch, heads, from_c):
     assert bool(forms.attention(seq, 128, micro_batch, heads) & forms.FROM_C) == from_c
+
+
+# (heads, seq, batches beyond the line, batches of them below it)
+@pytest.mark.parametrize("a,s,more,fewer", [(3, 2048, 6, 5), (5, 1024, 13, 12), (8, 384, 57, 2), (1, 256, 1025, 3)])
+def test_bits_of_the_two_launches_beyond_the_line(a, s, more, fewer):
+    assert not forms.attention(s, 128, more, a) & forms.FROM_C and forms.attention(s, 128, fewer, a) & forms.FROM_C
+    X = dOUT = None
+    got = []
+    for b in (more, fewer):
+        shape = (64, a, 128, 64, s, b)
+        for which in ("qkv", "proj", "fc1", "fc2"):     # (nothing ahead of dS is cut in one and not in the other)
+            assert forms.of_layer(shape, which)[2] == 1 and (which == "qkv" or forms.of_layer(shape, which + "_grads")[3] == 1)
+        cfg = synth.LayerConfig(synth.BF16, *shape, tp_size=2, tp_rank=1, seed=11, layer_id=5)
+        layer = GpuLayer(cfg, synth.make_params(cfg, random_ln=True))
+        layer.params["wqkv"].mul_(6.0)
+        if X is None:
+            X, dOUT = synth.make_x(cfg), synth.make_dout(cfg)
+        tap = layer.tap_gradients(["dS"])["dS"]
+        layer.workspace.fill_(0xFF)
+        layer.forward(X[:cfg.tokens], pm.STORE_ALL, step=3)
+        layer.backward(dOUT[:cfg.tokens])
+        torch.cuda.synchronize()
+        got.append(tap.view(b, a, s, s)[:fewer].tril())
+        layer.close()
+    assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))
