@@ -261,7 +261,9 @@ lynx_status lynx_layer_set_dry_run(lynx_layer_t layer, int on);
  * operators; an operator that ran inside the launch of the one before it has
  * no time of its own (-1) and is covered by that slot: OP5 by slot 4, and,
  * where the matrix-core kernels apply, OP3 by slot 4 too (scores, softmax and
- * dropout in one launch), OP8 by slot 7, OP13 by slot 12, and in small tiles OP11 by slot 10.  The
+ * dropout in one launch), OP8 by slot 7 and OP13 by slot 12; OP11 by slot 10 in fp32 and where
+ * FC1's product takes small tiles or cuts its contraction, unless Y2 or the partial sums of that
+ * cut are in the way of G.  The
  * rest are the backward kernels (likewise the GeLU backward may run inside
  * the FC2 gradient launch, dPd with the softmax backward as one launch, dK in the
  * launch and slot of dQ, in fp32 dV in those of dPd, and, in fp32 and in bf16 products of

@@ -311,7 +311,8 @@ hipError_t launch(const ScoresSoftmaxArgs& g, hipStream_t st) {
 // sums are known.  dPd never goes through memory.  The sums are of the same terms as in softmax_dropout_bwd_kernel, which
 // takes what is longer.  What bounds it: reading P and writing dS, then the vector ALU.  Two kernels and this one, us:
 // 128 slices of 1024, d = 64, 112 and 83; 100 of 1000 101 and 72; 21 of 328, d = 104, 15 and 11; dQ and dK right behind it gain 5
-// more, since dV then runs before it.
+// more, since dV then runs before it.  (The next block's V is asked for behind P, and only if there is one, so the compiler's
+// waits for P count without it: most of V has landed before the arithmetic that it could hide behind.)
 constexpr int kMaxGradientSeq = 1024;
 
 struct ScoreGradientArgs {
@@ -489,7 +490,8 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
 
 // Head dimension 128, whole tiles of 128 rows, the row sums known beforehand: as sum_dd dC[i, dd] C[i, dd], with the bits of
 // attn_rowdot and attn_dscores_kernel.  A block is finished and stored as soon as it is multiplied.  (A kernel of its own: as a
-// form of the one above it took that one's registers, 128 slices of 1024, d = 64, 86 -> 135 us.)
+// form of the one above it took that one's registers, 128 slices of 1024, d = 64, 86 -> 135 us.)  The buffer descriptors are more
+// than the scalar registers hold: 62 of them are kept in lanes of vector registers, which the block loop reads back.
 template <int WAVES>
 __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_gradient_from_c_kernel(ScoreGradientArgs g) {
   constexpr int KD = 128, kSlabs = KD / 64, kStepCols = kStepElems / KD, kSteps = kColsOfBlock / kStepCols;
@@ -556,7 +558,7 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
       for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
 #pragma unroll
     for (int step = 0; step < kSteps; ++step) {
-      // (V was asked for ahead of the four stores of the block before)
+      // (V was asked for ahead of the four stores of the block before; the waits for that block's P have seen to most of it)
       if (step > 0) wait_vmcnt<0>();
       else if (block != wave) wait_vmcnt<4>();
       asm volatile("" ::: "memory");

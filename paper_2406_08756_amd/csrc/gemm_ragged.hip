@@ -46,7 +46,9 @@ template <int TILE> constexpr int tile_waves_per_simd = TileShape<TILE, false>::
 // they say little beyond those sizes.  None of the products had an epilogue, nor had the pairs: the store pass with bias,
 // dropout and residual is not in the model, and for those the choice is that of the plain product; neither is the GeLU
 // pass (984 tokens of h 3016, f 1544: 51 us in 64 x 64 tiles, 47 in the 128 x 128 ones of the model before; of 60 layers'
-// FC2 gradients the one that got slower with this model, the others 1.00 to 2.45 times as fast, 1.13 on average).
+// FC2 gradients the one that got slower with this model, the others 1.00 to 2.45 times as fast, 1.13 on average).  The
+// fit is older than what the K-major tiles of four wavefronts do now (a third of the instructions ahead of the first loads, a slab's fragments
+// requested at once, GeLU in FC1's store pass) and was not repeated for them.
 struct TileCost {
   int bm, bn, share;
   double alone, one_each, full;

@@ -389,7 +389,8 @@ __device__ __forceinline__ void gemm_tile(const MfmaGemmArgs& g, const int block
         for (int m = 0; m < kMfmas; ++m) {
           if (working) {
             // (every second row of blocks backwards, so that each instruction has an operand of the one before it: 0.2 to 0.3 %
-            // of a pass of the 1.3B-, 7B- and 13B-shaped layers, whose products run at the clock that the power limit allows)
+            // of a pass of the 1.3B-, 7B- and 13B-shaped layers, whose products run at the clock that the power limit allows;
+            // no more than two runs of one build differ by)
             const int u = m / (TM * TN), i = (m / TM) % TN, j = (i & 1) != 0 ? TM - 1 - m % TM : m % TM;
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[u][i].operand(), fa[u][j].operand(), acc[i][j], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
