@@ -71,4 +71,16 @@ void lynx_form_pair(int tokens, int outputs, int inputs, int gelu, int* out) {
   out[4] = d.epi.kind == lynx::kEpiGeluBwd;
 }
 
+// fp32, a linear layer of `inputs` to `outputs`: {side of the tile, ring stages} of the forward product, of the pair of gradients.
+void lynx_form_f32(int tokens, int outputs, int inputs, int* out) {
+  lynx::GemmDesc f{}, d{}, w{};
+  f.M = tokens; f.N = outputs; f.K = inputs;
+  d.M = tokens; d.N = inputs; d.K = outputs;
+  w.M = outputs; w.N = inputs; w.K = tokens;
+  for (lynx::GemmDesc* g : {&f, &d, &w}) g->nz1 = g->nz2 = 1;
+  const lynx::F32Choice of_f = lynx::gemm_f32_choice(f), of_pair = lynx::gemm_f32_pair_choice(d, w);
+  out[0] = of_f.tile; out[1] = of_f.stages;
+  out[2] = of_pair.tile; out[3] = of_pair.stages;
+}
+
 }  // extern "C"

@@ -18,6 +18,7 @@
 #include "column_partials.h"
 #include "device_common.h"
 #include "dropout_host.h"
+#include "gemm_plans.h"
 #include "kernels.h"
 #include "mfma_common.h"
 #include "pointwise_math.h"
@@ -78,13 +79,13 @@ constexpr int kLarge = 64, kSmall = 32;   // tile sides
 constexpr long long kFarStride = 1ll << 23;  // row strides (elements) from which on 32 bits may not hold a load's offset in bytes
 // Ring stages of 16 KB.  64 x 64: three, so that three workgroups share a compute unit and cover each other's barriers,
 // fills and store passes; with four (two workgroups) a step of 1024 tokens of h 1024 takes 808 us where this takes 786, with
-// two (five workgroups, one slab ahead) 899.  32 x 32: four; such launches do not fill the chip, and a layer of 256 tokens
-// of h 256 takes 141.2 us this way, 142.5 with three.
-template <int BM> constexpr int kStages = BM == kLarge ? 3 : 4;
+// two (five workgroups, one slab ahead) 899.  Four where a third does not help: deep_ring().  32 x 32: four; such
+// launches do not fill the chip, and a layer of 256 tokens of h 256 takes 141.2 us this way, 142.5 with three.
+constexpr int kShallow = 3, kDeep = 4;
 constexpr int kPitchPad = 4;              // floats: keeps the 16-byte accesses of the staged tile off each other's banks
-template <int BM> constexpr size_t kLdsBytes = kStages<BM> * 2 * 2048 * sizeof(float);
-static_assert(kLdsBytes<kSmall> >= kWaves * 32 * (kSmall + kPitchPad) * sizeof(float) &&
-                  kLdsBytes<kLarge> >= kLarge * (kLarge + kPitchPad) * sizeof(float),
+template <int S> constexpr size_t kLdsBytes = S * 2 * 2048 * sizeof(float);
+static_assert(kLdsBytes<kDeep> >= kWaves * 32 * (kSmall + kPitchPad) * sizeof(float) &&
+                  kLdsBytes<kShallow> >= kLarge * (kLarge + kPitchPad) * sizeof(float),
               "the staged tile fits the ring");
 
 // Where a tile lies and what it contracts over.
@@ -197,9 +198,9 @@ __device__ __forceinline__ void store_tile(const GemmDesc& d, const DropoutKey& 
   }
 }
 
-template <bool AK, bool BK, int BM>
+template <bool AK, bool BK, int BM, int S>
 __device__ __forceinline__ void f32_tile(const GemmDesc& d, const DropoutKey& key, int block_x, int block_z) {
-  constexpr int S = kStages<BM>, kAhead = S - 1;
+  constexpr int kAhead = S - 1;
   using SA = SlabF<BM, AK>;
   using SB = SlabF<BM, BK>;
   constexpr bool kShareTile = BM == kSmall;  // the wavefronts divide the contraction, not the tile
@@ -322,43 +323,43 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& d, const DropoutKey& ke
   store_tile<BM>(d, key, t, smem, acc[0], wave, lane);
 }
 
-template <bool AK, bool BK, int BM>
+template <bool AK, bool BK, int BM, int S>
 __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmDesc d, DropoutKey key) {
-  f32_tile<AK, BK, BM>(d, key, blockIdx.x, blockIdx.y);
+  f32_tile<AK, BK, BM, S>(d, key, blockIdx.x, blockIdx.y);
 }
 
 // Input and weight gradient of a linear layer in one launch, so that together they fill the chip: the first n_first
 // workgroups belong to the one with the longer contraction, the others fill what it leaves idle.
-template <int BM>
+template <int BM, int S>
 __device__ __forceinline__ void f32_pair_tile(const GemmDesc& wgrad, const GemmDesc& dgrad, const DropoutKey& key, int n_first, int dgrad_first) {
   const int x = static_cast<int>(blockIdx.x), tile = x < n_first ? x : x - n_first;
-  if ((x < n_first) != (dgrad_first != 0)) f32_tile<false, false, BM>(wgrad, key, tile, 0);
-  else f32_tile<true, false, BM>(dgrad, key, tile, 0);
+  if ((x < n_first) != (dgrad_first != 0)) f32_tile<false, false, BM, S>(wgrad, key, tile, 0);
+  else f32_tile<true, false, BM, S>(dgrad, key, tile, 0);
 }
-template <int BM>
+template <int BM, int S>
 __global__ void __launch_bounds__(kThreads) gemm_f32_pair_kernel(GemmDesc wgrad, GemmDesc dgrad, DropoutKey key, int n_first, int dgrad_first) {
-  f32_pair_tile<BM>(wgrad, dgrad, key, n_first, dgrad_first);
+  f32_pair_tile<BM, S>(wgrad, dgrad, key, n_first, dgrad_first);
 }
 // ... and a column sum besides, in workgroups behind them.  The rows that the guest has in flight raise the registers of all
 // (VGPRs and AGPRs) from 100 (64 x 64) and 84 to 140; three wavefronts per SIMD, as the ring of 64 x 64 tiles is made
 // for, may have 168.  (No bound says so: given one, the compiler spends 128 and waits between the guest's loads.)
-template <int BM>
+template <int BM, int S>
 __global__ void __launch_bounds__(kThreads)
 gemm_f32_pair_guest_kernel(GemmDesc wgrad, GemmDesc dgrad, DropoutKey key, int n_first, int dgrad_first, ColumnPartials guest) {
   const int x = static_cast<int>(blockIdx.x);
   if (x >= guest.first) column_partials<float>(guest, (x - guest.first) * kWaves + static_cast<int>(threadIdx.x) / kWave);
-  else f32_pair_tile<BM>(wgrad, dgrad, key, n_first, dgrad_first);
+  else f32_pair_tile<BM, S>(wgrad, dgrad, key, n_first, dgrad_first);
 }
 
 // Two products of attention that do not need each other (batched alike) in one launch: few tiles each, and a launch of
 // either leaves half of the chip's wavefronts out.  Workgroups of both in turn as long as both have some.
-template <bool AK1, bool BK1, bool AK2, bool BK2, int BM>
+template <bool AK1, bool BK1, bool AK2, bool BK2, int BM, int S>
 __global__ void __launch_bounds__(kThreads) gemm_f32_two_kernel(GemmDesc d1, GemmDesc d2, int n1, int n2) {
   const int x = static_cast<int>(blockIdx.x), both = 2 * min(n1, n2);
   const bool second = x < both ? (x & 1) != 0 : n2 > n1;
   const int tile = x < both ? x >> 1 : x - both / 2;
-  if (second) f32_tile<AK2, BK2, BM>(d2, DropoutKey{}, tile, blockIdx.y);
-  else f32_tile<AK1, BK1, BM>(d1, DropoutKey{}, tile, blockIdx.y);
+  if (second) f32_tile<AK2, BK2, BM, S>(d2, DropoutKey{}, tile, blockIdx.y);
+  else f32_tile<AK1, BK1, BM, S>(d1, DropoutKey{}, tile, blockIdx.y);
 }
 
 long long tiles(const GemmDesc& d, int bm) {
@@ -372,29 +373,74 @@ long long tiles(const GemmDesc& d, int bm) {
 // 85 before; 1024^3, one 64 x 64 tile per unit: 25.3 against 24.7).
 bool small_tiles(long long tiles64) { return (tiles64 + 255) / 256 * 256 > 1.15 * tiles64; }
 
+// Four stages in 64 x 64 tiles, with three / four us each: one workgroup per unit, which nothing but its own loads can
+// cover (FC2's forward, 256 workgroups: 1024 tokens of h 1024, f 4096 84 / 79, f 2048 45 / 43, 256 tokens 26.1 / 25.6; dQ and dK of
+// 30 slices of s = 72, 240 workgroups, 7.3 / 6.4; with two per unit nothing is lost by three).
+bool deep_ring(long long workgroups) { return workgroups <= 256; }
+// Pairs, whose longer contraction comes first.  Four stages where
+//  - it alone takes 0.6 of the time that an even share of all does: its workgroups are done last, so what counts is their own
+//    time.  FC1's gradients of 192, 256, 384 and 512 tokens of h 1280 (2.1, 1.6, 1.1 and 0.8 of it) 100 / 94, 103 / 99, 116 / 108 and
+//    129 / 122, of 512 of h 768 (0.67) 69 / 63; at 0.5 FC1's of 1024 of h 1024 139 / 151, QKV's there 104 / 107;
+//  - all are placed at once, the third on units that have two long ones, where of two at a time the short ones would all go to
+//    units with a short one: FC1's of 1152 tokens of h 960, f 1920 (270 and 450 workgroups, 1920 and 1152 long) 84 / 75, a pass of 432 of
+//    h 640 (280 and 400, 640 and 432) 273 / 268; but 512 of h 640 (320 and 400) 37 / 44;
+//  - contractions are of much the same length and more than half of the units have a fourth, and none a fifth, which of three
+//    at a time runs alone: FC2's of 1024 tokens of h 1024, f 2048 88 / 77, QKV's of 1856 of h 872, 980 workgroups, 157 / 146; but 896
+//    of them, FC2's of 768 of h 1024, f 2048, 61 / 66.
+// With more of them, three: FC2's of 256 tokens of h 1280 62 / 70, of 512 117 / 125, FC1's of 1024 of h 1024 139 / 151.
+bool deep_ring_pair(const GemmDesc& a, long long n_a, const GemmDesc& b, long long n_b) {
+  const bool a_longer = a.K > b.K;
+  const long long even = (n_a * a.K + n_b * b.K) / 256, n = n_a + n_b, n_long = a_longer ? n_a : n_b;
+  const long long longer = a_longer ? a.K : b.K, shorter = a_longer ? b.K : a.K;
+  if (5 * longer > 3 * even) return true;
+  if (n > 768) return n > 896 && n <= 1024 && 2 * longer <= 3 * shorter;
+  if (n <= 512 || n_long <= 256 || n - 512 > 512 - n_long) return false;
+  const long long most = longer + 2 * shorter > 2 * longer ? longer + 2 * shorter : 2 * longer;  // of one unit, two at a time
+  return 16 * most < 15 * (2 * longer + shorter);
+}
+}  // namespace
+
+F32Choice gemm_f32_choice(const GemmDesc& d) {
+  if (small_tiles(tiles(d, kLarge) * d.nz1 * d.nz2)) return {kSmall, kDeep};
+  return {kLarge, deep_ring(tiles(d, kLarge) * d.nz1 * d.nz2) ? kDeep : kShallow};
+}
+F32Choice gemm_f32_pair_choice(const GemmDesc& dgrad, const GemmDesc& wgrad) {
+  const long long n_d = tiles(dgrad, kLarge), n_w = tiles(wgrad, kLarge);
+  if (small_tiles(n_d + n_w)) return {kSmall, kDeep};
+  return {kLarge, deep_ring_pair(dgrad, n_d, wgrad, n_w) ? kDeep : kShallow};
+}
+
+namespace {
 DropoutKey epilogue_key(const GemmDesc& d) {
   return d.epi.kind == kEpiBiasDropoutAdd ? make_dropout_key(d.epi.dp, d.epi.site) : DropoutKey{};
 }
 
-template <bool AK, bool BK, int BM>
+template <bool AK, bool BK, int BM, int S>
 hipError_t launch(const GemmDesc& d, hipStream_t st) {
-  hipLaunchKernelGGL((gemm_f32_kernel<AK, BK, BM>), dim3(static_cast<unsigned>(tiles(d, BM)), d.nz1 * d.nz2), dim3(kThreads),
-                     kLdsBytes<BM>, st, d, epilogue_key(d));
+  hipLaunchKernelGGL((gemm_f32_kernel<AK, BK, BM, S>), dim3(static_cast<unsigned>(tiles(d, BM)), d.nz1 * d.nz2), dim3(kThreads),
+                     kLdsBytes<S>, st, d, epilogue_key(d));
   return hipGetLastError();
 }
 template <bool AK, bool BK>
 hipError_t launch(const GemmDesc& d, hipStream_t st) {
-  return small_tiles(tiles(d, 64) * d.nz1 * d.nz2) ? launch<AK, BK, 32>(d, st) : launch<AK, BK, 64>(d, st);
+  const F32Choice c = gemm_f32_choice(d);
+  if (c.tile == kSmall) return launch<AK, BK, kSmall, kDeep>(d, st);
+  if (c.stages == kDeep) return launch<AK, BK, kLarge, kDeep>(d, st);
+  return launch<AK, BK, kLarge, kShallow>(d, st);
 }
 
+template <bool AK1, bool BK1, bool AK2, bool BK2, int BM, int S>
+hipError_t launch_two(const GemmDesc& a, const GemmDesc& b, hipStream_t st) {
+  const int n1 = static_cast<int>(tiles(a, BM)), n2 = static_cast<int>(tiles(b, BM));
+  hipLaunchKernelGGL((gemm_f32_two_kernel<AK1, BK1, AK2, BK2, BM, S>), dim3(n1 + n2, a.nz1 * a.nz2), dim3(kThreads), kLdsBytes<S>, st, a, b, n1, n2);
+  return hipGetLastError();
+}
 template <bool AK1, bool BK1, bool AK2, bool BK2>
 hipError_t launch_two(const GemmDesc& a, const GemmDesc& b, hipStream_t st) {
-  const int bm = small_tiles((tiles(a, 64) + tiles(b, 64)) * a.nz1 * a.nz2) ? 32 : 64;
-  const int n1 = static_cast<int>(tiles(a, bm)), n2 = static_cast<int>(tiles(b, bm));
-  const dim3 grid(n1 + n2, a.nz1 * a.nz2);
-  if (bm == 32) hipLaunchKernelGGL((gemm_f32_two_kernel<AK1, BK1, AK2, BK2, 32>), grid, dim3(kThreads), kLdsBytes<32>, st, a, b, n1, n2);
-  else hipLaunchKernelGGL((gemm_f32_two_kernel<AK1, BK1, AK2, BK2, 64>), grid, dim3(kThreads), kLdsBytes<64>, st, a, b, n1, n2);
-  return hipGetLastError();
+  const long long workgroups = (tiles(a, kLarge) + tiles(b, kLarge)) * a.nz1 * a.nz2;
+  if (small_tiles(workgroups)) return launch_two<AK1, BK1, AK2, BK2, kSmall, kDeep>(a, b, st);
+  if (deep_ring(workgroups)) return launch_two<AK1, BK1, AK2, BK2, kLarge, kDeep>(a, b, st);
+  return launch_two<AK1, BK1, AK2, BK2, kLarge, kShallow>(a, b, st);
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -436,30 +482,33 @@ hipError_t gemm_f32_two(const GemmDesc& a, const GemmDesc& b, hipStream_t st) {
 }
 
 size_t gemm_f32_pair_colsum_bytes(const GemmDesc& dgrad, const GemmDesc& wgrad) {
-  const int bm = small_tiles(tiles(dgrad, 64) + tiles(wgrad, 64)) ? 32 : 64;
+  const int bm = gemm_f32_pair_choice(dgrad, wgrad).tile;
   return static_cast<size_t>((dgrad.M + bm - 1) / bm) * dgrad.N * sizeof(float);
 }
 
 hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, const ColumnSumInput* in, ColumnSums* sums, hipStream_t st) {
-  const bool small = small_tiles(tiles(dgrad, 64) + tiles(wgrad, 64));
-  const int bm = small ? 32 : 64;
+  const F32Choice c = gemm_f32_pair_choice(dgrad, wgrad);
+  const int bm = c.tile;
   const int n_w = static_cast<int>(tiles(wgrad, bm)), n_d = static_cast<int>(tiles(dgrad, bm));
   const bool dgrad_first = dgrad.K > wgrad.K;
   const int n_first = dgrad_first ? n_d : n_w;
-  auto launch_pair = [&](auto bm_tag) {
-    constexpr int BM = decltype(bm_tag)::value;
+  auto launch_pair = [&](auto bm_tag, auto stages_tag) {
+    constexpr int BM = decltype(bm_tag)::value, S = decltype(stages_tag)::value;
     if (in != nullptr) {
       int n_guest;
       const ColumnPartials guest = guest_partials(in, n_w + n_d, kWaves, &n_guest);
-      hipLaunchKernelGGL((gemm_f32_pair_guest_kernel<BM>), dim3(n_w + n_d + n_guest), dim3(kThreads), kLdsBytes<BM>, st, wgrad, dgrad,
+      hipLaunchKernelGGL((gemm_f32_pair_guest_kernel<BM, S>), dim3(n_w + n_d + n_guest), dim3(kThreads), kLdsBytes<S>, st, wgrad, dgrad,
                          DropoutKey{}, n_first, dgrad_first ? 1 : 0, guest);
     } else {
-      hipLaunchKernelGGL((gemm_f32_pair_kernel<BM>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes<BM>, st, wgrad, dgrad, DropoutKey{},
+      hipLaunchKernelGGL((gemm_f32_pair_kernel<BM, S>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes<S>, st, wgrad, dgrad, DropoutKey{},
                          n_first, dgrad_first ? 1 : 0);
     }
   };
-  if (small) launch_pair(std::integral_constant<int, kSmall>{});
-  else launch_pair(std::integral_constant<int, kLarge>{});
+  constexpr std::integral_constant<int, kShallow> shallow{};
+  constexpr std::integral_constant<int, kDeep> deep{};
+  if (c.tile == kSmall) launch_pair(std::integral_constant<int, kSmall>{}, deep);
+  else if (c.stages == kDeep) launch_pair(std::integral_constant<int, kLarge>{}, deep);
+  else launch_pair(std::integral_constant<int, kLarge>{}, shallow);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && in != nullptr) e = sums->add(in->part, in->out, (in->rows + kPartialRows - 1) / kPartialRows, in->cols);
   if (e != hipSuccess || dgrad.epi.kind != kEpiGeluBwd) return e;

@@ -31,6 +31,9 @@ bool gemm_attention_pair_joint(const GemmDesc& rows);
 
 // fp32 storage (gemm_f32.hip).
 bool gemm_f32_supported(const GemmDesc& d);
+struct F32Choice { int tile, stages; };  // side of the tile, ring stages
+F32Choice gemm_f32_choice(const GemmDesc& d);
+F32Choice gemm_f32_pair_choice(const GemmDesc& dgrad, const GemmDesc& wgrad);
 hipError_t gemm_f32(const GemmDesc& d, hipStream_t st);
 // two products of attention, the second with both operands MN-major, in one launch
 hipError_t gemm_f32_two(const GemmDesc& a, const GemmDesc& b, hipStream_t st);

@@ -49,3 +49,10 @@ def of_layer(shape, which):
     if which.endswith("_grads"):
         return pair(T, outputs, inputs, which == "fc2_grads")
     return product(T, outputs, inputs)
+
+
+def f32(tokens, outputs, inputs):
+    """fp32, a linear layer: (side of the tile, ring stages) of the forward product, of the pair of gradients"""
+    out = (ctypes.c_int * 4)()
+    _lib.lynx_form_f32(tokens, outputs, inputs, out)
+    return tuple(out[:2]), tuple(out[2:])
