@@ -331,24 +331,24 @@ __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmDesc d, DropoutK
 // Input and weight gradient of a linear layer in one launch, so that together they fill the chip: the first n_first
 // workgroups belong to the one with the longer contraction, the others fill what it leaves idle.
 template <int BM, int S>
-__device__ __forceinline__ void f32_pair_tile(const GemmDesc& wgrad, const GemmDesc& dgrad, const DropoutKey& key, int n_first, int dgrad_first) {
-  const int x = static_cast<int>(blockIdx.x), tile = x < n_first ? x : x - n_first;
+__device__ __forceinline__ void f32_pair_tile(const GemmDesc& wgrad, const GemmDesc& dgrad, const DropoutKey& key, int n_first, int dgrad_first, int x) {
+  const int tile = x < n_first ? x : x - n_first;
   if ((x < n_first) != (dgrad_first != 0)) f32_tile<false, false, BM, S>(wgrad, key, tile, 0);
   else f32_tile<true, false, BM, S>(dgrad, key, tile, 0);
 }
 template <int BM, int S>
 __global__ void __launch_bounds__(kThreads) gemm_f32_pair_kernel(GemmDesc wgrad, GemmDesc dgrad, DropoutKey key, int n_first, int dgrad_first) {
-  f32_pair_tile<BM, S>(wgrad, dgrad, key, n_first, dgrad_first);
+  f32_pair_tile<BM, S>(wgrad, dgrad, key, n_first, dgrad_first, blockIdx.x);
 }
-// ... and a column sum besides, in workgroups behind them.  The rows that the guest has in flight raise the registers of all
+// ... and a column sum besides, in workgroups between them.  The rows that the guest has in flight raise the registers of all
 // (VGPRs and AGPRs) from 100 (64 x 64) and 84 to 140; three wavefronts per SIMD, as the ring of 64 x 64 tiles is made
 // for, may have 168.  (No bound says so: given one, the compiler spends 128 and waits between the guest's loads.)
 template <int BM, int S>
 __global__ void __launch_bounds__(kThreads)
 gemm_f32_pair_guest_kernel(GemmDesc wgrad, GemmDesc dgrad, DropoutKey key, int n_first, int dgrad_first, ColumnPartials guest) {
   const int x = static_cast<int>(blockIdx.x);
-  if (x >= guest.first) column_partials<float>(guest, (x - guest.first) * kWaves + static_cast<int>(threadIdx.x) / kWave);
-  else f32_pair_tile<BM, S>(wgrad, dgrad, key, n_first, dgrad_first);
+  if (x >= guest.first && x < guest.end) column_partials<float>(guest, (x - guest.first) * kWaves + static_cast<int>(threadIdx.x) / kWave);
+  else f32_pair_tile<BM, S>(wgrad, dgrad, key, n_first, dgrad_first, x < guest.first ? x : x - (guest.end - guest.first));
 }
 
 // Two products of attention that do not need each other (batched alike) in one launch: few tiles each, and a launch of
@@ -495,9 +495,8 @@ hipError_t gemm_f32_pair(const GemmDesc& dgrad, const GemmDesc& wgrad, const Col
   auto launch_pair = [&](auto bm_tag, auto stages_tag) {
     constexpr int BM = decltype(bm_tag)::value, S = decltype(stages_tag)::value;
     if (in != nullptr) {
-      int n_guest;
-      const ColumnPartials guest = guest_partials(in, n_w + n_d, kWaves, &n_guest);
-      hipLaunchKernelGGL((gemm_f32_pair_guest_kernel<BM, S>), dim3(n_w + n_d + n_guest), dim3(kThreads), kLdsBytes<S>, st, wgrad, dgrad,
+      const ColumnPartials guest = guest_partials(*in, n_first, n_w + n_d, kWaves);
+      hipLaunchKernelGGL((gemm_f32_pair_guest_kernel<BM, S>), dim3(n_w + n_d + guest.end - guest.first), dim3(kThreads), kLdsBytes<S>, st, wgrad, dgrad,
                          DropoutKey{}, n_first, dgrad_first ? 1 : 0, guest);
     } else {
       hipLaunchKernelGGL((gemm_f32_pair_kernel<BM, S>), dim3(n_w + n_d), dim3(kThreads), kLdsBytes<S>, st, wgrad, dgrad, DropoutKey{},

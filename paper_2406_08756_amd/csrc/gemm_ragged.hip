@@ -151,11 +151,11 @@ gemm_ragged_kernel(MfmaGemmArgs g) {
 // throughout: 237 us for 4000 tokens, 1600 inputs and 6400 outputs, whose input gradient has the longer
 // contraction; 198 this way.)
 template <int TILE, bool FAR>
-__device__ __forceinline__ void pair_tile(const MfmaGemmArgs& wgrad, const MfmaGemmArgs& dgrad, int n_first, int dgrad_first) {
+__device__ __forceinline__ void pair_tile(const MfmaGemmArgs& wgrad, const MfmaGemmArgs& dgrad, int n_first, int dgrad_first, int x) {
   using T = TileShape<TILE, false>;
   // the second product starts at a multiple of 8 workgroups, as its tile order, which takes the workgroup
   // id mod 8 for the XCD, needs it; the few workgroups in between idle
-  const int x = static_cast<int>(blockIdx.x), n_pad = (n_first + 7) & ~7;
+  const int n_pad = (n_first + 7) & ~7;
   if (x >= n_first && x < n_pad) return;
   const int tile = x < n_first ? x : x - n_pad;
   if ((x < n_first) != (dgrad_first != 0)) {
@@ -169,17 +169,17 @@ __device__ __forceinline__ void pair_tile(const MfmaGemmArgs& wgrad, const MfmaG
 template <int TILE, bool FAR>
 __global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
 gemm_ragged_pair_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int dgrad_first) {
-  pair_tile<TILE, FAR>(wgrad, dgrad, n_first, dgrad_first);
+  pair_tile<TILE, FAR>(wgrad, dgrad, n_first, dgrad_first, blockIdx.x);
 }
-// ... and a column sum besides, in workgroups behind them
+// ... and a column sum besides, in workgroups between them
 template <int TILE, bool FAR>
 __global__ void __launch_bounds__((tile_threads<TILE>), (tile_waves_per_simd<TILE>))
 gemm_ragged_pair_guest_kernel(MfmaGemmArgs wgrad, MfmaGemmArgs dgrad, int n_first, int dgrad_first, ColumnPartials guest) {
   const int x = static_cast<int>(blockIdx.x);
-  if (x >= guest.first)
+  if (x >= guest.first && x < guest.end)
     column_partials<bf16_t>(guest, (x - guest.first) * TileShape<TILE, false>::waves + static_cast<int>(threadIdx.x) / kWave);
   else
-    pair_tile<TILE, FAR>(wgrad, dgrad, n_first, dgrad_first);
+    pair_tile<TILE, FAR>(wgrad, dgrad, n_first, dgrad_first, x < guest.first ? x : x - (guest.end - guest.first));
 }
 
 template <bool AK, bool BK_, int TILE, bool FAR, TileForm FORM>
@@ -309,9 +309,8 @@ hipError_t launch_ragged_pair(MfmaGemmArgs w, MfmaGemmArgs d, const ColumnSumInp
     if (in != nullptr) {
       auto kern = gemm_ragged_pair_guest_kernel<TILE, FAR>;
       LYNX_RAISE_LDS_LIMIT(kern, smem);
-      int n_guest;
-      const ColumnPartials guest = guest_partials(in, n, T::waves, &n_guest);
-      hipLaunchKernelGGL(kern, dim3(n + n_guest), dim3(T::waves * kWave), smem, st, w, d, n_first, dgrad_first, guest);
+      const ColumnPartials guest = guest_partials(*in, n_pad, n, T::waves);
+      hipLaunchKernelGGL(kern, dim3(n + guest.end - guest.first), dim3(T::waves * kWave), smem, st, w, d, n_first, dgrad_first, guest);
       return hipGetLastError();
     }
   }

@@ -77,3 +77,27 @@ def test_qkv_bias_gradient_in_the_profile(shape, side, apart):
     slots = B.lynx_layer_profile_ms(layer.handle)
     layer.close()
     assert "b2_qkv_dgrad_wgrad" in slots and ("b2_bias_grad" in slots) == apart
+
+
+# (hidden, heads, head_dim, ffn, seq, micro_batch), side of the products' tile: fp32, the guest between the products, and
+# last where they have a unit each and it would not (248 and 256 of them)
+@pytest.mark.parametrize("shape,side", [((640, 10, 64, 64, 432, 1), 32), ((512, 8, 64, 64, 400, 1), 64), ((512, 8, 64, 64, 512, 1), 64),
+                                        ((520, 8, 64, 64, 392, 1), 32), ((1000, 15, 64, 64, 1000, 1), 64), ((1280, 10, 128, 64, 200, 1), 64)])
+def test_qkv_bias_gradient_beside_fp32_products(shape, side):
+    cfg = synth.LayerConfig(synth.F32, *shape, dropout_p=0.0)
+    assert forms.f32(cfg.tokens, 3 * cfg.proj, cfg.hidden)[1][0] == side
+    layer = GpuLayer(cfg, synth.make_params(cfg))
+    layer.workspace.fill_(0xFF)
+    taps = layer.tap_gradients(["dQKV", "dY1"])
+    layer.forward(synth.make_x(cfg), B.LYNX_RETAIN_STORE_ALL)
+    y1 = layer.activation_raw(1).view(cfg.tokens, -1).double()
+    layer.backward(synth.make_dout(cfg))
+    torch.cuda.synchronize()
+    dQKV, dY1 = taps["dQKV"].view(cfg.tokens, -1), taps["dY1"].view(cfg.tokens, -1)
+    got, w, dw = layer.grads["bqkv"].cpu().numpy(), layer.params["wqkv"].double(), layer.grads["wqkv"]
+    layer.close()
+    np.testing.assert_array_equal(got, column_sum(dQKV.cpu().numpy(), synth.F32))
+    # (and no tile of the products is missing or done twice: a sum of K products in fp32 is within K 2^-24 sum |a b|)
+    dQKV = dQKV.double()
+    for out, a, b in ((dY1, dQKV, w), (dw, dQKV.t(), y1)):
+        assert bool(((out - a @ b).abs() <= a.shape[1] * 2.0 ** -24 * (a.abs() @ b.abs())).all())
