@@ -321,6 +321,7 @@ struct ScoreGradientArgs {
   long long lddc, ldv;
   const bf16_t* P; bf16_t* dS;
   int s, d, a, nz, row_blocks;
+  int parts;  // (row sums from C) workgroups per 32 rows
   int global_heads, head0;
   float scale;
   DropoutKey key;
@@ -491,14 +492,18 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
 // Head dimension 128, whole tiles of 128 rows, the row sums known beforehand: as sum_dd dC[i, dd] C[i, dd], with the bits of
 // attn_rowdot and attn_dscores_kernel.  A block is finished and stored as soon as it is multiplied.  (A kernel of its own: as a
 // form of the one above it took that one's registers, 128 slices of 1024, d = 64, 86 -> 135 us.)  The buffer descriptors are more
-// than the scalar registers hold: 62 of them are kept in lanes of vector registers, which the block loop reads back.
+// than the scalar registers hold: 60 and more of them are kept in lanes of vector registers, which the block loop reads back.
+// The blocks of a row do not need each other, so `parts` workgroups divide them where there are few rows; each forms the sums of
+// its rows.  (V asked for whether or not a block follows, so that the waits for P do not include it: no faster at any of 58
+// sizes, and 1 to 1.8 % of a pass slower with 64 slices of 1024 or 128 of 512, for the loads after the last block.)
 template <int WAVES>
 __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_gradient_from_c_kernel(ScoreGradientArgs g) {
   constexpr int KD = 128, kSlabs = KD / 64, kStepCols = kStepElems / KD, kSteps = kColsOfBlock / kStepCols;
   using SQ = Slab<kRowsOfBlock, true, 64, 1>;
   using SK = Slab<kStepCols, true, 64, 1>;
-  const int rb = g.row_blocks - 1 - static_cast<int>(blockIdx.x) / g.nz;
-  const int bz = static_cast<int>(blockIdx.x) % g.nz;
+  const int of_rows = g.nz * g.parts, rest = static_cast<int>(blockIdx.x) % of_rows;
+  const int rb = g.row_blocks - 1 - static_cast<int>(blockIdx.x) / of_rows;
+  const int part = rest / g.nz, bz = rest - part * g.nz;
   extern __shared__ __align__(1024) unsigned char smem_raw[];
   bf16_t* sQ = reinterpret_cast<bf16_t*>(smem_raw);
   const int lane = threadIdx.x & 63;
@@ -518,7 +523,8 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
     for (int sl = 0; sl < kSlabs; ++sl) load_rows<SK, KD, false>(v, g.ldv, g.s, KD, col, sl, sK + sl * SK::kElems, lane);
   };
   if (wave < kSlabs) load_rows<SQ, KD, false>(dc, g.lddc, g.s, KD, r0, wave, sQ + wave * SQ::kElems, lane);
-  if (wave < active) load_v(wave * kColsOfBlock);
+  const int first = part * WAVES + wave, step_blocks = g.parts * WAVES;
+  if (first < active) load_v(first * kColsOfBlock);
 #pragma unroll
   for (int i = 0; i < kRowsOfBlock / (4 * WAVES); ++i) {
     const int row = 4 * (wave + WAVES * i) + (lane >> 4);
@@ -550,7 +556,7 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
 #pragma unroll
   for (int u = 0; u < 4; ++u) dot[u] = row_sum[u * 8 + lr];
 #pragma unroll 1
-  for (int block = wave; block < active; block += WAVES) {
+  for (int block = first; block < active; block += step_blocks) {
     floatx16_t acc[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -560,7 +566,7 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
     for (int step = 0; step < kSteps; ++step) {
       // (V was asked for ahead of the four stores of the block before; the waits for that block's P have seen to most of it)
       if (step > 0) wait_vmcnt<0>();
-      else if (block != wave) wait_vmcnt<4>();
+      else if (block != first) wait_vmcnt<4>();
       asm volatile("" ::: "memory");
 #pragma unroll
       for (int kk = 0; kk < KD / 16; ++kk) {
@@ -597,7 +603,7 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
     wait_lgkmcnt0();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    if (block + WAVES < active) load_v((block + WAVES) * kColsOfBlock);
+    if (block + step_blocks < active) load_v((block + step_blocks) * kColsOfBlock);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       Raw8<bf16_t> raw_x, raw_p;
@@ -612,7 +618,7 @@ __global__ void __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 3) attn_score_
       row_buffer_store(out, offset_of(block, u), uintx4_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])});
     }
   }
-  if (blocks > active && wave == (active & (WAVES - 1))) {
+  if (blocks > active && first == active % step_blocks) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) row_buffer_store(out, offset_of(active, u), uintx4_t{0u, 0u, 0u, 0u});
   }
@@ -623,7 +629,7 @@ hipError_t launch_from_c(const ScoreGradientArgs& g, hipStream_t st) {
   constexpr size_t smem = (kRowsOfBlock * 128 + WAVES * kStepElems) * sizeof(bf16_t) + kRowsOfBlock * sizeof(float);
   auto kern = attn_score_gradient_from_c_kernel<WAVES>;
   LYNX_RAISE_LDS_LIMIT(kern, smem);
-  hipLaunchKernelGGL(kern, dim3(g.row_blocks * g.nz), dim3(WAVES * kWave), smem, st, g);
+  hipLaunchKernelGGL(kern, dim3(g.row_blocks * g.nz * g.parts), dim3(WAVES * kWave), smem, st, g);
   return hipGetLastError();
 }
 
@@ -676,14 +682,23 @@ bool attn_score_gradient_supported(int dtype, int s, int d, long long ld, long l
   return s <= kMaxGradientSeq && attn_scores_softmax_supported(dtype, s, d, ld, slices);
 }
 
+// Workgroups of eight wavefronts that share 32 rows of attn_score_gradient_from_c_kernel.
+static long long attn_score_gradient_parts(int s, long long slices) {
+  const long long blocks = (s + kColsOfBlock - 1) / kColsOfBlock, most = (blocks + 7) / 8;
+  const long long at_once = 512 / ((s + kRowsOfBlock - 1) / kRowsOfBlock * slices);  // two per compute unit
+  return at_once < 1 ? 1 : at_once < most ? at_once : most;
+}
+
 // Head dimension 128 and whole tiles of 128 rows, where attn_rowdot and attn_dscores_kernel are the alternative, up to
-// 2^26 elements of dS.  Those two walk tiles of 128 rows and so read V a quarter as often, which is what counts once P and
-// dS, 256 MB together, outgrow the memory-side cache; this one is a launch less and has four times the workgroups.  Those two
-// and this one with the launch of dQ and dK behind it, us: 8 slices of s = 384 19.2 and 15.7, 32 of 1024 52 and 49, 64 of 768
-// 66 and 64, 128 of 512 72 and 72, 16 of 2048 92 and 89; beyond: 32 of 1536 105 and 101, 128 of 1024 189 and 198, 40 of
-// 2048 194 and 198, 64 of 2048 310 and 329.
+// 2^26 elements of dS and 3072 groups of 32 rows.  Those two walk tiles of 128 rows and so read V a quarter as often, which is what
+// counts once P and dS, 256 MB together, outgrow the memory-side cache, or with many short rows; this one is a launch less
+// and has four times the workgroups.  Passes with those two and with this one, us: 4 slices of s = 512 100 and 96, 64 of 768 282 and
+// 277, 256 of 384 382 and 382, 192 of 512 410 and 410, 64 of 1024 369 and 362; beyond: 448 of 384 582 and 596, 512 of 256 432 and
+// 439, 256 of 512 495 and 500, 1024 of 128 401 and 404.  The kernels with the launch of dQ and dK behind them beyond 2^26:
+// 128 of 1024 189 and 198, 40 of 2048 194 and 198, 64 of 2048 310 and 329.  Few long rows, whose workgroups share them:
+// one slice of 2048 148 and 145 (with a workgroup per 32 rows 154), three 162 and 160 (165), one of 1536 137 and 134 (140).
 bool attn_score_gradient_from_c(int dtype, int s, int d, long long ld, long long slices) {
-  return d == 128 && s % 128 == 0 && s <= kMaxSeq && slices * s * s <= (1ll << 26) &&
+  return d == 128 && s % 128 == 0 && s <= kMaxSeq && slices * s * s <= (1ll << 26) && s / kRowsOfBlock * slices <= 3072 &&
          attn_scores_softmax_supported(dtype, s, d, ld, slices);
 }
 
@@ -704,7 +719,10 @@ hipError_t attn_score_gradient(const void* dc, long long lddc, const void* v, lo
   g.scale = scale;
   g.key = make_dropout_key(dp, 0);
   if (from_c) {
+    g.parts = 1;
     if (sh.s <= 256 && static_cast<long long>(g.row_blocks) * g.nz <= 512) return launch_from_c<4>(g, st);
+    // as many as leave the longest row one block per wavefront, if they run at once
+    g.parts = static_cast<int>(attn_score_gradient_parts(sh.s, slices));
     return launch_from_c<8>(g, st);
   }
   const bool whole = sh.s % kColsOfBlock == 0 && (d == 64 || d == 128);

@@ -27,7 +27,7 @@ bool gemm_mfma_supported(int dtype, const GemmDesc& d) {
       // length.  Elsewhere attn_score_gradient forms the row dot products from the dPd that it differentiates (up to
       // s = 1024), or softmax_dropout_bwd does (beyond); those cancel that tensor's rounding, while these come from the
       // rounded C, which made the error of the QKV weight gradient against 64 bits 0.4 to 2.1 % larger at other shapes.
-      // (Up to 2^26 elements attn_score_gradient_from_c takes these shapes too, with the same dot products.)
+      // (Up to a size attn_score_gradient_from_c takes these shapes too, with the same dot products.)
       return d.causal == kCausalOutLower && d.bias == nullptr && d.M % 128 == 0 && d.K == 128 && a_k && b_k &&
              d.epi.aux != nullptr && aligned(d.epi.aux, 16) && d.epi.rowdot != nullptr;
     case kEpiBiasDropoutAdd:

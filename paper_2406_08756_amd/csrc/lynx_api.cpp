@@ -834,7 +834,7 @@ lynx_status backward_pass(Ctx& cx, const void* d_out, void* d_x, const lynx_grad
   // dPd = dC V^T, then B5 + B4: Pd = keep0 P c, P = softmax(S / sqrt(d)).  Where the row-block
   // kernel applies, the store pass of the product forms dS directly (dPd is never written);
   // the row dot products sum_j dP_ij P_ij it needs equal sum_dd dC[i, dd] C[i, dd] and come
-  // from a small kernel over dC and C, or, up to 2^26 elements, are formed in the launch that uses
+  // from a small kernel over dC and C, or, up to a size, are formed in the launch that uses
   // them (attn_score_gradient_from_c).  Otherwise dPd is stored and dS overwrites it.
   GemmDesc dpd = attn_outer(temp_ptr(cx, t_dc), D.p, col_block(qkv, D, 2), 3 * D.p, temp_ptr(cx, t_dpd), D);
   Temp t_rowdot;  // (a place on every path, whichever kernel runs: the sizes named are those they were)

@@ -111,7 +111,7 @@ def test_score_gradient(shape):
 
 # (head dimension 128 and whole tiles: the row sums come from C, so a row of V spoils its column only, a row of C its row;
 # four and eight wavefronts, one and several blocks each)
-@pytest.mark.parametrize("shape", [(2, 128, 128, 1), (9, 128, 256, 9), (1, 128, 640, 2), (1, 128, 2048, 1)],
+@pytest.mark.parametrize("shape", [(2, 128, 128, 1), (9, 128, 256, 9), (1, 128, 640, 2), (1, 128, 1536, 1), (1, 128, 2048, 1)],
                          ids=lambda s: "a%d_d%d_s%d_b%d" % s)
 def test_score_gradient_with_row_sums_from_c(shape):
     a, d, s, b = shape

@@ -13,7 +13,8 @@ from harness import GpuLayer
 pytestmark = pytest.mark.gpu
 
 # (heads, seq, micro_batch)
-SHAPES = [(1, 128, 1), (3, 128, 2), (8, 256, 8), (9, 256, 9), (2, 384, 1), (16, 512, 2), (5, 640, 1), (2, 1024, 2), (1, 1920, 1), (4, 2048, 4)]
+SHAPES = [(1, 128, 1), (3, 128, 2), (8, 256, 8), (9, 256, 9), (2, 384, 1), (16, 512, 2), (5, 640, 1), (2, 1024, 2), (1, 1920, 1), (4, 2048, 4),
+          (1, 1536, 1), (2, 768, 3), (3, 2048, 1)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "a%d_s%d_b%d" % s)
@@ -43,6 +44,12 @@ def test_bits_of_the_kernels_with_row_sums_of_their_own(shape):
 @pytest.mark.parametrize("seq,micro_batch,heads,from_c", [(2048, 4, 4, True), (2048, 17, 1, False), (1024, 8, 8, True),
                                                           (1024, 13, 5, False), (1000, 1, 1, False), (2176, 1, 1, False)])
 def test_the_line(seq, micro_batch, heads, from_c):
+    assert bool(forms.attention(seq, 128, micro_batch, heads) & forms.FROM_C) == from_c
+
+
+# (many short rows)
+@pytest.mark.parametrize("seq,micro_batch,heads,from_c", [(512, 4, 48, True), (512, 4, 64, False), (128, 48, 16, True), (128, 64, 16, False)])
+def test_the_line_of_rows(seq, micro_batch, heads, from_c):
     assert bool(forms.attention(seq, 128, micro_batch, heads) & forms.FROM_C) == from_c
 
 
