@@ -127,7 +127,7 @@ hipError_t gemm_pair(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad, fl
 // In 64 x 64 tiles: layers of which every launch is a hundredth (a pass of 768 tokens of h 512 113.6 -> 112.4 us, of a drawn
 // one 132.1 -> 130.0).  Larger tiles keep the launch of its own: with 256 x 256 it gained 0 to 0.4 % of a pass, with
 // 128 x 128 it lost 0.3 to 1.2 % (registers), and behind 263 workgroups of 256 x 128, seven more than there are units, the
-// launch took 125 us where the two take 107.
+// launch took 125 us where the two take 107 (larger tiles with the sum last in the launch; between the products not measured).
 bool gemm_pair_takes_column_sum(int dtype, const GemmDesc& dgrad, const GemmDesc& wgrad) {
   if (!gemm_pair_supported(dtype, dgrad, wgrad)) return false;
   if (dtype != 1) return true;
